@@ -104,20 +104,24 @@ typedef struct ifl_options {
   double cell_A;     /* stencil constant A of Eq. 7; default sqrt(3) */
   int32_t device;    /* HIP device ordinal; default 0. -1 = host-only handle: prepare,
                         export and save work, solves return IFL_EDEVICE */
-  int32_t batch;     /* columns per multi-RHS tile for ifl_filter: 0 = auto (default: the autotuner's
-                        width, else 32, at most a quarter of the call's columns), 1 = one solve at a
-                        time, 2..64 = fixed tile (rounded down to a power of two) */
+  int32_t batch;     /* how ifl_filter solves its columns: 0 = the library's choice (default; orders 1
+                        and 2: all scales of a field from one Chebyshev sequence of M^-1 K, FP64 in
+                        either precision; else CG tiles of the autotuner's width, or 32, at most a
+                        quarter of the call's columns), 1 = CG, one solve at a time, 2..64 = CG in a
+                        fixed tile (columns per tile, rounded down to a power of two) */
   void* stream;      /* hipStream_t to run on; NULL = the handle's own stream */
   int32_t reorder;   /* 1 = locality ordering of the rows (default): reverse Cuthill-McKee, on meshes of
                         >= 32768 dofs inside 8 Morton-curve parts; 0 = mesh order */
-  int32_t profile;   /* 1 = time the SpMV launches with HIP events (ifl_profile_read) */
+  int32_t profile;   /* 1 = time CG's SpMV launches with HIP events (ifl_profile_read); calls stay
+                        with CG */
   int32_t graphs;    /* 1 = the batched engine replays each 4-iteration chunk of a tile as one captured
                         HIP graph (default), 0 = launches every kernel; results are bitwise equal */
   int32_t solver;    /* IFL_SOLVER_KN (default) or IFL_SOLVER_SHIFTED (orders n >= 2; n = 1 uses
-                        IFL_SOLVER_KN). With SHIFTED, ifl_filter and ifl_spectrum run n = 2 in complex
-                        tiles of 'batch' / 2 columns (batch 0: the library's width; scalar operators
-                        with first-order rows of at most 6 entries 90% of the time), other orders and
-                        batch = 1 one column at a time; the serving engine serves n = 2 in a complex
+                        IFL_SOLVER_KN). With SHIFTED and batch >= 2, ifl_filter and ifl_spectrum run
+                        n = 2 in complex tiles of 'batch' / 2 columns (scalar operators with
+                        first-order rows of at most 6 entries 90% of the time), other orders and
+                        batch = 1 one column at a time (batch 0, n = 2: the sequence above, or the
+                        tiles where it does not pay); the serving engine serves n = 2 in a complex
                         tile of 2 x slots real columns (slots <= 32), other orders one column at a
                         time. Each shifted system stops on its own FP64 true residual: at rtol one
                         column at a time; in n = 2 tiles at rtol / (1 + |sigma| g), g >= ||K M^-1||,
@@ -128,8 +132,8 @@ typedef struct ifl_options {
 
 /* Per-solve statistics (one per field x scale). */
 typedef struct ifl_solve_stats {
-  int32_t iterations;   /* CG iterations */
-  int32_t refinements;  /* FP64 residual replacements (IFL_MIXED, and tiles of either precision) */
+  int32_t iterations;   /* CG iterations, or the degree of the scale's polynomial (batch = 0) */
+  int32_t refinements;  /* CG: FP64 residual replacements (IFL_MIXED, and tiles of either precision) */
   int32_t status;       /* IFL_OK or IFL_ENOTCONV */
   int32_t reserved;
   double rel_residual;  /* final ||M phi - S x|| / ||M phi||, FP64 on the GPU */

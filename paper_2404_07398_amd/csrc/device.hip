@@ -41,6 +41,7 @@
 
 #include "batch.h"
 #include "internal.h"
+#include "poly.h"
 
 namespace ifl {
 
@@ -243,6 +244,7 @@ struct DeviceState {
   int32_t* proj_tri = nullptr;
   double* proj_w = nullptr;
   double* proj_in = nullptr;      // device copy of a host cell field
+  PolyState* poly = nullptr;      // polynomial engine; NULL where it does not take the operator
 };
 
 // Partial sums of a one-column launch (units of G): two parities of five
@@ -1387,6 +1389,12 @@ ifl_status device_create(Handle* h) {
   // hipMemset of device memory may return before it completes, and the
   // solves run on streams that do not wait for the null stream
   IFL_HIP(hipDeviceSynchronize());
+  // without the memory for the polynomial engine the handle keeps to CG
+  if ((st = poly_create(h->op, h->opt.reorder != 0, d->own_stream, &d->poly)) != IFL_OK) {
+    poly_destroy(d->poly);
+    d->poly = nullptr;
+    if (st != IFL_ENOMEM) return st;
+  }
   return IFL_OK;
 }
 
@@ -1423,6 +1431,7 @@ void device_destroy(Handle* h) {
   if (d->field_stage) (void)hipFree(d->field_stage);
   if (d->field_rows) (void)hipFree(d->field_rows);
   if (d->col_stage) (void)hipFree(d->col_stage);
+  poly_destroy(d->poly);
   void* proj[] = {d->proj_ptr, d->proj_tri, d->proj_w, d->proj_in};
   for (void* p : proj)
     if (p) (void)hipFree(p);
@@ -2002,6 +2011,25 @@ ifl_status spare_tile(DeviceState* d, int R, bool mixed, hipStream_t s, BatchWor
   return batch_release(t, ~0ull, s);
 }
 
+// A call's fields in device memory: as they are, or copied from the host.
+ifl_status fields_on_device(Handle* h, int32_t n_fields, const double* fields, hipStream_t s, const double** out) {
+  DeviceState* d = h->dev;
+  *out = fields;
+  if (is_device_ptr(fields)) return IFL_OK;
+  const int64_t need = (int64_t)n_fields * h->op.field_len;
+  if (d->field_stage_len < need) {
+    if (d->field_stage) (void)hipFree(d->field_stage);
+    d->field_stage = nullptr;
+    d->field_stage_len = 0;
+    ifl_status st = dalloc(&d->field_stage, (size_t)need);
+    if (st != IFL_OK) return st;
+    d->field_stage_len = need;
+  }
+  IFL_HIP(hipMemcpyAsync(d->field_stage, fields, sizeof(double) * need, hipMemcpyHostToDevice, s));
+  *out = d->field_stage;
+  return IFL_OK;
+}
+
 // Many columns at once: slots of a tile of R columns are filled from the
 // (field, scale) list, iterated together, and refilled as columns finish.
 // A batched call's staging: the fields on the device, then in row order in
@@ -2013,19 +2041,8 @@ ifl_status stage_call(Handle* h, const BatchMatrix& bm, BatchWork& w, int32_t n_
   DeviceState* d = h->dev;
   const int64_t L = h->op.field_len;
   ifl_status st;
-  const double* fdev = fields;
-  if (!is_device_ptr(fields)) {
-    const int64_t need = (int64_t)n_fields * L;
-    if (d->field_stage_len < need) {
-      if (d->field_stage) (void)hipFree(d->field_stage);
-      d->field_stage = nullptr;
-      d->field_stage_len = 0;
-      if ((st = dalloc(&d->field_stage, (size_t)need)) != IFL_OK) return st;
-      d->field_stage_len = need;
-    }
-    IFL_HIP(hipMemcpyAsync(d->field_stage, fields, sizeof(double) * need, hipMemcpyHostToDevice, s));
-    fdev = d->field_stage;
-  }
+  const double* fdev = nullptr;
+  if ((st = fields_on_device(h, n_fields, fields, s, &fdev)) != IFL_OK) return st;
   if (out_cols > 0 && d->col_stage_len < (int64_t)out_cols * L) {
     if (d->col_stage) (void)hipFree(d->col_stage);
     d->col_stage = nullptr;
@@ -2322,10 +2339,61 @@ ifl_status filter_batched_cx(Handle* h, int Rc, int32_t n_fields, const double* 
   return IFL_OK;
 }
 
+namespace {
+
+// The polynomial engine on a call, *done = false where it leaves the call to
+// CG; the columns whose true residual misses the tolerance are solved again
+// one at a time by the handle's own solver.
+ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_t n_scales, const double* k,
+                       double* out, ifl_solve_stats* stats, double* energy, bool* done) {
+  DeviceState* d = h->dev;
+  PolyCall c;
+  c.order = h->op.order;
+  c.gamma = h->opt.gamma;
+  c.rtol = h->opt.rtol;
+  c.max_iter = h->opt.max_iter;
+  c.n_fields = n_fields;
+  c.n_scales = n_scales;
+  c.k = k;
+  c.out = out;
+  c.out_host = out && !is_device_ptr(out);
+  c.stats = stats;
+  c.energy = energy;
+  c.stream = stream_of(h);
+  *done = false;
+  if (!poly_takes(d->poly, c)) return IFL_OK;
+  ifl_status st = fields_on_device(h, n_fields, fields, c.stream, &c.fields);
+  std::vector<int64_t> failed;
+  if (st == IFL_OK) st = poly_filter(d->poly, c, &failed);
+  if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) return IFL_OK;  // CG needs less memory
+  *done = true;
+  if (st != IFL_OK) return st;
+  const int64_t L = h->op.field_len;
+  ifl_status agg = IFL_OK;
+  for (int64_t col : failed) {
+    st = filter_single(h, 1, fields + col / n_scales * L, 1, k + col % n_scales, out ? out + col * L : nullptr,
+                       stats ? stats + col : nullptr, energy ? energy + col : nullptr,
+                       ColScratch{d->w.part, d->w.sc, true, true});
+    if (st == IFL_ENOTCONV) agg = st;
+    else if (st != IFL_OK) return st;
+  }
+  if (agg != IFL_OK) return fail(agg, "at least one column did not converge (see stats)");
+  return IFL_OK;
+}
+
+}  // namespace
+
 ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int32_t n_scales, const double* k,
                          double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   IFL_HIP(hipSetDevice(d->device));
+  // the tile width left to the library: the polynomial engine. A fixed width
+  // (1: one solve at a time) asks for CG, and the profile times CG's kernels
+  if (h->opt.batch == 0 && !h->opt.profile) {
+    bool done = false;
+    ifl_status st = filter_poly(h, n_fields, fields, n_scales, k, out, stats, energy, &done);
+    if (done || st != IFL_OK) return st;
+  }
   const bool shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2;
   // order 2 (one complex shift) in complex tiles of first-order operators
   // with narrow rows; other orders, and batch = 1, one column at a time

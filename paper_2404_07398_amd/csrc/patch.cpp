@@ -1,0 +1,355 @@
+// Host side of the polynomial engine: the first-order operator's rows cut
+// into compact patches with halo rings, and the polynomial coefficients of a
+// filter scale.
+#include "poly.h"
+
+#include <algorithm>
+#include <atomic>
+#include <cmath>
+#include <complex>
+#include <thread>
+
+namespace ifl {
+
+namespace {
+
+// Runs f(0) .. f(count - 1) on up to 8 threads, indices dealt in turn.
+template <typename F>
+void parallel_for(int64_t count, const F& f) {
+  const int nt = (int)std::min<int64_t>(count, std::max(1u, std::min(8u, std::thread::hardware_concurrency())));
+  if (nt <= 1) {
+    for (int64_t i = 0; i < count; ++i) f(i);
+    return;
+  }
+  std::vector<std::thread> ts;
+  for (int t = 0; t < nt; ++t)
+    ts.emplace_back([&, t] {
+      for (int64_t i = t; i < count; i += nt) f(i);
+    });
+  for (std::thread& t : ts) t.join();
+}
+
+// Unit graph of an operator: unit u's neighbours other than itself, in
+// increasing order (a unit is a row, or the two rows of a vector dof).
+struct UnitGraph {
+  int64_t n = 0;
+  std::vector<int64_t> ptr;
+  std::vector<int32_t> adj;
+};
+
+UnitGraph unit_graph(int64_t n, int nc, const std::vector<int64_t>& rp, const std::vector<int32_t>& col) {
+  UnitGraph g;
+  g.n = n / nc;
+  g.ptr.assign(g.n + 1, 0);
+  const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8, g.n / 4096));
+  std::vector<std::vector<int32_t>> adj(parts);
+  parallel_for(parts, [&](int64_t p) {
+    std::vector<int32_t>& a = adj[p];
+    for (int64_t u = g.n * p / parts; u < g.n * (p + 1) / parts; ++u) {
+      const size_t from = a.size();
+      for (int64_t r = u * nc; r < (u + 1) * nc; ++r)
+        for (int64_t e = rp[r]; e < rp[r + 1]; ++e)
+          if (col[e] / nc != u) a.push_back(col[e] / nc);
+      if (nc > 1) {
+        std::sort(a.begin() + from, a.end());
+        a.erase(std::unique(a.begin() + from, a.end()), a.end());
+      }
+      g.ptr[u + 1] = (int64_t)(a.size() - from);
+    }
+  });
+  for (int64_t u = 0; u < g.n; ++u) g.ptr[u + 1] += g.ptr[u];
+  g.adj.resize((size_t)g.ptr[g.n]);
+  parallel_for(parts, [&](int64_t p) {
+    std::copy(adj[p].begin(), adj[p].end(), g.adj.begin() + g.ptr[g.n * p / parts]);
+  });
+  return g;
+}
+
+// Recursive bisection of ord[b, e) into 'leaves' ranges of equal size: the
+// range's units in breadth-first order from a peripheral unit, cut in
+// proportion. 'mark' holds a number per unit that only the range it belongs
+// to uses, so ranges are cut by different threads ('fork' levels of them).
+void bisect(const UnitGraph& g, std::vector<int32_t>& ord, std::atomic<int32_t>* mark, int64_t b, int64_t e,
+            int64_t leaves, int32_t node, int fork, std::vector<int64_t>* starts) {
+  if (leaves <= 1) {
+    starts->push_back(b);
+    return;
+  }
+  const auto mo = std::memory_order_relaxed;
+  std::vector<int32_t> queue((size_t)(e - b));
+  for (int64_t i = b; i < e; ++i) mark[ord[i]].store(4 * node, mo);
+  int32_t start = ord[b];
+  for (int pass = 0; pass < 2; ++pass) {
+    const int32_t from = 4 * node + pass, to = from + 1;
+    size_t head = 0, tail = 0;
+    int64_t next = b;
+    int32_t seed = start;
+    while (tail < queue.size()) {
+      if (mark[seed].load(mo) == from) {
+        mark[seed].store(to, mo);
+        queue[tail++] = seed;
+      }
+      for (; head < tail; ++head) {
+        const int32_t u = queue[head];
+        for (int64_t k = g.ptr[u]; k < g.ptr[u + 1]; ++k) {
+          const int32_t v = g.adj[k];
+          if (mark[v].load(mo) == from) {
+            mark[v].store(to, mo);
+            queue[tail++] = v;
+          }
+        }
+      }
+      if (tail < queue.size()) seed = ord[next++];  // another component of the range
+    }
+    start = queue.back();
+  }
+  std::copy(queue.begin(), queue.end(), ord.begin() + b);
+  std::vector<int32_t>().swap(queue);
+  const int64_t left = leaves / 2, cut = b + (e - b) * left / leaves;
+  if (fork > 0) {
+    std::vector<int64_t> right;
+    std::thread t([&] { bisect(g, ord, mark, cut, e, leaves - left, 2 * node + 1, fork - 1, &right); });
+    bisect(g, ord, mark, b, cut, left, 2 * node, fork - 1, starts);
+    t.join();
+    starts->insert(starts->end(), right.begin(), right.end());
+    return;
+  }
+  bisect(g, ord, mark, b, cut, left, 2 * node, 0, starts);
+  bisect(g, ord, mark, cut, e, leaves - left, 2 * node + 1, 0, starts);
+}
+
+}  // namespace
+
+bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
+  const bool own = op.order >= 2;
+  const std::vector<int64_t>& rp = own ? op.k1_row_ptr : op.row_ptr;
+  const std::vector<int32_t>& col = own ? op.k1_col : op.col;
+  const std::vector<double>& val = own ? op.k1_val : op.val;
+  const int nc = op.n_components;
+  if (rp.empty() || (nc != 1 && nc != 2) || op.n % nc) return false;
+  for (double m : op.mass)
+    if (!(m > 0.0)) return false;
+  if (nc == 2)  // a unit is one entity's (east, north) pair
+    for (int64_t i = 0; i < op.n; i += 2)
+      if (op.entity[i] % 2 || op.entity[i + 1] != op.entity[i] + 1) return false;
+  const UnitGraph g = unit_graph(op.n, nc, rp, col);
+  int width = 0;
+  for (int64_t u = 0; u < g.n; ++u) width = std::max(width, (int)(g.ptr[u + 1] - g.ptr[u]));
+  PatchPack& pp = *out;
+  pp = PatchPack();
+  pp.units = g.n;
+  pp.nc = nc;
+  pp.width = width <= 3 ? 3 : (width <= 6 ? 6 : (width <= 8 ? 8 : (width <= 12 ? 12 : 0)));
+  if (pp.width == 0 || (nc == 2 && pp.width > 8) || (nc == 1 && pp.width == 3)) {
+    if (nc == 1 && pp.width == 3) pp.width = 6;
+    else return false;
+  }
+  pp.single = g.n <= poly_single_units(nc, pp.width);
+  pp.cap = pp.single ? (int)g.n : poly_patch_units(nc, pp.width);
+  pp.depth = pp.single ? 0 : poly_patch_depth(nc, pp.width);
+
+  // the order: the parts of the rows' own locality order, each bisected
+  std::vector<int32_t> ord((size_t)g.n);
+  for (int64_t i = 0; i < g.n; ++i) ord[i] = (int32_t)i;
+  std::vector<int64_t> leaf;
+  if (pp.single) {
+    leaf = {0, g.n};
+  } else {
+    // interior units of a patch: what a round patch of the capacity has
+    // left inside its rings, fewer on meshes that would not fill the chip
+    const double side = std::sqrt((double)pp.cap) - 2.0 * pp.depth;
+    const int64_t most = std::max<int64_t>(64, (int64_t)(0.92 * side * side));
+    const int64_t want = std::max<int64_t>(64, std::min<int64_t>(most, (g.n + 255) / 256));
+    const int parts = local_order && g.n >= 32768 ? 8 : 1;
+    std::vector<std::atomic<int32_t>> mark((size_t)g.n);
+    for (int64_t i = 0; i < g.n; ++i) mark[i].store(0, std::memory_order_relaxed);
+    std::vector<std::vector<int64_t>> starts(parts);
+    parallel_for(parts, [&](int64_t p) {
+      const int64_t b = g.n * p / parts, e = g.n * (p + 1) / parts;
+      // tree nodes of part p are numbered from its own root
+      bisect(g, ord, mark.data(), b, e, (e - b + want - 1) / want, parts == 1 ? 1 : 8 + (int32_t)p,
+             parts == 1 ? 3 : 0, &starts[p]);
+    });
+    for (const auto& s : starts) leaf.insert(leaf.end(), s.begin(), s.end());
+    leaf.push_back(g.n);
+  }
+  pp.order = std::move(ord);
+  std::vector<int32_t> pos((size_t)g.n);
+  for (int64_t i = 0; i < g.n; ++i) pos[pp.order[i]] = (int32_t)i;
+
+  // rings of each patch, then its units' neighbours as local numbers; a
+  // patch that outgrows the capacity is cut in two
+  struct Local {
+    int64_t begin, end;
+    std::vector<int32_t> units;  // patch positions: interior, ring 1, ..
+    std::vector<int32_t> ends;   // depth + 1
+    std::vector<uint16_t> idx;   // [k][rows]
+  };
+  const int64_t groups = std::min<int64_t>(8, (int64_t)leaf.size() - 1);
+  std::vector<std::vector<Local>> made(groups);
+  parallel_for(groups, [&](int64_t q) {
+    std::vector<int32_t> loc((size_t)g.n, -1);
+    const int64_t lb = (int64_t)(leaf.size() - 1) * q / groups, le = (int64_t)(leaf.size() - 1) * (q + 1) / groups;
+    std::vector<std::pair<int64_t, int64_t>> todo;
+    for (int64_t l = le - 1; l >= lb; --l) todo.push_back({leaf[l], leaf[l + 1]});
+    while (!todo.empty()) {
+      const auto [b, e] = todo.back();
+      todo.pop_back();
+      Local L{b, e, {}, {}, {}};
+      for (int64_t i = b; i < e; ++i) {
+        loc[i] = (int32_t)(i - b);
+        L.units.push_back((int32_t)i);
+      }
+      L.ends.push_back((int32_t)L.units.size());
+      bool fits = (int64_t)L.units.size() <= pp.cap;
+      size_t from = 0;
+      for (int d = 0; fits && d < pp.depth; ++d) {
+        const size_t to = L.units.size();
+        for (size_t i = from; i < to; ++i) {
+          const int32_t u = pp.order[L.units[i]];
+          for (int64_t k = g.ptr[u]; k < g.ptr[u + 1]; ++k) {
+            const int32_t v = pos[g.adj[k]];
+            if (loc[v] < 0) {
+              loc[v] = 0;
+              L.units.push_back(v);
+            }
+          }
+        }
+        // a ring in increasing position: its rows are read in runs
+        std::sort(L.units.begin() + to, L.units.end());
+        for (size_t i = to; i < L.units.size(); ++i) loc[L.units[i]] = (int32_t)i;
+        from = to;
+        L.ends.push_back((int32_t)L.units.size());
+        fits = (int64_t)L.units.size() <= pp.cap;
+      }
+      if (!fits && e - b > 1) {
+        for (int32_t u : L.units) loc[u] = -1;
+        const int64_t mid = (b + e) / 2;
+        todo.push_back({mid, e});
+        todo.push_back({b, mid});
+        continue;
+      }
+      const size_t rows = pp.depth ? (size_t)L.ends[pp.depth - 1] : L.units.size();
+      L.idx.assign(rows * pp.width, 0);
+      for (size_t i = 0; fits && i < rows; ++i) {
+        const int32_t u = pp.order[L.units[i]];
+        int k = 0;
+        for (int64_t a = g.ptr[u]; a < g.ptr[u + 1]; ++a, ++k) L.idx[k * rows + i] = (uint16_t)loc[pos[g.adj[a]]];
+        for (; k < pp.width; ++k) L.idx[k * rows + i] = (uint16_t)i;
+      }
+      for (int32_t u : L.units) loc[u] = -1;
+      if (!fits) L.units.clear();  // one unit with more neighbours in its rings than the capacity
+      made[q].push_back(std::move(L));
+    }
+  });
+  for (const auto& m : made)
+    for (const Local& L : m) {
+      if (L.units.empty()) return false;
+      PatchInfo info{};
+      info.start = (int32_t)L.begin;
+      info.halo = (int64_t)pp.halo.size();
+      info.idx = (int64_t)pp.idx.size();
+      for (int d = 0; d <= kPolyDepth; ++d) info.end[d] = L.ends[std::min(d, pp.depth)];
+      info.rows = pp.depth ? L.ends[pp.depth - 1] : L.ends[0];
+      pp.patches.push_back(info);
+      pp.halo.insert(pp.halo.end(), L.units.begin() + L.ends[0], L.units.end());
+      pp.idx.insert(pp.idx.end(), L.idx.begin(), L.idx.end());
+      pp.largest = std::max<int>(pp.largest, (int)L.units.size());
+    }
+
+  // entries of M^-1 K by position: [k][units] (nc = 2: four couplings an
+  // entry), the unit's own block apart; and the columns by position
+  const int64_t U = g.n, W = pp.width, bb = nc * nc;
+  pp.val.assign((size_t)(W * U * bb), 0.0);
+  pp.own.assign((size_t)(U * bb), 0.0);
+  pp.col.assign((size_t)(W * U), 0);
+  pp.mass.resize((size_t)(U * nc));
+  const int64_t pieces = std::max<int64_t>(1, std::min<int64_t>(8, U / 4096));
+  parallel_for(pieces, [&](int64_t q) {
+    for (int64_t i = U * q / pieces; i < U * (q + 1) / pieces; ++i) {
+      const int32_t u = pp.order[i];
+      const int64_t a0 = g.ptr[u], a1 = g.ptr[u + 1];
+      for (int64_t k = 0; k < W; ++k) pp.col[k * U + i] = k < a1 - a0 ? pos[g.adj[a0 + k]] : (int32_t)i;
+      for (int c = 0; c < nc; ++c) {
+        const int64_t r = (int64_t)u * nc + c;
+        pp.mass[i * nc + c] = op.mass[r];
+        const double im = 1.0 / op.mass[r];
+        for (int64_t e = rp[r]; e < rp[r + 1]; ++e) {
+          const int32_t v = col[e] / nc, cc = col[e] % nc;
+          if (v == u) {
+            pp.own[i * bb + c * nc + cc] = val[e] * im;
+          } else {
+            const int64_t k = std::lower_bound(g.adj.begin() + a0, g.adj.begin() + a1, v) - (g.adj.begin() + a0);
+            pp.val[(k * U + i) * bb + c * nc + cc] = val[e] * im;
+          }
+        }
+      }
+    }
+  });
+  double mlo = pp.mass[0], mhi = pp.mass[0];
+  for (double m : pp.mass) {
+    mlo = std::min(mlo, m);
+    mhi = std::max(mhi, m);
+  }
+  pp.mass_ratio = mhi / mlo;
+  return true;
+}
+
+std::vector<double> poly_coefficients(int order, double c, double lam, double tol, int max_degree) {
+  // in extended precision: the coefficients of order 2 are read with the
+  // weight 1 + c lam^2, the condition number of the system
+  using real = long double;
+  using cx = std::complex<real>;
+  const int n = order;
+  if (n != 1 && n != 2) return {};
+  // one zero of 1 + c x^n in z (n = 2: the other is its conjugate), and
+  // rho, z = (rho + 1 / rho) / 2, |rho| > 1
+  const real at = 2.0L * std::pow((real)c, -1.0L / n) / (real)lam;
+  const cx z = n == 1 ? cx(-at - 1.0L, 0.0L) : cx(-1.0L, at);
+  const cx root = std::sqrt(z - (real)1) * std::sqrt(z + (real)1);
+  cx rho = z + root;
+  if (std::abs(rho) < 1.0L) rho = z - root;
+  const real slow = std::abs(rho);
+  if (!(slow > 1.0L) || !std::isfinite((double)slow)) return {};
+  // a of the residual a_0 T_{m+1} (n = 1), a_0 T_{m+1} + a_1 T_{m+2} (n = 2,
+  // real and imaginary part of its value 1 at z); its size
+  real a[2] = {0.0L, 0.0L};
+  auto solve = [&](int m) {
+    const cx p0 = std::pow(rho, (real)(m + 1)), t0 = 0.5L * (p0 + (real)1 / p0);
+    if (n == 1) {
+      a[0] = 1.0L / t0.real();
+      return std::abs(a[0]);
+    }
+    const cx p1 = p0 * rho, t1 = 0.5L * (p1 + (real)1 / p1);
+    const real det = t0.real() * t1.imag() - t1.real() * t0.imag();
+    a[0] = t1.imag() / det;
+    a[1] = -t0.imag() / det;
+    return std::abs(a[0]) + std::abs(a[1]);
+  };
+  const double guess = std::log(2.0 / tol) / (double)std::log(slow);
+  if (!(guess < 4.0 * max_degree + 64.0)) return {};
+  int m = std::max(0, (int)guess - 4);
+  while (m > 0 && solve(m) <= tol) m -= std::min(m, 4);
+  while (m <= max_degree && !(solve(m) <= tol)) ++m;
+  if (m > max_degree) return {};
+  // p = (1 - R) / (1 + c x^n): the factors z - z_i divided out one by one,
+  // from the highest term down (the growing direction of the recurrence)
+  std::vector<cx> q(m + n + 1, (real)0);
+  q[0] = (real)1;
+  for (int j = 0; j < n; ++j) q[m + 1 + j] -= a[j];
+  for (int i = 0; i < n; ++i) {
+    const cx zi = i == 0 ? z : std::conj(z);
+    const int d = (int)q.size() - 1;
+    std::vector<cx> s(d + 2, (real)0);
+    for (int k = d; k >= 1; --k) s[k - 1] = (real)2 * q[k] + (real)2 * zi * s[k] - s[k + 1];
+    s[0] *= 0.5L;
+    s.resize(d);
+    q = std::move(s);
+  }
+  const real lead = (real)c * std::pow(0.5L * (real)lam, (real)n);
+  std::vector<double> out(q.size());
+  for (size_t k = 0; k < q.size(); ++k) out[k] = (double)(q[k] / lead).real();
+  return out;
+}
+
+}  // namespace ifl

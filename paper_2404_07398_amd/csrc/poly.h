@@ -1,0 +1,100 @@
+// The polynomial engine: all scales of a field from one Chebyshev sequence
+// of the first-order operator (host and device declarations).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <vector>
+
+#include "internal.h"
+
+namespace ifl {
+
+// Rings of halo units around a patch, at most.
+constexpr int kPolyDepth = 8;
+
+// Threads of a patch's workgroup and units per thread; what a patch holds.
+constexpr int kPolyThreads = 512;
+constexpr int kPolySingleThreads = 1024;
+constexpr int poly_slots(int nc, int width) { return nc == 1 ? (width <= 8 ? 4 : 2) : (width <= 3 ? 2 : 1); }
+constexpr int poly_patch_units(int nc, int width) {
+  return nc == 1 ? kPolyThreads * poly_slots(nc, width) : 1024;
+}
+constexpr int poly_single_units(int nc, int width) { return kPolySingleThreads * poly_slots(nc, width); }
+constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 8 ? 8 : 4; }
+
+struct PatchInfo {
+  int32_t start;                // first interior position; the interior is contiguous
+  int32_t rows;                 // units with local neighbour numbers (all but the last ring)
+  int32_t end[kPolyDepth + 1];  // local units up to and with ring d
+  int64_t halo;                 // first halo entry (the positions of local units end[0] ..)
+  int64_t idx;                  // first neighbour number, [width][rows]
+};
+
+// M^-1 K in the patches' own order of the units ("positions"). A unit is a
+// row, or the two rows of a vector dof.
+struct PatchPack {
+  int64_t units = 0;
+  int nc = 1;      // components of a unit
+  int width = 6;   // neighbour entries per unit (padded with the unit itself, value 0)
+  int cap = 0;     // units a patch may hold
+  int depth = 0;   // rings
+  int largest = 0; // units of the largest patch
+  bool single = false;          // one patch without rings holds the mesh
+  double mass_ratio = 1.0;      // largest mass / smallest
+  std::vector<int32_t> order;   // position -> unit of the operator
+  std::vector<PatchInfo> patches;
+  std::vector<int32_t> halo;
+  std::vector<uint16_t> idx;
+  std::vector<int32_t> col;     // [width][units], positions
+  std::vector<double> val;      // [width][units][nc * nc]
+  std::vector<double> own;      // [units][nc * nc]
+  std::vector<double> mass;     // [units * nc]
+};
+
+// local_order: the rows are in the library's locality order. false (out
+// unspecified): the engine does not take this operator (rows too wide, or a
+// mass that is not positive).
+bool build_patches(const HostOperator& op, bool local_order, PatchPack* out);
+
+// Coefficients of the polynomial p of one filter scale, p(z) = sum_k c_k T_k(z)
+// on the spectrum [0, lam] of M^-1 K, z = 2 x / lam - 1, order 1 or 2: the
+// residual 1 - (1 + c x^n) p is the combination of T_{m+1} .. T_{m+n} that is
+// 1 at the n zeros of 1 + c x^n; m, the degree of p, is the least at which it
+// stays within tol on [-1, 1]. Empty: a degree above max_degree, or another
+// order.
+std::vector<double> poly_coefficients(int order, double c, double lam, double tol, int max_degree);
+
+// --------------------------------------------------------------- device side
+struct PolyState;  // defined in poly.hip
+
+// Device copy of the patches and the bound on the spectrum, on the current
+// device; *out stays NULL where the engine does not take the operator.
+ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out);
+void poly_destroy(PolyState* ps);
+
+struct PolyCall {
+  int order = 1;
+  double gamma = 0.5, rtol = 1e-12;
+  int max_iter = 20000;
+  int32_t n_fields = 0, n_scales = 0;
+  const double* fields = nullptr;  // device, n_fields x field_len
+  const double* k = nullptr;
+  double* out = nullptr;           // n_fields x n_scales x field_len, or NULL
+  bool out_host = false;
+  ifl_solve_stats* stats = nullptr;
+  double* energy = nullptr;
+  hipStream_t stream = nullptr;
+};
+
+// Whether the engine should run the call: its scales' degrees are within
+// max_iter, and its products with the operator are fewer than CG would need.
+bool poly_takes(const PolyState* ps, const PolyCall& call);
+
+// Filters every column; the numbers (field * n_scales + scale) of columns
+// whose true residual misses the tolerance go to *failed (their outputs hold
+// what was reached). IFL_ENOMEM: nothing was written.
+ifl_status poly_filter(PolyState* ps, const PolyCall& call, std::vector<int64_t>* failed);
+
+}  // namespace ifl

@@ -1,0 +1,952 @@
+// The polynomial engine: every scale of a field from one sequence of products
+// with the first-order operator.
+//
+// The filter of order n at scale factor c is f(A), f(x) = 1 / (1 + c x^n),
+// of A = M^-1 K alone, so all scales (and both orders) of a field share the
+// vectors t_k = T_k(2 A / lam - 1) phi of the Chebyshev recurrence
+//   t_{k+1} = (4 / lam) A t_k - 2 t_k - t_{k-1},
+// and a scale is the sum over k of its coefficients c_k times t_k. Where CG
+// takes one product per scale and iteration, a field with S scales takes the
+// products of its largest scale once; and the recurrence has no inner
+// products, so nothing has to be known across the mesh between two steps.
+// That is what the step kernel uses: a workgroup keeps a patch of the mesh
+// with its rings of halo units in LDS and advances it several steps per
+// launch.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <chrono>
+#include <cmath>
+#include <cstring>
+#include <string>
+
+#include "poly.h"
+
+namespace ifl {
+
+#define IFL_HIP(expr)                                                                          \
+  do {                                                                                         \
+    hipError_t e_ = (expr);                                                                    \
+    if (e_ != hipSuccess)                                                                      \
+      return fail(IFL_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_));            \
+  } while (0)
+
+namespace {
+
+constexpr int kXcd = 8;
+constexpr int kRed = 256;       // threads of the row kernels
+constexpr int kRedBlocks = 512; // blocks of the row kernels that write partial sums, at most
+constexpr int kLanczos = 32;    // steps of the spectrum estimate
+constexpr int kMaxGroup = 16;   // scales summed together
+
+struct PolyDev {
+  const PatchInfo* info = nullptr;
+  const int32_t* halo = nullptr;
+  const uint16_t* idx = nullptr;
+  const int32_t* col = nullptr;
+  const double* val = nullptr;
+  const double* own = nullptr;
+  const double* mass = nullptr;
+  const int32_t* entity = nullptr;  // caller index of each row
+  const int32_t* row_of = nullptr;  // row of each caller index, -1: none
+  int64_t units = 0, rows = 0, np = 0, field_len = 0;
+  int npatch = 0;
+};
+
+template <int NC>
+struct Unit;  // the NC components of a unit
+template <>
+struct Unit<1> {
+  double v[1];
+};
+template <>
+struct alignas(16) Unit<2> {
+  double v[2];
+};
+
+// Position of local unit i of a patch.
+__device__ __forceinline__ int64_t unit_at(const PatchInfo& p, const int32_t* halo, int i) {
+  return i < p.end[0] ? (int64_t)p.start + i : (int64_t)halo[p.halo + i - p.end[0]];
+}
+
+// 'steps' steps of the recurrence on one patch, field after field.
+//
+// A thread owns SLOTS units: their rows of (4 / lam) A stay in registers for
+// all steps and fields, their t_k and t_{k-1} too; the neighbours' t_k come
+// from LDS, written to the other buffer for the next step. Step j needs the
+// rings up to steps - j only, a prefix of the local numbering. With one
+// patch for the whole mesh (no rings) the steps are not limited.
+//
+// prev == nullptr: the sequence starts (cur = t_0, the first step is halved).
+// out: plane of the first new vector, the next ones 'plane' doubles on.
+template <int NC, int W, int SLOTS, int T>
+__global__ __launch_bounds__(T) void k_poly_steps(PolyDev m, const double* __restrict__ prev,
+                                                  const double* __restrict__ cur, double* __restrict__ out,
+                                                  int64_t plane, int n_fields, int steps, int ringed, double scale) {
+  // consecutive patches on one XCD: their halos overlap in its L2
+  const int per = (m.npatch + kXcd - 1) / kXcd;
+  const int pid = (int)(blockIdx.x % kXcd) * per + (int)(blockIdx.x / kXcd);
+  if (pid >= m.npatch || (int)(blockIdx.x / kXcd) >= per) return;
+  __shared__ Unit<NC> lds[2][T * SLOTS];
+  const PatchInfo p = m.info[pid];
+  const int tid = threadIdx.x;
+  const int inside = p.end[0];
+  const int loaded = p.end[ringed ? steps : 0];
+  const int first_lim = p.end[ringed ? steps - 1 : 0];
+  constexpr int BB = NC * NC;
+  double val[SLOTS][W][BB], own[SLOTS][BB];
+  uint32_t nb[SLOTS][(W + 1) / 2];
+  int64_t at[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int i = tid + s * T;
+    at[s] = i < loaded ? unit_at(p, m.halo, i) : 0;
+    if (i < first_lim) {
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        const uint32_t id = m.idx[p.idx + (int64_t)k * p.rows + i];
+        if (k % 2 == 0) nb[s][k / 2] = id;
+        else nb[s][k / 2] |= id << 16;
+#pragma unroll
+        for (int b = 0; b < BB; ++b) val[s][k][b] = scale * m.val[((int64_t)k * m.units + at[s]) * BB + b];
+      }
+#pragma unroll
+      for (int b = 0; b < BB; ++b) own[s][b] = scale * m.own[at[s] * BB + b] - (b % (NC + 1) == 0 ? 2.0 : 0.0);
+    } else {
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        nb[s][k / 2] = 0;
+#pragma unroll
+        for (int b = 0; b < BB; ++b) val[s][k][b] = 0.0;
+      }
+#pragma unroll
+      for (int b = 0; b < BB; ++b) own[s][b] = 0.0;
+    }
+  }
+  for (int f = blockIdx.y; f < n_fields; f += gridDim.y) {
+    const Unit<NC>* cf = reinterpret_cast<const Unit<NC>*>(cur + (int64_t)f * m.np);
+    const Unit<NC>* pf = reinterpret_cast<const Unit<NC>*>(prev + (prev ? (int64_t)f * m.np : 0));
+    Unit<NC> tc[SLOTS], tp[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      const int i = tid + s * T;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) tc[s].v[c] = tp[s].v[c] = 0.0;
+      if (i < loaded) tc[s] = cf[at[s]];
+      if (prev && i < first_lim) tp[s] = pf[at[s]];
+    }
+    __syncthreads();  // the previous field's last step has been read
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (tid + s * T < loaded) lds[0][tid + s * T] = tc[s];
+    __syncthreads();
+    double* of = out + (int64_t)f * m.np;
+    for (int j = 1; j <= steps; ++j, of += plane) {
+      const int lim = p.end[ringed ? steps - j : 0];
+      const Unit<NC>* from = lds[(j - 1) & 1];
+      Unit<NC>* to = lds[j & 1];
+      const double half = !prev && j == 1 ? 0.5 : 1.0;
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) {
+        const int i = tid + s * T;
+        if (i < lim) {
+          double acc[NC];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            acc[c] = -tp[s].v[c];
+#pragma unroll
+            for (int d = 0; d < NC; ++d) acc[c] += own[s][c * NC + d] * tc[s].v[d];
+          }
+#pragma unroll
+          for (int k = 0; k < W; ++k) {
+            const uint32_t id = k % 2 == 0 ? nb[s][k / 2] & 0xffffu : nb[s][k / 2] >> 16;
+            const Unit<NC> t = from[id];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+              for (int d = 0; d < NC; ++d) acc[c] += val[s][k][c * NC + d] * t.v[d];
+          }
+          tp[s] = tc[s];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) tc[s].v[c] = half * acc[c];
+          to[i] = tc[s];
+          if (i < inside) reinterpret_cast<Unit<NC>*>(of)[at[s]] = tc[s];
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Block-wide sum of one value per thread in a fixed order (valid in thread 0).
+template <int T>
+__device__ __forceinline__ double block_total(double v, double* lds) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  __syncthreads();
+  if (threadIdx.x % 64 == 0) lds[threadIdx.x / 64] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < T / 64; ++w) t += lds[w];
+  return t;
+}
+
+// Fields in the caller's numbering -> rows (grid.y = field), with ||M phi||^2
+// by block; a NaN or Inf raises *bad.
+__global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __restrict__ fields,
+                                                    double* __restrict__ phi, double* __restrict__ part,
+                                                    int* __restrict__ bad) {
+  __shared__ double lds[kRed / 64];
+  const double* src = fields + (int64_t)blockIdx.y * m.field_len;
+  double* dst = phi + (int64_t)blockIdx.y * m.np;
+  double sum = 0.0;
+  bool ok = true;
+  for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.np; r += (int64_t)gridDim.x * kRed) {
+    double v = 0.0;
+    if (r < m.rows) {
+      v = src[m.entity[r]];
+      ok = ok && isfinite(v);
+      const double b = m.mass[r] * v;
+      sum += b * b;
+    }
+    dst[r] = v;
+  }
+  if (!ok) *bad = 1;
+  const double t = block_total<kRed>(sum, lds);
+  if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
+}
+
+// x (rows x SC) = or += sum over k of coef[k][s] t_k, one thread per row
+// (grid.y = field): each t_k is read once for SC scales, the coefficients
+// come through the scalar cache. phi != nullptr: the sum starts with
+// coef[0] phi, and coef + SC belongs to the first of the n planes.
+template <int SC>
+__global__ __launch_bounds__(kRed) void k_poly_sum(const double* __restrict__ phi, const double* __restrict__ t,
+                                                   int64_t plane, int64_t np, int n,
+                                                   const double* __restrict__ coef, double* __restrict__ x) {
+  const int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x;
+  if (r >= np) return;
+  const int64_t at = (int64_t)blockIdx.y * np + r;
+  double acc[SC];
+  double* xr = x + at * SC;
+  if (phi) {
+    const double v = phi[at];
+#pragma unroll
+    for (int s = 0; s < SC; ++s) acc[s] = coef[s] * v;
+    coef += SC;
+  } else {
+#pragma unroll
+    for (int s = 0; s < SC; ++s) acc[s] = xr[s];
+  }
+  const double* tr = t + at;
+#pragma unroll 8
+  for (int k = 0; k < n; ++k) {
+    const double v = tr[(int64_t)k * plane];
+#pragma unroll
+    for (int s = 0; s < SC; ++s) acc[s] += coef[(int64_t)k * SC + s] * v;
+  }
+#pragma unroll
+  for (int s = 0; s < SC; ++s) xr[s] = acc[s];
+}
+
+// Lanes of a row of SC scales, and a lane's scales.
+constexpr int lane_scales(int sc) { return sc >= 2 ? 2 : 1; }
+
+template <int V>
+struct Lane;
+template <>
+struct Lane<1> {
+  double v[1];
+};
+template <>
+struct alignas(16) Lane<2> {
+  double v[2];
+};
+
+// The row's product with A: y = sum_j A_rj x_j for the lane's scales.
+template <int NC, int SC>
+__device__ __forceinline__ Lane<lane_scales(SC)> row_product(const PolyDev& m, int width, const double* xf, int64_t r,
+                                                             int q) {
+  constexpr int V = lane_scales(SC);
+  const Lane<V>* xt = reinterpret_cast<const Lane<V>*>(xf);
+  constexpr int LPR = SC / V, BB = NC * NC;
+  const int64_t u = r / NC;
+  const int c = (int)(r % NC);
+  Lane<V> y;
+#pragma unroll
+  for (int e = 0; e < V; ++e) y.v[e] = 0.0;
+#pragma unroll
+  for (int d = 0; d < NC; ++d) {
+    const double a = m.own[u * BB + c * NC + d];
+    const Lane<V> t = xt[(u * NC + d) * LPR + q];
+#pragma unroll
+    for (int e = 0; e < V; ++e) y.v[e] += a * t.v[e];
+  }
+  for (int k = 0; k < width; ++k) {
+    const int64_t j = m.col[(int64_t)k * m.units + u];
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {
+      const double a = m.val[((int64_t)k * m.units + u) * BB + c * NC + d];
+      const Lane<V> t = xt[(j * NC + d) * LPR + q];
+#pragma unroll
+      for (int e = 0; e < V; ++e) y.v[e] += a * t.v[e];
+    }
+  }
+  return y;
+}
+
+// y = A x (grid.y = field).
+template <int NC, int SC>
+__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, int width, const double* __restrict__ x,
+                                                     double* __restrict__ y) {
+  constexpr int V = lane_scales(SC), LPR = SC / V;
+  const int64_t g = (int64_t)blockIdx.x * kRed + threadIdx.x;
+  const int64_t r = g / LPR;
+  if (r >= m.rows) return;
+  const int64_t base = (int64_t)blockIdx.y * m.np * SC;
+  const int q = (int)(g % LPR);
+  reinterpret_cast<Lane<V>*>(y + base)[r * LPR + q] = row_product<NC, SC>(m, width, x + base, r, q);
+}
+
+struct GroupScales {
+  double c[kMaxGroup];      // scale factors
+  int32_t column[kMaxGroup]; // index of the scale in the call's list, -1: padding
+};
+
+// FP64 true residual M (phi - x - c A z), z = x (order 1) or A x (order 2):
+// block sums of its square, of (M x)^2 and of M x^2 per scale.
+template <int NC, int SC>
+__global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, int width, const double* __restrict__ phi,
+                                                     const double* __restrict__ x, const double* __restrict__ z,
+                                                     GroupScales gs, double* __restrict__ part) {
+  constexpr int V = lane_scales(SC), LPR = SC / V;
+  __shared__ double lds[kRed / 64][LPR][3 * V];
+  const int64_t base = (int64_t)blockIdx.y * m.np * SC;
+  const double* pf = phi + (int64_t)blockIdx.y * m.np;
+  const int q = threadIdx.x % LPR;
+  double sum[3 * V];
+#pragma unroll
+  for (int e = 0; e < 3 * V; ++e) sum[e] = 0.0;
+  constexpr int RPB = kRed / LPR;
+  for (int64_t r = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR; r < m.rows; r += (int64_t)gridDim.x * RPB) {
+    const Lane<V> y = row_product<NC, SC>(m, width, z + base, r, q);
+    const Lane<V> xr = reinterpret_cast<const Lane<V>*>(x + base)[r * LPR + q];
+    const double mr = m.mass[r], ph = pf[r];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const double res = mr * (ph - xr.v[e] - gs.c[q * V + e] * y.v[e]);
+      const double mx = mr * xr.v[e];
+      sum[e] += res * res;
+      sum[V + e] += mx * mx;
+      sum[2 * V + e] += mx * xr.v[e];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 3 * V; ++e) {
+#pragma unroll
+    for (int off = 32; off >= LPR; off >>= 1) sum[e] += __shfl_xor(sum[e], off, 64);
+  }
+  if (threadIdx.x % 64 < LPR)
+#pragma unroll
+    for (int e = 0; e < 3 * V; ++e) lds[threadIdx.x / 64][q][e] = sum[e];
+  __syncthreads();
+  if (threadIdx.x < LPR) {
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        double t = 0.0;
+        for (int w = 0; w < kRed / 64; ++w) t += lds[w][threadIdx.x][k * V + e];
+        part[(((int64_t)blockIdx.y * SC + threadIdx.x * V + e) * 3 + k) * gridDim.x + blockIdx.x] = t;
+      }
+  }
+}
+
+// Sums of 'g' partials: block b of the grid writes dst[b].
+__global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ part, int g, double* __restrict__ dst) {
+  __shared__ double lds[kRed / 64];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < g; i += kRed) s += part[(int64_t)blockIdx.x * g + i];
+  const double t = block_total<kRed>(s, lds);
+  if (threadIdx.x == 0) dst[blockIdx.x] = t;
+}
+
+// x (rows x SC) -> the caller's numbering, a thread per caller entry
+// (grid.y = field); entries without a row are 0. Nothing is written once a
+// field was found bad.
+template <int SC>
+__global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __restrict__ x, GroupScales gs,
+                                                   int n_scales, const int* __restrict__ bad,
+                                                   double* __restrict__ out) {
+  if (*bad) return;
+  const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
+  if (i >= m.field_len) return;
+  const int32_t r = m.row_of[i];
+  double v[SC];
+  const double* xr = x + ((int64_t)blockIdx.y * m.np + (r < 0 ? 0 : r)) * SC;
+#pragma unroll
+  for (int s = 0; s < SC; ++s) v[s] = r < 0 ? 0.0 : xr[s];
+  double* o = out + (int64_t)blockIdx.y * n_scales * m.field_len + i;
+#pragma unroll
+  for (int s = 0; s < SC; ++s)
+    if (gs.column[s] >= 0) o[gs.column[s] * m.field_len] = v[s];
+}
+
+// ---- the spectrum's upper end: Lanczos on A in the M inner product ----
+// u_j unnormalised, beta_j = ||u_{j+1}||_M; every block finishes the previous
+// launch's sums in the same order, so nothing returns to the host.
+__device__ __forceinline__ double partial_total(const double* part, int g, double* lds) {
+  double s = 0.0;
+  for (int i = threadIdx.x; i < g; i += kRed) s += part[i];
+  return block_total<kRed>(s, lds);
+}
+
+__global__ __launch_bounds__(kRed) void k_lanczos_start(PolyDev m, double* __restrict__ u, double* __restrict__ beta) {
+  __shared__ double lds[kRed / 64];
+  double sum = 0.0;
+  for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
+    uint64_t h = (uint64_t)m.entity[r] * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+    h ^= h >> 29;
+    h *= 0xBF58476D1CE4E5B9ull;
+    h ^= h >> 32;
+    const double v = (double)(int64_t)h * 1.0842021724855044e-19;
+    u[r] = v;
+    sum += m.mass[r] * v * v;
+  }
+  const double t = block_total<kRed>(sum, lds);
+  if (threadIdx.x == 0) beta[blockIdx.x] = t;
+}
+
+// w = A v - beta v_prev (v = u / b, v_prev = u_prev / b_prev, beta = b), (w, v)
+template <int NC>
+__global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, int width, const double* __restrict__ u,
+                                                          const double* __restrict__ u_prev, double* __restrict__ w,
+                                                          const double* __restrict__ beta,
+                                                          const double* __restrict__ beta_prev,
+                                                          double* __restrict__ alpha) {
+  __shared__ double lds[kRed / 64];
+  const double b = sqrt(partial_total(beta, gridDim.x, lds));
+  const double bp = beta_prev ? sqrt(partial_total(beta_prev, gridDim.x, lds)) : 0.0;
+  const double inv = b > 0.0 ? 1.0 / b : 0.0, invp = bp > 0.0 ? b / bp : 0.0;
+  double sum = 0.0;
+  for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
+    double y = inv * row_product<NC, 1>(m, width, u, r, 0).v[0];
+    if (beta_prev) y -= invp * u_prev[r];
+    w[r] = y;
+    sum += m.mass[r] * y * u[r] * inv;
+  }
+  const double t = block_total<kRed>(sum, lds);
+  if (threadIdx.x == 0) alpha[blockIdx.x] = t;
+}
+
+// w -= alpha v; ||w||_M^2
+__global__ __launch_bounds__(kRed) void k_lanczos_next(PolyDev m, const double* __restrict__ u, double* __restrict__ w,
+                                                       const double* __restrict__ beta,
+                                                       const double* __restrict__ alpha,
+                                                       double* __restrict__ beta_next) {
+  __shared__ double lds[kRed / 64];
+  const double b = sqrt(partial_total(beta, gridDim.x, lds));
+  const double a = partial_total(alpha, gridDim.x, lds);
+  const double f = b > 0.0 ? a / b : 0.0;
+  double sum = 0.0;
+  for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
+    const double y = w[r] - f * u[r];
+    w[r] = y;
+    sum += m.mass[r] * y * y;
+  }
+  const double t = block_total<kRed>(sum, lds);
+  if (threadIdx.x == 0) beta_next[blockIdx.x] = t;
+}
+
+// Largest eigenvalue of the symmetric tridiagonal (a, b) by bisection.
+double largest_eigenvalue(const std::vector<double>& a, const std::vector<double>& b) {
+  double lo = a[0], hi = a[0];
+  const int n = (int)a.size();
+  for (int i = 0; i < n; ++i) {
+    const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i + 1 < n ? std::fabs(b[i]) : 0.0);
+    lo = std::min(lo, a[i] - r);
+    hi = std::max(hi, a[i] + r);
+  }
+  for (int it = 0; it < 100; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    double q = 1.0;
+    bool below = true;  // no eigenvalue above mid: all pivots of mid - T positive
+    for (int i = 0; i < n && below; ++i) {
+      q = mid - a[i] - (i > 0 ? b[i - 1] * b[i - 1] / q : 0.0);
+      if (!(q > 0.0)) below = false;
+    }
+    (below ? hi : lo) = mid;
+  }
+  return hi;
+}
+
+}  // namespace
+
+struct PolyState {
+  int device = 0;
+  PolyDev m;
+  int nc = 1, width = 6, depth = 0, largest = 0;
+  bool single = false;
+  double lam = 0.0;         // upper end of the spectrum of A, with its margin
+  double lam_typical = 0.0; // the same of a mesh whose rows were all like 95% of the rows
+  double mass_ratio = 1.0, mass_sum = 0.0;
+  // work space, kept between calls
+  double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *part = nullptr, *coef = nullptr, *stage = nullptr;
+  size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, part_n = 0, coef_n = 0, stage_n = 0;
+  int* bad = nullptr;
+  double* sums = nullptr;       // device totals
+  size_t sums_n = 0;
+  double* host = nullptr;       // pinned: totals and the bad flag
+  size_t host_n = 0;
+  double* host_coef = nullptr;  // pinned
+  size_t host_coef_n = 0;
+};
+
+namespace {
+
+template <typename T>
+ifl_status up(const T** p, const std::vector<T>& v) {
+  T* d = nullptr;
+  if (hipMalloc((void**)&d, std::max<size_t>(1, v.size()) * sizeof(T)) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(IFL_ENOMEM, "hipMalloc failed for the patches");
+  }
+  *p = d;
+  if (!v.empty()) IFL_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+  return IFL_OK;
+}
+
+ifl_status grow(double** p, size_t* have, size_t want) {
+  if (*have >= want) return IFL_OK;
+  if (*p) (void)hipFree(*p);
+  *p = nullptr;
+  *have = 0;
+  if (hipMalloc((void**)p, want * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return fail(IFL_ENOMEM, "hipMalloc failed for the polynomial engine's work space");
+  }
+  *have = want;
+  return IFL_OK;
+}
+
+ifl_status grow_host(double** p, size_t* have, size_t want) {
+  if (*have >= want) return IFL_OK;
+  if (*p) (void)hipHostFree(*p);
+  *p = nullptr;
+  *have = 0;
+  if (hipHostMalloc((void**)p, want * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return fail(IFL_ENOMEM, "hipHostMalloc failed for the polynomial engine's work space");
+  }
+  *have = want;
+  return IFL_OK;
+}
+
+int red_blocks(int64_t items) { return (int)std::max<int64_t>(1, std::min<int64_t>(kRedBlocks, (items + kRed - 1) / kRed)); }
+
+template <int NC, int W, int SLOTS, int T>
+void steps_of(const PolyState* ps, const double* prev, const double* cur, double* out, int64_t plane, int F, int steps,
+              int ringed, hipStream_t s) {
+  const int per = (ps->m.npatch + kXcd - 1) / kXcd;
+  // fields side by side only where the patches alone do not fill the chip:
+  // a workgroup that walks the fields reads its rows of A once
+  const int gx = per * kXcd;
+  const int gy = std::min(F, std::max(1, 1024 / std::max(1, ps->m.npatch)));
+  k_poly_steps<NC, W, SLOTS, T><<<dim3(gx, gy), T, 0, s>>>(ps->m, prev, cur, out, plane, F, steps, ringed,
+                                                           4.0 / ps->lam);
+}
+
+void launch_steps(const PolyState* ps, const double* prev, const double* cur, double* out, int64_t plane, int F,
+                  int steps, hipStream_t s) {
+  const int L = ps->largest;
+  if (ps->nc == 1) {
+    if (ps->single) {
+      if (ps->width == 6) {
+        if (L <= 1024) steps_of<1, 6, 1, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+        else if (L <= 2048) steps_of<1, 6, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+        else steps_of<1, 6, 4, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+      } else if (ps->width == 8) {
+        if (L <= 2048) steps_of<1, 8, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+        else steps_of<1, 8, 4, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+      } else {
+        steps_of<1, 12, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+      }
+    } else if (ps->width == 6) {
+      if (L <= 2 * kPolyThreads) steps_of<1, 6, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+      else steps_of<1, 6, 4, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+    } else if (ps->width == 8) {
+      if (L <= 2 * kPolyThreads) steps_of<1, 8, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+      else steps_of<1, 8, 4, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+    } else {
+      steps_of<1, 12, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+    }
+  } else {
+    const int ringed = ps->single ? 0 : 1;
+    if (ps->width == 3) {
+      if (L <= 1024) steps_of<2, 3, 2, 512>(ps, prev, cur, out, plane, F, steps, ringed, s);
+      else steps_of<2, 3, 2, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
+    } else if (ps->width == 6) {
+      if (L <= 512) steps_of<2, 6, 1, 512>(ps, prev, cur, out, plane, F, steps, ringed, s);
+      else steps_of<2, 6, 1, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
+    } else {
+      steps_of<2, 8, 1, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
+    }
+  }
+}
+
+void launch_sum(int sc, const double* phi, const double* t, int64_t plane, int64_t np, int n, const double* coef,
+                double* x, int F, hipStream_t s) {
+  const dim3 g((unsigned)((np + kRed - 1) / kRed), (unsigned)F);
+  switch (sc) {
+    case 1: k_poly_sum<1><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+    case 2: k_poly_sum<2><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+    case 4: k_poly_sum<4><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+    case 8: k_poly_sum<8><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+    default: k_poly_sum<16><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+  }
+}
+
+template <int NC, int SC>
+void check_of(const PolyState* ps, int order, const double* phi, const double* x, double* z, const GroupScales& gs,
+              double* part, int G, int F, hipStream_t s) {
+  constexpr int LPR = SC / lane_scales(SC);
+  const double* src = x;
+  if (order == 2) {
+    const dim3 g((unsigned)((ps->m.rows * LPR + kRed - 1) / kRed), (unsigned)F);
+    k_poly_apply<NC, SC><<<g, kRed, 0, s>>>(ps->m, ps->width, x, z);
+    src = z;
+  }
+  k_poly_check<NC, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, ps->width, phi, x, src, gs, part);
+}
+
+template <int NC>
+void launch_check(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z,
+                  const GroupScales& gs, double* part, int G, int F, hipStream_t s) {
+  switch (sc) {
+    case 1: check_of<NC, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 2: check_of<NC, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 4: check_of<NC, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 8: check_of<NC, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    default: check_of<NC, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
+  }
+}
+
+void launch_out(const PolyState* ps, int sc, const double* x, const GroupScales& gs, int S, double* out, int F,
+                hipStream_t s) {
+  const dim3 g((unsigned)((ps->m.field_len + kRed - 1) / kRed), (unsigned)F);
+  switch (sc) {
+    case 1: k_poly_out<1><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+    case 2: k_poly_out<2><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+    case 4: k_poly_out<4><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+    case 8: k_poly_out<8><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+    default: k_poly_out<16><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+  }
+}
+
+ifl_status estimate_spectrum(PolyState* ps, hipStream_t s) {
+  const PolyDev& m = ps->m;
+  const int G = std::min(256, red_blocks(m.rows));
+  double *u[3] = {}, *ab = nullptr;
+  ifl_status st = IFL_OK;
+  size_t n0 = 0;
+  for (double*& v : u)
+    if (st == IFL_OK) st = grow(&v, &(n0 = 0), (size_t)m.np);
+  if (st == IFL_OK) st = grow(&ab, &(n0 = 0), (size_t)(2 * kLanczos + 1) * G);
+  std::vector<double> parts((size_t)(2 * kLanczos + 1) * G);
+  if (st == IFL_OK) {
+    double *beta = ab, *alpha = ab + (size_t)(kLanczos + 1) * G;
+    k_lanczos_start<<<G, kRed, 0, s>>>(m, u[0], beta);
+    for (int j = 0; j < kLanczos; ++j) {
+      double *cur = u[j % 3], *next = u[(j + 1) % 3], *prev = u[(j + 2) % 3];
+      const double* bp = j ? beta + (size_t)(j - 1) * G : nullptr;
+      if (ps->nc == 1)
+        k_lanczos_product<1><<<G, kRed, 0, s>>>(m, ps->width, cur, prev, next, beta + (size_t)j * G, bp,
+                                                alpha + (size_t)j * G);
+      else
+        k_lanczos_product<2><<<G, kRed, 0, s>>>(m, ps->width, cur, prev, next, beta + (size_t)j * G, bp,
+                                                alpha + (size_t)j * G);
+      k_lanczos_next<<<G, kRed, 0, s>>>(m, cur, next, beta + (size_t)j * G, alpha + (size_t)j * G,
+                                        beta + (size_t)(j + 1) * G);
+    }
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(parts.data(), ab, parts.size() * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) st = fail(IFL_EDEVICE, std::string("spectrum estimate: ") + hipGetErrorString(e));
+  }
+  for (double* v : u)
+    if (v) (void)hipFree(v);
+  if (ab) (void)hipFree(ab);
+  if (st != IFL_OK) return st;
+  std::vector<double> a, b;
+  double first = 0.0;
+  for (int j = 0; j < kLanczos; ++j) {
+    double bj = 0.0, aj = 0.0;
+    for (int i = 0; i < G; ++i) bj += parts[(size_t)j * G + i];
+    for (int i = 0; i < G; ++i) aj += parts[(size_t)(kLanczos + 1 + j) * G + i];
+    bj = std::sqrt(bj);
+    if (j == 0) first = bj;
+    // the space is exhausted (few rows): the eigenvalues so far are exact
+    if (!(bj > 0.0) || (j > 0 && bj <= 1e-10 * std::fabs(a[0]))) break;
+    if (j > 0) b.push_back(bj);
+    a.push_back(aj);
+  }
+  ps->lam = a.empty() || !(first > 0.0) ? 0.0 : 1.01 * largest_eigenvalue(a, b);
+  return IFL_OK;
+}
+
+}  // namespace
+
+ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out) {
+  *out = nullptr;
+  if (op.order < 1 || op.order > 2 || op.field_len > INT32_MAX) return IFL_OK;
+  PatchPack pp;
+  if (!build_patches(op, local_order, &pp)) return IFL_OK;
+  PolyState* ps = new PolyState();
+  *out = ps;
+  ps->nc = pp.nc;
+  ps->width = pp.width;
+  ps->depth = pp.depth;
+  ps->largest = pp.largest;
+  ps->single = pp.single;
+  ps->mass_ratio = pp.mass_ratio;
+  for (double a : op.mass) ps->mass_sum += a;
+  PolyDev& m = ps->m;
+  m.units = pp.units;
+  m.rows = pp.units * pp.nc;
+  m.np = (m.rows + 63) / 64 * 64;
+  m.field_len = op.field_len;
+  m.npatch = (int)pp.patches.size();
+  std::vector<int32_t> entity((size_t)m.rows), row_of((size_t)op.field_len, -1);
+  for (int64_t i = 0; i < pp.units; ++i)
+    for (int c = 0; c < pp.nc; ++c) {
+      const int64_t r = i * pp.nc + c;
+      entity[r] = (int32_t)op.entity[(int64_t)pp.order[i] * pp.nc + c];
+      row_of[entity[r]] = (int32_t)r;
+    }
+  ifl_status st;
+  if ((st = up(&m.info, pp.patches)) || (st = up(&m.halo, pp.halo)) || (st = up(&m.idx, pp.idx)) ||
+      (st = up(&m.col, pp.col)) || (st = up(&m.val, pp.val)) || (st = up(&m.own, pp.own)) ||
+      (st = up(&m.mass, pp.mass)) || (st = up(&m.entity, entity)) || (st = up(&m.row_of, row_of)))
+    return st;
+  {
+    std::vector<double> d((size_t)m.rows);
+    for (int64_t r = 0; r < m.rows; ++r) d[r] = pp.own[r / pp.nc * pp.nc * pp.nc + r % pp.nc * (pp.nc + 1)];
+    const size_t at = d.size() - 1 - d.size() / 20;
+    std::nth_element(d.begin(), d.begin() + at, d.end());
+    ps->lam_typical = 2.0 * d[at];
+  }
+  if (hipMalloc((void**)&ps->bad, sizeof(int)) != hipSuccess) return fail(IFL_ENOMEM, "hipMalloc failed");
+  return estimate_spectrum(ps, s);
+}
+
+void poly_destroy(PolyState* ps) {
+  if (!ps) return;
+  const PolyDev& m = ps->m;
+  const void* ptrs[] = {m.info, m.halo, m.idx,   m.col,   m.val, m.own,   m.mass,   m.entity,  m.row_of,
+                        ps->phi, ps->t, ps->x, ps->z, ps->part, ps->coef, ps->stage, ps->bad, ps->sums};
+  for (const void* p : ptrs)
+    if (p) (void)hipFree(const_cast<void*>(p));
+  if (ps->host) (void)hipHostFree(ps->host);
+  if (ps->host_coef) (void)hipHostFree(ps->host_coef);
+  delete ps;
+}
+
+namespace {
+
+// What the residual polynomial is kept within: a twentieth of the tolerance,
+// about where CG, which overshoots it between its tests, leaves the error
+// (with a half, the results were 1.5 to 10 times further from an exact
+// solution than CG's; ln 10 costs 13 of 180 products at 32 cells), and less
+// where the masses differ so much that the residual's norm can outgrow the
+// polynomial's bound (their ratio's root, beyond the 4 that meshes with a
+// coastline have without it).
+double poly_tol(const PolyState* ps, const PolyCall& c) {
+  return std::max(1e-15, 0.05 * c.rtol / std::max(1.0, 0.25 * std::sqrt(ps->mass_ratio)));
+}
+
+double scale_factor(const PolyCall& c, int32_t j) { return c.gamma / std::pow(c.k[j], 2.0 * c.order); }
+
+// About how many products a scale needs with lam as the spectrum's end.
+double steps_needed(int order, double c, double lam, double tol) {
+  const double b = std::pow(c, 1.0 / order) * lam;
+  return 0.5 * std::log(2.0 / tol) * std::sqrt(order == 1 ? 1.0 + b : 1.0 + 2.0 * b);
+}
+
+}  // namespace
+
+bool poly_takes(const PolyState* ps, const PolyCall& c) {
+  if (!ps || !(ps->lam > 0.0) || c.n_fields > 65535) return false;
+  const double tol = poly_tol(ps, c);
+  double most = 0.0, cg = 0.0;
+  for (int32_t j = 0; j < c.n_scales; ++j) {
+    const double f = scale_factor(c, j);
+    if (!(f > 0.0) || !std::isfinite(f)) return false;
+    most = std::max(most, steps_needed(c.order, f, ps->lam, tol));
+    cg += steps_needed(c.order, f, ps->lam_typical, tol);
+  }
+  // a step of the sequence costs less than half a CG iteration of one
+  // column; lam exceeds lam_typical where a few cells are much smaller than
+  // the rest, which CG mostly does not feel and the sequence does
+  return most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0;
+}
+
+ifl_status poly_filter(PolyState* ps, const PolyCall& c, std::vector<int64_t>* failed) {
+  const auto t0 = std::chrono::steady_clock::now();
+  const PolyDev& m = ps->m;
+  hipStream_t s = c.stream;
+  failed->clear();
+  const int S = c.n_scales, F = c.n_fields;
+  const double tol = poly_tol(ps, c);
+  // the scales' polynomials, largest degree first, in groups summed together
+  std::vector<std::vector<double>> poly((size_t)S);
+  std::vector<int> by((size_t)S);
+  for (int j = 0; j < S; ++j) {
+    poly[j] = poly_coefficients(c.order, scale_factor(c, j), ps->lam, tol, c.max_iter);
+    by[j] = j;
+    if (poly[j].empty()) return fail(IFL_EUNSUPPORTED, "a scale's polynomial exceeds max_iter");
+  }
+  std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return poly[a].size() > poly[b].size(); });
+  const int degree = (int)poly[by[0]].size() - 1;
+  struct Group {
+    int sc = 0, n = 0, degree = 0, pad0 = 0;  // scales padded to sc, real ones, largest degree, scales before
+    GroupScales gs;
+    size_t coef = 0;
+  };
+  std::vector<Group> groups;
+  size_t ncoef = 0;
+  int spad = 0;
+  for (int j = 0; j < S;) {
+    Group g;
+    g.n = std::min(kMaxGroup, S - j);
+    g.sc = 1;
+    while (g.sc < g.n) g.sc *= 2;
+    g.degree = (int)poly[by[j]].size() - 1;
+    g.pad0 = spad;
+    g.coef = ncoef;
+    for (int i = 0; i < kMaxGroup; ++i) {
+      g.gs.column[i] = i < g.n ? by[j + i] : -1;
+      g.gs.c[i] = i < g.n ? scale_factor(c, by[j + i]) : 0.0;
+    }
+    ncoef += (size_t)(g.degree + 1) * g.sc;
+    spad += g.sc;
+    j += g.n;
+    groups.push_back(g);
+  }
+  // fields at a time and vectors of the sequence kept at a time: up to 64
+  // vectors, and as many fields as about 6 GB hold
+  const size_t vec = (size_t)m.np * sizeof(double);
+  const int zpad = c.order == 2 ? groups[0].sc : 0;
+  int planes = std::min(degree, ps->single ? degree : 64);
+  constexpr size_t kBudget = (size_t)6 << 30;
+  while (planes > 16 && (size_t)(planes + spad + zpad) * vec > kBudget) planes = std::max(16, planes / 2);
+  planes = std::max(planes, std::min(degree, 2 * std::max(1, ps->depth)));
+  planes = std::max(planes, 1);
+  const int FG = (int)std::max<size_t>(1, std::min<size_t>((size_t)F, kBudget / ((planes + spad + zpad) * vec)));
+  const int G = red_blocks(m.rows);
+  const int GL = red_blocks(m.np);
+  ifl_status st;
+  const size_t nsums = (size_t)F + (size_t)F * spad * 3;
+  if ((st = grow(&ps->phi, &ps->phi_n, (size_t)F * m.np)) ||
+      (st = grow(&ps->t, &ps->t_n, (size_t)planes * FG * m.np)) ||
+      (st = grow(&ps->x, &ps->x_n, (size_t)FG * spad * m.np)) ||
+      (zpad && (st = grow(&ps->z, &ps->z_n, (size_t)FG * zpad * m.np))) ||
+      (st = grow(&ps->part, &ps->part_n, std::max((size_t)F * GL, (size_t)FG * kMaxGroup * 3 * G))) ||
+      (st = grow(&ps->coef, &ps->coef_n, ncoef)) || (st = grow(&ps->sums, &ps->sums_n, nsums)) ||
+      (c.out && c.out_host && (st = grow(&ps->stage, &ps->stage_n, (size_t)FG * S * m.field_len))) ||
+      (st = grow_host(&ps->host, &ps->host_n, nsums + 1)) || (st = grow_host(&ps->host_coef, &ps->host_coef_n, ncoef)))
+    return st;
+  for (const Group& g : groups)
+    for (int k = 0; k <= g.degree; ++k)
+      for (int i = 0; i < g.sc; ++i) {
+        const std::vector<double>* p = i < g.n ? &poly[g.gs.column[i]] : nullptr;
+        ps->host_coef[g.coef + (size_t)k * g.sc + i] = p && k < (int)p->size() ? (*p)[k] : 0.0;
+      }
+  IFL_HIP(hipMemcpyAsync(ps->coef, ps->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
+  IFL_HIP(hipMemsetAsync(ps->bad, 0, sizeof(int), s));
+  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, c.fields, ps->phi, ps->part, ps->bad);
+  k_poly_total<<<F, kRed, 0, s>>>(ps->part, GL, ps->sums);
+  IFL_HIP(hipGetLastError());
+  int* bad_host = reinterpret_cast<int*>(ps->host + nsums);
+  if (c.out && c.out_host) {  // the copies to the host must not start on a bad field
+    IFL_HIP(hipMemcpyAsync(bad_host, ps->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    IFL_HIP(hipStreamSynchronize(s));
+    if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
+  }
+  for (int f0 = 0; f0 < F; f0 += FG) {
+    const int nf = std::min(FG, F - f0);
+    const int64_t plane = (int64_t)nf * m.np;
+    const double* phi = ps->phi + (int64_t)f0 * m.np;
+    const double *prev = nullptr, *cur = phi;
+    for (int k0 = 0; k0 < degree || k0 == 0;) {
+      const int n = std::min(planes, degree - k0);
+      for (int j = 0; j < n;) {
+        const int d = std::min(ps->single ? n : ps->depth, n - j);
+        double* to = ps->t + (int64_t)j * plane;
+        launch_steps(ps, prev, cur, to, plane, nf, d, s);
+        prev = d >= 2 ? to + (int64_t)(d - 2) * plane : cur;
+        cur = to + (int64_t)(d - 1) * plane;
+        j += d;
+      }
+      for (const Group& g : groups) {
+        const int ng = std::min(n, g.degree - k0);
+        if (ng <= 0 && k0 > 0) continue;
+        launch_sum(g.sc, k0 == 0 ? phi : nullptr, ps->t, plane, m.np, std::max(0, ng),
+                   ps->coef + g.coef + (size_t)(k0 == 0 ? 0 : k0 + 1) * g.sc,
+                   ps->x + (size_t)g.pad0 * nf * m.np, nf, s);
+      }
+      IFL_HIP(hipGetLastError());
+      k0 += n;
+      if (n == 0) break;
+    }
+    double* dst = !c.out ? nullptr : (c.out_host ? ps->stage : c.out + (int64_t)f0 * S * m.field_len);
+    for (const Group& g : groups) {
+      const double* x = ps->x + (size_t)g.pad0 * nf * m.np;
+      if (ps->nc == 1) launch_check<1>(ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s);
+      else launch_check<2>(ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s);
+      k_poly_total<<<nf * g.sc * 3, kRed, 0, s>>>(ps->part, G,
+                                                  ps->sums + F + ((size_t)f0 * spad + (size_t)g.pad0 * nf) * 3);
+      if (dst) launch_out(ps, g.sc, x, g.gs, S, dst, nf, s);
+    }
+    IFL_HIP(hipGetLastError());
+    if (dst && c.out_host)
+      IFL_HIP(hipMemcpyAsync(c.out + (int64_t)f0 * S * m.field_len, ps->stage,
+                             sizeof(double) * (size_t)nf * S * m.field_len, hipMemcpyDeviceToHost, s));
+  }
+  IFL_HIP(hipMemcpyAsync(ps->host, ps->sums, nsums * sizeof(double), hipMemcpyDeviceToHost, s));
+  IFL_HIP(hipMemcpyAsync(bad_host, ps->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+  IFL_HIP(hipStreamSynchronize(s));
+  if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
+  const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  for (int f0 = 0; f0 < F; f0 += FG) {
+    const int nf = std::min(FG, F - f0);
+    for (const Group& g : groups)
+      for (int f = 0; f < nf; ++f)
+        for (int i = 0; i < g.n; ++i) {
+          const double bb = ps->host[f0 + f];
+          const double* q = ps->host + F + ((size_t)f0 * spad + (size_t)g.pad0 * nf + (size_t)f * g.sc + i) * 3;
+          const int64_t col = (int64_t)(f0 + f) * S + g.gs.column[i];
+          // attainable accuracy: what FP64 can tell of M phi - S x
+          const double floor = 8.0 * 1.1102230246251565e-16 *
+                               (std::sqrt(bb) + std::sqrt(q[1]) * (1.0 + g.gs.c[i] * std::pow(ps->lam, c.order)));
+          const double res = std::sqrt(q[0]);
+          if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
+          if (c.stats) {
+            ifl_solve_stats& so = c.stats[col];
+            so.iterations = bb > 0.0 ? (int32_t)poly[g.gs.column[i]].size() - 1 : 0;
+            so.refinements = 0;
+            so.status = IFL_OK;
+            so.reserved = 0;
+            so.rel_residual = bb > 0.0 ? res / std::sqrt(bb) : res;
+            so.seconds = secs;
+            so.energy = 0.5 * q[2] / ps->mass_sum;
+          }
+          if (c.energy) c.energy[col] = 0.5 * q[2] / ps->mass_sum;
+        }
+  }
+  std::sort(failed->begin(), failed->end());
+  return IFL_OK;
+}
+
+}  // namespace ifl
