@@ -183,7 +183,7 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
     int64_t begin, end;
     std::vector<int32_t> units;  // patch positions: interior, ring 1, ..
     std::vector<int32_t> ends;   // depth + 1
-    std::vector<uint16_t> idx;   // [k][rows]
+    std::vector<uint16_t> idx;   // records
   };
   const int64_t groups = std::min<int64_t>(8, (int64_t)leaf.size() - 1);
   std::vector<std::vector<Local>> made(groups);
@@ -230,12 +230,15 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
         continue;
       }
       const size_t rows = pp.depth ? (size_t)L.ends[pp.depth - 1] : L.units.size();
-      L.idx.assign(rows * pp.width, 0);
+      const size_t rec = (size_t)poly_idx_record(pp.width);
+      const uint32_t bytes = 8u * (uint32_t)nc;
+      L.idx.assign(rows * rec, 0);
       for (size_t i = 0; fits && i < rows; ++i) {
         const int32_t u = pp.order[L.units[i]];
-        int k = 0;
-        for (int64_t a = g.ptr[u]; a < g.ptr[u + 1]; ++a, ++k) L.idx[k * rows + i] = (uint16_t)loc[pos[g.adj[a]]];
-        for (; k < pp.width; ++k) L.idx[k * rows + i] = (uint16_t)i;
+        size_t k = 0;
+        for (int64_t a = g.ptr[u]; a < g.ptr[u + 1]; ++a, ++k)
+          L.idx[i * rec + k] = (uint16_t)(bytes * (uint32_t)loc[pos[g.adj[a]]]);
+        for (; k < rec; ++k) L.idx[i * rec + k] = (uint16_t)(bytes * (uint32_t)i);
       }
       for (int32_t u : L.units) loc[u] = -1;
       if (!fits) L.units.clear();  // one unit with more neighbours in its rings than the capacity
@@ -257,31 +260,27 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
       pp.largest = std::max<int>(pp.largest, (int)L.units.size());
     }
 
-  // entries of M^-1 K by position: [k][units] (nc = 2: four couplings an
-  // entry), the unit's own block apart; and the columns by position
-  const int64_t U = g.n, W = pp.width, bb = nc * nc;
-  pp.val.assign((size_t)(W * U * bb), 0.0);
-  pp.own.assign((size_t)(U * bb), 0.0);
-  pp.col.assign((size_t)(W * U), 0);
+  pp.halo.push_back(0);  // a patch without halo units still reads one entry
+  // M^-1 K by position, a record per unit, and the columns by position
+  const int64_t U = g.n, bb = nc * nc, rec = poly_val_record(nc, pp.width), crec = poly_col_record(pp.width);
+  pp.val.assign((size_t)(U * rec), 0.0);
+  pp.col.assign((size_t)(U * crec), 0);
   pp.mass.resize((size_t)(U * nc));
   const int64_t pieces = std::max<int64_t>(1, std::min<int64_t>(8, U / 4096));
   parallel_for(pieces, [&](int64_t q) {
     for (int64_t i = U * q / pieces; i < U * (q + 1) / pieces; ++i) {
       const int32_t u = pp.order[i];
       const int64_t a0 = g.ptr[u], a1 = g.ptr[u + 1];
-      for (int64_t k = 0; k < W; ++k) pp.col[k * U + i] = k < a1 - a0 ? pos[g.adj[a0 + k]] : (int32_t)i;
+      for (int64_t k = 0; k < crec; ++k) pp.col[i * crec + k] = k < a1 - a0 ? pos[g.adj[a0 + k]] : (int32_t)i;
       for (int c = 0; c < nc; ++c) {
         const int64_t r = (int64_t)u * nc + c;
         pp.mass[i * nc + c] = op.mass[r];
         const double im = 1.0 / op.mass[r];
         for (int64_t e = rp[r]; e < rp[r + 1]; ++e) {
           const int32_t v = col[e] / nc, cc = col[e] % nc;
-          if (v == u) {
-            pp.own[i * bb + c * nc + cc] = val[e] * im;
-          } else {
-            const int64_t k = std::lower_bound(g.adj.begin() + a0, g.adj.begin() + a1, v) - (g.adj.begin() + a0);
-            pp.val[(k * U + i) * bb + c * nc + cc] = val[e] * im;
-          }
+          int64_t k = 0;
+          if (v != u) k = 1 + std::lower_bound(g.adj.begin() + a0, g.adj.begin() + a1, v) - (g.adj.begin() + a0);
+          pp.val[i * rec + k * bb + c * nc + cc] = val[e] * im;
         }
       }
     }

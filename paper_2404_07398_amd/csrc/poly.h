@@ -17,19 +17,26 @@ constexpr int kPolyDepth = 8;
 // Threads of a patch's workgroup and units per thread; what a patch holds.
 constexpr int kPolyThreads = 512;
 constexpr int kPolySingleThreads = 1024;
-constexpr int poly_slots(int nc, int width) { return nc == 1 ? (width <= 8 ? 4 : 2) : (width <= 3 ? 2 : 1); }
+constexpr int poly_slots(int nc, int width) { return nc == 1 ? (width <= 6 ? 4 : 2) : (width <= 3 ? 2 : 1); }
 constexpr int poly_patch_units(int nc, int width) {
   return nc == 1 ? kPolyThreads * poly_slots(nc, width) : 1024;
 }
 constexpr int poly_single_units(int nc, int width) { return kPolySingleThreads * poly_slots(nc, width); }
-constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 8 ? 8 : 4; }
+constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 6 ? 8 : 4; }
+
+// Records, in whole 16-byte units (8 for 3 neighbours): a unit's own block
+// and its neighbours' (doubles); its neighbours' LDS offsets in a patch
+// (uint16_t, bytes of a buffer of units); its neighbours' positions.
+constexpr int poly_val_record(int nc, int width) { return ((1 + width) * nc * nc + 1) / 2 * 2; }
+constexpr int poly_idx_record(int width) { return width <= 4 ? 4 : (width + 7) / 8 * 8; }
+constexpr int poly_col_record(int width) { return (width + 3) / 4 * 4; }
 
 struct PatchInfo {
   int32_t start;                // first interior position; the interior is contiguous
   int32_t rows;                 // units with local neighbour numbers (all but the last ring)
   int32_t end[kPolyDepth + 1];  // local units up to and with ring d
   int64_t halo;                 // first halo entry (the positions of local units end[0] ..)
-  int64_t idx;                  // first neighbour number, [width][rows]
+  int64_t idx;                  // first entry of its rows' offset records
 };
 
 // M^-1 K in the patches' own order of the units ("positions"). A unit is a
@@ -47,9 +54,8 @@ struct PatchPack {
   std::vector<PatchInfo> patches;
   std::vector<int32_t> halo;
   std::vector<uint16_t> idx;
-  std::vector<int32_t> col;     // [width][units], positions
-  std::vector<double> val;      // [width][units][nc * nc]
-  std::vector<double> own;      // [units][nc * nc]
+  std::vector<int32_t> col;
+  std::vector<double> val;      // M^-1 K
   std::vector<double> mass;     // [units * nc]
 };
 

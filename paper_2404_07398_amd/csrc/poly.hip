@@ -45,7 +45,6 @@ struct PolyDev {
   const uint16_t* idx = nullptr;
   const int32_t* col = nullptr;
   const double* val = nullptr;
-  const double* own = nullptr;
   const double* mass = nullptr;
   const int32_t* entity = nullptr;  // caller index of each row
   const int32_t* row_of = nullptr;  // row of each caller index, -1: none
@@ -64,115 +63,171 @@ struct alignas(16) Unit<2> {
   double v[2];
 };
 
-// Position of local unit i of a patch.
-__device__ __forceinline__ int64_t unit_at(const PatchInfo& p, const int32_t* halo, int i) {
-  return i < p.end[0] ? (int64_t)p.start + i : (int64_t)halo[p.halo + i - p.end[0]];
+// What a thread of the step kernel owns: its units' rows of (4 / lam) A, the
+// neighbours' LDS offsets two to a register (kept packed: unpacked they cost
+// the registers of a second resident workgroup), and the two latest vectors.
+template <int NC, int W, int SLOTS>
+struct Rows {
+  double val[SLOTS][W][NC * NC], own[SLOTS][NC * NC];
+  uint32_t nb[SLOTS][(W + 1) / 2];
+  Unit<NC> t[2][SLOTS];
+};
+
+// One step for N of the thread's units from slot S on: the vector t[CUR] and
+// the LDS buffer CUR hold t_k; t[1 - CUR] holds t_{k-1} and becomes t_{k+1}.
+// All gathers are issued before the sums. Lanes past 'lim' compute on
+// whatever is there and write nothing.
+template <int NC, int W, int SLOTS, int T, int CUR, int N>
+__device__ __forceinline__ void step_slots(Rows<NC, W, SLOTS>& r, char* lds, int S, int tid, int lim, int inside,
+                                           double half, Unit<NC>* out) {
+  constexpr int BUF = T * SLOTS * (int)sizeof(Unit<NC>);
+  Unit<NC> g[N][W];
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int k = 0; k < W; k += 2) {
+      uint32_t two = r.nb[S + n][k / 2];
+      asm volatile("" : "+v"(two));  // keeps the unpacking from being hoisted into registers of its own
+      g[n][k] = *reinterpret_cast<const Unit<NC>*>(lds + CUR * BUF + (two & 0xffffu));
+      if (k + 1 < W) g[n][k + 1 < W ? k + 1 : k] = *reinterpret_cast<const Unit<NC>*>(lds + CUR * BUF + (two >> 16));
+    }
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const int s = S + n, i = tid + s * T;
+    double acc[NC], acc2[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      acc[c] = -r.t[1 - CUR][s].v[c];
+      acc2[c] = 0.0;
+#pragma unroll
+      for (int d = 0; d < NC; ++d) acc2[c] += r.own[s][c * NC + d] * r.t[CUR][s].v[d];
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+#pragma unroll
+        for (int d = 0; d < NC; ++d) {
+          double& a = k % 2 == 0 ? acc[c] : acc2[c];
+          a += r.val[s][k][c * NC + d] * g[n][k].v[d];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) r.t[1 - CUR][s].v[c] = half * (acc[c] + acc2[c]);
+    if (i < lim) *reinterpret_cast<Unit<NC>*>(lds + (1 - CUR) * BUF + i * (int)sizeof(Unit<NC>)) = r.t[1 - CUR][s];
+    if (i < inside) out[i] = r.t[1 - CUR][s];
+  }
+}
+
+template <int NC, int W, int SLOTS, int T, int CUR>
+__device__ __forceinline__ void step_all(Rows<NC, W, SLOTS>& r, char* lds, int tid, int lim, int inside, double half,
+                                         Unit<NC>* out) {
+  // first unit of this wavefront: the tests below are one scalar branch each
+  const int wave = __builtin_amdgcn_readfirstlane(tid & ~63);
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s)
+    if (wave + s * T < lim) step_slots<NC, W, SLOTS, T, CUR, 1>(r, lds, s, tid, lim, inside, half, out);
 }
 
 // 'steps' steps of the recurrence on one patch, field after field.
 //
-// A thread owns SLOTS units: their rows of (4 / lam) A stay in registers for
-// all steps and fields, their t_k and t_{k-1} too; the neighbours' t_k come
-// from LDS, written to the other buffer for the next step. Step j needs the
-// rings up to steps - j only, a prefix of the local numbering. With one
-// patch for the whole mesh (no rings) the steps are not limited.
+// A thread owns SLOTS units, kept in registers for all steps and fields; the
+// neighbours' t_k come from LDS, t_{k+1} goes to the other buffer. Step j
+// needs the rings up to steps - j only, a prefix of the local numbering. With
+// one patch for the whole mesh (no rings) the steps are not limited.
+//
+// What bounds it: the memory system. A patch's records, halo list and first
+// two vectors are read once per launch (about 2.7 local units per interior
+// one at 8 rings), and its new interior vectors written; within the steps
+// LDS gathers and FP64 FMAs take about as long as each other. Loads and
+// stores must therefore never be waited for inside the steps, and two
+// workgroups share a CU (128 registers) so that one loads while the other
+// steps. Measured on one field of the 2.6 M-vertex sphere: 319 us per 8
+// steps with the ring ends and the unpacked offsets in memory and the
+// records read entry by entry, 165 us (5.4 TB/s) now; 4 fields of the
+// 1.57 M-dof masked sphere 400 and 249 us.
 //
 // prev == nullptr: the sequence starts (cur = t_0, the first step is halved).
 // out: plane of the first new vector, the next ones 'plane' doubles on.
 template <int NC, int W, int SLOTS, int T>
-__global__ __launch_bounds__(T) void k_poly_steps(PolyDev m, const double* __restrict__ prev,
-                                                  const double* __restrict__ cur, double* __restrict__ out,
-                                                  int64_t plane, int n_fields, int steps, int ringed, double scale) {
+__global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __restrict__ prev,
+                                                     const double* __restrict__ cur, double* __restrict__ out,
+                                                     int64_t plane, int n_fields, int steps, int ringed,
+                                                     double scale) {
   // consecutive patches on one XCD: their halos overlap in its L2
   const int per = (m.npatch + kXcd - 1) / kXcd;
   const int pid = (int)(blockIdx.x % kXcd) * per + (int)(blockIdx.x / kXcd);
   if (pid >= m.npatch || (int)(blockIdx.x / kXcd) >= per) return;
-  __shared__ Unit<NC> lds[2][T * SLOTS];
-  const PatchInfo p = m.info[pid];
+  __shared__ __align__(16) char lds[2 * T * SLOTS * sizeof(Unit<NC>)];
+  const PatchInfo* p = m.info + pid;
   const int tid = threadIdx.x;
-  const int inside = p.end[0];
-  const int loaded = p.end[ringed ? steps : 0];
-  const int first_lim = p.end[ringed ? steps - 1 : 0];
-  constexpr int BB = NC * NC;
-  double val[SLOTS][W][BB], own[SLOTS][BB];
-  uint32_t nb[SLOTS][(W + 1) / 2];
-  int64_t at[SLOTS];
+  // the ring ends, lane d of each wavefront holding ring d's: a step's limit
+  // is read from there, since a load of it would wait for the stores before
+  const int ends = p->end[min(tid & 63, kPolyDepth)];
+  const int start = p->start, inside = p->end[0];
+  const int loaded = p->end[ringed ? steps : 0];
+  const int first_lim = p->end[ringed ? steps - 1 : 0];
+  constexpr int VR = poly_val_record(NC, W), IR = poly_idx_record(W), BB = NC * NC;
+  Rows<NC, W, SLOTS> r;
+  int32_t at[SLOTS];
+  // no branches between the loads, so that all are in flight together: units
+  // past the last one read the first one's data
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
     const int i = tid + s * T;
-    at[s] = i < loaded ? unit_at(p, m.halo, i) : 0;
-    if (i < first_lim) {
+    const int h = i >= inside && i < loaded ? i - inside : 0;
+    const int32_t q = ringed ? m.halo[p->halo + h] : 0;
+    at[s] = i < loaded ? (i < inside ? start + i : q) : start;
+  }
 #pragma unroll
-      for (int k = 0; k < W; ++k) {
-        const uint32_t id = m.idx[p.idx + (int64_t)k * p.rows + i];
-        if (k % 2 == 0) nb[s][k / 2] = id;
-        else nb[s][k / 2] |= id << 16;
+  for (int s = 0; s < SLOTS; ++s) {
+    const int i = tid + s * T < first_lim ? tid + s * T : 0;
+    const uint32_t* id = reinterpret_cast<const uint32_t*>(m.idx + p->idx + (int64_t)i * IR);
 #pragma unroll
-        for (int b = 0; b < BB; ++b) val[s][k][b] = scale * m.val[((int64_t)k * m.units + at[s]) * BB + b];
-      }
+    for (int k = 0; k < (W + 1) / 2; ++k) r.nb[s][k] = id[k];
+    const double* v = m.val + (int64_t)(tid + s * T < first_lim ? at[s] : start) * VR;
 #pragma unroll
-      for (int b = 0; b < BB; ++b) own[s][b] = scale * m.own[at[s] * BB + b] - (b % (NC + 1) == 0 ? 2.0 : 0.0);
-    } else {
+    for (int b = 0; b < BB; ++b) r.own[s][b] = v[b];
 #pragma unroll
-      for (int k = 0; k < W; ++k) {
-        nb[s][k / 2] = 0;
+    for (int k = 0; k < W; ++k)
 #pragma unroll
-        for (int b = 0; b < BB; ++b) val[s][k][b] = 0.0;
-      }
+      for (int b = 0; b < BB; ++b) r.val[s][k][b] = v[(k + 1) * BB + b];
+  }
 #pragma unroll
-      for (int b = 0; b < BB; ++b) own[s][b] = 0.0;
-    }
+  for (int s = 0; s < SLOTS; ++s) {
+#pragma unroll
+    for (int b = 0; b < BB; ++b) r.own[s][b] = scale * r.own[s][b] - (b % (NC + 1) == 0 ? 2.0 : 0.0);
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+#pragma unroll
+      for (int b = 0; b < BB; ++b) r.val[s][k][b] *= scale;
   }
   for (int f = blockIdx.y; f < n_fields; f += gridDim.y) {
     const Unit<NC>* cf = reinterpret_cast<const Unit<NC>*>(cur + (int64_t)f * m.np);
-    const Unit<NC>* pf = reinterpret_cast<const Unit<NC>*>(prev + (prev ? (int64_t)f * m.np : 0));
-    Unit<NC> tc[SLOTS], tp[SLOTS];
+    const Unit<NC>* pf = reinterpret_cast<const Unit<NC>*>(prev + (int64_t)f * m.np);
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) r.t[0][s] = cf[at[s]];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-      const int i = tid + s * T;
+      if (prev) r.t[1][s] = pf[tid + s * T < first_lim ? at[s] : start];
+      else
 #pragma unroll
-      for (int c = 0; c < NC; ++c) tc[s].v[c] = tp[s].v[c] = 0.0;
-      if (i < loaded) tc[s] = cf[at[s]];
-      if (prev && i < first_lim) tp[s] = pf[at[s]];
+        for (int c = 0; c < NC; ++c) r.t[1][s].v[c] = 0.0;
     }
+    // the loads end here (vmcnt 0): waited for inside a step, they would be
+    // waited for together with the stores of the steps before
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();  // the previous field's last step has been read
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s)
-      if (tid + s * T < loaded) lds[0][tid + s * T] = tc[s];
+      if (tid + s * T < loaded) reinterpret_cast<Unit<NC>*>(lds)[tid + s * T] = r.t[0][s];
     __syncthreads();
-    double* of = out + (int64_t)f * m.np;
-    for (int j = 1; j <= steps; ++j, of += plane) {
-      const int lim = p.end[ringed ? steps - j : 0];
-      const Unit<NC>* from = lds[(j - 1) & 1];
-      Unit<NC>* to = lds[j & 1];
-      const double half = !prev && j == 1 ? 0.5 : 1.0;
-#pragma unroll
-      for (int s = 0; s < SLOTS; ++s) {
-        const int i = tid + s * T;
-        if (i < lim) {
-          double acc[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            acc[c] = -tp[s].v[c];
-#pragma unroll
-            for (int d = 0; d < NC; ++d) acc[c] += own[s][c * NC + d] * tc[s].v[d];
-          }
-#pragma unroll
-          for (int k = 0; k < W; ++k) {
-            const uint32_t id = k % 2 == 0 ? nb[s][k / 2] & 0xffffu : nb[s][k / 2] >> 16;
-            const Unit<NC> t = from[id];
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-              for (int d = 0; d < NC; ++d) acc[c] += val[s][k][c * NC + d] * t.v[d];
-          }
-          tp[s] = tc[s];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) tc[s].v[c] = half * acc[c];
-          to[i] = tc[s];
-          if (i < inside) reinterpret_cast<Unit<NC>*>(of)[at[s]] = tc[s];
-        }
-      }
+    Unit<NC>* of = reinterpret_cast<Unit<NC>*>(out + (int64_t)f * m.np) + start;
+    const int64_t up = plane / NC;
+    for (int j = 1; j <= steps; j += 2, of += 2 * up) {
+      step_all<NC, W, SLOTS, T, 0>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j : 0), inside,
+                                   !prev && j == 1 ? 0.5 : 1.0, of);
+      __syncthreads();
+      if (j == steps) break;
+      step_all<NC, W, SLOTS, T, 1>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j - 1 : 0), inside,
+                                   1.0, of + up);
       __syncthreads();
     }
   }
@@ -264,40 +319,45 @@ struct alignas(16) Lane<2> {
 };
 
 // The row's product with A: y = sum_j A_rj x_j for the lane's scales.
-template <int NC, int SC>
-__device__ __forceinline__ Lane<lane_scales(SC)> row_product(const PolyDev& m, int width, const double* xf, int64_t r,
-                                                             int q) {
+template <int NC, int W, int SC>
+__device__ __forceinline__ Lane<lane_scales(SC)> row_product(const PolyDev& m, const double* xf, int64_t r, int q) {
   constexpr int V = lane_scales(SC);
   const Lane<V>* xt = reinterpret_cast<const Lane<V>*>(xf);
-  constexpr int LPR = SC / V, BB = NC * NC;
+  constexpr int LPR = SC / V, BB = NC * NC, VR = poly_val_record(NC, W), CR = poly_col_record(W);
   const int64_t u = r / NC;
   const int c = (int)(r % NC);
+  int32_t col[CR];
+#pragma unroll
+  for (int k = 0; k < CR; k += 4) {
+    const int4 q4 = *reinterpret_cast<const int4*>(m.col + u * CR + k);
+    col[k] = q4.x;
+    col[k + 1] = q4.y;
+    col[k + 2] = q4.z;
+    col[k + 3] = q4.w;
+  }
+  const double* a = m.val + u * VR + c * NC;
+  Lane<V> t[W + 1][NC];
+#pragma unroll
+  for (int k = 0; k <= W; ++k)
+#pragma unroll
+    for (int d = 0; d < NC; ++d) t[k][d] = xt[((k == 0 ? u : (int64_t)col[k == 0 ? 0 : k - 1]) * NC + d) * LPR + q];
   Lane<V> y;
 #pragma unroll
   for (int e = 0; e < V; ++e) y.v[e] = 0.0;
 #pragma unroll
-  for (int d = 0; d < NC; ++d) {
-    const double a = m.own[u * BB + c * NC + d];
-    const Lane<V> t = xt[(u * NC + d) * LPR + q];
-#pragma unroll
-    for (int e = 0; e < V; ++e) y.v[e] += a * t.v[e];
-  }
-  for (int k = 0; k < width; ++k) {
-    const int64_t j = m.col[(int64_t)k * m.units + u];
+  for (int k = 0; k <= W; ++k)
 #pragma unroll
     for (int d = 0; d < NC; ++d) {
-      const double a = m.val[((int64_t)k * m.units + u) * BB + c * NC + d];
-      const Lane<V> t = xt[(j * NC + d) * LPR + q];
+      const double v = a[k * BB + d];
 #pragma unroll
-      for (int e = 0; e < V; ++e) y.v[e] += a * t.v[e];
+      for (int e = 0; e < V; ++e) y.v[e] += v * t[k][d].v[e];
     }
-  }
   return y;
 }
 
 // y = A x (grid.y = field).
-template <int NC, int SC>
-__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, int width, const double* __restrict__ x,
+template <int NC, int W, int SC>
+__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, const double* __restrict__ x,
                                                      double* __restrict__ y) {
   constexpr int V = lane_scales(SC), LPR = SC / V;
   const int64_t g = (int64_t)blockIdx.x * kRed + threadIdx.x;
@@ -305,7 +365,7 @@ __global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, int width, const
   if (r >= m.rows) return;
   const int64_t base = (int64_t)blockIdx.y * m.np * SC;
   const int q = (int)(g % LPR);
-  reinterpret_cast<Lane<V>*>(y + base)[r * LPR + q] = row_product<NC, SC>(m, width, x + base, r, q);
+  reinterpret_cast<Lane<V>*>(y + base)[r * LPR + q] = row_product<NC, W, SC>(m, x + base, r, q);
 }
 
 struct GroupScales {
@@ -315,8 +375,8 @@ struct GroupScales {
 
 // FP64 true residual M (phi - x - c A z), z = x (order 1) or A x (order 2):
 // block sums of its square, of (M x)^2 and of M x^2 per scale.
-template <int NC, int SC>
-__global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, int width, const double* __restrict__ phi,
+template <int NC, int W, int SC>
+__global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __restrict__ phi,
                                                      const double* __restrict__ x, const double* __restrict__ z,
                                                      GroupScales gs, double* __restrict__ part) {
   constexpr int V = lane_scales(SC), LPR = SC / V;
@@ -329,7 +389,7 @@ __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, int width, const
   for (int e = 0; e < 3 * V; ++e) sum[e] = 0.0;
   constexpr int RPB = kRed / LPR;
   for (int64_t r = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR; r < m.rows; r += (int64_t)gridDim.x * RPB) {
-    const Lane<V> y = row_product<NC, SC>(m, width, z + base, r, q);
+    const Lane<V> y = row_product<NC, W, SC>(m, z + base, r, q);
     const Lane<V> xr = reinterpret_cast<const Lane<V>*>(x + base)[r * LPR + q];
     const double mr = m.mass[r], ph = pf[r];
 #pragma unroll
@@ -418,8 +478,8 @@ __global__ __launch_bounds__(kRed) void k_lanczos_start(PolyDev m, double* __res
 }
 
 // w = A v - beta v_prev (v = u / b, v_prev = u_prev / b_prev, beta = b), (w, v)
-template <int NC>
-__global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, int width, const double* __restrict__ u,
+template <int NC, int W>
+__global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, const double* __restrict__ u,
                                                           const double* __restrict__ u_prev, double* __restrict__ w,
                                                           const double* __restrict__ beta,
                                                           const double* __restrict__ beta_prev,
@@ -430,7 +490,7 @@ __global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, int width, 
   const double inv = b > 0.0 ? 1.0 / b : 0.0, invp = bp > 0.0 ? b / bp : 0.0;
   double sum = 0.0;
   for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
-    double y = inv * row_product<NC, 1>(m, width, u, r, 0).v[0];
+    double y = inv * row_product<NC, W, 1>(m, u, r, 0).v[0];
     if (beta_prev) y -= invp * u_prev[r];
     w[r] = y;
     sum += m.mass[r] * y * u[r] * inv;
@@ -568,8 +628,7 @@ void launch_steps(const PolyState* ps, const double* prev, const double* cur, do
         else if (L <= 2048) steps_of<1, 6, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
         else steps_of<1, 6, 4, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
       } else if (ps->width == 8) {
-        if (L <= 2048) steps_of<1, 8, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-        else steps_of<1, 8, 4, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+        steps_of<1, 8, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
       } else {
         steps_of<1, 12, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
       }
@@ -577,8 +636,7 @@ void launch_steps(const PolyState* ps, const double* prev, const double* cur, do
       if (L <= 2 * kPolyThreads) steps_of<1, 6, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
       else steps_of<1, 6, 4, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
     } else if (ps->width == 8) {
-      if (L <= 2 * kPolyThreads) steps_of<1, 8, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
-      else steps_of<1, 8, 4, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
+      steps_of<1, 8, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
     } else {
       steps_of<1, 12, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
     }
@@ -608,30 +666,44 @@ void launch_sum(int sc, const double* phi, const double* t, int64_t plane, int64
   }
 }
 
-template <int NC, int SC>
+template <int NC, int W, int SC>
 void check_of(const PolyState* ps, int order, const double* phi, const double* x, double* z, const GroupScales& gs,
               double* part, int G, int F, hipStream_t s) {
   constexpr int LPR = SC / lane_scales(SC);
   const double* src = x;
   if (order == 2) {
     const dim3 g((unsigned)((ps->m.rows * LPR + kRed - 1) / kRed), (unsigned)F);
-    k_poly_apply<NC, SC><<<g, kRed, 0, s>>>(ps->m, ps->width, x, z);
+    k_poly_apply<NC, W, SC><<<g, kRed, 0, s>>>(ps->m, x, z);
     src = z;
   }
-  k_poly_check<NC, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, ps->width, phi, x, src, gs, part);
+  k_poly_check<NC, W, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, src, gs, part);
 }
 
-template <int NC>
-void launch_check(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z,
+template <int NC, int W>
+void check_scales(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z,
                   const GroupScales& gs, double* part, int G, int F, hipStream_t s) {
   switch (sc) {
-    case 1: check_of<NC, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 2: check_of<NC, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 4: check_of<NC, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 8: check_of<NC, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    default: check_of<NC, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 1: check_of<NC, W, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 2: check_of<NC, W, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 4: check_of<NC, W, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 8: check_of<NC, W, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    default: check_of<NC, W, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
   }
 }
+
+// f with the operator's (components, entries a unit) as its template arguments
+#define IFL_POLY_FORMS(f, ...)                                  \
+  do {                                                          \
+    if (ps->nc == 1) {                                          \
+      if (ps->width == 6) f<1, 6> __VA_ARGS__;                  \
+      else if (ps->width == 8) f<1, 8> __VA_ARGS__;             \
+      else f<1, 12> __VA_ARGS__;                                \
+    } else {                                                    \
+      if (ps->width == 3) f<2, 3> __VA_ARGS__;                  \
+      else if (ps->width == 6) f<2, 6> __VA_ARGS__;             \
+      else f<2, 8> __VA_ARGS__;                                 \
+    }                                                           \
+  } while (0)
 
 void launch_out(const PolyState* ps, int sc, const double* x, const GroupScales& gs, int S, double* out, int F,
                 hipStream_t s) {
@@ -661,12 +733,8 @@ ifl_status estimate_spectrum(PolyState* ps, hipStream_t s) {
     for (int j = 0; j < kLanczos; ++j) {
       double *cur = u[j % 3], *next = u[(j + 1) % 3], *prev = u[(j + 2) % 3];
       const double* bp = j ? beta + (size_t)(j - 1) * G : nullptr;
-      if (ps->nc == 1)
-        k_lanczos_product<1><<<G, kRed, 0, s>>>(m, ps->width, cur, prev, next, beta + (size_t)j * G, bp,
-                                                alpha + (size_t)j * G);
-      else
-        k_lanczos_product<2><<<G, kRed, 0, s>>>(m, ps->width, cur, prev, next, beta + (size_t)j * G, bp,
-                                                alpha + (size_t)j * G);
+      IFL_POLY_FORMS(k_lanczos_product,
+                     <<<G, kRed, 0, s>>>(m, cur, prev, next, beta + (size_t)j * G, bp, alpha + (size_t)j * G));
       k_lanczos_next<<<G, kRed, 0, s>>>(m, cur, next, beta + (size_t)j * G, alpha + (size_t)j * G,
                                         beta + (size_t)(j + 1) * G);
     }
@@ -727,12 +795,12 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
     }
   ifl_status st;
   if ((st = up(&m.info, pp.patches)) || (st = up(&m.halo, pp.halo)) || (st = up(&m.idx, pp.idx)) ||
-      (st = up(&m.col, pp.col)) || (st = up(&m.val, pp.val)) || (st = up(&m.own, pp.own)) ||
+      (st = up(&m.col, pp.col)) || (st = up(&m.val, pp.val)) ||
       (st = up(&m.mass, pp.mass)) || (st = up(&m.entity, entity)) || (st = up(&m.row_of, row_of)))
     return st;
   {
     std::vector<double> d((size_t)m.rows);
-    for (int64_t r = 0; r < m.rows; ++r) d[r] = pp.own[r / pp.nc * pp.nc * pp.nc + r % pp.nc * (pp.nc + 1)];
+    for (int64_t r = 0; r < m.rows; ++r) d[r] = pp.val[r / pp.nc * poly_val_record(pp.nc, pp.width) + r % pp.nc * (pp.nc + 1)];
     const size_t at = d.size() - 1 - d.size() / 20;
     std::nth_element(d.begin(), d.begin() + at, d.end());
     ps->lam_typical = 2.0 * d[at];
@@ -744,7 +812,7 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
 void poly_destroy(PolyState* ps) {
   if (!ps) return;
   const PolyDev& m = ps->m;
-  const void* ptrs[] = {m.info, m.halo, m.idx,   m.col,   m.val, m.own,   m.mass,   m.entity,  m.row_of,
+  const void* ptrs[] = {m.info, m.halo, m.idx,   m.col,   m.val, m.mass,   m.entity,  m.row_of,
                         ps->phi, ps->t, ps->x, ps->z, ps->part, ps->coef, ps->stage, ps->bad, ps->sums};
   for (const void* p : ptrs)
     if (p) (void)hipFree(const_cast<void*>(p));
@@ -903,8 +971,7 @@ ifl_status poly_filter(PolyState* ps, const PolyCall& c, std::vector<int64_t>* f
     double* dst = !c.out ? nullptr : (c.out_host ? ps->stage : c.out + (int64_t)f0 * S * m.field_len);
     for (const Group& g : groups) {
       const double* x = ps->x + (size_t)g.pad0 * nf * m.np;
-      if (ps->nc == 1) launch_check<1>(ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s);
-      else launch_check<2>(ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s);
+      IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s));
       k_poly_total<<<nf * g.sc * 3, kRed, 0, s>>>(ps->part, G,
                                                   ps->sums + F + ((size_t)f0 * spad + (size_t)g.pad0 * nf) * 3);
       if (dst) launch_out(ps, g.sc, x, g.gs, S, dst, nf, s);
