@@ -418,9 +418,12 @@ ifl_status ifl_server_create(size_t hbm_budget_bytes, int32_t slots, ifl_server*
 
 /* Register a handle (borrowed: it must outlive the server). Handles of the
  * same mesh prepared for n = 1 and n = 2 are separate entries. The handle's
- * options at this call fix how its requests run: in a tile of 'slots'
- * columns (IFL_SOLVER_KN), or, for n >= 2 with IFL_SOLVER_SHIFTED, one
- * column at a time through the shifted first-order solves. IFL_ENOMEM when
+ * options at this call fix how its requests run: with batch = 0 and n <= 2 a
+ * request's scales together, as ifl_filter does, in a work space of a tile's
+ * size; else in a tile of 'slots' columns (IFL_SOLVER_KN; also where a tile
+ * of so few slots is too small for that), or, for n >= 2 with
+ * IFL_SOLVER_SHIFTED, one column at a time through the shifted first-order
+ * solves. IFL_ENOMEM when
  * the work space (tile, or shifted-solve vectors, plus staging) does not fit
  * the budget. */
 ifl_status ifl_server_add(ifl_server* s, ifl_handle* h, int32_t* mesh_id);

@@ -544,7 +544,7 @@ class Server:
         latency in seconds from submit to completion, server clock)."""
         stats = (ifl_solve_stats * max(1, n_scales))()
         while not self.poll(ticket):  # the latency is final once the ticket is done
-            time.sleep(0.0005)
+            time.sleep(0.00005)
         lat = float(lib().ifl_ticket_latency(ticket))
         st = lib().ifl_wait(ticket, stats)
         keep = self._keep.pop(ticket.value, None)

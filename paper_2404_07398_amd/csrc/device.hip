@@ -2011,25 +2011,6 @@ ifl_status spare_tile(DeviceState* d, int R, bool mixed, hipStream_t s, BatchWor
   return batch_release(t, ~0ull, s);
 }
 
-// A call's fields in device memory: as they are, or copied from the host.
-ifl_status fields_on_device(Handle* h, int32_t n_fields, const double* fields, hipStream_t s, const double** out) {
-  DeviceState* d = h->dev;
-  *out = fields;
-  if (is_device_ptr(fields)) return IFL_OK;
-  const int64_t need = (int64_t)n_fields * h->op.field_len;
-  if (d->field_stage_len < need) {
-    if (d->field_stage) (void)hipFree(d->field_stage);
-    d->field_stage = nullptr;
-    d->field_stage_len = 0;
-    ifl_status st = dalloc(&d->field_stage, (size_t)need);
-    if (st != IFL_OK) return st;
-    d->field_stage_len = need;
-  }
-  IFL_HIP(hipMemcpyAsync(d->field_stage, fields, sizeof(double) * need, hipMemcpyHostToDevice, s));
-  *out = d->field_stage;
-  return IFL_OK;
-}
-
 // Many columns at once: slots of a tile of R columns are filled from the
 // (field, scale) list, iterated together, and refilled as columns finish.
 // A batched call's staging: the fields on the device, then in row order in
@@ -2041,8 +2022,19 @@ ifl_status stage_call(Handle* h, const BatchMatrix& bm, BatchWork& w, int32_t n_
   DeviceState* d = h->dev;
   const int64_t L = h->op.field_len;
   ifl_status st;
-  const double* fdev = nullptr;
-  if ((st = fields_on_device(h, n_fields, fields, s, &fdev)) != IFL_OK) return st;
+  const double* fdev = fields;
+  if (!is_device_ptr(fields)) {
+    const int64_t need = (int64_t)n_fields * L;
+    if (d->field_stage_len < need) {
+      if (d->field_stage) (void)hipFree(d->field_stage);
+      d->field_stage = nullptr;
+      d->field_stage_len = 0;
+      if ((st = dalloc(&d->field_stage, (size_t)need)) != IFL_OK) return st;
+      d->field_stage_len = need;
+    }
+    IFL_HIP(hipMemcpyAsync(d->field_stage, fields, sizeof(double) * need, hipMemcpyHostToDevice, s));
+    fdev = d->field_stage;
+  }
   if (out_cols > 0 && d->col_stage_len < (int64_t)out_cols * L) {
     if (d->col_stage) (void)hipFree(d->col_stage);
     d->col_stage = nullptr;
@@ -2354,6 +2346,8 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   c.max_iter = h->opt.max_iter;
   c.n_fields = n_fields;
   c.n_scales = n_scales;
+  c.fields = fields;
+  c.fields_host = !is_device_ptr(fields);
   c.k = k;
   c.out = out;
   c.out_host = out && !is_device_ptr(out);
@@ -2362,9 +2356,8 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   c.stream = stream_of(h);
   *done = false;
   if (!poly_takes(d->poly, c)) return IFL_OK;
-  ifl_status st = fields_on_device(h, n_fields, fields, c.stream, &c.fields);
   std::vector<int64_t> failed;
-  if (st == IFL_OK) st = poly_filter(d->poly, c, &failed);
+  ifl_status st = poly_filter(d->poly, nullptr, c, &failed);
   if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) return IFL_OK;  // CG needs less memory
   *done = true;
   if (st != IFL_OK) return st;
@@ -2412,6 +2405,15 @@ ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int3
   const int R = shifted ? 1 : pick_tile(h, (int64_t)n_fields * n_scales);
   if (R <= 1) return filter_single(h, n_fields, fields, n_scales, k, out, stats, energy, ColScratch{d->w.part, d->w.sc, true, true});
   return filter_batched(h, R, n_fields, fields, n_scales, k, out, stats, energy);
+}
+
+PolyState* device_poly(Handle* h) { return h->dev ? h->dev->poly : nullptr; }
+
+ifl_status device_cg_column(Handle* h, const double* field, double k, double* out, ifl_solve_stats* st) {
+  std::lock_guard<std::mutex> lk(h->mu);
+  IFL_HIP(hipSetDevice(h->dev->device));
+  double energy = 0.0;
+  return filter_single(h, 1, field, 1, &k, out, st, &energy, ColScratch{h->dev->w.part, h->dev->w.sc, true, true});
 }
 
 // Streaming probe: dst = src in 16-byte units, one unit per thread and one

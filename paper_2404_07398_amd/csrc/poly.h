@@ -74,18 +74,27 @@ std::vector<double> poly_coefficients(int order, double c, double lam, double to
 
 // --------------------------------------------------------------- device side
 struct PolyState;  // defined in poly.hip
+struct PolyWork;
 
 // Device copy of the patches and the bound on the spectrum, on the current
 // device; *out stays NULL where the engine does not take the operator.
 ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out);
 void poly_destroy(PolyState* ps);
 
+// Work space for calls on any handle; one call at a time. limit: bytes its
+// large arrays take at most, allocated here (0: they grow with the calls).
+ifl_status poly_work_create(size_t limit, PolyWork** out);
+void poly_work_destroy(PolyWork* w);
+// Whether a work space of this size holds requests of a few scales.
+bool poly_work_takes(const PolyState* ps, size_t limit, int order);
+
 struct PolyCall {
   int order = 1;
   double gamma = 0.5, rtol = 1e-12;
   int max_iter = 20000;
   int32_t n_fields = 0, n_scales = 0;
-  const double* fields = nullptr;  // device, n_fields x field_len
+  const double* fields = nullptr;  // n_fields x field_len
+  bool fields_host = false;
   const double* k = nullptr;
   double* out = nullptr;           // n_fields x n_scales x field_len, or NULL
   bool out_host = false;
@@ -100,7 +109,8 @@ bool poly_takes(const PolyState* ps, const PolyCall& call);
 
 // Filters every column; the numbers (field * n_scales + scale) of columns
 // whose true residual misses the tolerance go to *failed (their outputs hold
-// what was reached). IFL_ENOMEM: nothing was written.
-ifl_status poly_filter(PolyState* ps, const PolyCall& call, std::vector<int64_t>* failed);
+// what was reached). IFL_ENOMEM, IFL_EUNSUPPORTED: nothing was written. w:
+// NULL for the handle's own work space (the caller holds the handle's lock).
+ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& call, std::vector<int64_t>* failed);
 
 }  // namespace ifl

@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ 
 // field was found bad.
 template <int SC>
 __global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __restrict__ x, GroupScales gs,
-                                                   int n_scales, const int* __restrict__ bad,
+                                                   int64_t field_stride, const int* __restrict__ bad,
                                                    double* __restrict__ out) {
   if (*bad) return;
   const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __re
   const double* xr = x + ((int64_t)blockIdx.y * m.np + (r < 0 ? 0 : r)) * SC;
 #pragma unroll
   for (int s = 0; s < SC; ++s) v[s] = r < 0 ? 0.0 : xr[s];
-  double* o = out + (int64_t)blockIdx.y * n_scales * m.field_len + i;
+  double* o = out + (int64_t)blockIdx.y * field_stride + i;
 #pragma unroll
   for (int s = 0; s < SC; ++s)
     if (gs.column[s] >= 0) o[gs.column[s] * m.field_len] = v[s];
@@ -550,16 +550,21 @@ struct PolyState {
   double lam = 0.0;         // upper end of the spectrum of A, with its margin
   double lam_typical = 0.0; // the same of a mesh whose rows were all like 95% of the rows
   double mass_ratio = 1.0, mass_sum = 0.0;
-  // work space, kept between calls
-  double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *part = nullptr, *coef = nullptr, *stage = nullptr;
-  size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, part_n = 0, coef_n = 0, stage_n = 0;
+  PolyWork* work = nullptr;  // of ifl_filter's calls (under the handle's lock)
+};
+
+// Work space of one caller at a time, kept between calls. With a limit its
+// large arrays live in one allocation of that size.
+struct PolyWork {
+  size_t limit = 0;         // bytes, 0: arrays grow as calls need them
+  double* arena = nullptr;
+  double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *in = nullptr, *stage = nullptr;
+  size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, in_n = 0, stage_n = 0;
+  double *part = nullptr, *coef = nullptr, *sums = nullptr;
+  size_t part_n = 0, coef_n = 0, sums_n = 0;
   int* bad = nullptr;
-  double* sums = nullptr;       // device totals
-  size_t sums_n = 0;
-  double* host = nullptr;       // pinned: totals and the bad flag
-  size_t host_n = 0;
-  double* host_coef = nullptr;  // pinned
-  size_t host_coef_n = 0;
+  double *host = nullptr, *host_coef = nullptr;  // pinned: totals and the bad flag, coefficients
+  size_t host_n = 0, host_coef_n = 0;
 };
 
 namespace {
@@ -705,15 +710,15 @@ void check_scales(const PolyState* ps, int sc, int order, const double* phi, con
     }                                                           \
   } while (0)
 
-void launch_out(const PolyState* ps, int sc, const double* x, const GroupScales& gs, int S, double* out, int F,
-                hipStream_t s) {
+void launch_out(const PolyState* ps, const int* bad, int sc, const double* x, const GroupScales& gs,
+                int64_t field_stride, double* out, int F, hipStream_t s) {
   const dim3 g((unsigned)((ps->m.field_len + kRed - 1) / kRed), (unsigned)F);
   switch (sc) {
-    case 1: k_poly_out<1><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
-    case 2: k_poly_out<2><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
-    case 4: k_poly_out<4><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
-    case 8: k_poly_out<8><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
-    default: k_poly_out<16><<<g, kRed, 0, s>>>(ps->m, x, gs, S, ps->bad, out); break;
+    case 1: k_poly_out<1><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
+    case 2: k_poly_out<2><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
+    case 4: k_poly_out<4><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
+    case 8: k_poly_out<8><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
+    default: k_poly_out<16><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
   }
 }
 
@@ -805,20 +810,56 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
     std::nth_element(d.begin(), d.begin() + at, d.end());
     ps->lam_typical = 2.0 * d[at];
   }
-  if (hipMalloc((void**)&ps->bad, sizeof(int)) != hipSuccess) return fail(IFL_ENOMEM, "hipMalloc failed");
+  if ((st = poly_work_create(0, &ps->work)) != IFL_OK) return st;
   return estimate_spectrum(ps, s);
 }
 
 void poly_destroy(PolyState* ps) {
   if (!ps) return;
   const PolyDev& m = ps->m;
-  const void* ptrs[] = {m.info, m.halo, m.idx,   m.col,   m.val, m.mass,   m.entity,  m.row_of,
-                        ps->phi, ps->t, ps->x, ps->z, ps->part, ps->coef, ps->stage, ps->bad, ps->sums};
+  const void* ptrs[] = {m.info, m.halo, m.idx, m.col, m.val, m.mass, m.entity, m.row_of};
   for (const void* p : ptrs)
     if (p) (void)hipFree(const_cast<void*>(p));
-  if (ps->host) (void)hipHostFree(ps->host);
-  if (ps->host_coef) (void)hipHostFree(ps->host_coef);
+  poly_work_destroy(ps->work);
   delete ps;
+}
+
+static void free_large(PolyWork* w) {
+  for (auto [p, n] : {std::pair<double**, size_t*>{&w->phi, &w->phi_n}, {&w->t, &w->t_n}, {&w->x, &w->x_n},
+                      {&w->z, &w->z_n}, {&w->in, &w->in_n}, {&w->stage, &w->stage_n}}) {
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    *n = 0;
+  }
+}
+
+ifl_status poly_work_create(size_t limit, PolyWork** out) {
+  PolyWork* w = new PolyWork();
+  *out = w;
+  w->limit = limit;
+  size_t n = 0;
+  ifl_status st = IFL_OK;
+  if (limit) st = grow(&w->arena, &n, limit / sizeof(double));
+  if (st == IFL_OK && hipMalloc((void**)&w->bad, sizeof(int)) != hipSuccess) {
+    (void)hipGetLastError();
+    st = fail(IFL_ENOMEM, "hipMalloc failed");
+  }
+  if (st != IFL_OK) {
+    poly_work_destroy(w);
+    *out = nullptr;
+  }
+  return st;
+}
+
+void poly_work_destroy(PolyWork* w) {
+  if (!w) return;
+  if (!w->limit) free_large(w);
+  void* ptrs[] = {w->arena, w->part, w->coef, w->sums, w->bad};
+  for (void* p : ptrs)
+    if (p) (void)hipFree(p);
+  if (w->host) (void)hipHostFree(w->host);
+  if (w->host_coef) (void)hipHostFree(w->host_coef);
+  delete w;
 }
 
 namespace {
@@ -860,14 +901,93 @@ bool poly_takes(const PolyState* ps, const PolyCall& c) {
   return most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0;
 }
 
-ifl_status poly_filter(PolyState* ps, const PolyCall& c, std::vector<int64_t>* failed) {
+namespace {
+
+// How a call goes through the work space: scales per sequence, vectors of
+// the sequence kept at a time, fields at a time, and outputs staged for the
+// host at a time and field; false: not even one scale and one field fit.
+struct Plan {
+  int scales = 0, planes = 0, fields = 0, staged = 0;
+};
+
+int padded_scales(int n) {
+  int p = n / kMaxGroup * kMaxGroup, r = 1;
+  if (n % kMaxGroup == 0) return p;
+  while (r < n % kMaxGroup) r *= 2;
+  return p + r;
+}
+
+bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree, Plan* out) {
+  const PolyDev& m = ps->m;
+  // without a limit: about 6 GB, which at level 9 holds 4 fields with 64
+  // vectors and 32 scales each
+  const size_t have = (limit ? limit : (size_t)6 << 30) / sizeof(double);
+  const int least = std::max(1, std::min(degree, ps->single ? 16 : 2 * ps->depth));
+  const int most = std::max(1, ps->single ? degree : std::min(degree, 64));
+  const int F = c.n_fields;
+  for (int sc = c.n_scales;; sc = (sc + 1) / 2) {
+    const size_t group = (size_t)padded_scales(std::min(sc, kMaxGroup));
+    const size_t rest = limit ? (size_t)F * m.np + (c.fields_host ? (size_t)F * m.field_len : 0) : 0;
+    const size_t vecs = m.np * ((size_t)padded_scales(sc) + (c.order == 2 ? group : 0));
+    // (with a limit also for energies alone: the grouping of the scales, and
+    // with it the order of their sums, does not depend on the outputs)
+    const size_t stage = limit || (c.out && c.out_host) ? (size_t)m.field_len : 0;
+    const size_t avail = have > rest ? have - rest : 0;
+    if (avail >= vecs + stage + least * (size_t)m.np || (!limit && sc == 1)) {
+      out->staged = stage == 0 ? 0 : (int)std::min<size_t>(
+          group, avail > vecs + least * (size_t)m.np ? (avail - vecs - least * (size_t)m.np) / stage : 1);
+      const size_t field = vecs + out->staged * stage;
+      const size_t left = avail > field ? (avail - field) / m.np : 0;
+      out->scales = sc;
+      out->planes = (int)std::max<size_t>(least, std::min<size_t>(most, left));
+      // whole launches of the step kernel
+      if (!ps->single && out->planes < degree && out->planes > ps->depth) out->planes -= out->planes % ps->depth;
+      out->fields = (int)std::max<size_t>(
+          1, std::min<size_t>((size_t)F, avail / (field + (size_t)out->planes * m.np)));
+      return true;
+    }
+    if (sc == 1) return false;
+  }
+}
+
+// A group of scales summed together, and where its totals are.
+struct Group {
+  int sc = 0, n = 0, degree = 0, pad0 = 0;  // scales padded to sc, real ones, largest degree, scales before
+  GroupScales gs;
+  size_t coef = 0;
+};
+struct Totals {
+  Group g;
+  int f0, nf;
+  size_t at;
+};
+
+}  // namespace
+
+bool poly_work_takes(const PolyState* ps, size_t limit, int order) {
+  if (!ps || !(ps->lam > 0.0)) return false;
+  // a request of 4 scales with its field and outputs in host memory, in one
+  // sequence
+  PolyCall c;
+  double some = 0.0;
+  c.order = order;
+  c.n_fields = 1;
+  c.n_scales = 4;
+  c.fields_host = c.out_host = true;
+  c.out = &some;
+  Plan plan;
+  return make_plan(ps, limit, c, 64, &plan) && plan.scales == 4;
+}
+
+ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vector<int64_t>* failed) {
   const auto t0 = std::chrono::steady_clock::now();
+  if (!w) w = ps->work;
   const PolyDev& m = ps->m;
   hipStream_t s = c.stream;
   failed->clear();
   const int S = c.n_scales, F = c.n_fields;
   const double tol = poly_tol(ps, c);
-  // the scales' polynomials, largest degree first, in groups summed together
+  // the scales' polynomials, largest degree first
   std::vector<std::vector<double>> poly((size_t)S);
   std::vector<int> by((size_t)S);
   for (int j = 0; j < S; ++j) {
@@ -876,142 +996,176 @@ ifl_status poly_filter(PolyState* ps, const PolyCall& c, std::vector<int64_t>* f
     if (poly[j].empty()) return fail(IFL_EUNSUPPORTED, "a scale's polynomial exceeds max_iter");
   }
   std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return poly[a].size() > poly[b].size(); });
-  const int degree = (int)poly[by[0]].size() - 1;
-  struct Group {
-    int sc = 0, n = 0, degree = 0, pad0 = 0;  // scales padded to sc, real ones, largest degree, scales before
-    GroupScales gs;
-    size_t coef = 0;
-  };
-  std::vector<Group> groups;
-  size_t ncoef = 0;
-  int spad = 0;
+  Plan plan;
+  if (!make_plan(ps, w->limit, c, (int)poly[by[0]].size() - 1, &plan))
+    return fail(IFL_ENOMEM, "the work space holds no sequence of this mesh");
+  const int FG = plan.fields, G = red_blocks(m.rows), GL = red_blocks(m.np);
+  // sequences of up to plan.scales scales, each summed in groups
+  std::vector<std::vector<Group>> seqs;
+  size_t ncoef = 0, nsums = (size_t)F;
   for (int j = 0; j < S;) {
-    Group g;
-    g.n = std::min(kMaxGroup, S - j);
-    g.sc = 1;
-    while (g.sc < g.n) g.sc *= 2;
-    g.degree = (int)poly[by[j]].size() - 1;
-    g.pad0 = spad;
-    g.coef = ncoef;
-    for (int i = 0; i < kMaxGroup; ++i) {
-      g.gs.column[i] = i < g.n ? by[j + i] : -1;
-      g.gs.c[i] = i < g.n ? scale_factor(c, by[j + i]) : 0.0;
-    }
-    ncoef += (size_t)(g.degree + 1) * g.sc;
-    spad += g.sc;
-    j += g.n;
-    groups.push_back(g);
-  }
-  // fields at a time and vectors of the sequence kept at a time: up to 64
-  // vectors, and as many fields as about 6 GB hold
-  const size_t vec = (size_t)m.np * sizeof(double);
-  const int zpad = c.order == 2 ? groups[0].sc : 0;
-  int planes = std::min(degree, ps->single ? degree : 64);
-  constexpr size_t kBudget = (size_t)6 << 30;
-  while (planes > 16 && (size_t)(planes + spad + zpad) * vec > kBudget) planes = std::max(16, planes / 2);
-  planes = std::max(planes, std::min(degree, 2 * std::max(1, ps->depth)));
-  planes = std::max(planes, 1);
-  const int FG = (int)std::max<size_t>(1, std::min<size_t>((size_t)F, kBudget / ((planes + spad + zpad) * vec)));
-  const int G = red_blocks(m.rows);
-  const int GL = red_blocks(m.np);
-  ifl_status st;
-  const size_t nsums = (size_t)F + (size_t)F * spad * 3;
-  if ((st = grow(&ps->phi, &ps->phi_n, (size_t)F * m.np)) ||
-      (st = grow(&ps->t, &ps->t_n, (size_t)planes * FG * m.np)) ||
-      (st = grow(&ps->x, &ps->x_n, (size_t)FG * spad * m.np)) ||
-      (zpad && (st = grow(&ps->z, &ps->z_n, (size_t)FG * zpad * m.np))) ||
-      (st = grow(&ps->part, &ps->part_n, std::max((size_t)F * GL, (size_t)FG * kMaxGroup * 3 * G))) ||
-      (st = grow(&ps->coef, &ps->coef_n, ncoef)) || (st = grow(&ps->sums, &ps->sums_n, nsums)) ||
-      (c.out && c.out_host && (st = grow(&ps->stage, &ps->stage_n, (size_t)FG * S * m.field_len))) ||
-      (st = grow_host(&ps->host, &ps->host_n, nsums + 1)) || (st = grow_host(&ps->host_coef, &ps->host_coef_n, ncoef)))
-    return st;
-  for (const Group& g : groups)
-    for (int k = 0; k <= g.degree; ++k)
-      for (int i = 0; i < g.sc; ++i) {
-        const std::vector<double>* p = i < g.n ? &poly[g.gs.column[i]] : nullptr;
-        ps->host_coef[g.coef + (size_t)k * g.sc + i] = p && k < (int)p->size() ? (*p)[k] : 0.0;
+    std::vector<Group> groups;
+    int pad = 0;
+    for (const int end = std::min(S, j + plan.scales); j < end;) {
+      Group g;
+      g.n = std::min(kMaxGroup, end - j);
+      g.sc = padded_scales(g.n);
+      g.degree = (int)poly[by[j]].size() - 1;
+      g.pad0 = pad;
+      g.coef = ncoef;
+      for (int i = 0; i < kMaxGroup; ++i) {
+        g.gs.column[i] = i < g.n ? by[j + i] : -1;
+        g.gs.c[i] = i < g.n ? scale_factor(c, by[j + i]) : 0.0;
       }
-  IFL_HIP(hipMemcpyAsync(ps->coef, ps->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
-  IFL_HIP(hipMemsetAsync(ps->bad, 0, sizeof(int), s));
-  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, c.fields, ps->phi, ps->part, ps->bad);
-  k_poly_total<<<F, kRed, 0, s>>>(ps->part, GL, ps->sums);
+      ncoef += (size_t)(g.degree + 1) * g.sc;
+      nsums += (size_t)F * g.sc * 3;
+      pad += g.sc;
+      j += g.n;
+      groups.push_back(g);
+    }
+    seqs.push_back(std::move(groups));
+  }
+  const size_t np = (size_t)m.np;
+  const size_t group = (size_t)padded_scales(std::min(plan.scales, kMaxGroup));
+  const size_t n_phi = F * np, n_t = (size_t)plan.planes * FG * np, n_x = (size_t)FG * padded_scales(plan.scales) * np;
+  const size_t n_z = c.order == 2 ? (size_t)FG * group * np : 0;
+  const size_t n_in = c.fields_host ? (size_t)F * m.field_len : 0;
+  const size_t n_stage = (size_t)FG * plan.staged * m.field_len;
+  ifl_status st;
+  if (w->limit) {
+    if ((n_phi + n_t + n_x + n_z + n_in + n_stage) * sizeof(double) > w->limit)
+      return fail(IFL_ENOMEM, "the work space holds no sequence of this mesh");
+    double* at = w->arena;
+    for (auto [p, n] : {std::pair<double**, size_t>{&w->phi, n_phi}, {&w->t, n_t}, {&w->x, n_x}, {&w->z, n_z},
+                        {&w->in, n_in}, {&w->stage, n_stage}}) {
+      *p = at;
+      at += n;
+    }
+  } else if ((st = grow(&w->phi, &w->phi_n, n_phi)) || (st = grow(&w->t, &w->t_n, n_t)) ||
+             (st = grow(&w->x, &w->x_n, n_x)) || (st = grow(&w->z, &w->z_n, n_z)) ||
+             (st = grow(&w->in, &w->in_n, n_in)) || (st = grow(&w->stage, &w->stage_n, n_stage))) {
+    free_large(w);  // the caller goes on with CG
+    return st;
+  }
+  if ((st = grow(&w->part, &w->part_n, std::max((size_t)F * GL, (size_t)FG * kMaxGroup * 3 * G))) ||
+      (st = grow(&w->coef, &w->coef_n, ncoef)) || (st = grow(&w->sums, &w->sums_n, nsums)) ||
+      (st = grow_host(&w->host, &w->host_n, nsums + 1)) || (st = grow_host(&w->host_coef, &w->host_coef_n, ncoef)))
+    return st;
+  for (const auto& groups : seqs)
+    for (const Group& g : groups)
+      for (int k = 0; k <= g.degree; ++k)
+        for (int i = 0; i < g.sc; ++i) {
+          const std::vector<double>* p = i < g.n ? &poly[g.gs.column[i]] : nullptr;
+          w->host_coef[g.coef + (size_t)k * g.sc + i] = p && k < (int)p->size() ? (*p)[k] : 0.0;
+        }
+  IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
+  IFL_HIP(hipMemsetAsync(w->bad, 0, sizeof(int), s));
+  const double* fields = c.fields;
+  if (c.fields_host) {
+    IFL_HIP(hipMemcpyAsync(w->in, c.fields, n_in * sizeof(double), hipMemcpyHostToDevice, s));
+    fields = w->in;
+  }
+  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, fields, w->phi, w->part, w->bad);
+  k_poly_total<<<F, kRed, 0, s>>>(w->part, GL, w->sums);
   IFL_HIP(hipGetLastError());
-  int* bad_host = reinterpret_cast<int*>(ps->host + nsums);
-  if (c.out && c.out_host) {  // the copies to the host must not start on a bad field
-    IFL_HIP(hipMemcpyAsync(bad_host, ps->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+  int* bad_host = reinterpret_cast<int*>(w->host + nsums);
+  if (n_stage) {  // the copies to the host must not start on a bad field
+    IFL_HIP(hipMemcpyAsync(bad_host, w->bad, sizeof(int), hipMemcpyDeviceToHost, s));
     IFL_HIP(hipStreamSynchronize(s));
     if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   }
+  std::vector<Totals> totals;
+  size_t sum_at = (size_t)F;
   for (int f0 = 0; f0 < F; f0 += FG) {
     const int nf = std::min(FG, F - f0);
     const int64_t plane = (int64_t)nf * m.np;
-    const double* phi = ps->phi + (int64_t)f0 * m.np;
-    const double *prev = nullptr, *cur = phi;
-    for (int k0 = 0; k0 < degree || k0 == 0;) {
-      const int n = std::min(planes, degree - k0);
-      for (int j = 0; j < n;) {
-        const int d = std::min(ps->single ? n : ps->depth, n - j);
-        double* to = ps->t + (int64_t)j * plane;
-        launch_steps(ps, prev, cur, to, plane, nf, d, s);
-        prev = d >= 2 ? to + (int64_t)(d - 2) * plane : cur;
-        cur = to + (int64_t)(d - 1) * plane;
-        j += d;
+    const double* phi = w->phi + (int64_t)f0 * m.np;
+    for (const auto& groups : seqs) {
+      const int degree = groups[0].degree;
+      const double *prev = nullptr, *cur = phi;
+      for (int k0 = 0; k0 < degree || k0 == 0;) {
+        const int n = std::min(plan.planes, degree - k0);
+        for (int j = 0; j < n;) {
+          const int d = std::min(ps->single ? n : ps->depth, n - j);
+          double* to = w->t + (int64_t)j * plane;
+          launch_steps(ps, prev, cur, to, plane, nf, d, s);
+          prev = d >= 2 ? to + (int64_t)(d - 2) * plane : cur;
+          cur = to + (int64_t)(d - 1) * plane;
+          j += d;
+        }
+        for (const Group& g : groups) {
+          const int ng = std::min(n, g.degree - k0);
+          if (ng <= 0 && k0 > 0) continue;
+          launch_sum(g.sc, k0 == 0 ? phi : nullptr, w->t, plane, m.np, std::max(0, ng),
+                     w->coef + g.coef + (size_t)(k0 == 0 ? 0 : k0 + 1) * g.sc, w->x + (size_t)g.pad0 * nf * np, nf, s);
+        }
+        IFL_HIP(hipGetLastError());
+        k0 += n;
+        if (n == 0) break;
       }
       for (const Group& g : groups) {
-        const int ng = std::min(n, g.degree - k0);
-        if (ng <= 0 && k0 > 0) continue;
-        launch_sum(g.sc, k0 == 0 ? phi : nullptr, ps->t, plane, m.np, std::max(0, ng),
-                   ps->coef + g.coef + (size_t)(k0 == 0 ? 0 : k0 + 1) * g.sc,
-                   ps->x + (size_t)g.pad0 * nf * m.np, nf, s);
+        const double* x = w->x + (size_t)g.pad0 * nf * np;
+        IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, w->z, g.gs, w->part, G, nf, s));
+        k_poly_total<<<nf * g.sc * 3, kRed, 0, s>>>(w->part, G, w->sums + sum_at);
+        totals.push_back({g, f0, nf, sum_at});
+        sum_at += (size_t)nf * g.sc * 3;
+        if (!c.out) continue;
+        if (!n_stage) {
+          launch_out(ps, w->bad, g.sc, x, g.gs, (int64_t)S * m.field_len, c.out + (int64_t)f0 * S * m.field_len, nf, s);
+          continue;
+        }
+        // to the host through the staging: columns in the caller's order, so
+        // that neighbouring scales leave in one copy
+        std::vector<int> cols(g.gs.column, g.gs.column + g.n);
+        std::sort(cols.begin(), cols.end());
+        for (int q = 0; q < g.n; q += plan.staged) {
+          const int qn = std::min(plan.staged, g.n - q);
+          GroupScales some = g.gs;
+          for (int i = 0; i < g.n; ++i) {
+            const int at = (int)(std::lower_bound(cols.begin(), cols.end(), g.gs.column[i]) - cols.begin()) - q;
+            some.column[i] = at >= 0 && at < qn ? at : -1;
+          }
+          launch_out(ps, w->bad, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
+          for (int f = 0; f < nf; ++f)
+            for (int i = q, e; i < q + qn; i = e) {
+              for (e = i + 1; e < q + qn && cols[e] == cols[e - 1] + 1;) ++e;
+              IFL_HIP(hipMemcpyAsync(c.out + ((int64_t)(f0 + f) * S + cols[i]) * m.field_len,
+                                     w->stage + ((int64_t)f * qn + i - q) * m.field_len,
+                                     sizeof(double) * (size_t)(e - i) * m.field_len, hipMemcpyDeviceToHost, s));
+            }
+        }
       }
       IFL_HIP(hipGetLastError());
-      k0 += n;
-      if (n == 0) break;
     }
-    double* dst = !c.out ? nullptr : (c.out_host ? ps->stage : c.out + (int64_t)f0 * S * m.field_len);
-    for (const Group& g : groups) {
-      const double* x = ps->x + (size_t)g.pad0 * nf * m.np;
-      IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, ps->z, g.gs, ps->part, G, nf, s));
-      k_poly_total<<<nf * g.sc * 3, kRed, 0, s>>>(ps->part, G,
-                                                  ps->sums + F + ((size_t)f0 * spad + (size_t)g.pad0 * nf) * 3);
-      if (dst) launch_out(ps, g.sc, x, g.gs, S, dst, nf, s);
-    }
-    IFL_HIP(hipGetLastError());
-    if (dst && c.out_host)
-      IFL_HIP(hipMemcpyAsync(c.out + (int64_t)f0 * S * m.field_len, ps->stage,
-                             sizeof(double) * (size_t)nf * S * m.field_len, hipMemcpyDeviceToHost, s));
   }
-  IFL_HIP(hipMemcpyAsync(ps->host, ps->sums, nsums * sizeof(double), hipMemcpyDeviceToHost, s));
-  IFL_HIP(hipMemcpyAsync(bad_host, ps->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+  IFL_HIP(hipMemcpyAsync(w->host, w->sums, nsums * sizeof(double), hipMemcpyDeviceToHost, s));
+  IFL_HIP(hipMemcpyAsync(bad_host, w->bad, sizeof(int), hipMemcpyDeviceToHost, s));
   IFL_HIP(hipStreamSynchronize(s));
   if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-  for (int f0 = 0; f0 < F; f0 += FG) {
-    const int nf = std::min(FG, F - f0);
-    for (const Group& g : groups)
-      for (int f = 0; f < nf; ++f)
-        for (int i = 0; i < g.n; ++i) {
-          const double bb = ps->host[f0 + f];
-          const double* q = ps->host + F + ((size_t)f0 * spad + (size_t)g.pad0 * nf + (size_t)f * g.sc + i) * 3;
-          const int64_t col = (int64_t)(f0 + f) * S + g.gs.column[i];
-          // attainable accuracy: what FP64 can tell of M phi - S x
-          const double floor = 8.0 * 1.1102230246251565e-16 *
-                               (std::sqrt(bb) + std::sqrt(q[1]) * (1.0 + g.gs.c[i] * std::pow(ps->lam, c.order)));
-          const double res = std::sqrt(q[0]);
-          if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
-          if (c.stats) {
-            ifl_solve_stats& so = c.stats[col];
-            so.iterations = bb > 0.0 ? (int32_t)poly[g.gs.column[i]].size() - 1 : 0;
-            so.refinements = 0;
-            so.status = IFL_OK;
-            so.reserved = 0;
-            so.rel_residual = bb > 0.0 ? res / std::sqrt(bb) : res;
-            so.seconds = secs;
-            so.energy = 0.5 * q[2] / ps->mass_sum;
-          }
-          if (c.energy) c.energy[col] = 0.5 * q[2] / ps->mass_sum;
+  for (const Totals& t : totals)
+    for (int f = 0; f < t.nf; ++f)
+      for (int i = 0; i < t.g.n; ++i) {
+        const double bb = w->host[t.f0 + f];
+        const double* q = w->host + t.at + ((size_t)f * t.g.sc + i) * 3;
+        const int64_t col = (int64_t)(t.f0 + f) * S + t.g.gs.column[i];
+        // attainable accuracy: what FP64 can tell of M phi - S x
+        const double floor = 8.0 * 1.1102230246251565e-16 *
+                             (std::sqrt(bb) + std::sqrt(q[1]) * (1.0 + t.g.gs.c[i] * std::pow(ps->lam, c.order)));
+        const double res = std::sqrt(q[0]);
+        if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
+        if (c.stats) {
+          ifl_solve_stats& so = c.stats[col];
+          so.iterations = bb > 0.0 ? (int32_t)poly[t.g.gs.column[i]].size() - 1 : 0;
+          so.refinements = 0;
+          so.status = IFL_OK;
+          so.reserved = 0;
+          so.rel_residual = bb > 0.0 ? res / std::sqrt(bb) : res;
+          so.seconds = secs;
+          so.energy = 0.5 * q[2] / ps->mass_sum;
         }
-  }
+        if (c.energy) c.energy[col] = 0.5 * q[2] / ps->mass_sum;
+      }
   std::sort(failed->begin(), failed->end());
   return IFL_OK;
 }

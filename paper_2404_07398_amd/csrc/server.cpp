@@ -8,6 +8,11 @@
 // admitted when its device footprint fits the server's memory budget. A
 // column's arithmetic does not depend on its tile neighbours, its slot or
 // its start time, so a result is the same alone and in any mix.
+//
+// Handles that leave the solver to the library (batch = 0) and whose operator
+// the polynomial engine takes are served by it instead of a tile: a worker
+// runs a request's scales together, request after request, in a work space of
+// the tile's size.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,6 +29,7 @@
 
 #include "batch.h"
 #include "internal.h"
+#include "poly.h"
 
 using namespace ifl;
 using Clock = std::chrono::steady_clock;
@@ -85,6 +91,10 @@ struct Worker {
   // column: real and imaginary parts) over the first-order operator
   bool cx = false;
   double* zero_rows = nullptr;  // n_pad zeros: the imaginary part of a field
+  // served by the polynomial engine, with the options of ifl_server_add
+  PolyState* poly = nullptr;
+  PolyWork* poly_work = nullptr;
+  ifl_options opt{};
 };
 
 }  // namespace
@@ -356,9 +366,72 @@ ifl_status run_worker_shifted(Worker* wk) {
   }
 }
 
+// The worker of a handle the polynomial engine serves: a request's columns
+// are one call of it. The field is read, checked and permuted there, and the
+// columns that miss the tolerance go to the handle's own CG.
+ifl_status run_worker_poly(Worker* wk) {
+  Handle* h = wk->h;
+  for (;;) {
+    cancel_pending(wk);
+    std::vector<ifl_ticket*> adm;
+    admit(wk, &adm);
+    for (ifl_ticket* t : adm)
+      for (int j = 0; j < t->n_scales; ++j) wk->pending.push_back({t, j});
+    if (wk->pending.empty()) {
+      std::unique_lock<std::mutex> lk(wk->srv->mu);
+      if (wk->srv->stop && wk->queue.empty()) return IFL_OK;
+      // a request that came since admit() looked is not slept over
+      if (!wk->queue.empty() && (wk->srv->used == 0 || wk->srv->tiles + wk->srv->used +
+                                                               wk->queue.front()->footprint <= wk->srv->budget))
+        continue;
+      wk->srv->cv.wait_for(lk, std::chrono::milliseconds(50));
+      continue;
+    }
+    // a request's columns wait together: all of them run, or none has been
+    // cancelled yet
+    ifl_ticket* t = wk->pending.front().t;
+    PolyCall c;
+    c.order = h->op.order;
+    c.gamma = wk->opt.gamma;
+    c.rtol = wk->opt.rtol;
+    c.max_iter = wk->opt.max_iter;
+    c.n_fields = 1;
+    c.n_scales = t->n_scales;
+    c.fields = t->field;
+    c.fields_host = true;
+    c.k = t->k.data();
+    c.out = t->out;
+    c.out_host = t->out != nullptr;
+    c.stats = t->stats.data();
+    c.stream = wk->stream;
+    std::vector<int64_t> failed;
+    ifl_status st = IFL_EUNSUPPORTED;
+    if (poly_takes(wk->poly, c)) st = poly_filter(wk->poly, wk->poly_work, c, &failed);
+    if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) {
+      failed.clear();
+      for (int j = 0; j < t->n_scales; ++j) failed.push_back(j);
+      st = IFL_OK;
+    }
+    for (size_t i = 0; st == IFL_OK && i < failed.size(); ++i) {
+      const int64_t j = failed[i];
+      const ifl_status e = device_cg_column(h, t->field, t->k[j], t->out ? t->out + j * wk->L : nullptr, &t->stats[j]);
+      if (e != IFL_OK && e != IFL_ENOTCONV) st = e;
+    }
+    if (st != IFL_OK && st != IFL_EINVAL) return st;  // with the request still pending
+    wk->pending.erase(wk->pending.begin(), wk->pending.begin() + t->n_scales);
+    t->remaining = 0;
+    if (st == IFL_EINVAL) {
+      release_ticket(wk, t);
+      finish_ticket(t, st, ifl_last_error());
+    } else {
+      complete_ticket(wk, t);
+    }
+  }
+}
+
 void worker_main(Worker* wk) {
   (void)hipSetDevice(wk->srv->device);
-  ifl_status st = wk->shifted ? run_worker_shifted(wk) : run_worker(wk);
+  ifl_status st = wk->poly ? run_worker_poly(wk) : wk->shifted ? run_worker_shifted(wk) : run_worker(wk);
   if (st != IFL_OK) {
     // fail everything this worker still holds, so no waiter blocks forever;
     // admitted requests (in a slot or waiting for one) give their memory
@@ -443,25 +516,38 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
       return fail(IFL_ENOMEM, "tile work space exceeds the server's memory budget");
     s->tiles += tile;
   }
+  {
+    std::lock_guard<std::mutex> lk(h->mu);
+    wk->opt = h->opt;
+  }
   ifl_status st = IFL_OK;
-  if (!wk->shifted) st = batch_alloc(&wk->w, wk->bm, wk->R, h->opt.precision == IFL_MIXED, wk->cx);
-  else if (hipMalloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess)  // only the field check's flag
+  // the polynomial engine where the handle leaves the solver to the library
+  // and a tile's memory holds its work space (few slots do not)
+  if (wk->opt.batch == 0 && poly_work_takes(device_poly(h), tile, h->op.order)) {
+    wk->poly = device_poly(h);
+    st = poly_work_create(tile, &wk->poly_work);
+  } else if (!wk->shifted) {
+    st = batch_alloc(&wk->w, wk->bm, wk->R, h->opt.precision == IFL_MIXED, wk->cx);
+  } else if (hipMalloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess) {  // only the field check's flag
     st = fail(IFL_ENOMEM, "hipMalloc of the field check flag failed");
-  if (st == IFL_OK && wk->cx) {
+  }
+  if (st == IFL_OK && wk->cx && !wk->poly) {
     wk->w.cx_g = handle_cx_gnorm(h);
     if (hipMalloc((void**)&wk->zero_rows, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
         hipMemset(wk->zero_rows, 0, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess)
       st = fail(IFL_ENOMEM, "allocation of the zero imaginary parts failed");
   }
-  if (st == IFL_OK && hipMalloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
+  if (st == IFL_OK && !wk->poly && hipMalloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
     st = fail(IFL_ENOMEM, "hipMalloc of the field staging failed");
-  if (st == IFL_OK && hipMalloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
+  if (st == IFL_OK && !wk->poly &&
+      hipMalloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
     st = fail(IFL_ENOMEM, "hipMalloc of the output staging failed");
   if (st == IFL_OK && hipStreamCreateWithFlags(&wk->stream, hipStreamNonBlocking) != hipSuccess)
     st = fail(IFL_EDEVICE, "hipStreamCreate failed");
   if (st != IFL_OK) {
     batch_free(&wk->w);
+    poly_work_destroy(wk->poly_work);
     if (wk->col_out) (void)hipFree(wk->col_out);
     if (wk->stage) (void)hipFree(wk->stage);
     if (wk->zero_rows) (void)hipFree(wk->zero_rows);
@@ -595,6 +681,7 @@ void ifl_server_destroy(ifl_server* s) {
     (void)hipSetDevice(s->device);
     if (wk->stream) (void)hipStreamSynchronize(wk->stream);
     batch_free(&wk->w);
+    poly_work_destroy(wk->poly_work);
     if (wk->col_out) (void)hipFree(wk->col_out);
     if (wk->stage) (void)hipFree(wk->stage);
     if (wk->zero_rows) (void)hipFree(wk->zero_rows);

@@ -139,3 +139,30 @@ def test_limits_and_bad_input(ifl):
     h.filter(torch.from_numpy(phi).cuda(), ks, out=d)
     assert np.array_equal(d.cpu().numpy(), host)
     h.close()
+
+
+@pytest.mark.parametrize("order,slots,scales", [(1, 4, 40), (2, 8, 19), (1, 64, 5)])
+def test_served_in_several_sequences(ifl, order, slots, scales):
+    """A request whose scales outgrow the worker's work space runs in several
+    sequences: bitwise the fields of ifl_filter on the same handle; their
+    energies up to the order of the sums (positive terms through trees of at
+    most 32 additions: 64 u), and bitwise those of the same request without
+    outputs."""
+    s = W.icosphere(5)
+    s = s.with_mask(W.land_mask(s, 0.3))
+    h = ifl.prepare_mesh(s, ifl.IFL_VERTEX_SCALAR, order, precision=ifl.IFL_MIXED)
+    phi = _noise(s.n_vertices, 4)
+    ks = W.log_scales(s.h, scales, lam_max_cells=20.0)[::-1].copy()
+    out, st = h.filter(phi, ks)
+    srv = ifl.Server(1 << 30, slots=slots)
+    mid = srv.add(h)
+    t, _ = srv.submit(mid, phi, ks)
+    code, stats, o, _ = srv.wait(t, scales)
+    assert code == 0 and np.array_equal(o, out[0])
+    for x, y in zip(stats, st):
+        assert abs(x.energy - y.energy) <= 64 * 2.0 ** -53 * y.energy
+    t, _ = srv.submit(mid, phi, ks, spectrum_only=True)
+    code, alone, _, _ = srv.wait(t, scales)
+    assert code == 0 and [x.energy for x in alone] == [x.energy for x in stats]
+    srv.close()
+    h.close()
