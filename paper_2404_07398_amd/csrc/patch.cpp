@@ -155,11 +155,14 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
   if (pp.single) {
     leaf = {0, g.n};
   } else {
-    // interior units of a patch: what a round patch of the capacity has
-    // left inside its rings, fewer on meshes that would not fill the chip
-    const double side = std::sqrt((double)pp.cap) - 2.0 * pp.depth;
-    const int64_t most = std::max<int64_t>(64, (int64_t)(0.92 * side * side));
-    const int64_t want = std::max<int64_t>(64, std::min<int64_t>(most, (g.n + 255) / 256));
+    // interior units of a patch: what a round patch of the capacity has left
+    // inside its rings; on meshes that would not fill the chip a patch per CU,
+    // with as many more rings as its capacity then holds
+    const double side = std::sqrt((double)pp.cap);
+    const double most = 0.92 * (side - 2.0 * pp.depth) * (side - 2.0 * pp.depth);
+    const int64_t want =
+        std::max<int64_t>(64, std::min<int64_t>(std::max<int64_t>(64, (int64_t)most), (g.n + 255) / 256));
+    pp.depth = std::max(pp.depth, std::min(kPolyDepth, (int)(0.5 * (side - std::sqrt((double)want / 0.8)))));
     const int parts = local_order && g.n >= 32768 ? 8 : 1;
     std::vector<std::atomic<int32_t>> mark((size_t)g.n);
     for (int64_t i = 0; i < g.n; ++i) mark[i].store(0, std::memory_order_relaxed);
@@ -257,7 +260,6 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
       pp.patches.push_back(info);
       pp.halo.insert(pp.halo.end(), L.units.begin() + L.ends[0], L.units.end());
       pp.idx.insert(pp.idx.end(), L.idx.begin(), L.idx.end());
-      pp.largest = std::max<int>(pp.largest, (int)L.units.size());
     }
 
   pp.halo.push_back(0);  // a patch without halo units still reads one entry
@@ -298,56 +300,69 @@ std::vector<double> poly_coefficients(int order, double c, double lam, double to
   // in extended precision: the coefficients of order 2 are read with the
   // weight 1 + c lam^2, the condition number of the system
   using real = long double;
-  using cx = std::complex<real>;
   const int n = order;
   if (n != 1 && n != 2) return {};
-  // one zero of 1 + c x^n in z (n = 2: the other is its conjugate), and
-  // rho, z = (rho + 1 / rho) / 2, |rho| > 1
-  const real at = 2.0L * std::pow((real)c, -1.0L / n) / (real)lam;
-  const cx z = n == 1 ? cx(-at - 1.0L, 0.0L) : cx(-1.0L, at);
-  const cx root = std::sqrt(z - (real)1) * std::sqrt(z + (real)1);
-  cx rho = z + root;
+  // one zero zr + i zi of 1 + c x^n in z (n = 2: the other is its conjugate),
+  // and rho, z = (rho + 1 / rho) / 2, |rho| > 1
+  const real at = 2.0L / (real)lam * (n == 1 ? 1.0L / (real)c : 1.0L / std::sqrt((real)c));
+  const real zr = n == 1 ? -1.0L - at : -1.0L, zi = n == 1 ? 0.0L : at;
+  const std::complex<real> z(zr, zi);
+  const std::complex<real> root = std::sqrt(z - (real)1) * std::sqrt(z + (real)1);
+  std::complex<real> rho = z + root;
   if (std::abs(rho) < 1.0L) rho = z - root;
-  const real slow = std::abs(rho);
-  if (!(slow > 1.0L) || !std::isfinite((double)slow)) return {};
+  const real grow = std::log(std::abs(rho)), turn = std::arg(rho);
+  if (!(grow > 0.0L) || !std::isfinite((double)grow)) return {};
   // a of the residual a_0 T_{m+1} (n = 1), a_0 T_{m+1} + a_1 T_{m+2} (n = 2,
   // real and imaginary part of its value 1 at z); its size
   real a[2] = {0.0L, 0.0L};
+  auto cheb = [&](int k, real* re, real* im) {
+    const real up = std::exp(k * grow), down = 1.0L / up;
+    *re = 0.5L * (up + down) * std::cos(k * turn);
+    *im = 0.5L * (up - down) * std::sin(k * turn);
+  };
   auto solve = [&](int m) {
-    const cx p0 = std::pow(rho, (real)(m + 1)), t0 = 0.5L * (p0 + (real)1 / p0);
+    real r0, i0, r1, i1;
+    cheb(m + 1, &r0, &i0);
     if (n == 1) {
-      a[0] = 1.0L / t0.real();
+      a[0] = 1.0L / r0;
       return std::abs(a[0]);
     }
-    const cx p1 = p0 * rho, t1 = 0.5L * (p1 + (real)1 / p1);
-    const real det = t0.real() * t1.imag() - t1.real() * t0.imag();
-    a[0] = t1.imag() / det;
-    a[1] = -t0.imag() / det;
+    cheb(m + 2, &r1, &i1);
+    const real det = r0 * i1 - r1 * i0;
+    a[0] = i1 / det;
+    a[1] = -i0 / det;
     return std::abs(a[0]) + std::abs(a[1]);
   };
-  const double guess = std::log(2.0 / tol) / (double)std::log(slow);
+  const double guess = std::log(2.0 / tol) / (double)grow;
   if (!(guess < 4.0 * max_degree + 64.0)) return {};
-  int m = std::max(0, (int)guess - 4);
-  while (m > 0 && solve(m) <= tol) m -= std::min(m, 4);
-  while (m <= max_degree && !(solve(m) <= tol)) ++m;
-  if (m > max_degree) return {};
-  // p = (1 - R) / (1 + c x^n): the factors z - z_i divided out one by one,
-  // from the highest term down (the growing direction of the recurrence)
-  std::vector<cx> q(m + n + 1, (real)0);
-  q[0] = (real)1;
-  for (int j = 0; j < n; ++j) q[m + 1 + j] -= a[j];
-  for (int i = 0; i < n; ++i) {
-    const cx zi = i == 0 ? z : std::conj(z);
-    const int d = (int)q.size() - 1;
-    std::vector<cx> s(d + 2, (real)0);
-    for (int k = d; k >= 1; --k) s[k - 1] = (real)2 * q[k] + (real)2 * zi * s[k] - s[k + 1];
-    s[0] *= 0.5L;
-    s.resize(d);
-    q = std::move(s);
+  int m = std::max(0, (int)guess);
+  if (solve(m) <= tol) {
+    while (m > 0 && solve(m - 1) <= tol) --m;
+  } else {
+    while (m <= max_degree && !(solve(m) <= tol)) ++m;
   }
-  const real lead = (real)c * std::pow(0.5L * (real)lam, (real)n);
-  std::vector<double> out(q.size());
-  for (size_t k = 0; k < q.size(); ++k) out[k] = (double)(q[k] / lead).real();
+  if (m > max_degree) return {};
+  solve(m);
+  // s = (1 - R) / (z - z_0), from the highest term down (the growing
+  // direction of the recurrence); p = s / (c (lam / 2)) for n = 1, and for
+  // n = 2, 1 / |z - z_0|^2 = Im (1 / (z - z_0)) / Im z_0 gives p from Im s
+  const real lead = n == 1 ? 1.0L / ((real)c * 0.5L * (real)lam)
+                           : 1.0L / ((real)c * 0.25L * (real)lam * (real)lam * zi);
+  std::vector<double> out((size_t)m + 1);
+  real sr = 0.0L, si = 0.0L, ur = 0.0L, ui = 0.0L;  // s_k, s_{k+1}
+  for (int k = m + n; k >= 1; --k) {
+    const real q = k > m ? -a[k - m - 1] : 0.0L;
+    real nr = 2.0L * (q + zr * sr - zi * si) - ur, ni = 2.0L * (zr * si + zi * sr) - ui;
+    if (k == 1) {
+      nr *= 0.5L;
+      ni *= 0.5L;
+    }
+    ur = sr;
+    ui = si;
+    sr = nr;
+    si = ni;
+    if (k - 1 <= m) out[(size_t)k - 1] = (double)((n == 1 ? sr : si) * lead);
+  }
   return out;
 }
 

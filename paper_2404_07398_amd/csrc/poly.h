@@ -12,7 +12,7 @@
 namespace ifl {
 
 // Rings of halo units around a patch, at most.
-constexpr int kPolyDepth = 8;
+constexpr int kPolyDepth = 16;
 
 // Threads of a patch's workgroup and units per thread; what a patch holds.
 constexpr int kPolyThreads = 512;
@@ -21,7 +21,8 @@ constexpr int poly_slots(int nc, int width) { return nc == 1 ? (width <= 6 ? 4 :
 constexpr int poly_patch_units(int nc, int width) {
   return nc == 1 ? kPolyThreads * poly_slots(nc, width) : 1024;
 }
-constexpr int poly_single_units(int nc, int width) { return kPolySingleThreads * poly_slots(nc, width); }
+constexpr int poly_single_units(int nc, int width) { return kPolySingleThreads * (poly_slots(nc, width) >= 2 ? 2 : 1); }
+// Rings of large meshes' patches (small ones take what their patches leave).
 constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 6 ? 8 : 4; }
 
 // Records, in whole 16-byte units (8 for 3 neighbours): a unit's own block
@@ -47,7 +48,6 @@ struct PatchPack {
   int width = 6;   // neighbour entries per unit (padded with the unit itself, value 0)
   int cap = 0;     // units a patch may hold
   int depth = 0;   // rings
-  int largest = 0; // units of the largest patch
   bool single = false;          // one patch without rings holds the mesh
   double mass_ratio = 1.0;      // largest mass / smallest
   std::vector<int32_t> order;   // position -> unit of the operator

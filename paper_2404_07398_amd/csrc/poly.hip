@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kRed) void k_poly_sum(const double* __restrict__ ph
     for (int s = 0; s < SC; ++s) acc[s] = xr[s];
   }
   const double* tr = t + at;
-#pragma unroll 8
+#pragma unroll 16
   for (int k = 0; k < n; ++k) {
     const double v = tr[(int64_t)k * plane];
 #pragma unroll
@@ -422,13 +422,22 @@ __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __
   }
 }
 
-// Sums of 'g' partials: block b of the grid writes dst[b].
-__global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ part, int g, double* __restrict__ dst) {
+// Sums of partials: block b of the first n writes the sum of its g partials
+// to dst[b], the others theirs (g2 each) to dst2. dst is pinned host memory:
+// no copy follows. bad_dst != nullptr: the flag goes there too.
+__global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ part, int g, int n,
+                                                     double* __restrict__ dst, const double* __restrict__ part2,
+                                                     int g2, double* __restrict__ dst2, const int* __restrict__ bad,
+                                                     int* __restrict__ bad_dst) {
   __shared__ double lds[kRed / 64];
+  const bool first = (int)blockIdx.x < n;
+  const int b = first ? blockIdx.x : blockIdx.x - n, len = first ? g : g2;
+  const double* p = (first ? part : part2) + (int64_t)b * len;
   double s = 0.0;
-  for (int i = threadIdx.x; i < g; i += kRed) s += part[(int64_t)blockIdx.x * g + i];
+  for (int i = threadIdx.x; i < len; i += kRed) s += p[i];
   const double t = block_total<kRed>(s, lds);
-  if (threadIdx.x == 0) dst[blockIdx.x] = t;
+  if (threadIdx.x == 0) (first ? dst : dst2)[b] = t;
+  if (bad_dst && blockIdx.x == 0 && threadIdx.x == 0) *bad_dst = *bad;
 }
 
 // x (rows x SC) -> the caller's numbering, a thread per caller entry
@@ -545,7 +554,8 @@ double largest_eigenvalue(const std::vector<double>& a, const std::vector<double
 struct PolyState {
   int device = 0;
   PolyDev m;
-  int nc = 1, width = 6, depth = 0, largest = 0;
+  int nc = 1, width = 6, depth = 0;
+  int largest[kPolyDepth + 1] = {};  // local units of the largest patch, up to and with ring d
   bool single = false;
   double lam = 0.0;         // upper end of the spectrum of A, with its margin
   double lam_typical = 0.0; // the same of a mesh whose rows were all like 95% of the rows
@@ -560,10 +570,9 @@ struct PolyWork {
   double* arena = nullptr;
   double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *in = nullptr, *stage = nullptr;
   size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, in_n = 0, stage_n = 0;
-  double *part = nullptr, *coef = nullptr, *sums = nullptr;
-  size_t part_n = 0, coef_n = 0, sums_n = 0;
-  int* bad = nullptr;
-  double *host = nullptr, *host_coef = nullptr;  // pinned: totals and the bad flag, coefficients
+  double *part = nullptr, *norm = nullptr, *coef = nullptr;  // coef: the coefficients, then the bad flag
+  size_t part_n = 0, norm_n = 0, coef_n = 0;
+  double *host = nullptr, *host_coef = nullptr;  // pinned: totals and the bad flag; source of coef
   size_t host_n = 0, host_coef_n = 0;
 };
 
@@ -625,13 +634,12 @@ void steps_of(const PolyState* ps, const double* prev, const double* cur, double
 
 void launch_steps(const PolyState* ps, const double* prev, const double* cur, double* out, int64_t plane, int F,
                   int steps, hipStream_t s) {
-  const int L = ps->largest;
+  const int L = ps->largest[ps->single ? 0 : steps];
   if (ps->nc == 1) {
     if (ps->single) {
       if (ps->width == 6) {
         if (L <= 1024) steps_of<1, 6, 1, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-        else if (L <= 2048) steps_of<1, 6, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-        else steps_of<1, 6, 4, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
+        else steps_of<1, 6, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
       } else if (ps->width == 8) {
         steps_of<1, 8, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
       } else {
@@ -781,7 +789,8 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   ps->nc = pp.nc;
   ps->width = pp.width;
   ps->depth = pp.depth;
-  ps->largest = pp.largest;
+  for (const PatchInfo& p : pp.patches)
+    for (int d = 0; d <= kPolyDepth; ++d) ps->largest[d] = std::max(ps->largest[d], p.end[d]);
   ps->single = pp.single;
   ps->mass_ratio = pp.mass_ratio;
   for (double a : op.mass) ps->mass_sum += a;
@@ -840,10 +849,6 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
   size_t n = 0;
   ifl_status st = IFL_OK;
   if (limit) st = grow(&w->arena, &n, limit / sizeof(double));
-  if (st == IFL_OK && hipMalloc((void**)&w->bad, sizeof(int)) != hipSuccess) {
-    (void)hipGetLastError();
-    st = fail(IFL_ENOMEM, "hipMalloc failed");
-  }
   if (st != IFL_OK) {
     poly_work_destroy(w);
     *out = nullptr;
@@ -854,7 +859,7 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
 void poly_work_destroy(PolyWork* w) {
   if (!w) return;
   if (!w->limit) free_large(w);
-  void* ptrs[] = {w->arena, w->part, w->coef, w->sums, w->bad};
+  void* ptrs[] = {w->arena, w->part, w->norm, w->coef};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (w->host) (void)hipHostFree(w->host);
@@ -904,10 +909,12 @@ bool poly_takes(const PolyState* ps, const PolyCall& c) {
 namespace {
 
 // How a call goes through the work space: scales per sequence, vectors of
-// the sequence kept at a time, fields at a time, and outputs staged for the
-// host at a time and field; false: not even one scale and one field fit.
+// the sequence kept at a time, steps of a launch (a launch must not write
+// where the two vectors it starts from are), fields at a time, and outputs
+// staged for the host at a time and field; false: not even one scale and one
+// field fit.
 struct Plan {
-  int scales = 0, planes = 0, fields = 0, staged = 0;
+  int scales = 0, planes = 0, steps = 0, fields = 0, staged = 0;
 };
 
 int padded_scales(int n) {
@@ -922,8 +929,10 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
   // without a limit: about 6 GB, which at level 9 holds 4 fields with 64
   // vectors and 32 scales each
   const size_t have = (limit ? limit : (size_t)6 << 30) / sizeof(double);
-  const int least = std::max(1, std::min(degree, ps->single ? 16 : 2 * ps->depth));
-  const int most = std::max(1, ps->single ? degree : std::min(degree, 64));
+  const int least = std::max(1, std::min(degree, 16));
+  // small meshes (32 MB a sequence) keep all of it, and sum once
+  const bool whole = ps->single || (size_t)degree * m.np * sizeof(double) <= (size_t)32 << 20;
+  const int most = std::max(1, whole ? degree : std::min(degree, 64));
   const int F = c.n_fields;
   for (int sc = c.n_scales;; sc = (sc + 1) / 2) {
     const size_t group = (size_t)padded_scales(std::min(sc, kMaxGroup));
@@ -940,10 +949,16 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
       const size_t left = avail > field ? (avail - field) / m.np : 0;
       out->scales = sc;
       out->planes = (int)std::max<size_t>(least, std::min<size_t>(most, left));
-      // whole launches of the step kernel
-      if (!ps->single && out->planes < degree && out->planes > ps->depth) out->planes -= out->planes % ps->depth;
       out->fields = (int)std::max<size_t>(
           1, std::min<size_t>((size_t)F, avail / (field + (size_t)out->planes * m.np)));
+      // where the patches of all fields run one after another on a CU, more
+      // rings than a large mesh's patch has cost more than the launches saved
+      const bool many = (int64_t)m.npatch * std::min(F, out->fields) > 512;
+      out->steps = ps->single ? out->planes : many ? std::min(ps->depth, 8) : ps->depth;
+      if (!ps->single && out->planes < degree) {
+        out->steps = std::min(out->steps, out->planes / 2);
+        out->planes -= out->planes % out->steps;  // whole launches
+      }
       return true;
     }
     if (sc == 1) return false;
@@ -1047,9 +1062,10 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
     free_large(w);  // the caller goes on with CG
     return st;
   }
-  if ((st = grow(&w->part, &w->part_n, std::max((size_t)F * GL, (size_t)FG * kMaxGroup * 3 * G))) ||
-      (st = grow(&w->coef, &w->coef_n, ncoef)) || (st = grow(&w->sums, &w->sums_n, nsums)) ||
-      (st = grow_host(&w->host, &w->host_n, nsums + 1)) || (st = grow_host(&w->host_coef, &w->host_coef_n, ncoef)))
+  if ((st = grow(&w->part, &w->part_n, (size_t)FG * kMaxGroup * 3 * G)) ||
+      (st = grow(&w->norm, &w->norm_n, (size_t)F * GL)) || (st = grow(&w->coef, &w->coef_n, ncoef + 1)) ||
+      (st = grow_host(&w->host, &w->host_n, nsums + 1)) ||
+      (st = grow_host(&w->host_coef, &w->host_coef_n, ncoef + 1)))
     return st;
   for (const auto& groups : seqs)
     for (const Group& g : groups)
@@ -1058,19 +1074,19 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
           const std::vector<double>* p = i < g.n ? &poly[g.gs.column[i]] : nullptr;
           w->host_coef[g.coef + (size_t)k * g.sc + i] = p && k < (int)p->size() ? (*p)[k] : 0.0;
         }
-  IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
-  IFL_HIP(hipMemsetAsync(w->bad, 0, sizeof(int), s));
+  w->host_coef[ncoef] = 0.0;
+  IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, (ncoef + 1) * sizeof(double), hipMemcpyHostToDevice, s));
+  int* bad = reinterpret_cast<int*>(w->coef + ncoef);
   const double* fields = c.fields;
   if (c.fields_host) {
     IFL_HIP(hipMemcpyAsync(w->in, c.fields, n_in * sizeof(double), hipMemcpyHostToDevice, s));
     fields = w->in;
   }
-  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, fields, w->phi, w->part, w->bad);
-  k_poly_total<<<F, kRed, 0, s>>>(w->part, GL, w->sums);
+  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, fields, w->phi, w->norm, bad);
   IFL_HIP(hipGetLastError());
   int* bad_host = reinterpret_cast<int*>(w->host + nsums);
   if (n_stage) {  // the copies to the host must not start on a bad field
-    IFL_HIP(hipMemcpyAsync(bad_host, w->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    IFL_HIP(hipMemcpyAsync(bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, s));
     IFL_HIP(hipStreamSynchronize(s));
     if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   }
@@ -1086,7 +1102,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       for (int k0 = 0; k0 < degree || k0 == 0;) {
         const int n = std::min(plan.planes, degree - k0);
         for (int j = 0; j < n;) {
-          const int d = std::min(ps->single ? n : ps->depth, n - j);
+          const int d = std::min(plan.steps, n - j);
           double* to = w->t + (int64_t)j * plane;
           launch_steps(ps, prev, cur, to, plane, nf, d, s);
           prev = d >= 2 ? to + (int64_t)(d - 2) * plane : cur;
@@ -1106,12 +1122,16 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       for (const Group& g : groups) {
         const double* x = w->x + (size_t)g.pad0 * nf * np;
         IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, w->z, g.gs, w->part, G, nf, s));
-        k_poly_total<<<nf * g.sc * 3, kRed, 0, s>>>(w->part, G, w->sums + sum_at);
+        // with the call's last group go the norms of all its fields
+        const bool last = f0 + nf == F && &g == &seqs.back().back();
+        const int n = nf * g.sc * 3;
+        k_poly_total<<<n + (last ? F : 0), kRed, 0, s>>>(w->part, G, n, w->host + sum_at, w->norm, GL, w->host, bad,
+                                                         last ? bad_host : nullptr);
         totals.push_back({g, f0, nf, sum_at});
         sum_at += (size_t)nf * g.sc * 3;
         if (!c.out) continue;
         if (!n_stage) {
-          launch_out(ps, w->bad, g.sc, x, g.gs, (int64_t)S * m.field_len, c.out + (int64_t)f0 * S * m.field_len, nf, s);
+          launch_out(ps, bad, g.sc, x, g.gs, (int64_t)S * m.field_len, c.out + (int64_t)f0 * S * m.field_len, nf, s);
           continue;
         }
         // to the host through the staging: columns in the caller's order, so
@@ -1125,7 +1145,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
             const int at = (int)(std::lower_bound(cols.begin(), cols.end(), g.gs.column[i]) - cols.begin()) - q;
             some.column[i] = at >= 0 && at < qn ? at : -1;
           }
-          launch_out(ps, w->bad, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
+          launch_out(ps, bad, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
           for (int f = 0; f < nf; ++f)
             for (int i = q, e; i < q + qn; i = e) {
               for (e = i + 1; e < q + qn && cols[e] == cols[e - 1] + 1;) ++e;
@@ -1138,8 +1158,6 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       IFL_HIP(hipGetLastError());
     }
   }
-  IFL_HIP(hipMemcpyAsync(w->host, w->sums, nsums * sizeof(double), hipMemcpyDeviceToHost, s));
-  IFL_HIP(hipMemcpyAsync(bad_host, w->bad, sizeof(int), hipMemcpyDeviceToHost, s));
   IFL_HIP(hipStreamSynchronize(s));
   if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
