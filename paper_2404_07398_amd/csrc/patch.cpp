@@ -144,8 +144,32 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
     if (nc == 1 && pp.width == 3) pp.width = 6;
     else return false;
   }
-  pp.single = g.n <= poly_single_units(nc, pp.width);
-  pp.cap = pp.single ? (int)g.n : poly_patch_units(nc, pp.width);
+  pp.block = nc * nc;
+  if (nc == 2 && pp.width >= 6) {  // [[a, b], [-b, a]] blocks throughout?
+    std::atomic<bool> turns{true};
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8, g.n / 4096));
+    parallel_for(parts, [&](int64_t q) {
+      for (int64_t u = g.n * q / parts; u < g.n * (q + 1) / parts && turns.load(); ++u) {
+        // the two rows' entries as (column unit, same component, other component)
+        const auto entry = [&](int64_t r, int32_t v, int cc) {
+          const auto at = std::lower_bound(col.begin() + rp[r], col.begin() + rp[r + 1], 2 * v + cc);
+          return at != col.begin() + rp[r + 1] && *at == 2 * v + cc ? val[at - col.begin()] : 0.0;
+        };
+        bool ok = op.mass[2 * u] == op.mass[2 * u + 1];
+        for (int64_t r = 2 * u; ok && r < 2 * u + 2; ++r)
+          for (int64_t e = rp[r]; ok && e < rp[r + 1]; ++e) {
+            const int32_t v = col[e] / 2;
+            const int c = (int)(r % 2), cc = col[e] % 2;
+            const double twin = entry(2 * u + 1 - c, v, 1 - cc);
+            ok = c == cc ? val[e] == twin : val[e] == -twin;
+          }
+        if (!ok) turns.store(false);
+      }
+    });
+    if (turns.load()) pp.block = 2;
+  }
+  pp.single = g.n <= poly_single_units(nc, pp.width, pp.block);
+  pp.cap = pp.single ? (int)g.n : poly_patch_units(nc, pp.width, pp.block);
   pp.depth = pp.single ? 0 : poly_patch_depth(nc, pp.width);
 
   // the order: the parts of the rows' own locality order, each bisected
@@ -264,7 +288,7 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
 
   pp.halo.push_back(0);  // a patch without halo units still reads one entry
   // M^-1 K by position, a record per unit, and the columns by position
-  const int64_t U = g.n, bb = nc * nc, rec = poly_val_record(nc, pp.width), crec = poly_col_record(pp.width);
+  const int64_t U = g.n, bb = pp.block, rec = poly_val_record(pp.width, pp.block), crec = poly_col_record(pp.width);
   pp.val.assign((size_t)(U * rec), 0.0);
   pp.col.assign((size_t)(U * crec), 0);
   pp.mass.resize((size_t)(U * nc));
@@ -282,7 +306,8 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
           const int32_t v = col[e] / nc, cc = col[e] % nc;
           int64_t k = 0;
           if (v != u) k = 1 + std::lower_bound(g.adj.begin() + a0, g.adj.begin() + a1, v) - (g.adj.begin() + a0);
-          pp.val[i * rec + k * bb + c * nc + cc] = val[e] * im;
+          if (bb == nc * nc) pp.val[i * rec + k * bb + c * nc + cc] = val[e] * im;
+          else if (c == 0) pp.val[i * rec + k * bb + cc] = val[e] * im;
         }
       }
     }

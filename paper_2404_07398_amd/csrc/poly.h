@@ -17,18 +17,24 @@ constexpr int kPolyDepth = 16;
 // Threads of a patch's workgroup and units per thread; what a patch holds.
 constexpr int kPolyThreads = 512;
 constexpr int kPolySingleThreads = 1024;
-constexpr int poly_slots(int nc, int width) { return nc == 1 ? (width <= 6 ? 4 : 2) : (width <= 3 ? 2 : 1); }
-constexpr int poly_patch_units(int nc, int width) {
-  return nc == 1 ? kPolyThreads * poly_slots(nc, width) : 1024;
+// (block: stored couplings of a neighbour block: 1, or of two components 4, or
+// 2 where every block is [[a, b], [-b, a]], as the vertex vectors' are)
+constexpr int poly_slots(int nc, int width, int block) {
+  return nc == 1 ? (width <= 6 ? 4 : 2) : (width <= 3 || block == 2 ? 2 : 1);
 }
-constexpr int poly_single_units(int nc, int width) { return kPolySingleThreads * (poly_slots(nc, width) >= 2 ? 2 : 1); }
+constexpr int poly_patch_units(int nc, int width, int block) {
+  return nc == 1 ? kPolyThreads * poly_slots(nc, width, block) : 1024;
+}
+constexpr int poly_single_units(int nc, int width, int block) {
+  return kPolySingleThreads * (poly_slots(nc, width, block) >= 2 && block != 2 ? 2 : 1);
+}
 // Rings of large meshes' patches (small ones take what their patches leave).
 constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 6 ? 8 : 4; }
 
 // Records, in whole 16-byte units (8 for 3 neighbours): a unit's own block
 // and its neighbours' (doubles); its neighbours' LDS offsets in a patch
 // (uint16_t, bytes of a buffer of units); its neighbours' positions.
-constexpr int poly_val_record(int nc, int width) { return ((1 + width) * nc * nc + 1) / 2 * 2; }
+constexpr int poly_val_record(int width, int block) { return ((1 + width) * block + 1) / 2 * 2; }
 constexpr int poly_idx_record(int width) { return width <= 4 ? 4 : (width + 7) / 8 * 8; }
 constexpr int poly_col_record(int width) { return (width + 3) / 4 * 4; }
 
@@ -46,6 +52,7 @@ struct PatchPack {
   int64_t units = 0;
   int nc = 1;      // components of a unit
   int width = 6;   // neighbour entries per unit (padded with the unit itself, value 0)
+  int block = 1;   // stored couplings of a block
   int cap = 0;     // units a patch may hold
   int depth = 0;   // rings
   bool single = false;          // one patch without rings holds the mesh

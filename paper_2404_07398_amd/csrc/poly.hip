@@ -63,23 +63,39 @@ struct alignas(16) Unit<2> {
   double v[2];
 };
 
+// Coupling of component c of a unit to component d of the block's unit.
+template <int NC, int BV>
+__device__ __forceinline__ double coupling(const double* b, int c, int d) {
+  if constexpr (BV == 2) return c == d ? b[0] : c == 0 ? b[1] : -b[1];
+  else return b[c * NC + d];
+}
+
+// Slots of a thread that may hold interior units when the step kernel sums.
+constexpr int sum_slots(int slots) { return slots < 2 ? slots : 2; }
+
 // What a thread of the step kernel owns: its units' rows of (4 / lam) A, the
 // neighbours' LDS offsets two to a register (kept packed: unpacked they cost
 // the registers of a second resident workgroup), and the two latest vectors.
-template <int NC, int W, int SLOTS>
+template <int NC, int W, int BV, int SLOTS, int ACC>
 struct Rows {
-  double val[SLOTS][W][NC * NC], own[SLOTS][NC * NC];
+  double val[SLOTS][W][BV], own[SLOTS][BV];
   uint32_t nb[SLOTS][(W + 1) / 2];
   Unit<NC> t[2][SLOTS];
+  // sums of ACC scales, for the slots that hold interior units
+  double acc[ACC ? sum_slots(SLOTS) : 1][ACC ? ACC : 1][NC];
 };
+
+// Coefficients, never written while a kernel runs: read through the scalar
+// cache (a vector load would be waited for together with the steps' stores).
+typedef const __attribute__((address_space(4))) double* Coef;
 
 // One step for N of the thread's units from slot S on: the vector t[CUR] and
 // the LDS buffer CUR hold t_k; t[1 - CUR] holds t_{k-1} and becomes t_{k+1}.
 // All gathers are issued before the sums. Lanes past 'lim' compute on
-// whatever is there and write nothing.
-template <int NC, int W, int SLOTS, int T, int CUR, int N>
-__device__ __forceinline__ void step_slots(Rows<NC, W, SLOTS>& r, char* lds, int S, int tid, int lim, int inside,
-                                           double half, Unit<NC>* out) {
+// whatever is there and write nothing. coef: the new vector's coefficients.
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, int CUR, int N>
+__device__ __forceinline__ void step_slots(Rows<NC, W, BV, SLOTS, ACC>& r, char* lds, int S, int tid, int lim, int inside,
+                                           double half, Unit<NC>* out, Coef coef) {
   constexpr int BUF = T * SLOTS * (int)sizeof(Unit<NC>);
   Unit<NC> g[N][W];
 #pragma unroll
@@ -100,30 +116,37 @@ __device__ __forceinline__ void step_slots(Rows<NC, W, SLOTS>& r, char* lds, int
       acc[c] = -r.t[1 - CUR][s].v[c];
       acc2[c] = 0.0;
 #pragma unroll
-      for (int d = 0; d < NC; ++d) acc2[c] += r.own[s][c * NC + d] * r.t[CUR][s].v[d];
+      for (int d = 0; d < NC; ++d) acc2[c] += coupling<NC, BV>(r.own[s], c, d) * r.t[CUR][s].v[d];
 #pragma unroll
       for (int k = 0; k < W; ++k)
 #pragma unroll
         for (int d = 0; d < NC; ++d) {
           double& a = k % 2 == 0 ? acc[c] : acc2[c];
-          a += r.val[s][k][c * NC + d] * g[n][k].v[d];
+          a += coupling<NC, BV>(r.val[s][k], c, d) * g[n][k].v[d];
         }
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) r.t[1 - CUR][s].v[c] = half * (acc[c] + acc2[c]);
     if (i < lim) *reinterpret_cast<Unit<NC>*>(lds + (1 - CUR) * BUF + i * (int)sizeof(Unit<NC>)) = r.t[1 - CUR][s];
-    if (i < inside) out[i] = r.t[1 - CUR][s];
+    if (ACC && s < sum_slots(SLOTS)) {
+#pragma unroll
+      for (int a = 0; a < ACC; ++a)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) r.acc[s < sum_slots(SLOTS) ? s : 0][a][c] += coef[a] * r.t[1 - CUR][s].v[c];
+    }
+    if ((ACC == 0 || out) && i < inside) out[i] = r.t[1 - CUR][s];
   }
 }
 
-template <int NC, int W, int SLOTS, int T, int CUR>
-__device__ __forceinline__ void step_all(Rows<NC, W, SLOTS>& r, char* lds, int tid, int lim, int inside, double half,
-                                         Unit<NC>* out) {
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, int CUR>
+__device__ __forceinline__ void step_all(Rows<NC, W, BV, SLOTS, ACC>& r, char* lds, int tid, int lim, int inside,
+                                         double half, Unit<NC>* out, Coef coef) {
   // first unit of this wavefront: the tests below are one scalar branch each
   const int wave = __builtin_amdgcn_readfirstlane(tid & ~63);
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s)
-    if (wave + s * T < lim) step_slots<NC, W, SLOTS, T, CUR, 1>(r, lds, s, tid, lim, inside, half, out);
+    if (wave + s * T < lim)
+      step_slots<NC, W, BV, SLOTS, T, ACC, CUR, 1>(r, lds, s, tid, lim, inside, half, out, coef);
 }
 
 // 'steps' steps of the recurrence on one patch, field after field.
@@ -146,11 +169,17 @@ __device__ __forceinline__ void step_all(Rows<NC, W, SLOTS>& r, char* lds, int t
 //
 // prev == nullptr: the sequence starts (cur = t_0, the first step is halved).
 // out: plane of the first new vector, the next ones 'plane' doubles on.
-template <int NC, int W, int SLOTS, int T>
+//
+// ACC > 0 (calls of few scales): the kernel sums as it goes, x (rows x ACC)
+// += coef[j][a] t, coef pointing at the coefficients of cur; then only the
+// last two vectors are written (two planes at out), and no launch reads the
+// sequence again: 16 ACC + 16 bytes a row and launch for 16 a row and step.
+template <int NC, int W, int BV, int SLOTS, int T, int ACC>
 __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __restrict__ prev,
                                                      const double* __restrict__ cur, double* __restrict__ out,
                                                      int64_t plane, int n_fields, int steps, int ringed,
-                                                     double scale) {
+                                                     double scale, const double* __restrict__ coef,
+                                                     double* __restrict__ x) {
   // consecutive patches on one XCD: their halos overlap in its L2
   const int per = (m.npatch + kXcd - 1) / kXcd;
   const int pid = (int)(blockIdx.x % kXcd) * per + (int)(blockIdx.x / kXcd);
@@ -164,8 +193,8 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
   const int start = p->start, inside = p->end[0];
   const int loaded = p->end[ringed ? steps : 0];
   const int first_lim = p->end[ringed ? steps - 1 : 0];
-  constexpr int VR = poly_val_record(NC, W), IR = poly_idx_record(W), BB = NC * NC;
-  Rows<NC, W, SLOTS> r;
+  constexpr int VR = poly_val_record(W, BV), IR = poly_idx_record(W);
+  Rows<NC, W, BV, SLOTS, ACC> r;
   int32_t at[SLOTS];
   // no branches between the loads, so that all are in flight together: units
   // past the last one read the first one's data
@@ -184,20 +213,20 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
     for (int k = 0; k < (W + 1) / 2; ++k) r.nb[s][k] = id[k];
     const double* v = m.val + (int64_t)(tid + s * T < first_lim ? at[s] : start) * VR;
 #pragma unroll
-    for (int b = 0; b < BB; ++b) r.own[s][b] = v[b];
+    for (int b = 0; b < BV; ++b) r.own[s][b] = v[b];
 #pragma unroll
     for (int k = 0; k < W; ++k)
 #pragma unroll
-      for (int b = 0; b < BB; ++b) r.val[s][k][b] = v[(k + 1) * BB + b];
+      for (int b = 0; b < BV; ++b) r.val[s][k][b] = v[(k + 1) * BV + b];
   }
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
 #pragma unroll
-    for (int b = 0; b < BB; ++b) r.own[s][b] = scale * r.own[s][b] - (b % (NC + 1) == 0 ? 2.0 : 0.0);
+    for (int b = 0; b < BV; ++b) r.own[s][b] = scale * r.own[s][b] - (b == 0 || b == 3 ? 2.0 : 0.0);
 #pragma unroll
     for (int k = 0; k < W; ++k)
 #pragma unroll
-      for (int b = 0; b < BB; ++b) r.val[s][k][b] *= scale;
+      for (int b = 0; b < BV; ++b) r.val[s][k][b] *= scale;
   }
   for (int f = blockIdx.y; f < n_fields; f += gridDim.y) {
     const Unit<NC>* cf = reinterpret_cast<const Unit<NC>*>(cur + (int64_t)f * m.np);
@@ -211,6 +240,17 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
 #pragma unroll
         for (int c = 0; c < NC; ++c) r.t[1][s].v[c] = 0.0;
     }
+    if (ACC) {
+#pragma unroll
+      for (int s = 0; s < sum_slots(SLOTS); ++s) {
+        const int i = tid + s * T < inside ? tid + s * T : 0;
+        const double* xr = x + ((int64_t)f * m.np + (int64_t)(start + i) * NC) * ACC;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int a = 0; a < ACC; ++a) r.acc[s][a][c] = prev ? xr[c * ACC + a] : coef[a] * r.t[0][s].v[c];
+      }
+    }
     // the loads end here (vmcnt 0): waited for inside a step, they would be
     // waited for together with the stores of the steps before
     __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -221,14 +261,30 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
     __syncthreads();
     Unit<NC>* of = reinterpret_cast<Unit<NC>*>(out + (int64_t)f * m.np) + start;
     const int64_t up = plane / NC;
-    for (int j = 1; j <= steps; j += 2, of += 2 * up) {
-      step_all<NC, W, SLOTS, T, 0>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j : 0), inside,
-                                   !prev && j == 1 ? 0.5 : 1.0, of);
+    Coef cj = (Coef)(uintptr_t)(coef + ACC);
+    for (int j = 1; j <= steps; j += 2, cj += 2 * ACC) {
+      // the plane of step j: every step's own, or the last two's
+      Unit<NC>* to = ACC == 0 ? of + (j - 1) * up : j >= steps - 1 ? of + (j - steps + 1) * up : nullptr;
+      step_all<NC, W, BV, SLOTS, T, ACC, 0>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j : 0), inside,
+                                        !prev && j == 1 ? 0.5 : 1.0, to, cj);
       __syncthreads();
       if (j == steps) break;
-      step_all<NC, W, SLOTS, T, 1>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j - 1 : 0), inside,
-                                   1.0, of + up);
+      to = ACC == 0 || j + 1 >= steps - 1 ? of + (ACC == 0 ? j : j - steps + 2) * up : nullptr;
+      step_all<NC, W, BV, SLOTS, T, ACC, 1>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j - 1 : 0),
+                                        inside, 1.0, to, cj + ACC);
       __syncthreads();
+    }
+    if (ACC) {
+#pragma unroll
+      for (int s = 0; s < sum_slots(SLOTS); ++s) {
+        const int i = tid + s * T;
+        double* xr = x + ((int64_t)f * m.np + (int64_t)(start + i) * NC) * ACC;
+        if (i < inside)
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int a = 0; a < ACC; ++a) xr[c * ACC + a] = r.acc[s][a][c];
+      }
     }
   }
 }
@@ -318,14 +374,14 @@ struct alignas(16) Lane<2> {
   double v[2];
 };
 
-// The row's product with A: y = sum_j A_rj x_j for the lane's scales.
-template <int NC, int W, int SC>
-__device__ __forceinline__ Lane<lane_scales(SC)> row_product(const PolyDev& m, const double* xf, int64_t r, int q) {
+// The unit's product with A: y[c] = sum_j A_uj x_j, component c, for the
+// lane's scales. A unit's rows share their gathers.
+template <int NC, int W, int BV, int SC>
+__device__ __forceinline__ void unit_product(const PolyDev& m, const double* xf, int64_t u, int q,
+                                             Lane<lane_scales(SC)> (&y)[NC]) {
   constexpr int V = lane_scales(SC);
   const Lane<V>* xt = reinterpret_cast<const Lane<V>*>(xf);
-  constexpr int LPR = SC / V, BB = NC * NC, VR = poly_val_record(NC, W), CR = poly_col_record(W);
-  const int64_t u = r / NC;
-  const int c = (int)(r % NC);
+  constexpr int LPR = SC / V, VR = poly_val_record(W, BV), CR = poly_col_record(W);
   int32_t col[CR];
 #pragma unroll
   for (int k = 0; k < CR; k += 4) {
@@ -335,37 +391,40 @@ __device__ __forceinline__ Lane<lane_scales(SC)> row_product(const PolyDev& m, c
     col[k + 2] = q4.z;
     col[k + 3] = q4.w;
   }
-  const double* a = m.val + u * VR + c * NC;
+  const double* a = m.val + u * VR;
   Lane<V> t[W + 1][NC];
 #pragma unroll
   for (int k = 0; k <= W; ++k)
 #pragma unroll
     for (int d = 0; d < NC; ++d) t[k][d] = xt[((k == 0 ? u : (int64_t)col[k == 0 ? 0 : k - 1]) * NC + d) * LPR + q];
-  Lane<V> y;
 #pragma unroll
-  for (int e = 0; e < V; ++e) y.v[e] = 0.0;
+  for (int c = 0; c < NC; ++c) {
 #pragma unroll
-  for (int k = 0; k <= W; ++k)
+    for (int e = 0; e < V; ++e) y[c].v[e] = 0.0;
 #pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      const double v = a[k * BB + d];
+    for (int k = 0; k <= W; ++k)
 #pragma unroll
-      for (int e = 0; e < V; ++e) y.v[e] += v * t[k][d].v[e];
-    }
-  return y;
+      for (int d = 0; d < NC; ++d) {
+        const double v = coupling<NC, BV>(a + k * BV, c, d);
+#pragma unroll
+        for (int e = 0; e < V; ++e) y[c].v[e] += v * t[k][d].v[e];
+      }
+  }
 }
 
-// y = A x (grid.y = field).
-template <int NC, int W, int SC>
-__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, const double* __restrict__ x,
-                                                     double* __restrict__ y) {
+// y = A x (grid.y = field), a lane's scales of one unit per thread.
+template <int NC, int W, int BV, int SC>
+__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, const double* __restrict__ x, double* __restrict__ y) {
   constexpr int V = lane_scales(SC), LPR = SC / V;
   const int64_t g = (int64_t)blockIdx.x * kRed + threadIdx.x;
-  const int64_t r = g / LPR;
-  if (r >= m.rows) return;
+  const int64_t u = g / LPR;
+  if (u >= m.units) return;
   const int64_t base = (int64_t)blockIdx.y * m.np * SC;
   const int q = (int)(g % LPR);
-  reinterpret_cast<Lane<V>*>(y + base)[r * LPR + q] = row_product<NC, W, SC>(m, x + base, r, q);
+  Lane<V> v[NC];
+  unit_product<NC, W, BV, SC>(m, x + base, u, q, v);
+#pragma unroll
+  for (int c = 0; c < NC; ++c) reinterpret_cast<Lane<V>*>(y + base)[(u * NC + c) * LPR + q] = v[c];
 }
 
 struct GroupScales {
@@ -375,7 +434,7 @@ struct GroupScales {
 
 // FP64 true residual M (phi - x - c A z), z = x (order 1) or A x (order 2):
 // block sums of its square, of (M x)^2 and of M x^2 per scale.
-template <int NC, int W, int SC>
+template <int NC, int W, int BV, int SC>
 __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __restrict__ phi,
                                                      const double* __restrict__ x, const double* __restrict__ z,
                                                      GroupScales gs, double* __restrict__ part) {
@@ -387,18 +446,23 @@ __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __
   double sum[3 * V];
 #pragma unroll
   for (int e = 0; e < 3 * V; ++e) sum[e] = 0.0;
-  constexpr int RPB = kRed / LPR;
-  for (int64_t r = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR; r < m.rows; r += (int64_t)gridDim.x * RPB) {
-    const Lane<V> y = row_product<NC, W, SC>(m, z + base, r, q);
-    const Lane<V> xr = reinterpret_cast<const Lane<V>*>(x + base)[r * LPR + q];
-    const double mr = m.mass[r], ph = pf[r];
+  constexpr int UPB = kRed / LPR;
+  for (int64_t u = (int64_t)blockIdx.x * UPB + threadIdx.x / LPR; u < m.units; u += (int64_t)gridDim.x * UPB) {
+    Lane<V> y[NC];
+    unit_product<NC, W, BV, SC>(m, z + base, u, q, y);
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const double res = mr * (ph - xr.v[e] - gs.c[q * V + e] * y.v[e]);
-      const double mx = mr * xr.v[e];
-      sum[e] += res * res;
-      sum[V + e] += mx * mx;
-      sum[2 * V + e] += mx * xr.v[e];
+    for (int c = 0; c < NC; ++c) {
+      const int64_t r = u * NC + c;
+      const Lane<V> xr = reinterpret_cast<const Lane<V>*>(x + base)[r * LPR + q];
+      const double mr = m.mass[r], ph = pf[r];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const double res = mr * (ph - xr.v[e] - gs.c[q * V + e] * y[c].v[e]);
+        const double mx = mr * xr.v[e];
+        sum[e] += res * res;
+        sum[V + e] += mx * mx;
+        sum[2 * V + e] += mx * xr.v[e];
+      }
     }
   }
 #pragma unroll
@@ -487,7 +551,7 @@ __global__ __launch_bounds__(kRed) void k_lanczos_start(PolyDev m, double* __res
 }
 
 // w = A v - beta v_prev (v = u / b, v_prev = u_prev / b_prev, beta = b), (w, v)
-template <int NC, int W>
+template <int NC, int W, int BV>
 __global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, const double* __restrict__ u,
                                                           const double* __restrict__ u_prev, double* __restrict__ w,
                                                           const double* __restrict__ beta,
@@ -498,11 +562,17 @@ __global__ __launch_bounds__(kRed) void k_lanczos_product(PolyDev m, const doubl
   const double bp = beta_prev ? sqrt(partial_total(beta_prev, gridDim.x, lds)) : 0.0;
   const double inv = b > 0.0 ? 1.0 / b : 0.0, invp = bp > 0.0 ? b / bp : 0.0;
   double sum = 0.0;
-  for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
-    double y = inv * row_product<NC, W, 1>(m, u, r, 0).v[0];
-    if (beta_prev) y -= invp * u_prev[r];
-    w[r] = y;
-    sum += m.mass[r] * y * u[r] * inv;
+  for (int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x; i < m.units; i += (int64_t)gridDim.x * kRed) {
+    Lane<1> v[NC];
+    unit_product<NC, W, BV, 1>(m, u, i, 0, v);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int64_t r = i * NC + c;
+      double y = inv * v[c].v[0];
+      if (beta_prev) y -= invp * u_prev[r];
+      w[r] = y;
+      sum += m.mass[r] * y * u[r] * inv;
+    }
   }
   const double t = block_total<kRed>(sum, lds);
   if (threadIdx.x == 0) alpha[blockIdx.x] = t;
@@ -554,7 +624,7 @@ double largest_eigenvalue(const std::vector<double>& a, const std::vector<double
 struct PolyState {
   int device = 0;
   PolyDev m;
-  int nc = 1, width = 6, depth = 0;
+  int nc = 1, width = 6, block = 1, depth = 0;
   int largest[kPolyDepth + 1] = {};  // local units of the largest patch, up to and with ring d
   bool single = false;
   double lam = 0.0;         // upper end of the spectrum of A, with its margin
@@ -620,51 +690,81 @@ ifl_status grow_host(double** p, size_t* have, size_t want) {
 
 int red_blocks(int64_t items) { return (int)std::max<int64_t>(1, std::min<int64_t>(kRedBlocks, (items + kRed - 1) / kRed)); }
 
-template <int NC, int W, int SLOTS, int T>
-void steps_of(const PolyState* ps, const double* prev, const double* cur, double* out, int64_t plane, int F, int steps,
-              int ringed, hipStream_t s) {
+// One launch of the step kernel: where it reads and writes.
+struct Steps {
+  const double *prev, *cur;
+  double* out;
+  int64_t plane;
+  int fields, steps;
+  const double* coef = nullptr;  // with acc > 0
+  double* x = nullptr;
+  int acc = 0;
+};
+
+template <int NC, int W, int BV, int SLOTS, int T, int ACC>
+void steps_acc(const PolyState* ps, const Steps& a, hipStream_t s) {
   const int per = (ps->m.npatch + kXcd - 1) / kXcd;
   // fields side by side only where the patches alone do not fill the chip:
   // a workgroup that walks the fields reads its rows of A once
-  const int gx = per * kXcd;
-  const int gy = std::min(F, std::max(1, 1024 / std::max(1, ps->m.npatch)));
-  k_poly_steps<NC, W, SLOTS, T><<<dim3(gx, gy), T, 0, s>>>(ps->m, prev, cur, out, plane, F, steps, ringed,
-                                                           4.0 / ps->lam);
+  const int gy = std::min(a.fields, std::max(1, 1024 / std::max(1, ps->m.npatch)));
+  k_poly_steps<NC, W, BV, SLOTS, T, ACC><<<dim3(per * kXcd, gy), T, 0, s>>>(
+      ps->m, a.prev, a.cur, a.out, a.plane, a.fields, a.steps, ps->single ? 0 : 1, 4.0 / ps->lam, a.coef, a.x);
 }
 
-void launch_steps(const PolyState* ps, const double* prev, const double* cur, double* out, int64_t plane, int F,
-                  int steps, hipStream_t s) {
-  const int L = ps->largest[ps->single ? 0 : steps];
-  if (ps->nc == 1) {
-    if (ps->single) {
-      if (ps->width == 6) {
-        if (L <= 1024) steps_of<1, 6, 1, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-        else steps_of<1, 6, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-      } else if (ps->width == 8) {
-        steps_of<1, 8, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-      } else {
-        steps_of<1, 12, 2, 1024>(ps, prev, cur, out, plane, F, steps, 0, s);
-      }
-    } else if (ps->width == 6) {
-      if (L <= 2 * kPolyThreads) steps_of<1, 6, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
-      else steps_of<1, 6, 4, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
-    } else if (ps->width == 8) {
-      steps_of<1, 8, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
-    } else {
-      steps_of<1, 12, 2, kPolyThreads>(ps, prev, cur, out, plane, F, steps, 1, s);
-    }
-  } else {
-    const int ringed = ps->single ? 0 : 1;
-    if (ps->width == 3) {
-      if (L <= 1024) steps_of<2, 3, 2, 512>(ps, prev, cur, out, plane, F, steps, ringed, s);
-      else steps_of<2, 3, 2, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
-    } else if (ps->width == 6) {
-      if (L <= 512) steps_of<2, 6, 1, 512>(ps, prev, cur, out, plane, F, steps, ringed, s);
-      else steps_of<2, 6, 1, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
-    } else {
-      steps_of<2, 8, 1, 1024>(ps, prev, cur, out, plane, F, steps, ringed, s);
-    }
+template <int NC, int W, int BV, int SLOTS, int T>
+void steps_of(const PolyState* ps, const Steps& a, hipStream_t s) {
+  switch (a.acc) {
+    case 0: steps_acc<NC, W, BV, SLOTS, T, 0>(ps, a, s); break;
+    case 1: steps_acc<NC, W, BV, SLOTS, T, 1>(ps, a, s); break;
+    case 2:
+      if constexpr (SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 2>(ps, a, s);
+      break;
+    default:
+      if constexpr (NC == 1 && SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 4>(ps, a, s);
+      break;
   }
+}
+
+// The smallest workgroup and slot count that hold the patches' units.
+void launch_steps(const PolyState* ps, const Steps& a, hipStream_t s) {
+  const int L = ps->largest[ps->single ? 0 : a.steps];
+  if (ps->nc == 1 && ps->width == 6) {
+    if (ps->single && L <= 1024) steps_of<1, 6, 1, 1, kPolySingleThreads>(ps, a, s);
+    else if (ps->single) steps_of<1, 6, 1, 2, kPolySingleThreads>(ps, a, s);
+    else if (L <= 2 * kPolyThreads) steps_of<1, 6, 1, 2, kPolyThreads>(ps, a, s);
+    else steps_of<1, 6, 1, 4, kPolyThreads>(ps, a, s);
+  } else if (ps->nc == 1 && ps->width == 8) {
+    if (ps->single) steps_of<1, 8, 1, 2, kPolySingleThreads>(ps, a, s);
+    else steps_of<1, 8, 1, 2, kPolyThreads>(ps, a, s);
+  } else if (ps->nc == 1) {
+    if (ps->single) steps_of<1, 12, 1, 2, kPolySingleThreads>(ps, a, s);
+    else steps_of<1, 12, 1, 2, kPolyThreads>(ps, a, s);
+  } else if (ps->block == 2 && ps->width == 6) {
+    if (L <= 512) steps_of<2, 6, 2, 1, 512>(ps, a, s);
+    else steps_of<2, 6, 2, 2, 512>(ps, a, s);
+  } else if (ps->block == 2) {
+    steps_of<2, 8, 2, 1, 1024>(ps, a, s);
+  } else if (ps->width == 3) {
+    if (L <= 1024) steps_of<2, 3, 4, 2, 512>(ps, a, s);
+    else steps_of<2, 3, 4, 2, 1024>(ps, a, s);
+  } else if (ps->width == 6) {
+    if (L <= 512) steps_of<2, 6, 4, 1, 512>(ps, a, s);
+    else steps_of<2, 6, 4, 1, 1024>(ps, a, s);
+  } else {
+    steps_of<2, 8, 4, 1, 1024>(ps, a, s);
+  }
+}
+
+// Whether the step kernel sums sc scales itself, by launches of 'steps' steps:
+// every interior unit has to be in a slot with sums, and their registers have
+// to be there. Kernels of 4 slots a thread are full: with 1 scale they spill
+// 10 registers and still win (one field of the 2.6 M-vertex sphere: 171 us a
+// launch for 165 + 32 of the separate sum, 1.65 ms a call for 1.90), with 4
+// they lose (level 7: 23 us a launch for 15 + 2).
+bool sums_itself(const PolyState* ps, int sc, int steps) {
+  const bool full = !ps->single && ps->width == 6 && ps->nc == 1 && ps->largest[steps] > 2 * kPolyThreads;
+  return sc <= (full ? 1 : ps->nc == 1 ? 4 : 2) &&
+         (ps->nc == 2 || ps->single || ps->largest[0] <= 2 * kPolyThreads);
 }
 
 void launch_sum(int sc, const double* phi, const double* t, int64_t plane, int64_t np, int n, const double* coef,
@@ -679,42 +779,46 @@ void launch_sum(int sc, const double* phi, const double* t, int64_t plane, int64
   }
 }
 
-template <int NC, int W, int SC>
+template <int NC, int W, int BV, int SC>
 void check_of(const PolyState* ps, int order, const double* phi, const double* x, double* z, const GroupScales& gs,
               double* part, int G, int F, hipStream_t s) {
   constexpr int LPR = SC / lane_scales(SC);
   const double* src = x;
   if (order == 2) {
-    const dim3 g((unsigned)((ps->m.rows * LPR + kRed - 1) / kRed), (unsigned)F);
-    k_poly_apply<NC, W, SC><<<g, kRed, 0, s>>>(ps->m, x, z);
+    const dim3 g((unsigned)((ps->m.units * LPR + kRed - 1) / kRed), (unsigned)F);
+    k_poly_apply<NC, W, BV, SC><<<g, kRed, 0, s>>>(ps->m, x, z);
     src = z;
   }
-  k_poly_check<NC, W, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, src, gs, part);
+  k_poly_check<NC, W, BV, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, src, gs, part);
 }
 
-template <int NC, int W>
+template <int NC, int W, int BV>
 void check_scales(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z,
                   const GroupScales& gs, double* part, int G, int F, hipStream_t s) {
   switch (sc) {
-    case 1: check_of<NC, W, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 2: check_of<NC, W, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 4: check_of<NC, W, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 8: check_of<NC, W, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    default: check_of<NC, W, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 1: check_of<NC, W, BV, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 2: check_of<NC, W, BV, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 4: check_of<NC, W, BV, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 8: check_of<NC, W, BV, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    default: check_of<NC, W, BV, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
   }
 }
 
-// f with the operator's (components, entries a unit) as its template arguments
+// f with the operator's (components, entries a unit, couplings a block) as
+// its template arguments
 #define IFL_POLY_FORMS(f, ...)                                  \
   do {                                                          \
     if (ps->nc == 1) {                                          \
-      if (ps->width == 6) f<1, 6> __VA_ARGS__;                  \
-      else if (ps->width == 8) f<1, 8> __VA_ARGS__;             \
-      else f<1, 12> __VA_ARGS__;                                \
+      if (ps->width == 6) f<1, 6, 1> __VA_ARGS__;               \
+      else if (ps->width == 8) f<1, 8, 1> __VA_ARGS__;          \
+      else f<1, 12, 1> __VA_ARGS__;                             \
+    } else if (ps->block == 2) {                                \
+      if (ps->width == 6) f<2, 6, 2> __VA_ARGS__;               \
+      else f<2, 8, 2> __VA_ARGS__;                              \
     } else {                                                    \
-      if (ps->width == 3) f<2, 3> __VA_ARGS__;                  \
-      else if (ps->width == 6) f<2, 6> __VA_ARGS__;             \
-      else f<2, 8> __VA_ARGS__;                                 \
+      if (ps->width == 3) f<2, 3, 4> __VA_ARGS__;               \
+      else if (ps->width == 6) f<2, 6, 4> __VA_ARGS__;          \
+      else f<2, 8, 4> __VA_ARGS__;                              \
     }                                                           \
   } while (0)
 
@@ -788,6 +892,7 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   *out = ps;
   ps->nc = pp.nc;
   ps->width = pp.width;
+  ps->block = pp.block;
   ps->depth = pp.depth;
   for (const PatchInfo& p : pp.patches)
     for (int d = 0; d <= kPolyDepth; ++d) ps->largest[d] = std::max(ps->largest[d], p.end[d]);
@@ -814,7 +919,8 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
     return st;
   {
     std::vector<double> d((size_t)m.rows);
-    for (int64_t r = 0; r < m.rows; ++r) d[r] = pp.val[r / pp.nc * poly_val_record(pp.nc, pp.width) + r % pp.nc * (pp.nc + 1)];
+    for (int64_t r = 0; r < m.rows; ++r)
+      d[r] = pp.val[r / pp.nc * poly_val_record(pp.width, pp.block) + (pp.block == 4 ? r % 2 * 3 : 0)];
     const size_t at = d.size() - 1 - d.size() / 20;
     std::nth_element(d.begin(), d.begin() + at, d.end());
     ps->lam_typical = 2.0 * d[at];
@@ -929,10 +1035,10 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
   // without a limit: about 6 GB, which at level 9 holds 4 fields with 64
   // vectors and 32 scales each
   const size_t have = (limit ? limit : (size_t)6 << 30) / sizeof(double);
-  const int least = std::max(1, std::min(degree, 16));
+  const int least = std::max(4, std::min(degree, 16));  // 4: the two pairs of a sequence summed as it goes
   // small meshes (32 MB a sequence) keep all of it, and sum once
   const bool whole = ps->single || (size_t)degree * m.np * sizeof(double) <= (size_t)32 << 20;
-  const int most = std::max(1, whole ? degree : std::min(degree, 64));
+  const int most = std::max(4, whole ? degree : std::min(degree, 64));
   const int F = c.n_fields;
   for (int sc = c.n_scales;; sc = (sc + 1) / 2) {
     const size_t group = (size_t)padded_scales(std::min(sc, kMaxGroup));
@@ -1099,12 +1205,22 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
     for (const auto& groups : seqs) {
       const int degree = groups[0].degree;
       const double *prev = nullptr, *cur = phi;
-      for (int k0 = 0; k0 < degree || k0 == 0;) {
+      const bool summing = degree > 0 && groups.size() == 1 && sums_itself(ps, groups[0].sc, plan.steps);
+      for (int k = 0, pair = 0; summing && k < degree; pair ^= 1) {
+        const int d = std::min(plan.steps, degree - k);
+        double* to = w->t + 2 * pair * plane;
+        launch_steps(ps, {prev, cur, to, plane, nf, d, w->coef + groups[0].coef + (size_t)k * groups[0].sc, w->x,
+                          groups[0].sc}, s);
+        prev = d >= 2 ? to : cur;
+        cur = to + plane;
+        k += d;
+      }
+      for (int k0 = 0; !summing && (k0 < degree || k0 == 0);) {
         const int n = std::min(plan.planes, degree - k0);
         for (int j = 0; j < n;) {
           const int d = std::min(plan.steps, n - j);
           double* to = w->t + (int64_t)j * plane;
-          launch_steps(ps, prev, cur, to, plane, nf, d, s);
+          launch_steps(ps, {prev, cur, to, plane, nf, d}, s);
           prev = d >= 2 ? to + (int64_t)(d - 2) * plane : cur;
           cur = to + (int64_t)(d - 1) * plane;
           j += d;
