@@ -321,31 +321,40 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
   return true;
 }
 
-std::vector<double> poly_coefficients(int order, double c, double lam, double tol, int max_degree) {
-  // in extended precision: the coefficients of order 2 are read with the
-  // weight 1 + c lam^2, the condition number of the system
-  using real = long double;
-  const int n = order;
-  if (n != 1 && n != 2) return {};
-  // one zero zr + i zi of 1 + c x^n in z (n = 2: the other is its conjugate),
-  // and rho, z = (rho + 1 / rho) / 2, |rho| > 1
-  const real at = 2.0L / (real)lam * (n == 1 ? 1.0L / (real)c : 1.0L / std::sqrt((real)c));
-  const real zr = n == 1 ? -1.0L - at : -1.0L, zi = n == 1 ? 0.0L : at;
-  const std::complex<real> z(zr, zi);
-  const std::complex<real> root = std::sqrt(z - (real)1) * std::sqrt(z + (real)1);
-  std::complex<real> rho = z + root;
-  if (std::abs(rho) < 1.0L) rho = z - root;
-  const real grow = std::log(std::abs(rho)), turn = std::arg(rho);
-  if (!(grow > 0.0L) || !std::isfinite((double)grow)) return {};
-  // a of the residual a_0 T_{m+1} (n = 1), a_0 T_{m+1} + a_1 T_{m+2} (n = 2,
-  // real and imaginary part of its value 1 at z); its size
+namespace {
+
+// In extended precision: the coefficients of order 2 are read with the
+// weight 1 + c lam^2, the condition number of the system.
+using real = long double;
+
+// One zero zr + i zi of 1 + c x^n in z (n = 2: the other is its conjugate),
+// as z = (rho + 1 / rho) / 2, rho = exp(grow + i turn), grow > 0, and the
+// residual of a degree, a_0 T_{m+1} (n = 1) or a_0 T_{m+1} + a_1 T_{m+2}
+// (n = 2, real, from the real and imaginary part of its value 1 at the zero).
+struct Residual {
+  int n;
+  real zr, zi, grow, turn;
   real a[2] = {0.0L, 0.0L};
-  auto cheb = [&](int k, real* re, real* im) {
+
+  Residual(int order, double c, double lam) : n(order) {
+    const real at = 2.0L / (real)lam * (n == 1 ? 1.0L / (real)c : 1.0L / std::sqrt((real)c));
+    zr = n == 1 ? -1.0L - at : -1.0L;
+    zi = n == 1 ? 0.0L : at;
+    const std::complex<real> z(zr, zi);
+    const std::complex<real> root = std::sqrt(z - (real)1) * std::sqrt(z + (real)1);
+    std::complex<real> rho = z + root;
+    if (std::abs(rho) < 1.0L) rho = z - root;
+    grow = std::log(std::abs(rho));
+    turn = std::arg(rho);
+  }
+  // T_k at the zero
+  void cheb(int k, real* re, real* im) const {
     const real up = std::exp(k * grow), down = 1.0L / up;
     *re = 0.5L * (up + down) * std::cos(k * turn);
     *im = 0.5L * (up - down) * std::sin(k * turn);
-  };
-  auto solve = [&](int m) {
+  }
+  // sets a for degree m; its size
+  real solve(int m) {
     real r0, i0, r1, i1;
     cheb(m + 1, &r0, &i0);
     if (n == 1) {
@@ -357,27 +366,36 @@ std::vector<double> poly_coefficients(int order, double c, double lam, double to
     a[0] = i1 / det;
     a[1] = -i0 / det;
     return std::abs(a[0]) + std::abs(a[1]);
-  };
-  const double guess = std::log(2.0 / tol) / (double)grow;
-  if (!(guess < 4.0 * max_degree + 64.0)) return {};
-  int m = std::max(0, (int)guess);
-  if (solve(m) <= tol) {
-    while (m > 0 && solve(m - 1) <= tol) --m;
-  } else {
-    while (m <= max_degree && !(solve(m) <= tol)) ++m;
   }
-  if (m > max_degree) return {};
-  solve(m);
+};
+
+}  // namespace
+
+int poly_degree(int order, double c, double lam, double tol, int max_degree) {
+  if (order != 1 && order != 2) return -1;
+  Residual r(order, c, lam);
+  if (!(r.grow > 0.0L) || !std::isfinite((double)r.grow)) return -1;
+  const double guess = std::log(2.0 / tol) / (double)r.grow;
+  if (!(guess < 4.0 * max_degree + 64.0)) return -1;
+  // n = 1: the size falls as 2 exp(-grow (m + 1)); n = 2: it swings about that
+  int m = std::max(0, (int)guess - (order == 1 ? 2 : 8));
+  while (m <= max_degree && !(r.solve(m) <= tol)) ++m;
+  return m > max_degree ? -1 : m;
+}
+
+void poly_coefficients(int order, double c, double lam, int m, double* out, int stride) {
+  Residual r(order, c, lam);
+  r.solve(m);
+  const int n = order;
   // s = (1 - R) / (z - z_0), from the highest term down (the growing
   // direction of the recurrence); p = s / (c (lam / 2)) for n = 1, and for
   // n = 2, 1 / |z - z_0|^2 = Im (1 / (z - z_0)) / Im z_0 gives p from Im s
   const real lead = n == 1 ? 1.0L / ((real)c * 0.5L * (real)lam)
-                           : 1.0L / ((real)c * 0.25L * (real)lam * (real)lam * zi);
-  std::vector<double> out((size_t)m + 1);
+                           : 1.0L / ((real)c * 0.25L * (real)lam * (real)lam * r.zi);
   real sr = 0.0L, si = 0.0L, ur = 0.0L, ui = 0.0L;  // s_k, s_{k+1}
   for (int k = m + n; k >= 1; --k) {
-    const real q = k > m ? -a[k - m - 1] : 0.0L;
-    real nr = 2.0L * (q + zr * sr - zi * si) - ur, ni = 2.0L * (zr * si + zi * sr) - ui;
+    const real q = k > m ? -r.a[k - m - 1] : 0.0L;
+    real nr = 2.0L * (q + r.zr * sr - r.zi * si) - ur, ni = 2.0L * (r.zr * si + r.zi * sr) - ui;
     if (k == 1) {
       nr *= 0.5L;
       ni *= 0.5L;
@@ -386,9 +404,8 @@ std::vector<double> poly_coefficients(int order, double c, double lam, double to
     ui = si;
     sr = nr;
     si = ni;
-    if (k - 1 <= m) out[(size_t)k - 1] = (double)((n == 1 ? sr : si) * lead);
+    if (k - 1 <= m) out[(int64_t)(k - 1) * stride] = (double)((n == 1 ? sr : si) * lead);
   }
-  return out;
 }
 
 }  // namespace ifl

@@ -303,10 +303,10 @@ __device__ __forceinline__ double block_total(double v, double* lds) {
 }
 
 // Fields in the caller's numbering -> rows (grid.y = field), with ||M phi||^2
-// by block; a NaN or Inf raises *bad.
+// by block; a NaN or Inf sets *bad to the call's number.
 __global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __restrict__ fields,
                                                     double* __restrict__ phi, double* __restrict__ part,
-                                                    int* __restrict__ bad) {
+                                                    int* __restrict__ bad, int call) {
   __shared__ double lds[kRed / 64];
   const double* src = fields + (int64_t)blockIdx.y * m.field_len;
   double* dst = phi + (int64_t)blockIdx.y * m.np;
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __r
     }
     dst[r] = v;
   }
-  if (!ok) *bad = 1;
+  if (!ok) *bad = call;
   const double t = block_total<kRed>(sum, lds);
   if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
 }
@@ -330,7 +330,9 @@ __global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __r
 // x (rows x SC) = or += sum over k of coef[k][s] t_k, one thread per row
 // (grid.y = field): each t_k is read once for SC scales, the coefficients
 // come through the scalar cache. phi != nullptr: the sum starts with
-// coef[0] phi, and coef + SC belongs to the first of the n planes.
+// coef[0] phi, and coef + SC belongs to the first of the n planes. Bound by
+// HBM: 5.0 TB/s over 16 fields x 30 scales at level 9 (the same with two rows
+// and 16-byte loads a thread, which takes twice as long on small meshes).
 template <int SC>
 __global__ __launch_bounds__(kRed) void k_poly_sum(const double* __restrict__ phi, const double* __restrict__ t,
                                                    int64_t plane, int64_t np, int n,
@@ -509,9 +511,9 @@ __global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ 
 // field was found bad.
 template <int SC>
 __global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __restrict__ x, GroupScales gs,
-                                                   int64_t field_stride, const int* __restrict__ bad,
+                                                   int64_t field_stride, const int* __restrict__ bad, int call,
                                                    double* __restrict__ out) {
-  if (*bad) return;
+  if (*bad == call) return;
   const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
   if (i >= m.field_len) return;
   const int32_t r = m.row_of[i];
@@ -640,7 +642,9 @@ struct PolyWork {
   double* arena = nullptr;
   double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *in = nullptr, *stage = nullptr;
   size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, in_n = 0, stage_n = 0;
-  double *part = nullptr, *norm = nullptr, *coef = nullptr;  // coef: the coefficients, then the bad flag
+  double *part = nullptr, *norm = nullptr, *coef = nullptr;
+  int* bad = nullptr;  // number of the last call with a non-finite field
+  int call = 0;        // number of the running call
   size_t part_n = 0, norm_n = 0, coef_n = 0;
   double *host = nullptr, *host_coef = nullptr;  // pinned: totals and the bad flag; source of coef
   size_t host_n = 0, host_coef_n = 0;
@@ -822,15 +826,15 @@ void check_scales(const PolyState* ps, int sc, int order, const double* phi, con
     }                                                           \
   } while (0)
 
-void launch_out(const PolyState* ps, const int* bad, int sc, const double* x, const GroupScales& gs,
+void launch_out(const PolyState* ps, const int* bad, int call, int sc, const double* x, const GroupScales& gs,
                 int64_t field_stride, double* out, int F, hipStream_t s) {
   const dim3 g((unsigned)((ps->m.field_len + kRed - 1) / kRed), (unsigned)F);
   switch (sc) {
-    case 1: k_poly_out<1><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
-    case 2: k_poly_out<2><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
-    case 4: k_poly_out<4><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
-    case 8: k_poly_out<8><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
-    default: k_poly_out<16><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, out); break;
+    case 1: k_poly_out<1><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, call, out); break;
+    case 2: k_poly_out<2><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, call, out); break;
+    case 4: k_poly_out<4><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, call, out); break;
+    case 8: k_poly_out<8><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, call, out); break;
+    default: k_poly_out<16><<<g, kRed, 0, s>>>(ps->m, x, gs, field_stride, bad, call, out); break;
   }
 }
 
@@ -955,6 +959,11 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
   size_t n = 0;
   ifl_status st = IFL_OK;
   if (limit) st = grow(&w->arena, &n, limit / sizeof(double));
+  if (st == IFL_OK && (hipMalloc((void**)&w->bad, sizeof(int)) != hipSuccess ||
+                       hipMemset(w->bad, 0, sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess)) {
+    (void)hipGetLastError();
+    st = fail(IFL_ENOMEM, "hipMalloc failed for the polynomial engine's work space");
+  }
   if (st != IFL_OK) {
     poly_work_destroy(w);
     *out = nullptr;
@@ -965,7 +974,7 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
 void poly_work_destroy(PolyWork* w) {
   if (!w) return;
   if (!w->limit) free_large(w);
-  void* ptrs[] = {w->arena, w->part, w->norm, w->coef};
+  void* ptrs[] = {w->arena, w->part, w->norm, w->coef, w->bad};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (w->host) (void)hipHostFree(w->host);
@@ -1030,11 +1039,14 @@ int padded_scales(int n) {
   return p + r;
 }
 
+// Without a limit: about 12 GB of the 288, which at level 9 hold 8 fields
+// with 64 vectors and 32 scales each (a patch's records are read once for
+// them; 4 fields took 7% longer).
+constexpr size_t kPolyBudget = (size_t)12 << 30;
+
 bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree, Plan* out) {
   const PolyDev& m = ps->m;
-  // without a limit: about 6 GB, which at level 9 holds 4 fields with 64
-  // vectors and 32 scales each
-  const size_t have = (limit ? limit : (size_t)6 << 30) / sizeof(double);
+  const size_t have = (limit ? limit : kPolyBudget) / sizeof(double);
   const int least = std::max(4, std::min(degree, 16));  // 4: the two pairs of a sequence summed as it goes
   // small meshes (32 MB a sequence) keep all of it, and sum once
   const bool whole = ps->single || (size_t)degree * m.np * sizeof(double) <= (size_t)32 << 20;
@@ -1109,16 +1121,15 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
   const int S = c.n_scales, F = c.n_fields;
   const double tol = poly_tol(ps, c);
   // the scales' polynomials, largest degree first
-  std::vector<std::vector<double>> poly((size_t)S);
-  std::vector<int> by((size_t)S);
+  std::vector<int> deg((size_t)S), by((size_t)S);
   for (int j = 0; j < S; ++j) {
-    poly[j] = poly_coefficients(c.order, scale_factor(c, j), ps->lam, tol, c.max_iter);
+    deg[j] = poly_degree(c.order, scale_factor(c, j), ps->lam, tol, c.max_iter);
     by[j] = j;
-    if (poly[j].empty()) return fail(IFL_EUNSUPPORTED, "a scale's polynomial exceeds max_iter");
+    if (deg[j] < 0) return fail(IFL_EUNSUPPORTED, "a scale's polynomial exceeds max_iter");
   }
-  std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return poly[a].size() > poly[b].size(); });
+  std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return deg[a] > deg[b]; });
   Plan plan;
-  if (!make_plan(ps, w->limit, c, (int)poly[by[0]].size() - 1, &plan))
+  if (!make_plan(ps, w->limit, c, deg[by[0]], &plan))
     return fail(IFL_ENOMEM, "the work space holds no sequence of this mesh");
   const int FG = plan.fields, G = red_blocks(m.rows), GL = red_blocks(m.np);
   // sequences of up to plan.scales scales, each summed in groups
@@ -1131,7 +1142,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       Group g;
       g.n = std::min(kMaxGroup, end - j);
       g.sc = padded_scales(g.n);
-      g.degree = (int)poly[by[j]].size() - 1;
+      g.degree = deg[by[j]];
       g.pad0 = pad;
       g.coef = ncoef;
       for (int i = 0; i < kMaxGroup; ++i) {
@@ -1169,33 +1180,40 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
     return st;
   }
   if ((st = grow(&w->part, &w->part_n, (size_t)FG * kMaxGroup * 3 * G)) ||
-      (st = grow(&w->norm, &w->norm_n, (size_t)F * GL)) || (st = grow(&w->coef, &w->coef_n, ncoef + 1)) ||
+      (st = grow(&w->norm, &w->norm_n, (size_t)F * GL)) || (st = grow(&w->coef, &w->coef_n, ncoef)) ||
       (st = grow_host(&w->host, &w->host_n, nsums + 1)) ||
-      (st = grow_host(&w->host_coef, &w->host_coef_n, ncoef + 1)))
+      (st = grow_host(&w->host_coef, &w->host_coef_n, ncoef)))
     return st;
-  for (const auto& groups : seqs)
-    for (const Group& g : groups)
-      for (int k = 0; k <= g.degree; ++k)
-        for (int i = 0; i < g.sc; ++i) {
-          const std::vector<double>* p = i < g.n ? &poly[g.gs.column[i]] : nullptr;
-          w->host_coef[g.coef + (size_t)k * g.sc + i] = p && k < (int)p->size() ? (*p)[k] : 0.0;
-        }
-  w->host_coef[ncoef] = 0.0;
-  IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, (ncoef + 1) * sizeof(double), hipMemcpyHostToDevice, s));
-  int* bad = reinterpret_cast<int*>(w->coef + ncoef);
+  const int call = ++w->call;
   const double* fields = c.fields;
   if (c.fields_host) {
     IFL_HIP(hipMemcpyAsync(w->in, c.fields, n_in * sizeof(double), hipMemcpyHostToDevice, s));
     fields = w->in;
   }
-  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, fields, w->phi, w->norm, bad);
+  k_poly_load<<<dim3(GL, F), kRed, 0, s>>>(m, fields, w->phi, w->norm, w->bad, call);
   IFL_HIP(hipGetLastError());
   int* bad_host = reinterpret_cast<int*>(w->host + nsums);
   if (n_stage) {  // the copies to the host must not start on a bad field
-    IFL_HIP(hipMemcpyAsync(bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    IFL_HIP(hipMemcpyAsync(bad_host, w->bad, sizeof(int), hipMemcpyDeviceToHost, s));
     IFL_HIP(hipStreamSynchronize(s));
-    if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
+    if (*bad_host == call) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   }
+  // the coefficients are worked out when the first launches are under way
+  bool sent = false;
+  auto send_coefficients = [&]() -> ifl_status {
+    if (sent) return IFL_OK;
+    sent = true;
+    for (const auto& groups : seqs)
+      for (const Group& g : groups)
+        for (int i = 0; i < g.sc; ++i) {
+          double* to = w->host_coef + g.coef + i;
+          const int d = i < g.n ? deg[g.gs.column[i]] : -1;
+          if (d >= 0) poly_coefficients(c.order, g.gs.c[i], ps->lam, d, to, g.sc);
+          for (int k = d + 1; k <= g.degree; ++k) to[(size_t)k * g.sc] = 0.0;
+        }
+    IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
+    return IFL_OK;
+  };
   std::vector<Totals> totals;
   size_t sum_at = (size_t)F;
   for (int f0 = 0; f0 < F; f0 += FG) {
@@ -1206,6 +1224,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       const int degree = groups[0].degree;
       const double *prev = nullptr, *cur = phi;
       const bool summing = degree > 0 && groups.size() == 1 && sums_itself(ps, groups[0].sc, plan.steps);
+      if (summing && (st = send_coefficients()) != IFL_OK) return st;
       for (int k = 0, pair = 0; summing && k < degree; pair ^= 1) {
         const int d = std::min(plan.steps, degree - k);
         double* to = w->t + 2 * pair * plane;
@@ -1225,6 +1244,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
           cur = to + (int64_t)(d - 1) * plane;
           j += d;
         }
+        if ((st = send_coefficients()) != IFL_OK) return st;
         for (const Group& g : groups) {
           const int ng = std::min(n, g.degree - k0);
           if (ng <= 0 && k0 > 0) continue;
@@ -1241,13 +1261,13 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
         // with the call's last group go the norms of all its fields
         const bool last = f0 + nf == F && &g == &seqs.back().back();
         const int n = nf * g.sc * 3;
-        k_poly_total<<<n + (last ? F : 0), kRed, 0, s>>>(w->part, G, n, w->host + sum_at, w->norm, GL, w->host, bad,
+        k_poly_total<<<n + (last ? F : 0), kRed, 0, s>>>(w->part, G, n, w->host + sum_at, w->norm, GL, w->host, w->bad,
                                                          last ? bad_host : nullptr);
         totals.push_back({g, f0, nf, sum_at});
         sum_at += (size_t)nf * g.sc * 3;
         if (!c.out) continue;
         if (!n_stage) {
-          launch_out(ps, bad, g.sc, x, g.gs, (int64_t)S * m.field_len, c.out + (int64_t)f0 * S * m.field_len, nf, s);
+          launch_out(ps, w->bad, call, g.sc, x, g.gs, (int64_t)S * m.field_len, c.out + (int64_t)f0 * S * m.field_len, nf, s);
           continue;
         }
         // to the host through the staging: columns in the caller's order, so
@@ -1261,7 +1281,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
             const int at = (int)(std::lower_bound(cols.begin(), cols.end(), g.gs.column[i]) - cols.begin()) - q;
             some.column[i] = at >= 0 && at < qn ? at : -1;
           }
-          launch_out(ps, bad, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
+          launch_out(ps, w->bad, call, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
           for (int f = 0; f < nf; ++f)
             for (int i = q, e; i < q + qn; i = e) {
               for (e = i + 1; e < q + qn && cols[e] == cols[e - 1] + 1;) ++e;
@@ -1275,7 +1295,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
     }
   }
   IFL_HIP(hipStreamSynchronize(s));
-  if (*bad_host) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
+  if (*bad_host == call) return fail(IFL_EINVAL, "field has a NaN or Inf at a wet entry");
   const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   for (const Totals& t : totals)
     for (int f = 0; f < t.nf; ++f)
@@ -1290,7 +1310,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
         if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
         if (c.stats) {
           ifl_solve_stats& so = c.stats[col];
-          so.iterations = bb > 0.0 ? (int32_t)poly[t.g.gs.column[i]].size() - 1 : 0;
+          so.iterations = bb > 0.0 ? deg[t.g.gs.column[i]] : 0;
           so.refinements = 0;
           so.status = IFL_OK;
           so.reserved = 0;
