@@ -145,6 +145,15 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
     else return false;
   }
   pp.block = nc * nc;
+  if (nc == 1)  // a constant field is left as it is: the diagonal is minus the row's other entries
+    for (int64_t r = 0; r < op.n; ++r) {
+      double sum = 0.0, size = 0.0;
+      for (int64_t e = rp[r]; e < rp[r + 1]; ++e) {
+        sum += val[e];
+        size += std::fabs(val[e]);
+      }
+      if (!(std::fabs(sum) <= 1e-14 * size)) return false;
+    }
   if (nc == 2 && pp.width >= 6) {  // [[a, b], [-b, a]] blocks throughout?
     std::atomic<bool> turns{true};
     const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8, g.n / 4096));
@@ -306,7 +315,9 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
           const int32_t v = col[e] / nc, cc = col[e] % nc;
           int64_t k = 0;
           if (v != u) k = 1 + std::lower_bound(g.adj.begin() + a0, g.adj.begin() + a1, v) - (g.adj.begin() + a0);
-          if (bb == nc * nc) pp.val[i * rec + k * bb + c * nc + cc] = val[e] * im;
+          if (bb == 1) {
+            if (k) pp.val[i * rec + k - 1] = val[e] * im;
+          } else if (bb == 4) pp.val[i * rec + k * bb + c * nc + cc] = val[e] * im;
           else if (c == 0) pp.val[i * rec + k * bb + cc] = val[e] * im;
         }
       }

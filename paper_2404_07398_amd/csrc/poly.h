@@ -31,11 +31,14 @@ constexpr int poly_single_units(int nc, int width, int block) {
 // Rings of large meshes' patches (small ones take what their patches leave).
 constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 6 ? 8 : 4; }
 
-// Records, in whole 16-byte units (8 for 3 neighbours): a unit's own block
-// and its neighbours' (doubles); its neighbours' LDS offsets in a patch
-// (uint16_t, bytes of a buffer of units); its neighbours' positions.
-constexpr int poly_val_record(int width, int block) { return ((1 + width) * block + 1) / 2 * 2; }
-constexpr int poly_idx_record(int width) { return width <= 4 ? 4 : (width + 7) / 8 * 8; }
+// Records: a unit's own block and its neighbours' (doubles, whole 16-byte
+// units; of a scalar the neighbours' alone, its row's sum being zero); its
+// neighbours' LDS offsets in a patch (uint16_t, bytes of a buffer of units);
+// its neighbours' positions.
+constexpr int poly_val_record(int width, int block) {
+  return block == 1 ? width : ((1 + width) * block + 1) / 2 * 2;
+}
+constexpr int poly_idx_record(int width) { return (width + 1) / 2 * 2; }
 constexpr int poly_col_record(int width) { return (width + 3) / 4 * 4; }
 
 struct PatchInfo {

@@ -70,6 +70,15 @@ __device__ __forceinline__ double coupling(const double* b, int c, int d) {
   else return b[c * NC + d];
 }
 
+// A scalar's own entry, from its neighbours'.
+template <int W>
+__device__ __forceinline__ double minus_sum(const double* v) {
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < W; ++k) s -= v[k];
+  return s;
+}
+
 // Slots of a thread that may hold interior units when the step kernel sums.
 constexpr int sum_slots(int slots) { return slots < 2 ? slots : 2; }
 
@@ -213,14 +222,16 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
     for (int k = 0; k < (W + 1) / 2; ++k) r.nb[s][k] = id[k];
     const double* v = m.val + (int64_t)(tid + s * T < first_lim ? at[s] : start) * VR;
 #pragma unroll
-    for (int b = 0; b < BV; ++b) r.own[s][b] = v[b];
+    for (int b = 0; b < BV; ++b)
+      if (BV > 1) r.own[s][b] = v[b];
 #pragma unroll
     for (int k = 0; k < W; ++k)
 #pragma unroll
-      for (int b = 0; b < BV; ++b) r.val[s][k][b] = v[(k + 1) * BV + b];
+      for (int b = 0; b < BV; ++b) r.val[s][k][b] = v[(BV > 1 ? k + 1 : k) * BV + b];
   }
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
+    if (BV == 1) r.own[s][0] = minus_sum<W>(&r.val[s][0][0]);
 #pragma unroll
     for (int b = 0; b < BV; ++b) r.own[s][b] = scale * r.own[s][b] - (b == 0 || b == 3 ? 2.0 : 0.0);
 #pragma unroll
@@ -407,7 +418,9 @@ __device__ __forceinline__ void unit_product(const PolyDev& m, const double* xf,
     for (int k = 0; k <= W; ++k)
 #pragma unroll
       for (int d = 0; d < NC; ++d) {
-        const double v = coupling<NC, BV>(a + k * BV, c, d);
+        double v;
+        if constexpr (BV == 1) v = k == 0 ? minus_sum<W>(a) : a[k == 0 ? 0 : k - 1];
+        else v = coupling<NC, BV>(a + k * BV, c, d);
 #pragma unroll
         for (int e = 0; e < V; ++e) y[c].v[e] += v * t[k][d].v[e];
       }
@@ -923,8 +936,14 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
     return st;
   {
     std::vector<double> d((size_t)m.rows);
-    for (int64_t r = 0; r < m.rows; ++r)
-      d[r] = pp.val[r / pp.nc * poly_val_record(pp.width, pp.block) + (pp.block == 4 ? r % 2 * 3 : 0)];
+    const int rec = poly_val_record(pp.width, pp.block);
+    for (int64_t r = 0; r < m.rows; ++r) {
+      const double* v = &pp.val[(size_t)(r / pp.nc * rec)];
+      if (pp.block == 1)
+        for (int k = 0; k < pp.width; ++k) d[r] -= v[k];
+      else
+        d[r] = v[pp.block == 4 ? r % 2 * 3 : 0];
+    }
     const size_t at = d.size() - 1 - d.size() / 20;
     std::nth_element(d.begin(), d.begin() + at, d.end());
     ps->lam_typical = 2.0 * d[at];
@@ -1048,9 +1067,6 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
   const PolyDev& m = ps->m;
   const size_t have = (limit ? limit : kPolyBudget) / sizeof(double);
   const int least = std::max(4, std::min(degree, 16));  // 4: the two pairs of a sequence summed as it goes
-  // small meshes (32 MB a sequence) keep all of it, and sum once
-  const bool whole = ps->single || (size_t)degree * m.np * sizeof(double) <= (size_t)32 << 20;
-  const int most = std::max(4, whole ? degree : std::min(degree, 64));
   const int F = c.n_fields;
   for (int sc = c.n_scales;; sc = (sc + 1) / 2) {
     const size_t group = (size_t)padded_scales(std::min(sc, kMaxGroup));
@@ -1066,7 +1082,14 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
       const size_t field = vecs + out->staged * stage;
       const size_t left = avail > field ? (avail - field) / m.np : 0;
       out->scales = sc;
-      out->planes = (int)std::max<size_t>(least, std::min<size_t>(most, left));
+      // the whole sequence where it fits, so that its vectors are summed once
+      // (the sums are read and written again after every part of it), for 8
+      // fields if it does (they share a patch's records); fewer fields rather
+      // than parts of less than 64 vectors
+      const size_t share = avail / (size_t)std::min(F, 8);
+      const size_t planes = share > field ? (share - field) / m.np : 0;
+      out->planes = (int)std::max<size_t>(
+          least, std::min<size_t>({left, (size_t)std::max(4, degree), std::max<size_t>(planes, 64)}));
       out->fields = (int)std::max<size_t>(
           1, std::min<size_t>((size_t)F, avail / (field + (size_t)out->planes * m.np)));
       // where the patches of all fields run one after another on a CU, more
