@@ -3,31 +3,16 @@
 // filter scale.
 #include "poly.h"
 
+#include "parallel.h"
+
 #include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <complex>
-#include <thread>
 
 namespace ifl {
 
 namespace {
-
-// Runs f(0) .. f(count - 1) on up to 8 threads, indices dealt in turn.
-template <typename F>
-void parallel_for(int64_t count, const F& f) {
-  const int nt = (int)std::min<int64_t>(count, std::max(1u, std::min(8u, std::thread::hardware_concurrency())));
-  if (nt <= 1) {
-    for (int64_t i = 0; i < count; ++i) f(i);
-    return;
-  }
-  std::vector<std::thread> ts;
-  for (int t = 0; t < nt; ++t)
-    ts.emplace_back([&, t] {
-      for (int64_t i = t; i < count; i += nt) f(i);
-    });
-  for (std::thread& t : ts) t.join();
-}
 
 // Unit graph of an operator: unit u's neighbours other than itself, in
 // increasing order (a unit is a row, or the two rows of a vector dof).
@@ -41,7 +26,7 @@ UnitGraph unit_graph(int64_t n, int nc, const std::vector<int64_t>& rp, const st
   UnitGraph g;
   g.n = n / nc;
   g.ptr.assign(g.n + 1, 0);
-  const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8, g.n / 4096));
+  const int64_t parts = pieces_of(g.n);
   std::vector<std::vector<int32_t>> adj(parts);
   parallel_for(parts, [&](int64_t p) {
     std::vector<int32_t>& a = adj[p];
@@ -108,9 +93,10 @@ void bisect(const UnitGraph& g, std::vector<int32_t>& ord, std::atomic<int32_t>*
   const int64_t left = leaves / 2, cut = b + (e - b) * left / leaves;
   if (fork > 0) {
     std::vector<int64_t> right;
-    std::thread t([&] { bisect(g, ord, mark, cut, e, leaves - left, 2 * node + 1, fork - 1, &right); });
-    bisect(g, ord, mark, b, cut, left, 2 * node, fork - 1, starts);
-    t.join();
+    parallel_for(2, [&](int64_t h) {
+      if (h == 0) bisect(g, ord, mark, b, cut, left, 2 * node, fork - 1, starts);
+      else bisect(g, ord, mark, cut, e, leaves - left, 2 * node + 1, fork - 1, &right);
+    });
     starts->insert(starts->end(), right.begin(), right.end());
     return;
   }
@@ -156,7 +142,7 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
     }
   if (nc == 2 && pp.width >= 6) {  // [[a, b], [-b, a]] blocks throughout?
     std::atomic<bool> turns{true};
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8, g.n / 4096));
+    const int64_t parts = pieces_of(g.n);
     parallel_for(parts, [&](int64_t q) {
       for (int64_t u = g.n * q / parts; u < g.n * (q + 1) / parts && turns.load(); ++u) {
         // the two rows' entries as (column unit, same component, other component)
@@ -221,7 +207,7 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
     std::vector<int32_t> ends;   // depth + 1
     std::vector<uint16_t> idx;   // records
   };
-  const int64_t groups = std::min<int64_t>(8, (int64_t)leaf.size() - 1);
+  const int64_t groups = std::min<int64_t>(16, (int64_t)leaf.size() - 1);
   std::vector<std::vector<Local>> made(groups);
   parallel_for(groups, [&](int64_t q) {
     std::vector<int32_t> loc((size_t)g.n, -1);
@@ -301,7 +287,7 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
   pp.val.assign((size_t)(U * rec), 0.0);
   pp.col.assign((size_t)(U * crec), 0);
   pp.mass.resize((size_t)(U * nc));
-  const int64_t pieces = std::max<int64_t>(1, std::min<int64_t>(8, U / 4096));
+  const int64_t pieces = pieces_of(U);
   parallel_for(pieces, [&](int64_t q) {
     for (int64_t i = U * q / pieces; i < U * (q + 1) / pieces; ++i) {
       const int32_t u = pp.order[i];

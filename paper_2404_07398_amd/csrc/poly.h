@@ -11,8 +11,9 @@
 
 namespace ifl {
 
-// Rings of halo units around a patch, at most.
-constexpr int kPolyDepth = 16;
+// Rings of halo units around a patch, at most (16 rings make a call on 4,096
+// to 30,000 units 2% faster than 12, and its patches a third larger).
+constexpr int kPolyDepth = 12;
 
 // Threads of a patch's workgroup and units per thread; what a patch holds.
 constexpr int kPolyThreads = 512;

@@ -18,6 +18,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 
 #include "poly.h"
@@ -549,15 +550,20 @@ __device__ __forceinline__ double partial_total(const double* part, int g, doubl
   return block_total<kRed>(s, lds);
 }
 
+// a start value of a row, by its place in the caller's numbering
+__device__ __forceinline__ double lanczos_noise(const PolyDev& m, int64_t r) {
+  uint64_t h = (uint64_t)m.entity[r] * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+  h ^= h >> 29;
+  h *= 0xBF58476D1CE4E5B9ull;
+  h ^= h >> 32;
+  return (double)(int64_t)h * 1.0842021724855044e-19;
+}
+
 __global__ __launch_bounds__(kRed) void k_lanczos_start(PolyDev m, double* __restrict__ u, double* __restrict__ beta) {
   __shared__ double lds[kRed / 64];
   double sum = 0.0;
   for (int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x; r < m.rows; r += (int64_t)gridDim.x * kRed) {
-    uint64_t h = (uint64_t)m.entity[r] * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
-    h ^= h >> 29;
-    h *= 0xBF58476D1CE4E5B9ull;
-    h ^= h >> 32;
-    const double v = (double)(int64_t)h * 1.0842021724855044e-19;
+    const double v = lanczos_noise(m, r);
     u[r] = v;
     sum += m.mass[r] * v * v;
   }
@@ -612,6 +618,53 @@ __global__ __launch_bounds__(kRed) void k_lanczos_next(PolyDev m, const double* 
   if (threadIdx.x == 0) beta_next[blockIdx.x] = t;
 }
 
+// All of it in one workgroup, for meshes so small that the launches above
+// would take longer (32 x 32 units: 0.45 ms in 65 launches). u: 3 vectors of
+// np; beta[j], alpha[j] as the sums of those launches.
+constexpr int kSmall = 1024;
+template <int NC, int W, int BV>
+__global__ __launch_bounds__(kSmall) void k_lanczos_small(PolyDev m, double* u, double* beta, double* alpha) {
+  __shared__ double lds[kSmall / 64];
+  double sum = 0.0;
+  for (int64_t r = threadIdx.x; r < m.rows; r += kSmall) {
+    u[r] = lanczos_noise(m, r);
+    sum += m.mass[r] * u[r] * u[r];
+  }
+  double b2 = block_total<kSmall>(sum, lds), bp2 = 0.0;
+  if (threadIdx.x == 0) beta[0] = b2;
+  for (int j = 0; j < kLanczos; ++j) {
+    const double *cur = u + j % 3 * m.np, *prev = u + (j + 2) % 3 * m.np;
+    double* next = u + (j + 1) % 3 * m.np;
+    const double b = sqrt(b2), inv = b > 0.0 ? 1.0 / b : 0.0, invp = bp2 > 0.0 ? b / sqrt(bp2) : 0.0;
+    sum = 0.0;
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < m.units; i += kSmall) {
+      Lane<1> v[NC];
+      unit_product<NC, W, BV, 1>(m, cur, i, 0, v);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int64_t r = i * NC + c;
+        double y = inv * v[c].v[0];
+        if (j) y -= invp * prev[r];
+        next[r] = y;
+        sum += m.mass[r] * y * cur[r] * inv;
+      }
+    }
+    const double a = block_total<kSmall>(sum, lds), f = a * inv;
+    if (threadIdx.x == 0) alpha[j] = a;
+    sum = 0.0;
+    __syncthreads();
+    for (int64_t r = threadIdx.x; r < m.rows; r += kSmall) {
+      const double y = next[r] - f * cur[r];
+      next[r] = y;
+      sum += m.mass[r] * y * y;
+    }
+    bp2 = b2;
+    b2 = block_total<kSmall>(sum, lds);
+    if (threadIdx.x == 0) beta[j + 1] = b2;
+  }
+}
+
 // Largest eigenvalue of the symmetric tridiagonal (a, b) by bisection.
 double largest_eigenvalue(const std::vector<double>& a, const std::vector<double>& b) {
   double lo = a[0], hi = a[0];
@@ -639,6 +692,7 @@ double largest_eigenvalue(const std::vector<double>& a, const std::vector<double
 struct PolyState {
   int device = 0;
   PolyDev m;
+  void* arrays = nullptr;  // the allocation that m's pointers are in
   int nc = 1, width = 6, block = 1, depth = 0;
   int largest[kPolyDepth + 1] = {};  // local units of the largest patch, up to and with ring d
   bool single = false;
@@ -665,17 +719,38 @@ struct PolyWork {
 
 namespace {
 
-template <typename T>
-ifl_status up(const T** p, const std::vector<T>& v) {
-  T* d = nullptr;
-  if (hipMalloc((void**)&d, std::max<size_t>(1, v.size()) * sizeof(T)) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(IFL_ENOMEM, "hipMalloc failed for the patches");
+// The arrays of a PolyDev in one allocation, sent in one copy.
+struct Upload {
+  struct Item {
+    const void** to;
+    const void* from;
+    size_t bytes, at;
+  };
+  std::vector<Item> items;
+  size_t bytes = 0;
+  template <typename T>
+  void add(const T** to, const std::vector<T>& v) {
+    items.push_back({(const void**)to, v.data(), v.size() * sizeof(T), bytes});
+    bytes += (v.size() * sizeof(T) + 255) / 256 * 256;
   }
-  *p = d;
-  if (!v.empty()) IFL_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
-  return IFL_OK;
-}
+  ifl_status run(void** base) {
+    if (hipMalloc(base, std::max<size_t>(bytes, 256)) != hipSuccess) {
+      (void)hipGetLastError();
+      *base = nullptr;
+      return fail(IFL_ENOMEM, "hipMalloc failed for the patches");
+    }
+    if (bytes <= (size_t)4 << 20) {  // small: gathered on the host
+      std::vector<char> all(bytes);
+      for (const Item& i : items) std::memcpy(all.data() + i.at, i.from, i.bytes);
+      IFL_HIP(hipMemcpy(*base, all.data(), bytes, hipMemcpyHostToDevice));
+    } else {
+      for (const Item& i : items)
+        if (i.bytes) IFL_HIP(hipMemcpy((char*)*base + i.at, i.from, i.bytes, hipMemcpyHostToDevice));
+    }
+    for (const Item& i : items) *i.to = (char*)*base + i.at;
+    return IFL_OK;
+  }
+};
 
 ifl_status grow(double** p, size_t* have, size_t want) {
   if (*have >= want) return IFL_OK;
@@ -853,16 +928,19 @@ void launch_out(const PolyState* ps, const int* bad, int call, int sc, const dou
 
 ifl_status estimate_spectrum(PolyState* ps, hipStream_t s) {
   const PolyDev& m = ps->m;
-  const int G = std::min(256, red_blocks(m.rows));
-  double *u[3] = {}, *ab = nullptr;
-  ifl_status st = IFL_OK;
-  size_t n0 = 0;
-  for (double*& v : u)
-    if (st == IFL_OK) st = grow(&v, &(n0 = 0), (size_t)m.np);
-  if (st == IFL_OK) st = grow(&ab, &(n0 = 0), (size_t)(2 * kLanczos + 1) * G);
-  std::vector<double> parts((size_t)(2 * kLanczos + 1) * G);
-  if (st == IFL_OK) {
-    double *beta = ab, *alpha = ab + (size_t)(kLanczos + 1) * G;
+  const bool small = m.rows <= 4096;
+  const int G = small ? 1 : std::min(256, red_blocks(m.rows));
+  const size_t nab = (size_t)(2 * kLanczos + 1) * G;
+  double* work = nullptr;  // three vectors, then the sums
+  size_t have = 0;
+  ifl_status st = grow(&work, &have, 3 * (size_t)m.np + nab);
+  if (st != IFL_OK) return st;
+  std::vector<double> parts(nab);
+  double *u[3] = {work, work + m.np, work + 2 * m.np}, *beta = work + 3 * m.np;
+  double* alpha = beta + (size_t)(kLanczos + 1) * G;
+  if (small) {
+    IFL_POLY_FORMS(k_lanczos_small, <<<1, kSmall, 0, s>>>(m, work, beta, alpha));
+  } else {
     k_lanczos_start<<<G, kRed, 0, s>>>(m, u[0], beta);
     for (int j = 0; j < kLanczos; ++j) {
       double *cur = u[j % 3], *next = u[(j + 1) % 3], *prev = u[(j + 2) % 3];
@@ -872,15 +950,12 @@ ifl_status estimate_spectrum(PolyState* ps, hipStream_t s) {
       k_lanczos_next<<<G, kRed, 0, s>>>(m, cur, next, beta + (size_t)j * G, alpha + (size_t)j * G,
                                         beta + (size_t)(j + 1) * G);
     }
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(parts.data(), ab, parts.size() * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) st = fail(IFL_EDEVICE, std::string("spectrum estimate: ") + hipGetErrorString(e));
   }
-  for (double* v : u)
-    if (v) (void)hipFree(v);
-  if (ab) (void)hipFree(ab);
-  if (st != IFL_OK) return st;
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(parts.data(), beta, nab * sizeof(double), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  (void)hipFree(work);
+  if (e != hipSuccess) return fail(IFL_EDEVICE, std::string("spectrum estimate: ") + hipGetErrorString(e));
   std::vector<double> a, b;
   double first = 0.0;
   for (int j = 0; j < kLanczos; ++j) {
@@ -904,7 +979,11 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   *out = nullptr;
   if (op.order < 1 || op.order > 2 || op.field_len > INT32_MAX) return IFL_OK;
   PatchPack pp;
-  if (!build_patches(op, local_order, &pp)) return IFL_OK;
+  try {
+    if (!build_patches(op, local_order, &pp)) return IFL_OK;
+  } catch (const std::bad_alloc&) {
+    return fail(IFL_ENOMEM, "out of host memory for the patches");
+  }
   PolyState* ps = new PolyState();
   *out = ps;
   ps->nc = pp.nc;
@@ -929,11 +1008,17 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
       entity[r] = (int32_t)op.entity[(int64_t)pp.order[i] * pp.nc + c];
       row_of[entity[r]] = (int32_t)r;
     }
-  ifl_status st;
-  if ((st = up(&m.info, pp.patches)) || (st = up(&m.halo, pp.halo)) || (st = up(&m.idx, pp.idx)) ||
-      (st = up(&m.col, pp.col)) || (st = up(&m.val, pp.val)) ||
-      (st = up(&m.mass, pp.mass)) || (st = up(&m.entity, entity)) || (st = up(&m.row_of, row_of)))
-    return st;
+  Upload u;
+  u.add(&m.info, pp.patches);
+  u.add(&m.halo, pp.halo);
+  u.add(&m.idx, pp.idx);
+  u.add(&m.col, pp.col);
+  u.add(&m.val, pp.val);
+  u.add(&m.mass, pp.mass);
+  u.add(&m.entity, entity);
+  u.add(&m.row_of, row_of);
+  ifl_status st = u.run(&ps->arrays);
+  if (st != IFL_OK) return st;
   {
     std::vector<double> d((size_t)m.rows);
     const int rec = poly_val_record(pp.width, pp.block);
@@ -954,10 +1039,7 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
 
 void poly_destroy(PolyState* ps) {
   if (!ps) return;
-  const PolyDev& m = ps->m;
-  const void* ptrs[] = {m.info, m.halo, m.idx, m.col, m.val, m.mass, m.entity, m.row_of};
-  for (const void* p : ptrs)
-    if (p) (void)hipFree(const_cast<void*>(p));
+  if (ps->arrays) (void)hipFree(ps->arrays);
   poly_work_destroy(ps->work);
   delete ps;
 }

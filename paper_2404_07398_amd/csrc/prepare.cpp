@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "parallel.h"
 
 namespace ifl {
 namespace {
@@ -75,26 +76,44 @@ void to_csr(int64_t n, const Triplets& t, std::vector<int64_t>& row_ptr, std::ve
     bc[p] = t.c[e];
     bv[p] = t.v[e];
   }
+  // each row sorted by column in place (stable: by insertion, rows are
+  // short) and its duplicates summed; the rows then move together
   row_ptr.assign(n + 1, 0);
-  col.clear();
-  val.clear();
-  col.reserve(m);
-  val.reserve(m);
-  std::vector<int64_t> idx;
-  for (int64_t i = 0; i < n; ++i) {
-    const int64_t b = cnt[i], e = cnt[i + 1];
-    idx.resize(e - b);
-    std::iota(idx.begin(), idx.end(), b);
-    std::stable_sort(idx.begin(), idx.end(), [&](int64_t a, int64_t q) { return bc[a] < bc[q]; });
-    for (size_t k = 0; k < idx.size();) {
-      const int32_t cc = bc[idx[k]];
-      double s = 0.0;
-      while (k < idx.size() && bc[idx[k]] == cc) s += bv[idx[k++]];
-      col.push_back(cc);
-      val.push_back(s);
+  const int64_t parts = pieces_of(n);
+  parallel_for(parts, [&](int64_t q) {
+    for (int64_t i = n * q / parts; i < n * (q + 1) / parts; ++i) {
+      const int64_t b = cnt[i], e = cnt[i + 1];
+      for (int64_t k = b + 1; k < e; ++k) {
+        const int32_t ck = bc[k];
+        const double vk = bv[k];
+        int64_t j = k;
+        for (; j > b && bc[j - 1] > ck; --j) {
+          bc[j] = bc[j - 1];
+          bv[j] = bv[j - 1];
+        }
+        bc[j] = ck;
+        bv[j] = vk;
+      }
+      int64_t w = b;
+      for (int64_t k = b; k < e; ++w) {
+        const int32_t cc = bc[k];
+        double s = 0.0;
+        for (; k < e && bc[k] == cc; ++k) s += bv[k];
+        bc[w] = cc;
+        bv[w] = s;
+      }
+      row_ptr[i + 1] = w - b;
     }
-    row_ptr[i + 1] = (int64_t)col.size();
-  }
+  });
+  for (int64_t i = 0; i < n; ++i) row_ptr[i + 1] += row_ptr[i];
+  col.resize((size_t)row_ptr[n]);
+  val.resize((size_t)row_ptr[n]);
+  parallel_for(parts, [&](int64_t q) {
+    for (int64_t i = n * q / parts; i < n * (q + 1) / parts; ++i) {
+      std::copy(bc.begin() + cnt[i], bc.begin() + cnt[i] + (row_ptr[i + 1] - row_ptr[i]), col.begin() + row_ptr[i]);
+      std::copy(bv.begin() + cnt[i], bv.begin() + cnt[i] + (row_ptr[i + 1] - row_ptr[i]), val.begin() + row_ptr[i]);
+    }
+  });
 }
 
 // C = A diag(1/m) B for CSR A, B with sorted columns. Entry (i, j) sums
@@ -105,36 +124,49 @@ void spgemm_scaled(int64_t n, const std::vector<int64_t>& ap, const std::vector<
                    const std::vector<int32_t>& bc, const std::vector<double>& bv,
                    const std::vector<double>& m, std::vector<int64_t>& cp, std::vector<int32_t>& cc,
                    std::vector<double>& cv) {
-  std::vector<double> acc(n, 0.0);
-  std::vector<int64_t> mark(n, -1);
-  std::vector<int32_t> touched;
+  // pieces of rows, each with its own accumulator
+  const int64_t parts = pieces_of(n);
+  std::vector<std::vector<int32_t>> pc((size_t)parts);
+  std::vector<std::vector<double>> pv((size_t)parts);
   cp.assign(n + 1, 0);
-  cc.clear();
-  cv.clear();
-  for (int64_t i = 0; i < n; ++i) {
-    touched.clear();
-    for (int64_t a = ap[i]; a < ap[i + 1]; ++a) {
-      const int32_t k = ac[a];
-      const double aik = av[a];
-      for (int64_t b = bp[k]; b < bp[k + 1]; ++b) {
-        const int32_t j = bc[b];
-        const double t = (aik * bv[b]) / m[k];
-        if (mark[j] != i) {
-          mark[j] = i;
-          acc[j] = t;
-          touched.push_back(j);
-        } else {
-          acc[j] += t;
+  parallel_for(parts, [&](int64_t q) {
+    std::vector<double> acc(n, 0.0);
+    std::vector<int64_t> mark(n, -1);
+    std::vector<int32_t> touched;
+    std::vector<int32_t>& cc = pc[(size_t)q];
+    std::vector<double>& cv = pv[(size_t)q];
+    for (int64_t i = n * q / parts; i < n * (q + 1) / parts; ++i) {
+      touched.clear();
+      for (int64_t a = ap[i]; a < ap[i + 1]; ++a) {
+        const int32_t k = ac[a];
+        const double aik = av[a];
+        for (int64_t b = bp[k]; b < bp[k + 1]; ++b) {
+          const int32_t j = bc[b];
+          const double t = (aik * bv[b]) / m[k];
+          if (mark[j] != i) {
+            mark[j] = i;
+            acc[j] = t;
+            touched.push_back(j);
+          } else {
+            acc[j] += t;
+          }
         }
       }
+      std::sort(touched.begin(), touched.end());
+      for (int32_t j : touched) {
+        cc.push_back(j);
+        cv.push_back(acc[j]);
+      }
+      cp[i + 1] = (int64_t)touched.size();
     }
-    std::sort(touched.begin(), touched.end());
-    for (int32_t j : touched) {
-      cc.push_back(j);
-      cv.push_back(acc[j]);
-    }
-    cp[i + 1] = (int64_t)cc.size();
-  }
+  });
+  for (int64_t i = 0; i < n; ++i) cp[i + 1] += cp[i];
+  cc.resize((size_t)cp[n]);
+  cv.resize((size_t)cp[n]);
+  parallel_for(parts, [&](int64_t q) {
+    std::copy(pc[(size_t)q].begin(), pc[(size_t)q].end(), cc.begin() + cp[n * q / parts]);
+    std::copy(pv[(size_t)q].begin(), pv[(size_t)q].end(), cv.begin() + cp[n * q / parts]);
+  });
 }
 
 // C = (A + A^T) / 2 for a CSR matrix with a symmetric pattern and sorted
@@ -248,7 +280,12 @@ std::vector<int64_t> rcm(int64_t n, const std::vector<int64_t>& ptr, const std::
           nb.push_back(w);
         }
       }
-      std::stable_sort(nb.begin(), nb.end(), [&](int64_t a, int64_t b) { return deg[a] < deg[b]; });
+      for (size_t k = 1; k < nb.size(); ++k) {  // stable, by degree
+        const int64_t w = nb[k];
+        size_t j = k;
+        for (; j > 0 && deg[nb[j - 1]] > deg[w]; --j) nb[j] = nb[j - 1];
+        nb[j] = w;
+      }
       for (int64_t w : nb) order.push_back(w);
     }
   }
@@ -289,31 +326,45 @@ std::vector<int64_t> locality_order(int64_t n, const std::vector<int64_t>& ptr, 
   const double ext = std::max({hi.x - lo.x, hi.y - lo.y, hi.z - lo.z, 1e-300});
   const double qs = 2097151.0 / ext;
   std::vector<std::pair<uint64_t, int64_t>> key(n);
-  for (int64_t i = 0; i < n; ++i) {
-    const uint64_t ix = (uint64_t)((pts[i].x - lo.x) * qs), iy = (uint64_t)((pts[i].y - lo.y) * qs),
-                   iz = (uint64_t)((pts[i].z - lo.z) * qs);
-    key[i] = {spread3(ix) | (spread3(iy) << 1) | (spread3(iz) << 2), i};
-  }
-  std::sort(key.begin(), key.end());
-  std::vector<int64_t> order;
-  order.reserve(n);
-  std::vector<int64_t> loc(n, -1);
-  for (int p = 0; p < kParts; ++p) {
+  parallel_for(kParts, [&](int64_t p) {  // sorted pieces, merged below
+    const int64_t b = n * p / kParts, e = n * (p + 1) / kParts;
+    for (int64_t i = b; i < e; ++i) {
+      const uint64_t ix = (uint64_t)((pts[i].x - lo.x) * qs), iy = (uint64_t)((pts[i].y - lo.y) * qs),
+                     iz = (uint64_t)((pts[i].z - lo.z) * qs);
+      key[i] = {spread3(ix) | (spread3(iy) << 1) | (spread3(iz) << 2), i};
+    }
+    std::sort(key.begin() + b, key.begin() + e);
+  });
+  for (int64_t w = 1; w < kParts; w *= 2)
+    parallel_for(kParts / (2 * w), [&](int64_t p) {
+      const auto at = [&](int64_t k) { return key.begin() + n * k / kParts; };
+      std::inplace_merge(at(2 * w * p), at(2 * w * p + w), at(2 * w * p + 2 * w));
+    });
+  // the place of each dof in its part, and the part
+  std::vector<int64_t> order((size_t)n);
+  std::vector<int64_t> loc(n);
+  std::vector<char> part(n);
+  parallel_for(kParts, [&](int64_t p) {
+    const int64_t b = n * p / kParts, e = n * (p + 1) / kParts;
+    for (int64_t i = b; i < e; ++i) {
+      loc[key[i].second] = i - b;
+      part[key[i].second] = (char)p;
+    }
+  });
+  parallel_for(kParts, [&](int64_t p) {
     const int64_t b = n * p / kParts, e = n * (p + 1) / kParts;
     const int64_t m = e - b;
-    for (int64_t i = 0; i < m; ++i) loc[key[b + i].second] = i;
     std::vector<int64_t> sp(m + 1, 0);
     std::vector<int32_t> sa;
     for (int64_t i = 0; i < m; ++i) {
       const int64_t u = key[b + i].second;
       for (int64_t k = ptr[u]; k < ptr[u + 1]; ++k)
-        if (loc[adj[k]] >= 0) sa.push_back((int32_t)loc[adj[k]]);
+        if (part[adj[k]] == (char)p) sa.push_back((int32_t)loc[adj[k]]);
       sp[i + 1] = (int64_t)sa.size();
     }
     const std::vector<int64_t> r = rcm(m, sp, sa);
-    for (int64_t i = 0; i < m; ++i) order.push_back(key[b + r[i]].second);
-    for (int64_t i = 0; i < m; ++i) loc[key[b + i].second] = -1;
-  }
+    for (int64_t i = 0; i < m; ++i) order[b + i] = key[b + r[i]].second;
+  });
   return order;
 }
 
@@ -363,19 +414,21 @@ void permute_csr(int64_t n, const std::vector<int64_t>& order, const std::vector
   np.assign(n + 1, 0);
   nc.resize(c.size());
   nv.resize(v.size());
-  std::vector<std::pair<int32_t, double>> row;
-  for (int64_t r = 0; r < n; ++r) {
-    const int64_t o = order[r];
-    row.clear();
-    for (int64_t e = p[o]; e < p[o + 1]; ++e) row.push_back({(int32_t)inv[c[e]], v[e]});
-    std::sort(row.begin(), row.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
-    int64_t base = np[r];
-    for (size_t k = 0; k < row.size(); ++k) {
-      nc[base + k] = row[k].first;
-      nv[base + k] = row[k].second;
+  for (int64_t r = 0; r < n; ++r) np[r + 1] = np[r] + p[order[r] + 1] - p[order[r]];
+  const int64_t parts = pieces_of(n);
+  parallel_for(parts, [&](int64_t q) {
+    std::vector<std::pair<int32_t, double>> row;
+    for (int64_t r = n * q / parts; r < n * (q + 1) / parts; ++r) {
+      const int64_t o = order[r];
+      row.clear();
+      for (int64_t e = p[o]; e < p[o + 1]; ++e) row.push_back({(int32_t)inv[c[e]], v[e]});
+      std::sort(row.begin(), row.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+      for (size_t k = 0; k < row.size(); ++k) {
+        nc[np[r] + k] = row[k].first;
+        nv[np[r] + k] = row[k].second;
+      }
     }
-    np[r + 1] = base + (int64_t)row.size();
-  }
+  });
 }
 
 // Scalars on vertices. Median-dual control volumes and P1 elements (Sect.
@@ -944,29 +997,32 @@ void pack_sell_csr(int64_t n, const std::vector<int64_t>& row_ptr, const std::ve
   // kernels may load a fixed number of entries per row without bounds checks
   out->col.assign(out->slice_ptr[ns] + kSellTail, 0);
   out->val.assign(out->slice_ptr[ns] + kSellTail, 0.0);
-  for (int64_t s = 0; s < ns; ++s) {
-    for (int64_t l = 0; l < 64; ++l) {
-      const int64_t r = s * 64 + l;
-      const int32_t self = (int32_t)std::min(r, n - 1);
-      int32_t k = 0;
-      if (r < n) {
-        out->mass[r] = mass[r];
-        for (int64_t e = row_ptr[r]; e < row_ptr[r + 1]; ++e) {
-          if (col[e] == r) {
-            out->diag[r] = val[e];
-          } else {
-            out->col[out->slice_ptr[s] + 64 * k + l] = col[e];
-            out->val[out->slice_ptr[s] + 64 * k + l] = val[e];
-            ++k;
+  const int64_t parts = pieces_of(n);
+  parallel_for(parts, [&](int64_t q) {
+    for (int64_t s = ns * q / parts; s < ns * (q + 1) / parts; ++s) {
+      for (int64_t l = 0; l < 64; ++l) {
+        const int64_t r = s * 64 + l;
+        const int32_t self = (int32_t)std::min(r, n - 1);
+        int32_t k = 0;
+        if (r < n) {
+          out->mass[r] = mass[r];
+          for (int64_t e = row_ptr[r]; e < row_ptr[r + 1]; ++e) {
+            if (col[e] == r) {
+              out->diag[r] = val[e];
+            } else {
+              out->col[out->slice_ptr[s] + 64 * k + l] = col[e];
+              out->val[out->slice_ptr[s] + 64 * k + l] = val[e];
+              ++k;
+            }
           }
         }
-      }
-      for (; k < width[s]; ++k) {
-        out->col[out->slice_ptr[s] + 64 * k + l] = self;
-        out->val[out->slice_ptr[s] + 64 * k + l] = 0.0;
+        for (; k < width[s]; ++k) {
+          out->col[out->slice_ptr[s] + 64 * k + l] = self;
+          out->val[out->slice_ptr[s] + 64 * k + l] = 0.0;
+        }
       }
     }
-  }
+  });
 }
 
 void pack_sell(const HostOperator& op, SellPack* out) { pack_sell_csr(op.n, op.row_ptr, op.col, op.val, op.mass, out); }
