@@ -71,6 +71,14 @@ __device__ __forceinline__ double coupling(const double* b, int c, int d) {
   else return b[c * NC + d];
 }
 
+// A store past the caches (see the launch for where it pays).
+__device__ __forceinline__ void pass_by(const Unit<1>& t, Unit<1>* to) { __builtin_nontemporal_store(t.v[0], &to->v[0]); }
+__device__ __forceinline__ void pass_by(const Unit<2>& t, Unit<2>* to) {
+  typedef double Two __attribute__((ext_vector_type(2)));
+  Two v = {t.v[0], t.v[1]};
+  __builtin_nontemporal_store(v, reinterpret_cast<Two*>(to));
+}
+
 // A scalar's own entry, from its neighbours'.
 template <int W>
 __device__ __forceinline__ double minus_sum(const double* v) {
@@ -103,7 +111,7 @@ typedef const __attribute__((address_space(4))) double* Coef;
 // the LDS buffer CUR hold t_k; t[1 - CUR] holds t_{k-1} and becomes t_{k+1}.
 // All gathers are issued before the sums. Lanes past 'lim' compute on
 // whatever is there and write nothing. coef: the new vector's coefficients.
-template <int NC, int W, int BV, int SLOTS, int T, int ACC, int CUR, int N>
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, bool PAST, int CUR, int N>
 __device__ __forceinline__ void step_slots(Rows<NC, W, BV, SLOTS, ACC>& r, char* lds, int S, int tid, int lim, int inside,
                                            double half, Unit<NC>* out, Coef coef) {
   constexpr int BUF = T * SLOTS * (int)sizeof(Unit<NC>);
@@ -144,11 +152,14 @@ __device__ __forceinline__ void step_slots(Rows<NC, W, BV, SLOTS, ACC>& r, char*
 #pragma unroll
         for (int c = 0; c < NC; ++c) r.acc[s < sum_slots(SLOTS) ? s : 0][a][c] += coef[a] * r.t[1 - CUR][s].v[c];
     }
-    if ((ACC == 0 || out) && i < inside) out[i] = r.t[1 - CUR][s];
+    if ((ACC == 0 || out) && i < inside) {
+      if constexpr (PAST) pass_by(r.t[1 - CUR][s], out + i);
+      else out[i] = r.t[1 - CUR][s];
+    }
   }
 }
 
-template <int NC, int W, int BV, int SLOTS, int T, int ACC, int CUR>
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, bool PAST, int CUR>
 __device__ __forceinline__ void step_all(Rows<NC, W, BV, SLOTS, ACC>& r, char* lds, int tid, int lim, int inside,
                                          double half, Unit<NC>* out, Coef coef) {
   // first unit of this wavefront: the tests below are one scalar branch each
@@ -156,7 +167,7 @@ __device__ __forceinline__ void step_all(Rows<NC, W, BV, SLOTS, ACC>& r, char* l
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s)
     if (wave + s * T < lim)
-      step_slots<NC, W, BV, SLOTS, T, ACC, CUR, 1>(r, lds, s, tid, lim, inside, half, out, coef);
+      step_slots<NC, W, BV, SLOTS, T, ACC, PAST, CUR, 1>(r, lds, s, tid, lim, inside, half, out, coef);
 }
 
 // 'steps' steps of the recurrence on one patch, field after field.
@@ -184,7 +195,7 @@ __device__ __forceinline__ void step_all(Rows<NC, W, BV, SLOTS, ACC>& r, char* l
 // += coef[j][a] t, coef pointing at the coefficients of cur; then only the
 // last two vectors are written (two planes at out), and no launch reads the
 // sequence again: 16 ACC + 16 bytes a row and launch for 16 a row and step.
-template <int NC, int W, int BV, int SLOTS, int T, int ACC>
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, bool PAST>
 __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __restrict__ prev,
                                                      const double* __restrict__ cur, double* __restrict__ out,
                                                      int64_t plane, int n_fields, int steps, int ringed,
@@ -277,12 +288,12 @@ __global__ __launch_bounds__(T, 4) void k_poly_steps(PolyDev m, const double* __
     for (int j = 1; j <= steps; j += 2, cj += 2 * ACC) {
       // the plane of step j: every step's own, or the last two's
       Unit<NC>* to = ACC == 0 ? of + (j - 1) * up : j >= steps - 1 ? of + (j - steps + 1) * up : nullptr;
-      step_all<NC, W, BV, SLOTS, T, ACC, 0>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j : 0), inside,
+      step_all<NC, W, BV, SLOTS, T, ACC, PAST, 0>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j : 0), inside,
                                         !prev && j == 1 ? 0.5 : 1.0, to, cj);
       __syncthreads();
       if (j == steps) break;
       to = ACC == 0 || j + 1 >= steps - 1 ? of + (ACC == 0 ? j : j - steps + 2) * up : nullptr;
-      step_all<NC, W, BV, SLOTS, T, ACC, 1>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j - 1 : 0),
+      step_all<NC, W, BV, SLOTS, T, ACC, PAST, 1>(r, lds, tid, __builtin_amdgcn_readlane(ends, ringed ? steps - j - 1 : 0),
                                         inside, 1.0, to, cj + ACC);
       __syncthreads();
     }
@@ -793,26 +804,40 @@ struct Steps {
   int acc = 0;
 };
 
-template <int NC, int W, int BV, int SLOTS, int T, int ACC>
+template <int NC, int W, int BV, int SLOTS, int T, int ACC, bool PAST>
 void steps_acc(const PolyState* ps, const Steps& a, hipStream_t s) {
   const int per = (ps->m.npatch + kXcd - 1) / kXcd;
   // fields side by side only where the patches alone do not fill the chip:
   // a workgroup that walks the fields reads its rows of A once
   const int gy = std::min(a.fields, std::max(1, 1024 / std::max(1, ps->m.npatch)));
-  k_poly_steps<NC, W, BV, SLOTS, T, ACC><<<dim3(per * kXcd, gy), T, 0, s>>>(
+  k_poly_steps<NC, W, BV, SLOTS, T, ACC, PAST><<<dim3(per * kXcd, gy), T, 0, s>>>(
       ps->m, a.prev, a.cur, a.out, a.plane, a.fields, a.steps, ps->single ? 0 : 1, 4.0 / ps->lam, a.coef, a.x);
+}
+
+// The new vectors go past the caches where most of them are read only by the
+// sums, much later, and would push the halos out of L2: several fields, or
+// launches of 8 steps (of which the next launch reads the last two). Measured
+// plain / past: 8 level-9 fields 440 / 394 us a launch, 8 vertex-vector
+// fields 9.4 / 8.8 ms a call, 2 level-7 fields 0.48 / 0.45 ms; but one
+// cell-vector field with 4 steps a launch 4.66 / 5.03 ms, and 64 x 64 units,
+// whose sequence stays in L2, 207 / 216 us.
+bool past_caches(const PolyState* ps, const Steps& a) {
+  return (a.fields > 1 || a.steps >= 8) && (int64_t)a.fields * ps->m.np >= 1 << 17;
 }
 
 template <int NC, int W, int BV, int SLOTS, int T>
 void steps_of(const PolyState* ps, const Steps& a, hipStream_t s) {
   switch (a.acc) {
-    case 0: steps_acc<NC, W, BV, SLOTS, T, 0>(ps, a, s); break;
-    case 1: steps_acc<NC, W, BV, SLOTS, T, 1>(ps, a, s); break;
+    case 0:
+      if (past_caches(ps, a)) steps_acc<NC, W, BV, SLOTS, T, 0, true>(ps, a, s);
+      else steps_acc<NC, W, BV, SLOTS, T, 0, false>(ps, a, s);
+      break;
+    case 1: steps_acc<NC, W, BV, SLOTS, T, 1, true>(ps, a, s); break;
     case 2:
-      if constexpr (SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 2>(ps, a, s);
+      if constexpr (SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 2, true>(ps, a, s);
       break;
     default:
-      if constexpr (NC == 1 && SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 4>(ps, a, s);
+      if constexpr (NC == 1 && SLOTS < 4) steps_acc<NC, W, BV, SLOTS, T, 4, true>(ps, a, s);
       break;
   }
 }
