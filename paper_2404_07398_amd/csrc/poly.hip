@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kRed) void k_poly_sum(const double* __restrict__ ph
   const double* tr = t + at;
 #pragma unroll 16
   for (int k = 0; k < n; ++k) {
-    const double v = tr[(int64_t)k * plane];
+    const double v = __builtin_nontemporal_load(tr + (int64_t)k * plane);
 #pragma unroll
     for (int s = 0; s < SC; ++s) acc[s] += coef[(int64_t)k * SC + s] * v;
   }
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __re
   double* o = out + (int64_t)blockIdx.y * field_stride + i;
 #pragma unroll
   for (int s = 0; s < SC; ++s)
-    if (gs.column[s] >= 0) o[gs.column[s] * m.field_len] = v[s];
+    if (gs.column[s] >= 0) __builtin_nontemporal_store(v[s], o + gs.column[s] * m.field_len);
 }
 
 // ---- the spectrum's upper end: Lanczos on A in the M inner product ----
