@@ -183,10 +183,13 @@ __device__ __forceinline__ void step_all(Rows<NC, W, BV, SLOTS, ACC>& r, char* l
 // LDS gathers and FP64 FMAs take about as long as each other. Loads and
 // stores must therefore never be waited for inside the steps, and two
 // workgroups share a CU (128 registers) so that one loads while the other
-// steps. Measured on one field of the 2.6 M-vertex sphere: 319 us per 8
-// steps with the ring ends and the unpacked offsets in memory and the
-// records read entry by entry, 165 us (5.4 TB/s) now; 4 fields of the
-// 1.57 M-dof masked sphere 400 and 249 us.
+// steps. Measured on one field of the 2.6 M-vertex sphere, per 8 steps: 319 us
+// with the ring ends and the unpacked offsets in memory and the records read
+// entry by entry, 150 us now with its one scale summed; of the 1.57 M-dof
+// masked sphere 400 us for 4 fields, and 394 us now for 8 (822 MB written and
+// 236 MB read, 2.7 TB/s): there its waves wait for LDS and memory in 46% of
+// their cycles and for an issue slot in 36%, and bank conflicts of the gathers
+// are 44% of LDS's busy cycles.
 //
 // prev == nullptr: the sequence starts (cur = t_0, the first step is halved).
 // out: plane of the first new vector, the next ones 'plane' doubles on.
@@ -326,7 +329,8 @@ __device__ __forceinline__ double block_total(double v, double* lds) {
 }
 
 // Fields in the caller's numbering -> rows (grid.y = field), with ||M phi||^2
-// by block; a NaN or Inf sets *bad to the call's number.
+// by block; a NaN or Inf sets *bad to the call's number. Bound by HBM (the
+// order is local: 16 level-9 fields 172 us, 3.1 TB/s).
 __global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __restrict__ fields,
                                                     double* __restrict__ phi, double* __restrict__ part,
                                                     int* __restrict__ bad, int call) {
@@ -353,36 +357,60 @@ __global__ __launch_bounds__(kRed) void k_poly_load(PolyDev m, const double* __r
 // x (rows x SC) = or += sum over k of coef[k][s] t_k, one thread per row
 // (grid.y = field): each t_k is read once for SC scales, the coefficients
 // come through the scalar cache. phi != nullptr: the sum starts with
-// coef[0] phi, and coef + SC belongs to the first of the n planes. Bound by
-// HBM: 5.0 TB/s over 16 fields x 30 scales at level 9 (the same with two rows
-// and 16-byte loads a thread, which takes twice as long on small meshes).
-template <int SC>
+// coef[0] phi, and coef + SC belongs to the first of the n planes. SB > 0:
+// the next group's SB scales too, of at most n planes (nb of them), so that
+// their vectors are read once for both (all stores come last: a store before
+// the second loop would send its coefficients through vector loads). Bound by
+// HBM: 5.2 TB/s over 8 level-9 fields x 16 scales, 4.2 TB/s x 32; 30 scales
+// of 16 fields 10.3 ms, with the groups' vectors read apart 11.5 (two rows
+// and 16-byte loads a thread: the same, and twice as long on small meshes).
+template <int SC, int SB>
 __global__ __launch_bounds__(kRed) void k_poly_sum(const double* __restrict__ phi, const double* __restrict__ t,
                                                    int64_t plane, int64_t np, int n,
-                                                   const double* __restrict__ coef, double* __restrict__ x) {
+                                                   const double* __restrict__ coef, double* __restrict__ x, int nb,
+                                                   const double* __restrict__ coefb, double* __restrict__ xb) {
   const int64_t r = (int64_t)blockIdx.x * kRed + threadIdx.x;
   if (r >= np) return;
   const int64_t at = (int64_t)blockIdx.y * np + r;
-  double acc[SC];
+  double acc[SC], accb[SB > 0 ? SB : 1];
   double* xr = x + at * SC;
+  double* xbr = xb + at * SB;
   if (phi) {
     const double v = phi[at];
 #pragma unroll
     for (int s = 0; s < SC; ++s) acc[s] = coef[s] * v;
+#pragma unroll
+    for (int s = 0; s < SB; ++s) accb[s] = coefb[s] * v;
     coef += SC;
+    coefb += SB;
   } else {
 #pragma unroll
     for (int s = 0; s < SC; ++s) acc[s] = xr[s];
+#pragma unroll
+    for (int s = 0; s < SB; ++s) accb[s] = xbr[s];
   }
   const double* tr = t + at;
+  int k = 0;
+  if constexpr (SB > 0) {
+#pragma unroll 8
+    for (; k < nb; ++k) {
+      const double v = __builtin_nontemporal_load(tr + (int64_t)k * plane);
+#pragma unroll
+      for (int s = 0; s < SC; ++s) acc[s] += coef[(int64_t)k * SC + s] * v;
+#pragma unroll
+      for (int s = 0; s < SB; ++s) accb[s] += coefb[(int64_t)k * SB + s] * v;
+    }
+  }
 #pragma unroll 16
-  for (int k = 0; k < n; ++k) {
+  for (; k < n; ++k) {
     const double v = __builtin_nontemporal_load(tr + (int64_t)k * plane);
 #pragma unroll
     for (int s = 0; s < SC; ++s) acc[s] += coef[(int64_t)k * SC + s] * v;
   }
 #pragma unroll
   for (int s = 0; s < SC; ++s) xr[s] = acc[s];
+#pragma unroll
+  for (int s = 0; s < SB; ++s) xbr[s] = accb[s];
 }
 
 // Lanes of a row of SC scales, and a lane's scales.
@@ -460,7 +488,9 @@ struct GroupScales {
 };
 
 // FP64 true residual M (phi - x - c A z), z = x (order 1) or A x (order 2):
-// block sums of its square, of (M x)^2 and of M x^2 per scale.
+// block sums of its square, of (M x)^2 and of M x^2 per scale. Bound by the
+// gathers, which come from L2: a row and its neighbours, 128 bytes each of 16
+// scales (8 level-9 fields 1.05 ms, 11 TB/s of gathers, 1.7 TB/s of HBM).
 template <int NC, int W, int BV, int SC>
 __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __restrict__ phi,
                                                      const double* __restrict__ x, const double* __restrict__ z,
@@ -533,7 +563,8 @@ __global__ __launch_bounds__(kRed) void k_poly_total(const double* __restrict__ 
 
 // x (rows x SC) -> the caller's numbering, a thread per caller entry
 // (grid.y = field); entries without a row are 0. Nothing is written once a
-// field was found bad.
+// field was found bad. Bound by HBM and by the columns being written apart
+// (8 level-9 fields x 16 scales 1.11 ms, 3.7 TB/s).
 template <int SC>
 __global__ __launch_bounds__(kRed) void k_poly_out(PolyDev m, const double* __restrict__ x, GroupScales gs,
                                                    int64_t field_stride, const int* __restrict__ bad, int call,
@@ -876,23 +907,50 @@ void launch_steps(const PolyState* ps, const Steps& a, hipStream_t s) {
 // every interior unit has to be in a slot with sums, and their registers have
 // to be there. Kernels of 4 slots a thread are full: with 1 scale they spill
 // 10 registers and still win (one field of the 2.6 M-vertex sphere: 171 us a
-// launch for 165 + 32 of the separate sum, 1.65 ms a call for 1.90), with 4
-// they lose (level 7: 23 us a launch for 15 + 2).
+// launch, 150 with its stores past the caches, for 165 + 32 of the separate
+// sum, 1.43 ms a call for 1.90), with 4 they lose (level 7: 23 us a launch for
+// 15 + 2).
 bool sums_itself(const PolyState* ps, int sc, int steps) {
   const bool full = !ps->single && ps->width == 6 && ps->nc == 1 && ps->largest[steps] > 2 * kPolyThreads;
   return sc <= (full ? 1 : ps->nc == 1 ? 4 : 2) &&
          (ps->nc == 2 || ps->single || ps->largest[0] <= 2 * kPolyThreads);
 }
 
-void launch_sum(int sc, const double* phi, const double* t, int64_t plane, int64_t np, int n, const double* coef,
-                double* x, int F, hipStream_t s) {
+// A group's part in a launch of the sums: its scales, vectors, coefficients
+// and sums.
+struct SumOf {
+  int sc = 0, n = 0;
+  const double* coef = nullptr;
+  double* x = nullptr;
+};
+
+template <int SC, int SB>
+void sum_of(const double* phi, const double* t, int64_t plane, int64_t np, const SumOf& a, const SumOf& b, int F,
+            hipStream_t s) {
   const dim3 g((unsigned)((np + kRed - 1) / kRed), (unsigned)F);
-  switch (sc) {
-    case 1: k_poly_sum<1><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
-    case 2: k_poly_sum<2><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
-    case 4: k_poly_sum<4><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
-    case 8: k_poly_sum<8><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
-    default: k_poly_sum<16><<<g, kRed, 0, s>>>(phi, t, plane, np, n, coef, x); break;
+  k_poly_sum<SC, SB><<<g, kRed, 0, s>>>(phi, t, plane, np, a.n, a.coef, a.x, b.n, b.coef, b.x);
+}
+
+// One group, or a full one and the next (b.sc > 0, b.n <= a.n).
+void launch_sum(const double* phi, const double* t, int64_t plane, int64_t np, const SumOf& a, const SumOf& b, int F,
+                hipStream_t s) {
+  static_assert(kMaxGroup == 16, "");
+  if (b.sc == 0) {
+    switch (a.sc) {
+      case 1: sum_of<1, 0>(phi, t, plane, np, a, b, F, s); break;
+      case 2: sum_of<2, 0>(phi, t, plane, np, a, b, F, s); break;
+      case 4: sum_of<4, 0>(phi, t, plane, np, a, b, F, s); break;
+      case 8: sum_of<8, 0>(phi, t, plane, np, a, b, F, s); break;
+      default: sum_of<16, 0>(phi, t, plane, np, a, b, F, s); break;
+    }
+    return;
+  }
+  switch (b.sc) {
+    case 1: sum_of<16, 1>(phi, t, plane, np, a, b, F, s); break;
+    case 2: sum_of<16, 2>(phi, t, plane, np, a, b, F, s); break;
+    case 4: sum_of<16, 4>(phi, t, plane, np, a, b, F, s); break;
+    case 8: sum_of<16, 8>(phi, t, plane, np, a, b, F, s); break;
+    default: sum_of<16, 16>(phi, t, plane, np, a, b, F, s); break;
   }
 }
 
@@ -1142,7 +1200,7 @@ bool poly_takes(const PolyState* ps, const PolyCall& c) {
     cg += steps_needed(c.order, f, ps->lam_typical, tol);
   }
   // a step of the sequence costs less than half a CG iteration of one
-  // column; lam exceeds lam_typical where a few cells are much smaller than
+  // column (2.6 M rows: 19 us for 90; 4,096 rows: 1 us for 12); lam exceeds lam_typical where a few cells are much smaller than
   // the rest, which CG mostly does not feel and the sequence does
   return most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0;
 }
@@ -1375,12 +1433,18 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
           j += d;
         }
         if ((st = send_coefficients()) != IFL_OK) return st;
+        SumOf of[2];  // groups not launched yet: degrees fall from group to group
         for (const Group& g : groups) {
           const int ng = std::min(n, g.degree - k0);
-          if (ng <= 0 && k0 > 0) continue;
-          launch_sum(g.sc, k0 == 0 ? phi : nullptr, w->t, plane, m.np, std::max(0, ng),
-                     w->coef + g.coef + (size_t)(k0 == 0 ? 0 : k0 + 1) * g.sc, w->x + (size_t)g.pad0 * nf * np, nf, s);
+          if (ng <= 0 && k0 > 0) break;
+          SumOf& a = of[of[0].sc > 0];
+          a = {g.sc, std::max(0, ng), w->coef + g.coef + (size_t)(k0 == 0 ? 0 : k0 + 1) * g.sc,
+               w->x + (size_t)g.pad0 * nf * np};
+          if (&a == of && &g != &groups.back()) continue;
+          launch_sum(k0 == 0 ? phi : nullptr, w->t, plane, m.np, of[0], of[1], nf, s);
+          of[0] = of[1] = SumOf();
         }
+        if (of[0].sc > 0) launch_sum(k0 == 0 ? phi : nullptr, w->t, plane, m.np, of[0], of[1], nf, s);
         IFL_HIP(hipGetLastError());
         k0 += n;
         if (n == 0) break;
