@@ -258,7 +258,7 @@ def vector_leg(ifl):
     1,310,720 triangles; 30% land and dry polar caps, where lon/lat
     components are singular): 8 k^-3 velocity fields (rotational + 10%
     divergent) x 8 scales (wavelengths 32h .. 2h), n = 1, mixed precision,
-    auto-width tiles, one ifl_filter call. Vertex vectors (Sect. 2.1.2) take
+    the library's choice (batch 0), one ifl_filter call. Vertex vectors (Sect. 2.1.2) take
     the cell velocities through ifl_project_cells (timed on its own); cell
     vectors (Eq. 7) filter them in place. Fields are resident in HBM."""
     import torch
@@ -327,9 +327,9 @@ def vector_leg(ifl):
 def c1_leg(ifl):
     """C1, the latency-bound configuration: 64 x 64 periodic split-square
     mesh (4,096 vertices, jitter +-0.2 cell), one k^-3 field, n = 1, 8
-    scales (wavelengths 32 .. 2 cells), the plain FP64 path one column at a
-    time. One SpMV moves ~0.5 MB, so the rate is set by launch and reduction
-    latency, not bandwidth. Field and outputs resident on the device."""
+    scales (wavelengths 32 .. 2 cells): the plain FP64 path one column at a
+    time, mixed tiles, and the library's choice (batch 0). One SpMV moves
+    ~0.5 MB, so the rate is set by launch and reduction latency, not bandwidth. Field and outputs resident on the device."""
     import torch
 
     import workloads as W
@@ -339,7 +339,8 @@ def c1_leg(ifl):
     ks = W.log_scales(1.0, 8)
     res = {"workload": "64x64 periodic split square (4,096 vertices, jitter 0.2), 1 k^-3 field x 8 scales "
                        "(wavelengths 32..2 cells), n=1"}
-    for prec, batch, name in ((ifl.IFL_FP64, 1, "fp64_single_column"), (ifl.IFL_MIXED, 0, "mixed_batched")):
+    for prec, batch, name in ((ifl.IFL_FP64, 1, "fp64_single_column"), (ifl.IFL_MIXED, 2, "mixed_batched"),
+                              (ifl.IFL_FP64, 0, "default")):
         h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1, precision=prec, batch=batch, device=0)
         out = torch.empty((1, ks.size, h.field_length), dtype=torch.float64, device="cuda:0")
         h.filter(phi, ks, out=out)
@@ -363,7 +364,7 @@ def c1_leg(ifl):
 def c2_leg(ifl):
     """C2: level-8 icosphere (655,362 vertices), 10% jitter, 30% land mask
     (40 caps), one k^-3 field, n = 2 (biharmonic), 20 scales (wavelengths
-    32h .. 2h): the batched mixed-precision form (auto tile width) against
+    32h .. 2h): the library's choice (batch 0) and mixed-precision tiles against
     the plain FP64 path one column at a time, same GPU, same call; and the
     same solves as one complex-shifted first-order system each
     (IFL_SOLVER_SHIFTED, FP64 and mixed). The
@@ -381,11 +382,11 @@ def c2_leg(ifl):
     res = {"workload": f"icosphere-L8 {s.n_vertices} vertices, 30% land mask ({h.num_dofs} dofs), n=2, "
                        f"1 k^-3 field x 20 scales (wavelengths 32h..2h)"}
     out = torch.empty((1, ks.size, h.field_length), dtype=torch.float64, device="cuda:0")
-    for prec, batch, solver, name in ((ifl.IFL_MIXED, 0, 0, "mixed_batched"), (ifl.IFL_FP64, 1, 0, "fp64_single_column"),
+    for prec, batch, solver, name in ((ifl.IFL_FP64, 0, 0, "default"), (ifl.IFL_MIXED, 4, 0, "mixed_batched"), (ifl.IFL_FP64, 1, 0, "fp64_single_column"),
                                       (ifl.IFL_FP64, 1, 1, "shifted_fp64_single_column"),
                                       (ifl.IFL_MIXED, 1, 1, "shifted_mixed_single_column"),
-                                      (ifl.IFL_FP64, 0, 1, "shifted_fp64_complex_tiles"),
-                                      (ifl.IFL_MIXED, 0, 1, "shifted_mixed_complex_tiles")):
+                                      (ifl.IFL_FP64, 16, 1, "shifted_fp64_complex_tiles"),
+                                      (ifl.IFL_MIXED, 16, 1, "shifted_mixed_complex_tiles")):
         h.set_options(precision=prec, batch=batch, solver=solver)
         h.filter(phi, ks, out=out)  # untimed: the same call, so the tile of its width exists
         torch.cuda.synchronize()
@@ -397,6 +398,8 @@ def c2_leg(ifl):
                      "mean_cg_iterations": round(sum(x.iterations for x in st) / len(st), 1),
                      "max_cg_iterations": int(max(x.iterations for x in st)),
                      "fp64_replacements": int(sum(x.refinements for x in st))}
+    res["speedup_default_vs_plain_fp64"] = round(res["default"]["solves_per_s"] /
+                                                 res["fp64_single_column"]["solves_per_s"], 3)
     res["speedup_mixed_batched_vs_plain_fp64"] = round(res["mixed_batched"]["solves_per_s"] /
                                                        res["fp64_single_column"]["solves_per_s"], 3)
     res["speedup_shifted_fp64_vs_plain_fp64"] = round(res["shifted_fp64_single_column"]["solves_per_s"] /
@@ -405,7 +408,7 @@ def c2_leg(ifl):
                                                             res["fp64_single_column"]["solves_per_s"], 3)
     res["shifted"] = ("IFL_SOLVER_SHIFTED: S^-1 = Re (M + i c^(1/2) K)^-1 for n = 2, one complex-shifted "
                       "first-order system per solve, Jacobi-COCG, one column at a time (batch 1) or in complex "
-                      "tiles (auto width)")
+                      "tiles (16 real columns)")
     h.close()
     return res
 
@@ -565,8 +568,8 @@ def serve_leg(args, ifl):
 
     res = {"workload": f"icosphere levels {args.serve_levels} (30% land mask) x n in {{1,2}}, "
                        f"{args.serve_slots} slots per mesh, mixed precision, 1-32 log-uniform scales per request; "
-                       + ("n = 2 requests by the shifted first-order solves in complex tiles"
-                          if args.serve_n2_solver == "shifted" else "n = 2 requests by Jacobi-PCG on K_2 in tiles"),
+                       + ("n = 2 handles with the shifted solver"
+                          if args.serve_n2_solver == "shifted" else "n = 2 handles with the solver on K_2"),
            "prepare_s": round(prep_s, 1), "budget_bytes": int(args.serve_budget_gib * (1 << 30))}
     res["stream"] = stream(args.serve_rate, draw(args.serve_warmup + args.serve_requests), args.serve_warmup, True,
                            drain_s=args.serve_drain_s)
@@ -745,8 +748,7 @@ def main():
     ap.add_argument("--serve-sweep-requests", type=int, default=60)
     ap.add_argument("--serve-sweep-drain-s", type=float, default=8.0)
     ap.add_argument("--serve-n2-solver", choices=["shifted", "kn"], default="shifted",
-                    help="how the served n = 2 requests are solved: the shifted first-order solves (one column at "
-                         "a time) or Jacobi-PCG on K_2 in tiles")
+                    help="solver option of the served n = 2 handles")
     ap.add_argument("--serve-drain-s", type=float, default=20.0,
                     help="the stated stream's window: requests not finished this long after the last arrival "
                          "are cancelled and counted as such (their latency exceeds the window)")
@@ -860,7 +862,7 @@ def main():
             "dofs": h.num_dofs,
             "solves_per_step": n_solves,
             "precision": args.precision,
-            "batch": args.batch if args.batch else (f"autotuned ({tune['batch']})" if tune else "auto (32)"),
+            "batch": args.batch or "the library's choice",
             "autotune": tune,
             "graphs": not args.no_graphs,
             "rtol": 1e-12,

@@ -383,8 +383,8 @@ ifl_status ifl_stream_probe(int32_t device, int64_t bytes, int32_t reps, double*
  * columns for tile sizes 16, 32 and 64 and several grid sizes of the
  * gathering and streaming kernels on this handle's matrix in the handle's
  * current precision, and keeps the fastest per column-iteration: the grid
- * sizes per tile size, and the tile size used by ifl_filter when
- * options.batch = 0. Results computed afterwards may differ from untuned
+ * sizes per tile size, and the tile size of ifl_filter's calls that run in
+ * tiles with options.batch = 0. Results computed afterwards may differ from untuned
  * ones in the last bits (another reduction order); runs with the same
  * tuning are bitwise reproducible. Takes ~0.1-1 s; needs device memory for
  * one tile of 64 columns. out may be NULL.

@@ -70,6 +70,22 @@ def test_planar_sizes(ifl, nx, ny, order, scales):
     h.close()
 
 
+@pytest.mark.parametrize("scales", [18, 20, 24, 32, 37])
+def test_scale_groups(ifl, scales):
+    """More than 16 scales: a full group and the next, of every width, are
+    summed together; a third one by itself."""
+    m = W.split_square(65, jitter=0.2, ny=64)
+    field = _noise(65 * 64, 21)
+    ks = W.log_scales(1.0, scales, lam_max_cells=16.0)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1)
+    out, st = h.filter(field, ks)
+    assert _sequence_ran(st, 1, scales)
+    ref = O.filter_scalar(O.scalar_operator(m, 1), field, ks)
+    for j in range(scales):
+        assert relative_l2(out[0, j], ref[j]) <= TOL, j
+    h.close()
+
+
 @pytest.mark.parametrize("n", [60, 500, 2500])
 def test_wide_and_uneven_rows(ifl, n):
     """Random Delaunay meshes: 8 to 12 neighbours a row; the widest, and
