@@ -853,7 +853,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64" if precision == ifl.IFL_MIXED else "f64",
+        "dtype": "f32+f64" if precision == ifl.IFL_MIXED and args.batch else "f64",  # batch 0: FP64 in both
         "data": "synthetic",
         "config": {
             "workload": f"icosphere-L{args.level} {mesh.n_vertices} vertices, {int(args.mask * 100)}% land mask, "
