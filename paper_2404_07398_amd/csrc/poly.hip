@@ -427,13 +427,22 @@ struct alignas(16) Lane<2> {
   double v[2];
 };
 
+// High words of a lane's doubles: magnitudes, of which 20 bits are plenty.
+template <int V>
+struct alignas(4 * V) LaneHigh {
+  int v[V];
+};
+
 // The unit's product with A: y[c] = sum_j A_uj x_j, component c, for the
-// lane's scales. A unit's rows share their gathers.
-template <int NC, int W, int BV, int SC>
+// lane's scales, and the sizes of its terms, mag[c] = sum_j |A_uj| s_j (MAG 1:
+// s = |x|, MAG 2: what sizes holds). A unit's rows share their gathers.
+template <int NC, int W, int BV, int SC, int MAG = 0>
 __device__ __forceinline__ void unit_product(const PolyDev& m, const double* xf, int64_t u, int q,
-                                             Lane<lane_scales(SC)> (&y)[NC]) {
+                                             Lane<lane_scales(SC)> (&y)[NC],
+                                             Lane<lane_scales(SC)> (*mag)[NC] = nullptr, const int* sizes = nullptr) {
   constexpr int V = lane_scales(SC);
   const Lane<V>* xt = reinterpret_cast<const Lane<V>*>(xf);
+  const LaneHigh<V>* st = reinterpret_cast<const LaneHigh<V>*>(sizes);
   constexpr int LPR = SC / V, VR = poly_val_record(W, BV), CR = poly_col_record(W);
   int32_t col[CR];
 #pragma unroll
@@ -446,14 +455,22 @@ __device__ __forceinline__ void unit_product(const PolyDev& m, const double* xf,
   }
   const double* a = m.val + u * VR;
   Lane<V> t[W + 1][NC];
+  LaneHigh<V> h[MAG == 2 ? W + 1 : 1][NC];
 #pragma unroll
   for (int k = 0; k <= W; ++k)
 #pragma unroll
-    for (int d = 0; d < NC; ++d) t[k][d] = xt[((k == 0 ? u : (int64_t)col[k == 0 ? 0 : k - 1]) * NC + d) * LPR + q];
+    for (int d = 0; d < NC; ++d) {
+      const int64_t at = ((k == 0 ? u : (int64_t)col[k == 0 ? 0 : k - 1]) * NC + d) * LPR + q;
+      t[k][d] = xt[at];
+      if (MAG == 2) h[MAG == 2 ? k : 0][d] = st[at];
+    }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
 #pragma unroll
-    for (int e = 0; e < V; ++e) y[c].v[e] = 0.0;
+    for (int e = 0; e < V; ++e) {
+      y[c].v[e] = 0.0;
+      if (MAG) (*mag)[c].v[e] = 0.0;
+    }
 #pragma unroll
     for (int k = 0; k <= W; ++k)
 #pragma unroll
@@ -462,24 +479,37 @@ __device__ __forceinline__ void unit_product(const PolyDev& m, const double* xf,
         if constexpr (BV == 1) v = k == 0 ? minus_sum<W>(a) : a[k == 0 ? 0 : k - 1];
         else v = coupling<NC, BV>(a + k * BV, c, d);
 #pragma unroll
-        for (int e = 0; e < V; ++e) y[c].v[e] += v * t[k][d].v[e];
+        for (int e = 0; e < V; ++e) {
+          y[c].v[e] += v * t[k][d].v[e];
+          if (MAG)
+            (*mag)[c].v[e] +=
+                fabs(v) * (MAG == 2 ? __hiloint2double(h[MAG == 2 ? k : 0][d].v[e], 0) : fabs(t[k][d].v[e]));
+        }
       }
   }
 }
 
-// y = A x (grid.y = field), a lane's scales of one unit per thread.
+// y = A x and the high words of |A| |x| (grid.y = field), a lane's scales of
+// one unit per thread.
 template <int NC, int W, int BV, int SC>
-__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, const double* __restrict__ x, double* __restrict__ y) {
+__global__ __launch_bounds__(kRed) void k_poly_apply(PolyDev m, const double* __restrict__ x, double* __restrict__ y,
+                                                     int* __restrict__ sizes) {
   constexpr int V = lane_scales(SC), LPR = SC / V;
   const int64_t g = (int64_t)blockIdx.x * kRed + threadIdx.x;
   const int64_t u = g / LPR;
   if (u >= m.units) return;
   const int64_t base = (int64_t)blockIdx.y * m.np * SC;
   const int q = (int)(g % LPR);
-  Lane<V> v[NC];
-  unit_product<NC, W, BV, SC>(m, x + base, u, q, v);
+  Lane<V> v[NC], mag[NC];
+  unit_product<NC, W, BV, SC, 1>(m, x + base, u, q, v, &mag);
 #pragma unroll
-  for (int c = 0; c < NC; ++c) reinterpret_cast<Lane<V>*>(y + base)[(u * NC + c) * LPR + q] = v[c];
+  for (int c = 0; c < NC; ++c) {
+    reinterpret_cast<Lane<V>*>(y + base)[(u * NC + c) * LPR + q] = v[c];
+    LaneHigh<V> h;
+#pragma unroll
+    for (int e = 0; e < V; ++e) h.v[e] = __double2hiint(mag[c].v[e]);
+    reinterpret_cast<LaneHigh<V>*>(sizes + base)[(u * NC + c) * LPR + q] = h;
+  }
 }
 
 struct GroupScales {
@@ -488,13 +518,17 @@ struct GroupScales {
 };
 
 // FP64 true residual M (phi - x - c A z), z = x (order 1) or A x (order 2):
-// block sums of its square, of (M x)^2 and of M x^2 per scale. Bound by the
-// gathers, which come from L2: a row and its neighbours, 128 bytes each of 16
-// scales (8 level-9 fields 1.05 ms, 11 TB/s of gathers, 1.7 TB/s of HBM).
-template <int NC, int W, int BV, int SC>
+// block sums of its square, of the squared sizes of its terms row by row, M
+// (|phi| + |x| + c |A| |z|) (the residual's rounding error is a small multiple
+// of u times their norm; order 2, TWICE: |A| |x| for |z|, from sizes), and of
+// M x^2 per scale. Bound by the gathers, which come from L2: a row and its
+// neighbours, 128 bytes each of 16 scales (8 level-9 fields 1.05 ms, 11 TB/s
+// of gathers, 1.7 TB/s of HBM).
+template <int NC, int W, int BV, int SC, bool TWICE>
 __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __restrict__ phi,
                                                      const double* __restrict__ x, const double* __restrict__ z,
-                                                     GroupScales gs, double* __restrict__ part) {
+                                                     const int* __restrict__ sizes, GroupScales gs,
+                                                     double* __restrict__ part) {
   constexpr int V = lane_scales(SC), LPR = SC / V;
   __shared__ double lds[kRed / 64][LPR][3 * V];
   const int64_t base = (int64_t)blockIdx.y * m.np * SC;
@@ -505,8 +539,8 @@ __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __
   for (int e = 0; e < 3 * V; ++e) sum[e] = 0.0;
   constexpr int UPB = kRed / LPR;
   for (int64_t u = (int64_t)blockIdx.x * UPB + threadIdx.x / LPR; u < m.units; u += (int64_t)gridDim.x * UPB) {
-    Lane<V> y[NC];
-    unit_product<NC, W, BV, SC>(m, z + base, u, q, y);
+    Lane<V> y[NC], mag[NC];
+    unit_product<NC, W, BV, SC, TWICE ? 2 : 1>(m, z + base, u, q, y, &mag, sizes + base);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int64_t r = u * NC + c;
@@ -515,10 +549,10 @@ __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __
 #pragma unroll
       for (int e = 0; e < V; ++e) {
         const double res = mr * (ph - xr.v[e] - gs.c[q * V + e] * y[c].v[e]);
-        const double mx = mr * xr.v[e];
+        const double size = mr * (fabs(ph) + fabs(xr.v[e]) + gs.c[q * V + e] * mag[c].v[e]);
         sum[e] += res * res;
-        sum[V + e] += mx * mx;
-        sum[2 * V + e] += mx * xr.v[e];
+        sum[V + e] += size * size;
+        sum[2 * V + e] += mr * xr.v[e] * xr.v[e];
       }
     }
   }
@@ -955,27 +989,27 @@ void launch_sum(const double* phi, const double* t, int64_t plane, int64_t np, c
 }
 
 template <int NC, int W, int BV, int SC>
-void check_of(const PolyState* ps, int order, const double* phi, const double* x, double* z, const GroupScales& gs,
-              double* part, int G, int F, hipStream_t s) {
+void check_of(const PolyState* ps, int order, const double* phi, const double* x, double* z, int* sizes,
+              const GroupScales& gs, double* part, int G, int F, hipStream_t s) {
   constexpr int LPR = SC / lane_scales(SC);
-  const double* src = x;
   if (order == 2) {
     const dim3 g((unsigned)((ps->m.units * LPR + kRed - 1) / kRed), (unsigned)F);
-    k_poly_apply<NC, W, BV, SC><<<g, kRed, 0, s>>>(ps->m, x, z);
-    src = z;
+    k_poly_apply<NC, W, BV, SC><<<g, kRed, 0, s>>>(ps->m, x, z, sizes);
+    k_poly_check<NC, W, BV, SC, true><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, z, sizes, gs, part);
+  } else {
+    k_poly_check<NC, W, BV, SC, false><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, x, nullptr, gs, part);
   }
-  k_poly_check<NC, W, BV, SC><<<dim3(G, F), kRed, 0, s>>>(ps->m, phi, x, src, gs, part);
 }
 
 template <int NC, int W, int BV>
-void check_scales(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z,
+void check_scales(const PolyState* ps, int sc, int order, const double* phi, const double* x, double* z, int* sizes,
                   const GroupScales& gs, double* part, int G, int F, hipStream_t s) {
   switch (sc) {
-    case 1: check_of<NC, W, BV, 1>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 2: check_of<NC, W, BV, 2>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 4: check_of<NC, W, BV, 4>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    case 8: check_of<NC, W, BV, 8>(ps, order, phi, x, z, gs, part, G, F, s); break;
-    default: check_of<NC, W, BV, 16>(ps, order, phi, x, z, gs, part, G, F, s); break;
+    case 1: check_of<NC, W, BV, 1>(ps, order, phi, x, z, sizes, gs, part, G, F, s); break;
+    case 2: check_of<NC, W, BV, 2>(ps, order, phi, x, z, sizes, gs, part, G, F, s); break;
+    case 4: check_of<NC, W, BV, 4>(ps, order, phi, x, z, sizes, gs, part, G, F, s); break;
+    case 8: check_of<NC, W, BV, 8>(ps, order, phi, x, z, sizes, gs, part, G, F, s); break;
+    default: check_of<NC, W, BV, 16>(ps, order, phi, x, z, sizes, gs, part, G, F, s); break;
   }
 }
 
@@ -1231,7 +1265,8 @@ constexpr size_t kPolyBudget = (size_t)12 << 30;
 bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree, Plan* out) {
   const PolyDev& m = ps->m;
   const size_t have = (limit ? limit : kPolyBudget) / sizeof(double);
-  const int least = std::max(4, std::min(degree, 16));  // 4: the two pairs of a sequence summed as it goes
+  // 4: the two pairs of a sequence summed as it goes; 8: the sizes of a check of order 2
+  const int least = std::max(c.order == 2 ? kMaxGroup / 2 : 4, std::min(degree, 16));
   const int F = c.n_fields;
   for (int sc = c.n_scales;; sc = (sc + 1) / 2) {
     const size_t group = (size_t)padded_scales(std::min(sc, kMaxGroup));
@@ -1254,7 +1289,7 @@ bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree,
       const size_t share = avail / (size_t)std::min(F, 8);
       const size_t planes = share > field ? (share - field) / m.np : 0;
       out->planes = (int)std::max<size_t>(
-          least, std::min<size_t>({left, (size_t)std::max(4, degree), std::max<size_t>(planes, 64)}));
+          least, std::min<size_t>({left, (size_t)std::max(least, degree), std::max<size_t>(planes, 64)}));
       out->fields = (int)std::max<size_t>(
           1, std::min<size_t>((size_t)F, avail / (field + (size_t)out->planes * m.np)));
       // where the patches of all fields run one after another on a CU, more
@@ -1451,7 +1486,9 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       }
       for (const Group& g : groups) {
         const double* x = w->x + (size_t)g.pad0 * nf * np;
-        IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, w->z, g.gs, w->part, G, nf, s));
+        // (the sequence is done with: its space holds the sizes, half of g.sc vectors)
+        IFL_POLY_FORMS(check_scales, (ps, g.sc, c.order, phi, x, w->z, reinterpret_cast<int*>(w->t), g.gs, w->part, G,
+                                      nf, s));
         // with the call's last group go the norms of all its fields
         const bool last = f0 + nf == F && &g == &seqs.back().back();
         const int n = nf * g.sc * 3;
@@ -1497,9 +1534,8 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
         const double bb = w->host[t.f0 + f];
         const double* q = w->host + t.at + ((size_t)f * t.g.sc + i) * 3;
         const int64_t col = (int64_t)(t.f0 + f) * S + t.g.gs.column[i];
-        // attainable accuracy: what FP64 can tell of M phi - S x
-        const double floor = 8.0 * 1.1102230246251565e-16 *
-                             (std::sqrt(bb) + std::sqrt(q[1]) * (1.0 + t.g.gs.c[i] * std::pow(ps->lam, c.order)));
+        // attainable accuracy, as CG has it: what FP64 can tell of M phi - S x
+        const double floor = 8.0 * 1.1102230246251565e-16 * std::sqrt(q[1]);
         const double res = std::sqrt(q[0]);
         if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
         if (c.stats) {
