@@ -405,4 +405,11 @@ void poly_coefficients(int order, double c, double lam, int m, double* out, int 
   }
 }
 
+bool poly_accepts(double res2, double size2, double bb, double rtol) {
+  if (!std::isfinite(bb)) return !std::isnan(res2);
+  if (!std::isfinite(res2)) return false;
+  const double floor = std::isfinite(size2) ? 8.0 * 1.1102230246251565e-16 * std::sqrt(size2) : 0.0;
+  return std::sqrt(res2) <= std::max(rtol * std::sqrt(bb), floor);
+}
+
 }  // namespace ifl

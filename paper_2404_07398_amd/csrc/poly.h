@@ -84,6 +84,14 @@ int poly_degree(int order, double c, double lam, double tol, int max_degree);
 // c_0 .. c_m of degree m to out[k * stride].
 void poly_coefficients(int order, double c, double lam, int m, double* out, int stride);
 
+// Whether a column with ||M phi - S x||^2 = res2, ||M phi||^2 = bb and terms of
+// the residual of norm^2 size2 counts as converged: within rtol, or within what
+// FP64 can tell, as CG has it. An overflowed sum proves nothing: a residual
+// must be finite, and an infinite size2 raises no bar. Only where bb itself
+// overflows (fields above 1e150, which CG returns unfiltered) is a column
+// passed on any residual but NaN.
+bool poly_accepts(double res2, double size2, double bb, double rtol);
+
 // --------------------------------------------------------------- device side
 struct PolyState;  // defined in poly.hip
 struct PolyWork;

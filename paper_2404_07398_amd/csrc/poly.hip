@@ -1534,10 +1534,8 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
         const double bb = w->host[t.f0 + f];
         const double* q = w->host + t.at + ((size_t)f * t.g.sc + i) * 3;
         const int64_t col = (int64_t)(t.f0 + f) * S + t.g.gs.column[i];
-        // attainable accuracy, as CG has it: what FP64 can tell of M phi - S x
-        const double floor = 8.0 * 1.1102230246251565e-16 * std::sqrt(q[1]);
         const double res = std::sqrt(q[0]);
-        if (!(res <= std::max(c.rtol * std::sqrt(bb), floor))) failed->push_back(col);
+        if (!poly_accepts(q[0], q[1], bb, c.rtol)) failed->push_back(col);
         if (c.stats) {
           ifl_solve_stats& so = c.stats[col];
           so.iterations = bb > 0.0 ? deg[t.g.gs.column[i]] : 0;
