@@ -1,9 +1,14 @@
-"""Host side of the polynomial engine (CPU only), through the library's C++
-functions: what they decide where no call reaches on its own."""
+"""Host side of the polynomial engine and of preparing a handle (CPU only):
+what the library's C++ functions decide where no call reaches on its own, and
+the prepare phase's limits."""
 import ctypes
 import os
+import time
 
+import numpy as np
 import pytest
+
+import workloads as W
 
 ifl = pytest.importorskip("paper_2404_07398_amd")
 
@@ -29,3 +34,24 @@ def _function(name, restype, *argtypes):
 def test_columns_counted_as_converged(res2, size2, bb, ok):
     accepts = _function("_ZN3ifl12poly_acceptsEdddd", ctypes.c_bool, *[ctypes.c_double] * 4)
     assert accepts(res2, size2, bb, 1e-12) is ok
+
+
+def test_prepare_of_a_vertex_with_very_many_neighbours():
+    """A fan of 100,000 triangles in a shuffled numbering: its hub's row is
+    sorted in n log n (a quadratic sort takes over 15 s, this 0.3)."""
+    if not os.path.exists(ifl.LIB_PATH):
+        pytest.skip("libifl.so not built")
+    n = 100_000
+    rim = np.random.default_rng(1).permutation(n) + 1
+    a = 2.0 * np.pi * np.arange(n) / n
+    xy = np.zeros((n + 1, 2))
+    xy[rim] = 1000.0 * np.stack([np.cos(a), np.sin(a)], axis=1)
+    tris = np.stack([np.zeros(n, np.int64), rim, np.roll(rim, -1)], axis=1).astype(np.int32)
+    m = W.Mesh(coords=xy, tris=tris, geometry=W.GEOM_PLANAR, h=1.0)
+    t0 = time.perf_counter()
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1, device=-1)
+    assert time.perf_counter() - t0 < 6.0
+    rp, col, val, mass, ent = h.export_operator()
+    rows = np.diff(rp)
+    assert rows.max() == n + 1 and np.all(np.diff(col[rp[rows.argmax()]:rp[rows.argmax() + 1]]) > 0)
+    h.close()
