@@ -137,38 +137,52 @@ void spgemm_scaled(int64_t n, const std::vector<int64_t>& ap, const std::vector<
                    const std::vector<int32_t>& bc, const std::vector<double>& bv,
                    const std::vector<double>& m, std::vector<int64_t>& cp, std::vector<int32_t>& cc,
                    std::vector<double>& cv) {
-  // pieces of rows, each with its own accumulator
+  // pieces of rows, each with an accumulator of its own: a table of the row's
+  // columns, so that memory does not grow with the threads times n
   const int64_t parts = pieces_of(n);
   std::vector<std::vector<int32_t>> pc((size_t)parts);
   std::vector<std::vector<double>> pv((size_t)parts);
   cp.assign(n + 1, 0);
   parallel_for(parts, [&](int64_t q) {
-    std::vector<double> acc(n, 0.0);
-    std::vector<int64_t> mark(n, -1);
-    std::vector<int32_t> touched;
+    struct Slot {
+      int64_t row = -1;
+      int32_t col = 0;
+      double sum = 0.0;
+    };
+    std::vector<Slot> table(256);
+    std::vector<std::pair<int32_t, size_t>> touched;  // column, its slot
     std::vector<int32_t>& cc = pc[(size_t)q];
     std::vector<double>& cv = pv[(size_t)q];
     for (int64_t i = n * q / parts; i < n * (q + 1) / parts; ++i) {
       touched.clear();
+      size_t products = 0;
+      for (int64_t a = ap[i]; a < ap[i + 1]; ++a) products += (size_t)(bp[ac[a] + 1] - bp[ac[a]]);
+      if (table.size() < 2 * products) {
+        size_t want = table.size();
+        while (want < 2 * products) want *= 2;
+        table.assign(want, Slot());
+      }
+      const size_t last = table.size() - 1;
       for (int64_t a = ap[i]; a < ap[i + 1]; ++a) {
         const int32_t k = ac[a];
         const double aik = av[a];
         for (int64_t b = bp[k]; b < bp[k + 1]; ++b) {
           const int32_t j = bc[b];
           const double t = (aik * bv[b]) / m[k];
-          if (mark[j] != i) {
-            mark[j] = i;
-            acc[j] = t;
-            touched.push_back(j);
+          size_t at = ((uint32_t)j * 2654435761u) & last;
+          while (table[at].row == i && table[at].col != j) at = (at + 1) & last;
+          if (table[at].row != i) {
+            table[at] = {i, j, t};
+            touched.push_back({j, at});
           } else {
-            acc[j] += t;
+            table[at].sum += t;
           }
         }
       }
       std::sort(touched.begin(), touched.end());
-      for (int32_t j : touched) {
+      for (const auto& [j, at] : touched) {
         cc.push_back(j);
-        cv.push_back(acc[j]);
+        cv.push_back(table[at].sum);
       }
       cp[i + 1] = (int64_t)touched.size();
     }

@@ -7,7 +7,9 @@ import time
 
 import numpy as np
 import pytest
+import scipy.sparse as sp
 
+import oracle as O
 import workloads as W
 
 ifl = pytest.importorskip("paper_2404_07398_amd")
@@ -55,3 +57,30 @@ def test_prepare_of_a_vertex_with_very_many_neighbours():
     rows = np.diff(rp)
     assert rows.max() == n + 1 and np.all(np.diff(col[rp[rows.argmax()]:rp[rows.argmax() + 1]]) > 0)
     h.close()
+
+
+@pytest.mark.parametrize("order", [2, 3])
+def test_operator_products_with_rows_of_very_different_lengths(order):
+    """K M^-1 K .. of a fan whose hub has 700 neighbours: the product's
+    accumulator grows to its widest row."""
+    if not os.path.exists(ifl.LIB_PATH):
+        pytest.skip("libifl.so not built")
+    n = 700
+    rng = np.random.default_rng(2)
+    rim = rng.permutation(n) + 1
+    a = 2.0 * np.pi * np.arange(n) / n
+    xy = np.zeros((n + 1, 2))
+    xy[rim] = (10.0 + rng.uniform(-0.5, 0.5, n))[:, None] * np.stack([np.cos(a), np.sin(a)], axis=1)
+    tris = np.stack([np.zeros(n, np.int64), rim, np.roll(rim, -1)], axis=1).astype(np.int32)
+    m = W.Mesh(coords=xy, tris=tris, geometry=W.GEOM_PLANAR, h=1.0)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, order, device=-1)
+    rp, col, val, mass, ent = h.export_operator()
+    h.close()
+    ref = O.scalar_operator(m, order)
+    mine = sp.csr_matrix((val, col, rp), shape=(n + 1, n + 1)).toarray()
+    want = ref.Kn.toarray()[np.ix_(ref.dof_of[ent], ref.dof_of[ent])]
+    # each entry sums at most n products, at 2 (order - 1) roundings each way
+    size = abs(want).max()
+    assert np.abs(mine - want).max() <= 4 * order * n * 2.0 ** -53 * size
+    for i in range(n + 1):
+        assert np.all(np.diff(col[rp[i]:rp[i + 1]]) > 0)
