@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <cstdint>
 #include <exception>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -29,7 +28,7 @@ void parallel_for(int64_t count, const F& f) {
   for (int t = 1; t < nt; ++t) {
     try {
       ts.emplace_back(share, t);
-    } catch (const std::system_error&) {
+    } catch (...) {
       share(t);
     }
   }

@@ -3,6 +3,7 @@ what the library's C++ functions decide where no call reaches on its own, and
 the prepare phase's limits."""
 import ctypes
 import os
+import subprocess
 import time
 
 import numpy as np
@@ -84,3 +85,45 @@ def test_operator_products_with_rows_of_very_different_lengths(order):
     assert np.abs(mine - want).max() <= 4 * order * n * 2.0 ** -53 * size
     for i in range(n + 1):
         assert np.all(np.diff(col[rp[i]:rp[i + 1]]) > 0)
+
+
+def test_threads_that_cannot_be_started(tmp_path):
+    """parallel_for with every allocation in turn refused: the work is done or
+    std::bad_alloc arrives; the process does not end."""
+    src = tmp_path / "t.cpp"
+    src.write_text(r"""
+#include "parallel.h"
+#include <cstdio>
+#include <cstdlib>
+#include <new>
+static thread_local long left = -1;
+void* operator new(std::size_t n) {
+  if (left >= 0 && left-- == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(n)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+int main() {
+  int done = 0, thrown = 0;
+  for (long refuse = 0; refuse < 40; ++refuse) {
+    int hit[64] = {};
+    try {
+      left = refuse;
+      ifl::parallel_for(64, [&](int64_t i) { hit[i] += 1; });
+      left = -1;
+      for (int h : hit) if (h != 1) return 2;
+      ++done;
+    } catch (const std::bad_alloc&) {
+      left = -1;
+      ++thrown;
+    }
+  }
+  std::printf("%d %d\n", done, thrown);
+  return done > 0 && thrown > 0 ? 0 : 3;
+}
+""")
+    exe = tmp_path / "t"
+    inc = os.path.join(os.path.dirname(ifl.LIB_PATH), "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(src), "-o", str(exe), "-pthread"], check=True)
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
