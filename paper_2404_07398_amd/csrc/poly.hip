@@ -1092,15 +1092,9 @@ ifl_status estimate_spectrum(PolyState* ps, hipStream_t s) {
 
 }  // namespace
 
-ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out) {
-  *out = nullptr;
-  if (op.order < 1 || op.order > 2 || op.field_len > INT32_MAX) return IFL_OK;
+static ifl_status create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out) {
   PatchPack pp;
-  try {
-    if (!build_patches(op, local_order, &pp)) return IFL_OK;
-  } catch (const std::bad_alloc&) {
-    return fail(IFL_ENOMEM, "out of host memory for the patches");
-  }
+  if (!build_patches(op, local_order, &pp)) return IFL_OK;
   PolyState* ps = new PolyState();
   *out = ps;
   ps->nc = pp.nc;
@@ -1152,6 +1146,16 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   }
   if ((st = poly_work_create(0, &ps->work)) != IFL_OK) return st;
   return estimate_spectrum(ps, s);
+}
+
+ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, PolyState** out) {
+  *out = nullptr;
+  if (op.order < 1 || op.order > 2 || op.field_len > INT32_MAX) return IFL_OK;
+  try {
+    return create(op, local_order, s, out);
+  } catch (const std::bad_alloc&) {
+    return fail(IFL_ENOMEM, "out of host memory for the patches");
+  }
 }
 
 void poly_destroy(PolyState* ps) {
@@ -1335,9 +1339,8 @@ bool poly_work_takes(const PolyState* ps, size_t limit, int order) {
   return make_plan(ps, limit, c, 64, &plan) && plan.scales == 4;
 }
 
-ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vector<int64_t>* failed) {
+static ifl_status run_call(PolyState* ps, PolyWork* w, const PolyCall& c, std::vector<int64_t>* failed) {
   const auto t0 = std::chrono::steady_clock::now();
-  if (!w) w = ps->work;
   const PolyDev& m = ps->m;
   hipStream_t s = c.stream;
   failed->clear();
@@ -1437,8 +1440,11 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
     IFL_HIP(hipMemcpyAsync(w->coef, w->host_coef, ncoef * sizeof(double), hipMemcpyHostToDevice, s));
     return IFL_OK;
   };
-  std::vector<Totals> totals;
-  size_t sum_at = (size_t)F;
+  std::vector<Totals> totals;  // (no allocation once outputs may have been written)
+  size_t sum_at = (size_t)F, n_groups = 0;
+  for (const auto& groups : seqs) n_groups += groups.size();
+  totals.reserve(n_groups * (size_t)((F + FG - 1) / FG));
+  failed->reserve((size_t)S * F);
   for (int f0 = 0; f0 < F; f0 += FG) {
     const int nf = std::min(FG, F - f0);
     const int64_t plane = (int64_t)nf * m.np;
@@ -1503,13 +1509,14 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
         }
         // to the host through the staging: columns in the caller's order, so
         // that neighbouring scales leave in one copy
-        std::vector<int> cols(g.gs.column, g.gs.column + g.n);
-        std::sort(cols.begin(), cols.end());
+        int cols[kMaxGroup];
+        std::copy(g.gs.column, g.gs.column + g.n, cols);
+        std::sort(cols, cols + g.n);
         for (int q = 0; q < g.n; q += plan.staged) {
           const int qn = std::min(plan.staged, g.n - q);
           GroupScales some = g.gs;
           for (int i = 0; i < g.n; ++i) {
-            const int at = (int)(std::lower_bound(cols.begin(), cols.end(), g.gs.column[i]) - cols.begin()) - q;
+            const int at = (int)(std::lower_bound(cols, cols + g.n, g.gs.column[i]) - cols) - q;
             some.column[i] = at >= 0 && at < qn ? at : -1;
           }
           launch_out(ps, w->bad, call, g.sc, x, some, (int64_t)qn * m.field_len, w->stage, nf, s);
@@ -1550,6 +1557,15 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
       }
   std::sort(failed->begin(), failed->end());
   return IFL_OK;
+}
+
+ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vector<int64_t>* failed) {
+  try {
+    return run_call(ps, w ? w : ps->work, c, failed);
+  } catch (const std::bad_alloc&) {
+    (void)hipStreamSynchronize(c.stream);  // of what was launched before
+    return fail(IFL_ENOMEM, "out of host memory for a call's scales");
+  }
 }
 
 }  // namespace ifl
