@@ -245,6 +245,7 @@ struct DeviceState {
   double* proj_w = nullptr;
   double* proj_in = nullptr;      // device copy of a host cell field
   PolyState* poly = nullptr;      // polynomial engine; NULL where it does not take the operator
+  bool poly_made = false;         // poly has been looked for (see ensure_poly)
 };
 
 // Partial sums of a one-column launch (units of G): two parities of five
@@ -1261,6 +1262,27 @@ static int head_class(const SellPack& sp) {
   return w90 <= 6 ? 6 : (w90 <= 12 ? 12 : 20);
 }
 
+// Whether calls with these options go to the polynomial engine: the solver
+// left to the library, and no launch events of CG asked for.
+static bool wants_poly(const ifl_options& o) { return o.batch == 0 && !o.profile; }
+
+// The handle's polynomial engine, made with the handle or, where its options
+// did not want it, by the first call that does: patches and the spectrum's
+// estimate are 0.35 to 4 ms on small meshes, which a handle of a fixed width
+// never uses. Without the memory for it the handle keeps to CG.
+static ifl_status ensure_poly(Handle* h) {
+  DeviceState* d = h->dev;
+  if (d->poly_made) return IFL_OK;
+  d->poly_made = true;
+  const ifl_status st = poly_create(h->op, h->opt.reorder != 0, d->own_stream, &d->poly);
+  if (st != IFL_OK) {
+    poly_destroy(d->poly);
+    d->poly = nullptr;
+    if (st != IFL_ENOMEM) return st;
+  }
+  return IFL_OK;
+}
+
 ifl_status device_create(Handle* h) {
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) {
@@ -1389,13 +1411,7 @@ ifl_status device_create(Handle* h) {
   // hipMemset of device memory may return before it completes, and the
   // solves run on streams that do not wait for the null stream
   IFL_HIP(hipDeviceSynchronize());
-  // without the memory for the polynomial engine the handle keeps to CG
-  if ((st = poly_create(h->op, h->opt.reorder != 0, d->own_stream, &d->poly)) != IFL_OK) {
-    poly_destroy(d->poly);
-    d->poly = nullptr;
-    if (st != IFL_ENOMEM) return st;
-  }
-  return IFL_OK;
+  return wants_poly(h->opt) ? ensure_poly(h) : IFL_OK;
 }
 
 void device_destroy(Handle* h) {
@@ -2382,9 +2398,11 @@ ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int3
   IFL_HIP(hipSetDevice(d->device));
   // the tile width left to the library: the polynomial engine. A fixed width
   // (1: one solve at a time) asks for CG, and the profile times CG's kernels
-  if (h->opt.batch == 0 && !h->opt.profile) {
+  if (wants_poly(h->opt)) {
     bool done = false;
-    ifl_status st = filter_poly(h, n_fields, fields, n_scales, k, out, stats, energy, &done);
+    ifl_status st = ensure_poly(h);
+    if (st != IFL_OK) return st;
+    st = filter_poly(h, n_fields, fields, n_scales, k, out, stats, energy, &done);
     if (done || st != IFL_OK) return st;
   }
   const bool shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2;
@@ -2407,7 +2425,13 @@ ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int3
   return filter_batched(h, R, n_fields, fields, n_scales, k, out, stats, energy);
 }
 
-PolyState* device_poly(Handle* h) { return h->dev ? h->dev->poly : nullptr; }
+ifl_status device_poly(Handle* h, PolyState** out) {
+  *out = nullptr;
+  if (!h->dev || h->opt.batch != 0) return IFL_OK;
+  const ifl_status st = ensure_poly(h);
+  *out = h->dev->poly;
+  return st;
+}
 
 ifl_status device_cg_column(Handle* h, const double* field, double k, double* out, ifl_solve_stats* st) {
   std::lock_guard<std::mutex> lk(h->mu);

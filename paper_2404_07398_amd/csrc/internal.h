@@ -130,10 +130,11 @@ ifl_status device_stream_probe(int device, int64_t bytes, int reps, double* best
 // NULL: energy only). Runs on the handle's stream; the caller holds h->mu.
 ifl_status device_solve_shifted_rows(Handle* h, const double* phi_rows, double k, double* out_dev,
                                      ifl_solve_stats* st);
-// The polynomial engine of a handle (NULL: it does not take the operator),
-// for callers with a work space and a stream of their own.
+// The polynomial engine of a handle with batch = 0 (NULL: a fixed width, or it
+// does not take the operator), for callers with a work space and a stream of
+// their own; the caller holds h->mu.
 struct PolyState;
-PolyState* device_poly(Handle* h);
+ifl_status device_poly(Handle* h, PolyState** out);
 // One served column by the handle's own CG (field and out in host memory);
 // takes the handle's lock.
 ifl_status device_cg_column(Handle* h, const double* field, double k, double* out, ifl_solve_stats* st);

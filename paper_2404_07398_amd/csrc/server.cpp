@@ -516,15 +516,19 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
       return fail(IFL_ENOMEM, "tile work space exceeds the server's memory budget");
     s->tiles += tile;
   }
+  PolyState* poly = nullptr;
+  ifl_status st;
   {
     std::lock_guard<std::mutex> lk(h->mu);
     wk->opt = h->opt;
+    st = device_poly(h, &poly);
   }
-  ifl_status st = IFL_OK;
   // the polynomial engine where the handle leaves the solver to the library
   // and a tile's memory holds its work space (few slots do not)
-  if (wk->opt.batch == 0 && poly_work_takes(device_poly(h), tile, h->op.order)) {
-    wk->poly = device_poly(h);
+  if (st != IFL_OK) {
+    // reported below
+  } else if (poly_work_takes(poly, tile, h->op.order)) {
+    wk->poly = poly;
     st = poly_work_create(tile, &wk->poly_work);
   } else if (!wk->shifted) {
     st = batch_alloc(&wk->w, wk->bm, wk->R, h->opt.precision == IFL_MIXED, wk->cx);

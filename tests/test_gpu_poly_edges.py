@@ -61,3 +61,33 @@ def test_residual_at_the_attainable_accuracy(ifl, jitter, cells):
     assert st[0].status == 0
     assert st[0].rel_residual <= max(1e-12, 1.01 * _attainable(op, phi, out[0, 0], k, 2))
     h.close()
+
+
+def test_fixed_width_handles_hold_no_patches(ifl):
+    """The engine's patches are made with handles that leave the solver to the
+    library, and otherwise by the first call that uses them (level 6: 40,962
+    records of over 100 bytes)."""
+    import torch
+
+    s = W.icosphere(6)
+    phi = np.random.default_rng(4).normal(size=s.n_vertices)
+    ks = W.log_scales(s.h, 3, lam_max_cells=8.0)
+
+    def held(**kw):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        h = ifl.prepare_mesh(s, ifl.IFL_VERTEX_SCALAR, 1, **kw)
+        torch.cuda.synchronize()
+        return h, before - torch.cuda.mem_get_info()[0]
+
+    held()[0].close()  # the device's pools have grown
+    h0, with_patches = held()
+    ref, st0 = h0.filter(phi, ks)
+    for kw in (dict(batch=8), dict(profile=1)):
+        h, without = held(**kw)
+        assert with_patches - without >= 4 << 20
+        h.set_options(batch=0, profile=0)
+        out, st = h.filter(phi, ks)
+        assert np.array_equal(out, ref) and [x.iterations for x in st] == [x.iterations for x in st0]
+        h.close()
+    h0.close()
