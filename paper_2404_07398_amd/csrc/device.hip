@@ -2349,9 +2349,35 @@ ifl_status filter_batched_cx(Handle* h, int Rc, int32_t n_fields, const double* 
 
 namespace {
 
+// The columns that missed the tolerance in the engine (in increasing order),
+// one at a time by the handle's own solver. Their fields come from the
+// engine's rows, since out, which may overlap fields, has been written.
+ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_scales, const double* k, double* out,
+                         ifl_solve_stats* stats, double* energy) {
+  DeviceState* d = h->dev;
+  const int64_t L = h->op.field_len;
+  double* field = nullptr;
+  ifl_status st = dalloc(&field, (size_t)L);
+  ifl_status agg = IFL_OK;
+  for (size_t i = 0; st == IFL_OK && i < failed.size(); ++i) {
+    const int64_t col = failed[i], f = col / n_scales;
+    if (i == 0 || failed[i - 1] / n_scales != f) st = poly_fields(d->poly, (int)f, 1, field, stream_of(h));
+    if (st == IFL_OK)
+      st = filter_single(h, 1, field, 1, k + col % n_scales, out ? out + col * L : nullptr,
+                         stats ? stats + col : nullptr, energy ? energy + col : nullptr,
+                         ColScratch{d->w.part, d->w.sc, true, true});
+    if (st == IFL_ENOTCONV) {
+      agg = st;
+      st = IFL_OK;
+    }
+  }
+  (void)hipFree(field);
+  if (st == IFL_OK && agg != IFL_OK) return fail(agg, "at least one column did not converge (see stats)");
+  return st;
+}
+
 // The polynomial engine on a call, *done = false where it leaves the call to
-// CG; the columns whose true residual misses the tolerance are solved again
-// one at a time by the handle's own solver.
+// CG.
 ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_t n_scales, const double* k,
                        double* out, ifl_solve_stats* stats, double* energy, bool* done) {
   DeviceState* d = h->dev;
@@ -2376,18 +2402,8 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   ifl_status st = poly_filter(d->poly, nullptr, c, &failed);
   if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) return IFL_OK;  // CG needs less memory
   *done = true;
-  if (st != IFL_OK) return st;
-  const int64_t L = h->op.field_len;
-  ifl_status agg = IFL_OK;
-  for (int64_t col : failed) {
-    st = filter_single(h, 1, fields + col / n_scales * L, 1, k + col % n_scales, out ? out + col * L : nullptr,
-                       stats ? stats + col : nullptr, energy ? energy + col : nullptr,
-                       ColScratch{d->w.part, d->w.sc, true, true});
-    if (st == IFL_ENOTCONV) agg = st;
-    else if (st != IFL_OK) return st;
-  }
-  if (agg != IFL_OK) return fail(agg, "at least one column did not converge (see stats)");
-  return IFL_OK;
+  if (st != IFL_OK || failed.empty()) return st;
+  return filter_failed(h, failed, n_scales, k, out, stats, energy);
 }
 
 }  // namespace

@@ -132,5 +132,8 @@ bool poly_takes(const PolyState* ps, const PolyCall& call);
 // what was reached). IFL_ENOMEM, IFL_EUNSUPPORTED: nothing was written. w:
 // NULL for the handle's own work space (the caller holds the handle's lock).
 ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& call, std::vector<int64_t>* failed);
+// Fields f0 .. f0 + n - 1 of the last call in the handle's own work space, in
+// the caller's numbering (0 where there is no row), to device memory.
+ifl_status poly_fields(PolyState* ps, int f0, int n, double* out, hipStream_t stream);
 
 }  // namespace ifl

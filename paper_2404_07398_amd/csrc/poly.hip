@@ -1568,4 +1568,12 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vecto
   }
 }
 
+ifl_status poly_fields(PolyState* ps, int f0, int n, double* out, hipStream_t stream) {
+  const PolyWork* w = ps->work;
+  GroupScales one{};
+  launch_out(ps, w->bad, w->call, 1, w->phi + (int64_t)f0 * ps->m.np, one, ps->m.field_len, out, n, stream);
+  IFL_HIP(hipGetLastError());
+  return IFL_OK;
+}
+
 }  // namespace ifl

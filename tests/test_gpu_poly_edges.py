@@ -91,3 +91,28 @@ def test_fixed_width_handles_hold_no_patches(ifl):
         assert np.array_equal(out, ref) and [x.iterations for x in st] == [x.iterations for x in st0]
         h.close()
     h0.close()
+
+
+# On _waves of the 64 x 64 square, order 2 at 128 cells and more: the
+# sequence's rounding (5e-11 of ||M phi||) stays above what FP64 can attain on
+# a filtered field that small (5e-12), so the check sends the columns to CG.
+FAILING = 2.0 * np.pi / np.array([128.0, 145.0, 165.0, 190.0])
+
+
+@pytest.mark.parametrize("device", [False, True])
+def test_outputs_over_the_fields(ifl, device):
+    """A call whose outputs take the place of its fields, with columns that
+    pass the check and columns that do not: what it gives elsewhere."""
+    import torch
+
+    m = W.split_square(64, jitter=0.2)
+    for n_fields, k in ((3, FAILING[0]), (3, 2.0 * np.pi / 8.0), (1, FAILING[1])):
+        fields = np.stack([(1.0 + f) * _waves(m, 0.01 + 0.01 * f) for f in range(n_fields)])
+        h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2)
+        ref, rt = h.filter(fields, np.array([k]), raise_on_notconv=False)
+        buf = torch.from_numpy(fields.copy()).cuda() if device else fields.copy()
+        _, st = h.filter(buf, np.array([k]), out=buf.reshape(n_fields, 1, -1), raise_on_notconv=False)
+        assert [x.status for x in st] == [x.status for x in rt]
+        got = buf.cpu().numpy() if device else buf
+        assert np.array_equal(got, ref[:, 0])
+        h.close()
