@@ -2349,29 +2349,66 @@ ifl_status filter_batched_cx(Handle* h, int Rc, int32_t n_fields, const double* 
 
 namespace {
 
+// CG: in tiles, or one column at a time.
+ifl_status filter_cg(Handle* h, int32_t n_fields, const double* fields, int32_t n_scales, const double* k, double* out,
+                     ifl_solve_stats* stats, double* energy) {
+  DeviceState* d = h->dev;
+  const bool shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2;
+  // order 2 (one complex shift) in complex tiles of first-order operators
+  // with narrow rows; other orders, and batch = 1, one column at a time
+  if (handle_cx_tiles(h) && h->opt.batch != 1) {
+    const int64_t ncols = (int64_t)n_fields * n_scales;
+    int Rc = 1;
+    if (h->opt.batch >= 2) {
+      Rc = std::min(32, std::max(1, h->opt.batch / 2));
+    } else {
+      while (Rc * 2 <= std::min<int64_t>(16, std::max<int64_t>(1, ncols / 2))) Rc *= 2;
+    }
+    int Rp = 1;  // tiles come in powers of two
+    while (Rp * 2 <= Rc) Rp *= 2;
+    return filter_batched_cx(h, Rp, n_fields, fields, n_scales, k, out, stats, energy);
+  }
+  const int R = shifted ? 1 : pick_tile(h, (int64_t)n_fields * n_scales);
+  if (R <= 1)
+    return filter_single(h, n_fields, fields, n_scales, k, out, stats, energy,
+                         ColScratch{d->w.part, d->w.sc, true, true});
+  return filter_batched(h, R, n_fields, fields, n_scales, k, out, stats, energy);
+}
+
 // The columns that missed the tolerance in the engine (in increasing order),
-// one at a time by the handle's own solver. Their fields come from the
-// engine's rows, since out, which may overlap fields, has been written.
-ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_scales, const double* k, double* out,
-                         ifl_solve_stats* stats, double* energy) {
+// by CG: all in one call if all did, else a field's neighbouring scales
+// together. Their fields come from the engine's rows, since out, which may
+// overlap fields, has been written.
+ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
+                         const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   const int64_t L = h->op.field_len;
-  double* field = nullptr;
-  ifl_status st = dalloc(&field, (size_t)L);
+  const bool all = (int64_t)failed.size() == (int64_t)n_fields * n_scales;
+  double* fields = nullptr;
+  ifl_status st = all ? dalloc(&fields, (size_t)n_fields * L) : IFL_ENOMEM;
+  const bool together = st == IFL_OK;
+  if (!together) {
+    (void)hipGetLastError();
+    st = dalloc(&fields, (size_t)L);
+  }
+  if (together) {
+    st = poly_fields(d->poly, 0, n_fields, fields, stream_of(h));
+    if (st == IFL_OK) st = filter_cg(h, n_fields, fields, n_scales, k, out, stats, energy);
+  }
   ifl_status agg = IFL_OK;
-  for (size_t i = 0; st == IFL_OK && i < failed.size(); ++i) {
+  for (size_t i = 0, e; !together && st == IFL_OK && i < failed.size(); i = e) {
     const int64_t col = failed[i], f = col / n_scales;
-    if (i == 0 || failed[i - 1] / n_scales != f) st = poly_fields(d->poly, (int)f, 1, field, stream_of(h));
+    for (e = i + 1; e < failed.size() && failed[e] == failed[e - 1] + 1 && failed[e] / n_scales == f;) ++e;
+    if (i == 0 || failed[i - 1] / n_scales != f) st = poly_fields(d->poly, (int)f, 1, fields, stream_of(h));
     if (st == IFL_OK)
-      st = filter_single(h, 1, field, 1, k + col % n_scales, out ? out + col * L : nullptr,
-                         stats ? stats + col : nullptr, energy ? energy + col : nullptr,
-                         ColScratch{d->w.part, d->w.sc, true, true});
+      st = filter_cg(h, 1, fields, (int32_t)(e - i), k + col % n_scales, out ? out + col * L : nullptr,
+                     stats ? stats + col : nullptr, energy ? energy + col : nullptr);
     if (st == IFL_ENOTCONV) {
       agg = st;
       st = IFL_OK;
     }
   }
-  (void)hipFree(field);
+  (void)hipFree(fields);
   if (st == IFL_OK && agg != IFL_OK) return fail(agg, "at least one column did not converge (see stats)");
   return st;
 }
@@ -2403,7 +2440,7 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) return IFL_OK;  // CG needs less memory
   *done = true;
   if (st != IFL_OK || failed.empty()) return st;
-  return filter_failed(h, failed, n_scales, k, out, stats, energy);
+  return filter_failed(h, failed, n_fields, n_scales, k, out, stats, energy);
 }
 
 }  // namespace
@@ -2421,24 +2458,7 @@ ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int3
     st = filter_poly(h, n_fields, fields, n_scales, k, out, stats, energy, &done);
     if (done || st != IFL_OK) return st;
   }
-  const bool shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2;
-  // order 2 (one complex shift) in complex tiles of first-order operators
-  // with narrow rows; other orders, and batch = 1, one column at a time
-  if (handle_cx_tiles(h) && h->opt.batch != 1) {
-    const int64_t ncols = (int64_t)n_fields * n_scales;
-    int Rc = 1;
-    if (h->opt.batch >= 2) {
-      Rc = std::min(32, std::max(1, h->opt.batch / 2));
-    } else {
-      while (Rc * 2 <= std::min<int64_t>(16, std::max<int64_t>(1, ncols / 2))) Rc *= 2;
-    }
-    int Rp = 1;  // tiles come in powers of two
-    while (Rp * 2 <= Rc) Rp *= 2;
-    return filter_batched_cx(h, Rp, n_fields, fields, n_scales, k, out, stats, energy);
-  }
-  const int R = shifted ? 1 : pick_tile(h, (int64_t)n_fields * n_scales);
-  if (R <= 1) return filter_single(h, n_fields, fields, n_scales, k, out, stats, energy, ColScratch{d->w.part, d->w.sc, true, true});
-  return filter_batched(h, R, n_fields, fields, n_scales, k, out, stats, energy);
+  return filter_cg(h, n_fields, fields, n_scales, k, out, stats, energy);
 }
 
 ifl_status device_poly(Handle* h, PolyState** out) {

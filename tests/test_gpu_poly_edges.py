@@ -99,6 +99,33 @@ def test_fixed_width_handles_hold_no_patches(ifl):
 FAILING = 2.0 * np.pi / np.array([128.0, 145.0, 165.0, 190.0])
 
 
+def test_columns_that_fail_the_check_run_in_tiles(ifl):
+    """All of a call's columns: bitwise the call of a handle that stays with CG
+    (its launch events asked for), tile width and all."""
+    m = W.split_square(64, jitter=0.2)
+    fields = np.stack([_waves(m), 2.0 * _waves(m, 0.02), -_waves(m, 0.005)])
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2)
+    cg = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2, profile=1)
+    out, st = h.filter(fields, FAILING, raise_on_notconv=False)
+    ref, rt = cg.filter(fields, FAILING, raise_on_notconv=False)
+    assert all(x.refinements > 0 for x in rt)
+    assert [(x.iterations, x.refinements, x.status) for x in st] == [(x.iterations, x.refinements, x.status) for x in rt]
+    assert np.array_equal(out, ref)
+    # some of them: the rest keep the engine's results, and neighbours run together
+    ks = np.concatenate([2.0 * np.pi / np.array([4.0]), FAILING[:2], 2.0 * np.pi / np.array([6.0, 8.0])])
+    out, st = h.filter(fields, ks, raise_on_notconv=False)
+    few, _ = h.filter(fields, ks[[0, 3, 4]])
+    assert np.array_equal(out[:, [0, 3, 4]], few)
+    for f in range(3):
+        ref, rt = cg.filter(fields[f], FAILING[:2], raise_on_notconv=False)
+        mine = st[5 * f:5 * f + 5]
+        assert [x.refinements > 0 for x in mine] == [False, True, True, False, False]
+        assert [x.iterations for x in mine[1:3]] == [x.iterations for x in rt]
+        assert np.array_equal(out[f, 1:3], ref[0])
+    h.close()
+    cg.close()
+
+
 @pytest.mark.parametrize("device", [False, True])
 def test_outputs_over_the_fields(ifl, device):
     """A call whose outputs take the place of its fields, with columns that
