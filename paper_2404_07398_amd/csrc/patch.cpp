@@ -405,6 +405,54 @@ void poly_coefficients(int order, double c, double lam, int m, double* out, int 
   }
 }
 
+double spectrum_bound(const double* alpha, const double* beta, int m, int nb, double least) {
+  // the largest eigenvalue of the tridiagonal by bisection
+  double lo = alpha[0], hi = alpha[0];
+  const int off = std::min(nb, m - 1);
+  for (int i = 0; i < m; ++i) {
+    const double r = (i > 0 && i - 1 < off ? std::fabs(beta[i - 1]) : 0.0) + (i < off ? std::fabs(beta[i]) : 0.0);
+    lo = std::min(lo, alpha[i] - r);
+    hi = std::max(hi, alpha[i] + r);
+  }
+  for (int it = 0; it < 100; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    double q = 1.0;
+    bool below = true;  // no eigenvalue above mid: all pivots of mid - T positive
+    for (int i = 0; i < m && below; ++i) {
+      q = mid - alpha[i] - (i > 0 && i - 1 < off ? beta[i - 1] * beta[i - 1] / q : 0.0);
+      if (!(q > 0.0)) below = false;
+    }
+    (below ? hi : lo) = mid;
+  }
+  const double theta = hi;
+  if (nb < m || !(theta > 0.0) || !(least > 0.0)) return 1.01 * theta;
+  // log |p_m| above theta, where p_m increases
+  const auto growth = [&](double x) {
+    double p0 = 0.0, p1 = 1.0, log = 0.0;
+    for (int j = 0; j < m; ++j) {
+      const double p2 = ((x - alpha[j]) * p1 - (j > 0 ? beta[j - 1] * p0 : 0.0)) / beta[j];
+      p0 = p1;
+      p1 = p2;
+      const double size = std::max(std::fabs(p0), std::fabs(p1));
+      if (!(size > 0.0)) return -HUGE_VAL;
+      p0 /= size;
+      p1 /= size;
+      log += std::log(size);
+    }
+    return log + std::log(std::fabs(p1));
+  };
+  double a = theta, b = 1.01 * theta;
+  while (growth(b) < -std::log(least) && b < 16.0 * theta) {
+    a = b;
+    b += 0.5 * (b - theta) + 0.01 * theta;
+  }
+  for (int it = 0; it < 40 && b > 1.01 * theta; ++it) {
+    const double mid = 0.5 * (a + b);
+    (growth(mid) < -std::log(least) ? a : b) = mid;
+  }
+  return std::max(b, 1.01 * theta);
+}
+
 bool poly_accepts(double res2, double size2, double bb, double rtol) {
   if (!std::isfinite(bb)) return !std::isnan(res2);
   if (!std::isfinite(res2)) return false;

@@ -84,6 +84,18 @@ int poly_degree(int order, double c, double lam, double tol, int max_degree);
 // c_0 .. c_m of degree m to out[k * stride].
 void poly_coefficients(int order, double c, double lam, int m, double* out, int stride);
 
+// Upper end of the spectrum from the tridiagonal of m Lanczos steps: alpha[0 ..
+// m), beta[0 .. nb), beta[j] coupling steps j and j + 1 (nb < m: the space was
+// exhausted). The largest Ritz value lies below the largest eigenvalue, by
+// more than a margin of 1% where an eigenvalue stands that far above the rest
+// and the start vector has little of it. Of an eigenvalue x the next Lanczos
+// vector has the part p_m(x) times the start's, p_m the polynomial of the
+// recurrence, and no part exceeds 1: with a start's part of at least 'least'
+// no eigenvalue lies above the x where p_m(x) = 1 / least (van Dorsselaer,
+// Hochstenbach, van der Vorst, SIAM J. Matrix Anal. 22 (2000)). At least 1%
+// above the Ritz value.
+double spectrum_bound(const double* alpha, const double* beta, int m, int nb, double least);
+
 // Whether a column with ||M phi - S x||^2 = res2, ||M phi||^2 = bb and terms of
 // the residual of norm^2 size2 counts as converged: within rtol, or within what
 // FP64 can tell, as CG has it. An overflowed sum proves nothing: a residual

@@ -127,3 +127,46 @@ int main() {
     inc = os.path.join(os.path.dirname(ifl.LIB_PATH), "csrc")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(src), "-o", str(exe), "-pthread"], check=True)
     assert subprocess.run([str(exe)], timeout=60).returncode == 0
+
+
+def _lanczos(values, start, steps):
+    v = start / np.linalg.norm(start)
+    prev, b, alpha, beta = np.zeros_like(v), 0.0, [], []
+    for _ in range(steps):
+        w = values * v - b * prev
+        a = w @ v
+        w -= a * v
+        b = np.linalg.norm(w)
+        alpha.append(a)
+        beta.append(b)
+        prev, v = v, w / b
+    return np.array(alpha), np.array(beta)
+
+
+@pytest.mark.parametrize("steps,least", [(32, 2e-6), (64, 5e-7)])
+@pytest.mark.parametrize("above", [0.0, 0.011, 0.02, 0.05, 0.3])
+def test_upper_end_of_the_spectrum(steps, least, above):
+    """One eigenvalue above a full band, and as little of its eigenvector in the
+    start as the bound allows for: the bound covers it, a margin of 1% on the
+    largest Ritz value does not always."""
+    p = ctypes.POINTER(ctypes.c_double)
+    bound = _function("_ZN3ifl14spectrum_boundEPKdS1_iid", ctypes.c_double, p, p, ctypes.c_int, ctypes.c_int,
+                      ctypes.c_double)
+    rng = np.random.default_rng(7)
+    n = 200_000
+    values = np.sort(rng.uniform(0.0, 1.0, n))
+    start = rng.uniform(-1.0, 1.0, n)
+    if above:
+        values[-1] = 1.0 + above
+        start[-1] = 1.01 * least * np.linalg.norm(start[:-1])
+    alpha, beta = _lanczos(values, start, steps)
+    ritz = np.linalg.eigvalsh(np.diag(alpha) + np.diag(beta[:-1], 1) + np.diag(beta[:-1], -1))[-1]
+    lam = bound(alpha.ctypes.data_as(p), beta.ctypes.data_as(p), steps, steps, least)
+    assert lam >= max(values[-1], 1.01 * ritz * (1 - 1e-12))
+    # no larger than Lanczos' own convergence allows: log(2 / least) growth at
+    # acosh(1 + 2 x) a step above the band's end
+    assert lam <= max(1.011 * ritz, (1.0 + np.log(4.0 * n / least) ** 2 / (4.0 * steps ** 2)) * max(ritz, 1.0))
+    if above == 0.02 and steps == 32:
+        assert 1.01 * ritz < values[-1]
+    # an exhausted space: the Ritz value is an eigenvalue
+    assert bound(alpha.ctypes.data_as(p), beta.ctypes.data_as(p), steps, steps - 1, least) == pytest.approx(1.01 * ritz)
