@@ -2376,37 +2376,61 @@ ifl_status filter_cg(Handle* h, int32_t n_fields, const double* fields, int32_t 
 }
 
 // The columns that missed the tolerance in the engine (in increasing order),
-// by CG: all in one call if all did, else a field's neighbouring scales
-// together. Their fields come from the engine's rows, since out, which may
+// by CG in one call: every field with such a column at every scale that has
+// one, since a tile costs about the same however full it is (2 of 8 scales
+// apart 31 ms, all 8 in one tile 23; fewer fields at a time where memory is
+// short). The fields come from the engine's rows, since out, which may
 // overlap fields, has been written.
 ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
                          const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
+  hipStream_t s = stream_of(h);
   const int64_t L = h->op.field_len;
-  const bool all = (int64_t)failed.size() == (int64_t)n_fields * n_scales;
+  std::vector<int32_t> fs, ss, place(n_scales, -1);
+  for (int64_t col : failed) {
+    if (fs.empty() || fs.back() != col / n_scales) fs.push_back((int32_t)(col / n_scales));
+    place[col % n_scales] = 0;
+  }
+  std::vector<double> ks;
+  for (int32_t j = 0; j < n_scales; ++j) {
+    if (place[j] < 0) continue;
+    place[j] = (int32_t)ss.size();
+    ss.push_back(j);
+    ks.push_back(k[j]);
+  }
+  const int32_t nf = (int32_t)fs.size(), ns = (int32_t)ss.size();
+  const bool direct = (int64_t)failed.size() == (int64_t)n_fields * n_scales;  // into out itself
   double* fields = nullptr;
-  ifl_status st = all ? dalloc(&fields, (size_t)n_fields * L) : IFL_ENOMEM;
-  const bool together = st == IFL_OK;
-  if (!together) {
+  ifl_status st = IFL_ENOMEM;
+  int32_t step = nf;
+  for (;; step = (step + 1) / 2) {
+    st = dalloc(&fields, (size_t)step * L * (direct || !out ? 1 : 1 + ns));
+    if (st == IFL_OK || step == 1) break;
     (void)hipGetLastError();
-    st = dalloc(&fields, (size_t)L);
   }
-  if (together) {
-    st = poly_fields(d->poly, 0, n_fields, fields, stream_of(h));
-    if (st == IFL_OK) st = filter_cg(h, n_fields, fields, n_scales, k, out, stats, energy);
-  }
+  double* res = fields ? fields + (int64_t)step * L : nullptr;
+  std::vector<ifl_solve_stats> so((size_t)step * ns);
+  std::vector<double> eo((size_t)step * ns);
   ifl_status agg = IFL_OK;
-  for (size_t i = 0, e; !together && st == IFL_OK && i < failed.size(); i = e) {
-    const int64_t col = failed[i], f = col / n_scales;
-    for (e = i + 1; e < failed.size() && failed[e] == failed[e - 1] + 1 && failed[e] / n_scales == f;) ++e;
-    if (i == 0 || failed[i - 1] / n_scales != f) st = poly_fields(d->poly, (int)f, 1, fields, stream_of(h));
+  size_t at = 0;  // in failed
+  for (int32_t f0 = 0; st == IFL_OK && f0 < nf; f0 += step) {
+    const int32_t n = std::min(step, nf - f0);
+    for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, fs[f0 + f], 1, fields + f * L, s);
     if (st == IFL_OK)
-      st = filter_cg(h, 1, fields, (int32_t)(e - i), k + col % n_scales, out ? out + col * L : nullptr,
-                     stats ? stats + col : nullptr, energy ? energy + col : nullptr);
-    if (st == IFL_ENOTCONV) {
-      agg = st;
-      st = IFL_OK;
+      st = filter_cg(h, n, fields, ns, ks.data(), !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res,
+                     so.data(), eo.data());
+    if (st == IFL_ENOTCONV) st = IFL_OK;
+    for (; st == IFL_OK && at < failed.size() && failed[at] / n_scales <= fs[f0 + n - 1]; ++at) {
+      const int64_t col = failed[at];
+      const int64_t from = (std::lower_bound(fs.begin(), fs.end(), (int32_t)(col / n_scales)) - fs.begin() - f0) * ns +
+                           place[col % n_scales];
+      if (so[from].status != IFL_OK) agg = IFL_ENOTCONV;
+      if (stats) stats[col] = so[from];
+      if (energy) energy[col] = eo[from];
+      if (out && !direct && hipMemcpyAsync(out + col * L, res + from * L, sizeof(double) * L, hipMemcpyDefault, s) != hipSuccess)
+        st = fail(IFL_EDEVICE, "copy of a column solved by CG failed");
     }
+    if (hipStreamSynchronize(s) != hipSuccess && st == IFL_OK) st = fail(IFL_EDEVICE, "hipStreamSynchronize failed");
   }
   (void)hipFree(fields);
   if (st == IFL_OK && agg != IFL_OK) return fail(agg, "at least one column did not converge (see stats)");

@@ -111,17 +111,19 @@ def test_columns_that_fail_the_check_run_in_tiles(ifl):
     assert all(x.refinements > 0 for x in rt)
     assert [(x.iterations, x.refinements, x.status) for x in st] == [(x.iterations, x.refinements, x.status) for x in rt]
     assert np.array_equal(out, ref)
-    # some of them: the rest keep the engine's results, and neighbours run together
-    ks = np.concatenate([2.0 * np.pi / np.array([4.0]), FAILING[:2], 2.0 * np.pi / np.array([6.0, 8.0])])
+    # some of them: the rest keep the engine's results, and those of all
+    # fields, apart as their scales are, run in one tile
+    ks = np.concatenate([2.0 * np.pi / np.array([4.0]), FAILING[:1], 2.0 * np.pi / np.array([6.0, 8.0]), FAILING[1:2]])
     out, st = h.filter(fields, ks, raise_on_notconv=False)
-    few, _ = h.filter(fields, ks[[0, 3, 4]])
-    assert np.array_equal(out[:, [0, 3, 4]], few)
-    for f in range(3):
-        ref, rt = cg.filter(fields[f], FAILING[:2], raise_on_notconv=False)
-        mine = st[5 * f:5 * f + 5]
-        assert [x.refinements > 0 for x in mine] == [False, True, True, False, False]
-        assert [x.iterations for x in mine[1:3]] == [x.iterations for x in rt]
-        assert np.array_equal(out[f, 1:3], ref[0])
+    few, _ = h.filter(fields, ks[[0, 2, 3]])
+    ref, rt = cg.filter(fields, FAILING[:2], raise_on_notconv=False)
+    assert np.array_equal(out[:, [0, 2, 3]], few) and np.array_equal(out[:, [1, 4]], ref)
+    assert [x.refinements > 0 for x in st] == 3 * [False, True, False, False, True]
+    assert [x.iterations for x in st if x.refinements] == [x.iterations for x in rt]
+    up = np.sort(ks)
+    _, st = h.filter(fields[0], up, raise_on_notconv=False)
+    assert [x.refinements > 0 for x in st] == [True, True, False, False, False]
+    assert list(h.spectrum(fields[0], up)[0]) == [x.energy for x in st]
     h.close()
     cg.close()
 
