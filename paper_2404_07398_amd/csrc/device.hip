@@ -2349,15 +2349,14 @@ ifl_status filter_batched_cx(Handle* h, int Rc, int32_t n_fields, const double* 
 
 namespace {
 
-// CG: in tiles, or one column at a time.
-ifl_status filter_cg(Handle* h, int32_t n_fields, const double* fields, int32_t n_scales, const double* k, double* out,
-                     ifl_solve_stats* stats, double* energy) {
+// CG: in tiles, of a width for ncols columns, or one column at a time.
+ifl_status filter_cg(Handle* h, int64_t ncols, int32_t n_fields, const double* fields, int32_t n_scales,
+                     const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   const bool shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2;
   // order 2 (one complex shift) in complex tiles of first-order operators
   // with narrow rows; other orders, and batch = 1, one column at a time
   if (handle_cx_tiles(h) && h->opt.batch != 1) {
-    const int64_t ncols = (int64_t)n_fields * n_scales;
     int Rc = 1;
     if (h->opt.batch >= 2) {
       Rc = std::min(32, std::max(1, h->opt.batch / 2));
@@ -2368,7 +2367,7 @@ ifl_status filter_cg(Handle* h, int32_t n_fields, const double* fields, int32_t 
     while (Rp * 2 <= Rc) Rp *= 2;
     return filter_batched_cx(h, Rp, n_fields, fields, n_scales, k, out, stats, energy);
   }
-  const int R = shifted ? 1 : pick_tile(h, (int64_t)n_fields * n_scales);
+  const int R = shifted ? 1 : pick_tile(h, ncols);
   if (R <= 1)
     return filter_single(h, n_fields, fields, n_scales, k, out, stats, energy,
                          ColScratch{d->w.part, d->w.sc, true, true});
@@ -2376,10 +2375,10 @@ ifl_status filter_cg(Handle* h, int32_t n_fields, const double* fields, int32_t 
 }
 
 // The columns that missed the tolerance in the engine (in increasing order),
-// by CG in one call: every field with such a column at every scale that has
-// one, since a tile costs about the same however full it is (2 of 8 scales
-// apart 31 ms, all 8 in one tile 23; fewer fields at a time where memory is
-// short). The fields come from the engine's rows, since out, which may
+// by CG in one call, of the width that the whole call would have had: every
+// field with such a column at every scale that has one, since a tile costs
+// about the same however full it is (2 of 8 scales one by one 31 ms, all 8 in
+// one tile 23; fewer fields at a time where memory is short). The fields come from the engine's rows, since out, which may
 // overlap fields, has been written.
 ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
                          const double* k, double* out, ifl_solve_stats* stats, double* energy) {
@@ -2417,7 +2416,7 @@ ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t 
     const int32_t n = std::min(step, nf - f0);
     for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, fs[f0 + f], 1, fields + f * L, s);
     if (st == IFL_OK)
-      st = filter_cg(h, n, fields, ns, ks.data(), !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res,
+      st = filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(), !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res,
                      so.data(), eo.data());
     if (st == IFL_ENOTCONV) st = IFL_OK;
     for (; st == IFL_OK && at < failed.size() && failed[at] / n_scales <= fs[f0 + n - 1]; ++at) {
@@ -2444,6 +2443,7 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   DeviceState* d = h->dev;
   PolyCall c;
   c.order = h->op.order;
+  c.shifted = h->opt.solver == IFL_SOLVER_SHIFTED;
   c.gamma = h->opt.gamma;
   c.rtol = h->opt.rtol;
   c.max_iter = h->opt.max_iter;
@@ -2482,7 +2482,7 @@ ifl_status device_filter(Handle* h, int32_t n_fields, const double* fields, int3
     st = filter_poly(h, n_fields, fields, n_scales, k, out, stats, energy, &done);
     if (done || st != IFL_OK) return st;
   }
-  return filter_cg(h, n_fields, fields, n_scales, k, out, stats, energy);
+  return filter_cg(h, (int64_t)n_fields * n_scales, n_fields, fields, n_scales, k, out, stats, energy);
 }
 
 ifl_status device_poly(Handle* h, PolyState** out) {

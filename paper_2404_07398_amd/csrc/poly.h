@@ -122,6 +122,7 @@ bool poly_work_takes(const PolyState* ps, size_t limit, int order);
 
 struct PolyCall {
   int order = 1;
+  bool shifted = false;  // what CG would solve: shifted first-order systems
   double gamma = 0.5, rtol = 1e-12;
   int max_iter = 20000;
   int32_t n_fields = 0, n_scales = 0;

@@ -1215,18 +1215,40 @@ double steps_needed(int order, double c, double lam, double tol) {
 
 bool poly_takes(const PolyState* ps, const PolyCall& c) {
   if (!ps || !(ps->lam > 0.0) || c.n_fields > 65535) return false;
-  const double tol = poly_tol(ps, c);
-  double most = 0.0, cg = 0.0;
+  const double tol = poly_tol(ps, c), side = std::sqrt((double)ps->m.units);
+  double most = 0.0, cg = 0.0, few = 0.0;
+  bool rounds = false;
   for (int32_t j = 0; j < c.n_scales; ++j) {
     const double f = scale_factor(c, j);
     if (!(f > 0.0) || !std::isfinite(f)) return false;
-    most = std::max(most, steps_needed(c.order, f, ps->lam, tol));
-    cg += steps_needed(c.order, f, ps->lam_typical, tol);
+    const double steps = steps_needed(c.order, f, ps->lam, tol), its = steps_needed(c.order, f, ps->lam_typical, tol);
+    most = std::max(most, steps);
+    cg += its;
+    // where the scale outgrows the mesh CG has resolved its modes: order 1,
+    // 1,000 cells, 212 iterations on 32 x 32, 382 on 64 x 64, 700 on 128 x 128,
+    // 1,208 on 256 x 256; shifted systems of order 2, 250 cells, 280 and 488 on
+    // the first two (K_2 itself takes thousands)
+    few += c.order == 1 ? std::min(its, 6.5 * side) : c.shifted ? std::min(its, 9.0 * side) : its;
+    // about the largest residual that rounding leaves, per ||M phi||: of smooth
+    // fields whose filtered part is small (a sequence at the edge z = -1 loses
+    // a digit for every one of its length, until the mesh's own lowest mode;
+    // order 2 at 64 cells 4e-12, order 1 at 250 cells of 256 x 256 1.1e-12)
+    const double u = 1.1102230246251565e-16;
+    const double left = c.order == 1 ? u * std::min(0.017 * steps * steps, 0.08 * steps * side)
+                                     : 0.12 * u * f * std::pow(ps->lam, 2.0);
+    rounds = rounds || left > c.rtol;
   }
   // a step of the sequence costs less than half a CG iteration of one
   // column (2.6 M rows: 19 us for 90; 4,096 rows: 1 us for 12); lam exceeds lam_typical where a few cells are much smaller than
   // the rest, which CG mostly does not feel and the sequence does
-  return most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0;
+  if (!(most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0)) return false;
+  // 64 x 64, one scale: 250 cells 1.3 ms for CG's 3.4, 1,000 cells 5.1 for 4.1
+  if (most > 5.0 * few) return false;
+  // where columns may have to be solved again by CG, only if the sequence
+  // is short beside that (256 x 256, one scale: 250 cells 1.3 of 10 ms, 1,000
+  // cells 6 of 19), and not where a few small cells set lam: the rounding
+  // grows with lam, what CG's rule lets pass with the rows' own
+  return !rounds || (most <= 2.0 * few && std::pow(ps->lam / ps->lam_typical, c.order) <= 7.0);
 }
 
 namespace {

@@ -392,6 +392,7 @@ ifl_status run_worker_poly(Worker* wk) {
     ifl_ticket* t = wk->pending.front().t;
     PolyCall c;
     c.order = h->op.order;
+    c.shifted = wk->opt.solver == IFL_SOLVER_SHIFTED;
     c.gamma = wk->opt.gamma;
     c.rtol = wk->opt.rtol;
     c.max_iter = wk->opt.max_iter;

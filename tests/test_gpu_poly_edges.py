@@ -112,14 +112,14 @@ def test_columns_that_fail_the_check_run_in_tiles(ifl):
     assert [(x.iterations, x.refinements, x.status) for x in st] == [(x.iterations, x.refinements, x.status) for x in rt]
     assert np.array_equal(out, ref)
     # some of them: the rest keep the engine's results, and those of all
-    # fields, apart as their scales are, run in one tile
+    # fields, apart as their scales are, run in the tile of the whole call
     ks = np.concatenate([2.0 * np.pi / np.array([4.0]), FAILING[:1], 2.0 * np.pi / np.array([6.0, 8.0]), FAILING[1:2]])
     out, st = h.filter(fields, ks, raise_on_notconv=False)
     few, _ = h.filter(fields, ks[[0, 2, 3]])
-    ref, rt = cg.filter(fields, FAILING[:2], raise_on_notconv=False)
-    assert np.array_equal(out[:, [0, 2, 3]], few) and np.array_equal(out[:, [1, 4]], ref)
+    ref, rt = cg.filter(fields, ks, raise_on_notconv=False)
+    assert np.array_equal(out[:, [0, 2, 3]], few) and np.array_equal(out[:, [1, 4]], ref[:, [1, 4]])
     assert [x.refinements > 0 for x in st] == 3 * [False, True, False, False, True]
-    assert [x.iterations for x in st if x.refinements] == [x.iterations for x in rt]
+    assert [x.iterations for x in st if x.refinements] == [rt[5 * f + j].iterations for f in range(3) for j in (1, 4)]
     up = np.sort(ks)
     _, st = h.filter(fields[0], up, raise_on_notconv=False)
     assert [x.refinements > 0 for x in st] == [True, True, False, False, False]
@@ -145,3 +145,23 @@ def test_outputs_over_the_fields(ifl, device):
         got = buf.cpu().numpy() if device else buf
         assert np.array_equal(got, ref[:, 0])
         h.close()
+
+
+@pytest.mark.parametrize("nx,order,jitter,cells,sequence", [
+    (64, 1, 0.2, 32.0, True), (64, 1, 0.2, 128.0, True), (64, 1, 0.2, 1000.0, False), (32, 1, 0.2, 2000.0, False),
+    (64, 2, 0.2, 32.0, True), (64, 2, 0.3, 16.0, True), (64, 2, 0.3, 64.0, False), (256, 1, 0.2, 1000.0, False),
+])
+def test_scales_beyond_the_mesh_stay_with_cg(ifl, nx, order, jitter, cells, sequence):
+    """Where CG has resolved every mode of the mesh long before the sequence
+    ends, or rounding would fail the columns, the call is CG's alone: bitwise
+    that of a handle whose launch events are asked for."""
+    m = W.split_square(nx, jitter=jitter)
+    phi, ks = _waves(m), np.array([2.0 * np.pi / cells])
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, order)
+    out, st = h.filter(phi, ks)
+    assert (st[0].refinements == 0) == sequence
+    h.set_options(profile=1)
+    ref, rt = h.filter(phi, ks)
+    if not sequence:
+        assert np.array_equal(out, ref) and st[0].iterations == rt[0].iterations
+    h.close()
