@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "batch.h"
+#include "poly.h"
 
 namespace ifl {
 
@@ -2280,7 +2281,7 @@ BVec<T> bvec(BatchWork& w) {
 template <typename T>
 ifl_status dalloc_b(T** p, size_t count) {
   if (count == 0) count = 1;
-  hipError_t e = hipMalloc((void**)p, count * sizeof(T));
+  hipError_t e = device_malloc((void**)p, count * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
     return fail(IFL_ENOMEM, std::string("hipMalloc failed (batched work space): ") + hipGetErrorString(e));

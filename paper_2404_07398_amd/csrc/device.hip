@@ -1191,7 +1191,7 @@ namespace {
 template <typename T>
 ifl_status dalloc(T** p, size_t count) {
   if (count == 0) count = 1;
-  hipError_t e = hipMalloc((void**)p, count * sizeof(T));
+  hipError_t e = device_malloc((void**)p, count * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
     return fail(IFL_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
@@ -2380,7 +2380,7 @@ ifl_status filter_cg(Handle* h, int64_t ncols, int32_t n_fields, const double* f
 // about the same however full it is (2 of 8 scales one by one 31 ms, all 8 in
 // one tile 23; fewer fields at a time where memory is short). The fields come from the engine's rows, since out, which may
 // overlap fields, has been written.
-ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
+ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
                          const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   hipStream_t s = stream_of(h);
@@ -2414,7 +2414,7 @@ ifl_status filter_failed(Handle* h, const std::vector<int64_t>& failed, int32_t 
   size_t at = 0;  // in failed
   for (int32_t f0 = 0; st == IFL_OK && f0 < nf; f0 += step) {
     const int32_t n = std::min(step, nf - f0);
-    for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, fs[f0 + f], 1, fields + f * L, s);
+    for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, w, fs[f0 + f], 1, fields + f * L, s);
     if (st == IFL_OK)
       st = filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(), !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res,
                      so.data(), eo.data());
@@ -2459,12 +2459,22 @@ ifl_status filter_poly(Handle* h, int32_t n_fields, const double* fields, int32_
   c.stream = stream_of(h);
   *done = false;
   if (!poly_takes(d->poly, c)) return IFL_OK;
+  PolyWork* w = nullptr;
   std::vector<int64_t> failed;
-  ifl_status st = poly_filter(d->poly, nullptr, c, &failed);
-  if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) return IFL_OK;  // CG needs less memory
-  *done = true;
-  if (st != IFL_OK || failed.empty()) return st;
-  return filter_failed(h, failed, n_fields, n_scales, k, out, stats, energy);
+  ifl_status st = poly_work_borrow(d->poly, n_fields, n_scales, &w);
+  if (st == IFL_OK) st = poly_filter(d->poly, w, c, &failed);
+  if (st == IFL_ENOMEM) {  // CG needs less, and gets this
+    poly_work_destroy(w);
+    return IFL_OK;
+  }
+  *done = st != IFL_EUNSUPPORTED;
+  if (!*done) st = IFL_OK;
+  else if (st == IFL_OK && !failed.empty())
+    st = filter_failed(h, w, failed, n_fields, n_scales, k, out, stats, energy);
+  else if (st == IFL_EDEVICE)
+    (void)hipStreamSynchronize(c.stream);
+  poly_work_return(d->poly, w);
+  return st;
 }
 
 }  // namespace

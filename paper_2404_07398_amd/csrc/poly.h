@@ -117,6 +117,13 @@ void poly_destroy(PolyState* ps);
 // large arrays take at most, allocated here (0: they grow with the calls).
 ifl_status poly_work_create(size_t limit, PolyWork** out);
 void poly_work_destroy(PolyWork* w);
+// hipMalloc that gives the device's idle work spaces back and tries again where
+// memory is short (the runtime's last error is cleared).
+hipError_t device_malloc(void** p, size_t bytes);
+// A work space without a limit for one call on ps, from those idle on its
+// device; to be returned when nothing of the call is under way any more.
+ifl_status poly_work_borrow(PolyState* ps, int32_t n_fields, int32_t n_scales, PolyWork** out);
+void poly_work_return(PolyState* ps, PolyWork* w);
 // Whether a work space of this size holds requests of a few scales.
 bool poly_work_takes(const PolyState* ps, size_t limit, int order);
 
@@ -142,11 +149,11 @@ bool poly_takes(const PolyState* ps, const PolyCall& call);
 
 // Filters every column; the numbers (field * n_scales + scale) of columns
 // whose true residual misses the tolerance go to *failed (their outputs hold
-// what was reached). IFL_ENOMEM, IFL_EUNSUPPORTED: nothing was written. w:
-// NULL for the handle's own work space (the caller holds the handle's lock).
+// what was reached). IFL_ENOMEM, IFL_EUNSUPPORTED: nothing was written, and
+// the work space is worth giving up.
 ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& call, std::vector<int64_t>* failed);
-// Fields f0 .. f0 + n - 1 of the last call in the handle's own work space, in
-// the caller's numbering (0 where there is no row), to device memory.
-ifl_status poly_fields(PolyState* ps, int f0, int n, double* out, hipStream_t stream);
+// Fields f0 .. f0 + n - 1 of w's last call, in the caller's numbering (0 where
+// there is no row), to device memory.
+ifl_status poly_fields(PolyState* ps, const PolyWork* w, int f0, int n, double* out, hipStream_t stream);
 
 }  // namespace ifl

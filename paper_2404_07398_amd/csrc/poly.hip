@@ -18,6 +18,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -42,6 +43,11 @@ constexpr int kRedBlocks = 512; // blocks of the row kernels that write partial 
 // at most 0.2% after 64).
 constexpr int kLanczos = 64, kLanczosSmall = 32;
 constexpr int kMaxGroup = 16;   // scales summed together
+
+// Without a limit: about 12 GB of the 288, which at level 9 hold 8 fields
+// with 64 vectors and 32 scales each (a patch's records are read once for
+// them; 4 fields took 7% longer).
+constexpr size_t kPolyBudget = (size_t)12 << 30;
 
 struct PolyDev {
   const PatchInfo* info = nullptr;
@@ -756,13 +762,14 @@ struct PolyState {
   double lam = 0.0;         // upper end of the spectrum of A, with its margin
   double lam_typical = 0.0; // the same of a mesh whose rows were all like 95% of the rows
   double mass_ratio = 1.0, mass_sum = 0.0;
-  PolyWork* work = nullptr;  // of ifl_filter's calls (under the handle's lock)
 };
 
 // Work space of one caller at a time, kept between calls. With a limit its
 // large arrays live in one allocation of that size.
 struct PolyWork {
   size_t limit = 0;         // bytes, 0: arrays grow as calls need them
+  int device = 0;
+  const PolyState* last = nullptr;  // whose call had it last
   double* arena = nullptr;
   double *phi = nullptr, *t = nullptr, *x = nullptr, *z = nullptr, *in = nullptr, *stage = nullptr;
   size_t phi_n = 0, t_n = 0, x_n = 0, z_n = 0, in_n = 0, stage_n = 0;
@@ -791,8 +798,7 @@ struct Upload {
     bytes += (v.size() * sizeof(T) + 255) / 256 * 256;
   }
   ifl_status run(void** base) {
-    if (hipMalloc(base, std::max<size_t>(bytes, 256)) != hipSuccess) {
-      (void)hipGetLastError();
+    if (device_malloc(base, std::max<size_t>(bytes, 256)) != hipSuccess) {
       *base = nullptr;
       return fail(IFL_ENOMEM, "hipMalloc failed for the patches");
     }
@@ -814,8 +820,7 @@ ifl_status grow(double** p, size_t* have, size_t want) {
   if (*p) (void)hipFree(*p);
   *p = nullptr;
   *have = 0;
-  if (hipMalloc((void**)p, want * sizeof(double)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (device_malloc((void**)p, want * sizeof(double)) != hipSuccess) {
     *p = nullptr;
     return fail(IFL_ENOMEM, "hipMalloc failed for the polynomial engine's work space");
   }
@@ -1081,6 +1086,7 @@ static ifl_status create(const HostOperator& op, bool local_order, hipStream_t s
   if (!build_patches(op, local_order, &pp)) return IFL_OK;
   PolyState* ps = new PolyState();
   *out = ps;
+  IFL_HIP(hipGetDevice(&ps->device));
   ps->nc = pp.nc;
   ps->width = pp.width;
   ps->block = pp.block;
@@ -1128,7 +1134,9 @@ static ifl_status create(const HostOperator& op, bool local_order, hipStream_t s
     std::nth_element(d.begin(), d.begin() + at, d.end());
     ps->lam_typical = 2.0 * d[at];
   }
-  if ((st = poly_work_create(0, &ps->work)) != IFL_OK) return st;
+  PolyWork* w = nullptr;  // the first call finds one made
+  if ((st = poly_work_create(0, &w)) != IFL_OK) return st;
+  poly_work_return(ps, w);
   // (the noise is uniform in the rows: the part is smallest in an eigenvector
   // of the row of least mass alone)
   return estimate_spectrum(ps, 1e-3 * std::sqrt(*std::min_element(op.mass.begin(), op.mass.end()) / ps->mass_sum), s);
@@ -1144,13 +1152,6 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   }
 }
 
-void poly_destroy(PolyState* ps) {
-  if (!ps) return;
-  if (ps->arrays) (void)hipFree(ps->arrays);
-  poly_work_destroy(ps->work);
-  delete ps;
-}
-
 static void free_large(PolyWork* w) {
   for (auto [p, n] : {std::pair<double**, size_t*>{&w->phi, &w->phi_n}, {&w->t, &w->t_n}, {&w->x, &w->x_n},
                       {&w->z, &w->z_n}, {&w->in, &w->in_n}, {&w->stage, &w->stage_n}}) {
@@ -1164,6 +1165,7 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
   PolyWork* w = new PolyWork();
   *out = w;
   w->limit = limit;
+  (void)hipGetDevice(&w->device);
   size_t n = 0;
   ifl_status st = IFL_OK;
   if (limit) st = grow(&w->arena, &n, limit / sizeof(double));
@@ -1188,6 +1190,103 @@ void poly_work_destroy(PolyWork* w) {
   if (w->host) (void)hipHostFree(w->host);
   if (w->host_coef) (void)hipHostFree(w->host_coef);
   delete w;
+}
+
+// Work spaces between calls, at most kIdle bytes of them on a device. A call
+// takes the one of its handle's last call if that is large enough, else the
+// smallest that is, so that many large handles used in turn hold one together
+// (handles used at the same time grow one each).
+namespace {
+
+constexpr size_t kIdle = (size_t)16 << 30;
+std::mutex g_idle_mu;
+std::vector<PolyWork*> g_idle;  // least recently used first
+
+size_t work_bytes(const PolyWork* w) {
+  return sizeof(double) * (w->phi_n + w->t_n + w->x_n + w->z_n + w->in_n + w->stage_n + w->part_n + w->norm_n + w->coef_n);
+}
+
+// Frees the idle work spaces that 'which' is true of; whether there were any.
+template <typename F>
+bool drop_idle(const F& which) {
+  std::vector<PolyWork*> drop;
+  {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    const auto from = std::stable_partition(g_idle.begin(), g_idle.end(), [&](PolyWork* w) { return !which(w); });
+    drop.assign(from, g_idle.end());
+    g_idle.erase(from, g_idle.end());
+  }
+  for (PolyWork* w : drop) poly_work_destroy(w);
+  return !drop.empty();
+}
+
+}  // namespace
+
+ifl_status poly_work_borrow(PolyState* ps, int32_t n_fields, int32_t n_scales, PolyWork** out) {
+  // half of what the call will need, roughly: a hundred vectors a field beside
+  // its scales, within the budget
+  const double need = 0.5 * std::min((double)kPolyBudget, 8.0 * ps->m.np * n_fields * (n_scales + 100.0));
+  {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    int own = -1, enough = -1;
+    for (int i = 0; i < (int)g_idle.size(); ++i) {
+      if (g_idle[i]->device != ps->device) continue;
+      const size_t bytes = work_bytes(g_idle[i]);
+      if (g_idle[i]->last == ps) own = i;
+      if (bytes >= need && (enough < 0 || bytes < work_bytes(g_idle[enough]))) enough = i;
+    }
+    const int take = own >= 0 && (enough < 0 || work_bytes(g_idle[own]) >= need) ? own : enough;
+    if (take >= 0) {
+      *out = g_idle[take];
+      g_idle.erase(g_idle.begin() + take);
+      return IFL_OK;
+    }
+  }
+  return poly_work_create(0, out);
+}
+
+void poly_work_return(PolyState* ps, PolyWork* w) {
+  if (!w) return;
+  w->last = ps;
+  std::vector<PolyWork*> drop;
+  {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    try {
+      drop.reserve(g_idle.size() + 1);
+      g_idle.push_back(w);
+    } catch (const std::bad_alloc&) {
+      poly_work_destroy(w);
+      return;
+    }
+    size_t bytes = 0;
+    for (size_t i = g_idle.size(); i-- > 0;) {
+      if (g_idle[i]->device != ps->device) continue;
+      if (bytes + work_bytes(g_idle[i]) > kIdle) {
+        drop.push_back(g_idle[i]);
+        g_idle.erase(g_idle.begin() + (int64_t)i);
+      } else {
+        bytes += work_bytes(g_idle[i]);
+      }
+    }
+  }
+  for (PolyWork* d : drop) poly_work_destroy(d);
+}
+
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess || !drop_idle([&](const PolyWork* w) { return w->device == device; })) return e;
+  if ((e = hipMalloc(p, bytes)) != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
+void poly_destroy(PolyState* ps) {
+  if (!ps) return;
+  if (ps->arrays) (void)hipFree(ps->arrays);
+  drop_idle([&](const PolyWork* w) { return w->last == ps; });
+  delete ps;
 }
 
 namespace {
@@ -1268,11 +1367,6 @@ int padded_scales(int n) {
   while (r < n % kMaxGroup) r *= 2;
   return p + r;
 }
-
-// Without a limit: about 12 GB of the 288, which at level 9 hold 8 fields
-// with 64 vectors and 32 scales each (a patch's records are read once for
-// them; 4 fields took 7% longer).
-constexpr size_t kPolyBudget = (size_t)12 << 30;
 
 bool make_plan(const PolyState* ps, size_t limit, const PolyCall& c, int degree, Plan* out) {
   const PolyDev& m = ps->m;
@@ -1410,7 +1504,6 @@ static ifl_status run_call(PolyState* ps, PolyWork* w, const PolyCall& c, std::v
   } else if ((st = grow(&w->phi, &w->phi_n, n_phi)) || (st = grow(&w->t, &w->t_n, n_t)) ||
              (st = grow(&w->x, &w->x_n, n_x)) || (st = grow(&w->z, &w->z_n, n_z)) ||
              (st = grow(&w->in, &w->in_n, n_in)) || (st = grow(&w->stage, &w->stage_n, n_stage))) {
-    free_large(w);  // the caller goes on with CG
     return st;
   }
   if ((st = grow(&w->part, &w->part_n, (size_t)FG * kMaxGroup * 3 * G)) ||
@@ -1569,15 +1662,14 @@ static ifl_status run_call(PolyState* ps, PolyWork* w, const PolyCall& c, std::v
 
 ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& c, std::vector<int64_t>* failed) {
   try {
-    return run_call(ps, w ? w : ps->work, c, failed);
+    return run_call(ps, w, c, failed);
   } catch (const std::bad_alloc&) {
     (void)hipStreamSynchronize(c.stream);  // of what was launched before
     return fail(IFL_ENOMEM, "out of host memory for a call's scales");
   }
 }
 
-ifl_status poly_fields(PolyState* ps, int f0, int n, double* out, hipStream_t stream) {
-  const PolyWork* w = ps->work;
+ifl_status poly_fields(PolyState* ps, const PolyWork* w, int f0, int n, double* out, hipStream_t stream) {
   GroupScales one{};
   launch_out(ps, w->bad, w->call, 1, w->phi + (int64_t)f0 * ps->m.np, one, ps->m.field_len, out, n, stream);
   IFL_HIP(hipGetLastError());

@@ -197,7 +197,7 @@ void stage_admitted(Worker* wk) {
     if (!wk->field_pool.empty()) {
       t->dev_field = wk->field_pool.back();
       wk->field_pool.pop_back();
-    } else if (hipMalloc((void**)&t->dev_field, sizeof(double) * wk->bm.n_pad) != hipSuccess) {
+    } else if (device_malloc((void**)&t->dev_field, sizeof(double) * wk->bm.n_pad) != hipSuccess) {
       t->dev_field = nullptr;
     }
     // the field goes through the staging buffer into row order (stream order
@@ -533,20 +533,20 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
     st = poly_work_create(tile, &wk->poly_work);
   } else if (!wk->shifted) {
     st = batch_alloc(&wk->w, wk->bm, wk->R, h->opt.precision == IFL_MIXED, wk->cx);
-  } else if (hipMalloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess) {  // only the field check's flag
+  } else if (device_malloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess) {  // only the field check's flag
     st = fail(IFL_ENOMEM, "hipMalloc of the field check flag failed");
   }
   if (st == IFL_OK && wk->cx && !wk->poly) {
     wk->w.cx_g = handle_cx_gnorm(h);
-    if (hipMalloc((void**)&wk->zero_rows, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
+    if (device_malloc((void**)&wk->zero_rows, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
         hipMemset(wk->zero_rows, 0, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess)
       st = fail(IFL_ENOMEM, "allocation of the zero imaginary parts failed");
   }
-  if (st == IFL_OK && !wk->poly && hipMalloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
+  if (st == IFL_OK && !wk->poly && device_malloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
     st = fail(IFL_ENOMEM, "hipMalloc of the field staging failed");
   if (st == IFL_OK && !wk->poly &&
-      hipMalloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
+      device_malloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
     st = fail(IFL_ENOMEM, "hipMalloc of the output staging failed");
   if (st == IFL_OK && hipStreamCreateWithFlags(&wk->stream, hipStreamNonBlocking) != hipSuccess)
     st = fail(IFL_EDEVICE, "hipStreamCreate failed");

@@ -165,3 +165,64 @@ def test_scales_beyond_the_mesh_stay_with_cg(ifl, nx, order, jitter, cells, sequ
     if not sequence:
         assert np.array_equal(out, ref) and st[0].iterations == rt[0].iterations
     h.close()
+
+
+def test_many_handles_share_a_work_space(ifl):
+    """Handles used in turn hold one large work space (9 GB here) together, and
+    give it back when they are closed."""
+    import torch
+
+    s = W.icosphere(8)
+    s = s.with_mask(W.land_mask(s, 0.3))
+    handles = [ifl.prepare_mesh(s, ifl.IFL_VERTEX_SCALAR, 1) for _ in range(3)]
+    L = s.n_vertices
+    fields = torch.randn((8, L), dtype=torch.float64, generator=torch.Generator().manual_seed(2)).cuda()
+    out = torch.zeros((8, 32, L), dtype=torch.float64, device="cuda")
+    ks = W.log_scales(s.h, 32)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    start = free()
+    handles[0].filter(fields, ks, out=out)
+    one = start - free()
+    assert 4 << 30 < one < 16 << 30
+    first = out.clone()
+    base = free()
+    for h in handles[1:] + handles[:1]:
+        h.filter(fields, ks, out=out)
+        assert bool((out == first).all())
+    assert base - free() < 1 << 30
+    for h in handles:
+        h.close()
+    assert start - free() < out.numel() * 8 + (1 << 30)  # the clone, and change
+
+
+def test_handles_on_several_threads(ifl):
+    """Calls at the same time, each with a work space of its own."""
+    import threading
+
+    jobs = []
+    for i, (nx, order, scales) in enumerate([(32, 1, 1), (64, 1, 8), (97, 2, 5), (150, 1, 17), (64, 2, 3)]):
+        m = W.split_square(nx, jitter=0.2, ny=nx - 1)
+        h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, order)
+        f = np.random.default_rng(i).normal(size=(1 + i % 3, nx * (nx - 1)))
+        ks = W.log_scales(1.0, scales, lam_max_cells=16.0)
+        jobs.append((h, f, ks, h.filter(f, ks)[0]))
+    wrong = []
+
+    def work(j):
+        h, f, ks, ref = jobs[j]
+        for _ in range(20):
+            if not np.array_equal(h.filter(f, ks)[0], ref):
+                wrong.append(j)
+
+    threads = [threading.Thread(target=work, args=(j,)) for j in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    for h, *_ in jobs:
+        h.close()
