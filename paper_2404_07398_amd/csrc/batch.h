@@ -171,7 +171,7 @@ BatchMatrix handle_batch_matrix(Handle* h, int R, bool mixed);
 // wavenumber k (slot 2j's and 2j + 1's c).
 bool handle_cx_tiles(const Handle* h);
 BatchMatrix handle_batch_matrix_k1(Handle* h, int R, bool mixed);
-void cx_shift(const Handle* h, double k, double* sigma_re, double* sigma_im);
+void cx_shift(double gamma, double k, double* sigma_re, double* sigma_im);
 // g >= ||K M^-1||_2 for the first-order operator K of an order >= 2 handle
 double handle_cx_gnorm(const Handle* h);
 double handle_mass_sum(const Handle* h);

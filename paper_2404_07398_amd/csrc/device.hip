@@ -1986,9 +1986,9 @@ bool handle_cx_tiles(const Handle* h) {
 
 // sigma = -b / w_0 for the shift pair with Im >= 0 (w_0 = exp(i pi / 2),
 // b = c^(1/2), c = gamma / k^4), as the one-column shifted solves take it
-void cx_shift(const Handle* h, double k, double* sigma_re, double* sigma_im) {
+void cx_shift(double gamma, double k, double* sigma_re, double* sigma_im) {
   const double pi = 3.14159265358979323846, th = pi / 2;
-  const double b = std::sqrt(h->opt.gamma / std::pow(k, 4.0));
+  const double b = std::sqrt(gamma / std::pow(k, 4.0));
   *sigma_re = -std::cos(th) * b;
   *sigma_im = std::sin(th) * b;
 }
@@ -2296,7 +2296,7 @@ ifl_status filter_batched_cx(Handle* h, int Rc, int32_t n_fields, const double* 
       const int64_t f = col / n_scales, sc = col % n_scales;
       src[2 * q] = d->field_rows + f * bm.n_pad;
       src[2 * q + 1] = d->zero_rows;
-      cx_shift(h, k[sc], &cs.c[2 * q], &cs.c[2 * q + 1]);
+      cx_shift(h->opt.gamma, k[sc], &cs.c[2 * q], &cs.c[2 * q + 1]);
       slot_col[q] = col;
       t_in[q] = std::chrono::steady_clock::now();
       mask |= 3ull << (2 * q);
@@ -2501,13 +2501,6 @@ ifl_status device_poly(Handle* h, PolyState** out) {
   const ifl_status st = ensure_poly(h);
   *out = h->dev->poly;
   return st;
-}
-
-ifl_status device_cg_column(Handle* h, const double* field, double k, double* out, ifl_solve_stats* st) {
-  std::lock_guard<std::mutex> lk(h->mu);
-  IFL_HIP(hipSetDevice(h->dev->device));
-  double energy = 0.0;
-  return filter_single(h, 1, field, 1, &k, out, st, &energy, ColScratch{h->dev->w.part, h->dev->w.sc, true, true});
 }
 
 // Streaming probe: dst = src in 16-byte units, one unit per thread and one

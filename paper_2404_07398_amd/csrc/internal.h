@@ -135,9 +135,6 @@ ifl_status device_solve_shifted_rows(Handle* h, const double* phi_rows, double k
 // their own; the caller holds h->mu.
 struct PolyState;
 ifl_status device_poly(Handle* h, PolyState** out);
-// One served column by the handle's own CG (field and out in host memory);
-// takes the handle's lock.
-ifl_status device_cg_column(Handle* h, const double* field, double k, double* out, ifl_solve_stats* st);
 // Allocates (once per handle) the work space of the shifted solves and
 // returns its size in bytes; the caller holds h->mu.
 ifl_status device_shift_work(Handle* h, size_t* bytes);

@@ -124,7 +124,8 @@ hipError_t device_malloc(void** p, size_t bytes);
 // device; to be returned when nothing of the call is under way any more.
 ifl_status poly_work_borrow(PolyState* ps, int32_t n_fields, int32_t n_scales, PolyWork** out);
 void poly_work_return(PolyState* ps, PolyWork* w);
-// Whether a work space of this size holds requests of a few scales.
+// Whether the engine should serve requests of a few scales in a work space of
+// this size.
 bool poly_work_takes(const PolyState* ps, size_t limit, int order);
 
 struct PolyCall {

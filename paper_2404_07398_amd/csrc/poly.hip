@@ -1427,7 +1427,9 @@ struct Totals {
 }  // namespace
 
 bool poly_work_takes(const PolyState* ps, size_t limit, int order) {
-  if (!ps || !(ps->lam > 0.0)) return false;
+  // (a few small cells that stretch the spectrum 16 times: the engine would
+  // decline 4 scales of an octave each)
+  if (!ps || !(ps->lam > 0.0) || ps->lam > 16.0 * ps->lam_typical) return false;
   // a request of 4 scales with its field and outputs in host memory, in one
   // sequence
   PolyCall c;

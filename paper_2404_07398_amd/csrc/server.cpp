@@ -12,7 +12,9 @@
 // Handles that leave the solver to the library (batch = 0) and whose operator
 // the polynomial engine takes are served by it instead of a tile: a worker
 // runs a request's scales together, request after request, in a work space of
-// the tile's size.
+// the tile's size. Requests that the engine declines, and columns that miss
+// the tolerance there, run in the tile, which takes the work space's place
+// while there are any.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,6 +50,7 @@ struct ifl_ticket {
   std::vector<ifl_solve_stats> stats;
   int remaining = 0;
   size_t footprint = 0;
+  bool tiled = false;  // the engine's work space did not hold it
   double* dev_field = nullptr;
   Clock::time_point t_submit, t_done;
 };
@@ -91,10 +94,13 @@ struct Worker {
   // column: real and imaginary parts) over the first-order operator
   bool cx = false;
   double* zero_rows = nullptr;  // n_pad zeros: the imaginary part of a field
-  // served by the polynomial engine, with the options of ifl_server_add
+  ifl_options opt{};  // of ifl_server_add
+  // served by the polynomial engine: its work space (NULL while a tile has its
+  // memory), and the columns of requests that wait for the tile to be done
   PolyState* poly = nullptr;
   PolyWork* poly_work = nullptr;
-  ifl_options opt{};
+  size_t poly_limit = 0;
+  std::deque<Column> parked;
 };
 
 }  // namespace
@@ -171,6 +177,8 @@ void release_ticket(Worker* wk, ifl_ticket* t) {
 // with IFL_ECANCELED (their requests finish once no column is left running).
 void cancel_pending(Worker* wk) {
   if (!wk->cancel.exchange(false)) return;
+  wk->pending.insert(wk->pending.end(), wk->parked.begin(), wk->parked.end());
+  wk->parked.clear();
   for (const Column& c : wk->pending) {
     ifl_ticket* t = c.t;
     t->stats[c.scale].status = IFL_ECANCELED;
@@ -188,38 +196,49 @@ void cancel_pending(Worker* wk) {
   wk->pending.clear();
 }
 
-// Admit queued requests that fit the budget, stage each field on the device
-// in row order (checked for NaN / Inf there), and queue its columns.
+// Stages an admitted request's field on the device in row order (checked for
+// NaN / Inf there); false: it could not be, and the request has ended.
+bool stage_ticket(Worker* wk, ifl_ticket* t) {
+  if (!wk->field_pool.empty()) {
+    t->dev_field = wk->field_pool.back();
+    wk->field_pool.pop_back();
+  } else if (device_malloc((void**)&t->dev_field, sizeof(double) * wk->bm.n_pad) != hipSuccess) {
+    t->dev_field = nullptr;
+  }
+  // the field goes through the staging buffer into row order (stream order
+  // keeps the staging buffer's reuse safe); the permutation raises the
+  // device flag on a NaN or Inf at a wet entry
+  bool bad = false;
+  if (!t->dev_field || batch_clear_flag(wk->w, wk->stream) != IFL_OK ||
+      hipMemcpyAsync(wk->stage, t->field, sizeof(double) * wk->L, hipMemcpyHostToDevice, wk->stream) != hipSuccess ||
+      batch_permute_fields(wk->bm, wk->stage, wk->L, 1, t->dev_field, wk->w.flag, wk->stream) != IFL_OK ||
+      batch_check_flag(wk->w, wk->stream, &bad) != IFL_OK) {
+    (void)hipGetLastError();
+    release_ticket(wk, t);
+    finish_ticket(t, IFL_ENOMEM, "device allocation or copy for the request failed");
+    return false;
+  }
+  if (bad) {
+    release_ticket(wk, t);
+    finish_ticket(t, IFL_EINVAL, "field has a NaN or Inf at a wet entry");
+    return false;
+  }
+  return true;
+}
+
+bool poly_serves(const Worker* wk, const ifl_ticket* t);
+
+// Admit queued requests that fit the budget, stage them, and queue their
+// columns. In the tile of a worker that the polynomial engine serves, only
+// requests that it declines, and none behind one that it would take.
 void stage_admitted(Worker* wk) {
+  if (!wk->parked.empty()) return;
   std::vector<ifl_ticket*> adm;
   admit(wk, &adm);
   for (ifl_ticket* t : adm) {
-    if (!wk->field_pool.empty()) {
-      t->dev_field = wk->field_pool.back();
-      wk->field_pool.pop_back();
-    } else if (device_malloc((void**)&t->dev_field, sizeof(double) * wk->bm.n_pad) != hipSuccess) {
-      t->dev_field = nullptr;
-    }
-    // the field goes through the staging buffer into row order (stream order
-    // keeps the staging buffer's reuse safe); the permutation raises the
-    // device flag on a NaN or Inf at a wet entry
-    bool bad = false;
-    if (!t->dev_field || batch_clear_flag(wk->w, wk->stream) != IFL_OK ||
-        hipMemcpyAsync(wk->stage, t->field, sizeof(double) * wk->L, hipMemcpyHostToDevice, wk->stream) !=
-            hipSuccess ||
-        batch_permute_fields(wk->bm, wk->stage, wk->L, 1, t->dev_field, wk->w.flag, wk->stream) != IFL_OK ||
-        batch_check_flag(wk->w, wk->stream, &bad) != IFL_OK) {
-      (void)hipGetLastError();
-      release_ticket(wk, t);
-      finish_ticket(t, IFL_ENOMEM, "device allocation or copy for the request failed");
-      continue;
-    }
-    if (bad) {
-      release_ticket(wk, t);
-      finish_ticket(t, IFL_EINVAL, "field has a NaN or Inf at a wet entry");
-      continue;
-    }
-    for (int j = 0; j < t->n_scales; ++j) wk->pending.push_back({t, j});
+    const bool park = wk->poly && poly_serves(wk, t);
+    if (!park && !stage_ticket(wk, t)) continue;
+    for (int j = 0; j < t->n_scales; ++j) (park ? wk->parked : wk->pending).push_back({t, j});
   }
 }
 
@@ -235,13 +254,15 @@ void complete_ticket(Worker* wk, ifl_ticket* t) {
   else finish_ticket(t, all_ok ? IFL_OK : IFL_ENOTCONV, all_ok ? "" : "a column did not converge");
 }
 
+// The worker of a tile; for a handle that the polynomial engine serves, until
+// no column is left for the tile.
 ifl_status run_worker(Worker* wk) {
   Handle* h = wk->h;
   const int R = wk->R;
-  const double rtol = h->opt.rtol;
+  const double rtol = wk->opt.rtol;
   BatchParams prm;
-  prm.max_iter = h->opt.max_iter;
-  prm.graphs = h->opt.graphs != 0;
+  prm.max_iter = wk->opt.max_iter;
+  prm.graphs = wk->opt.graphs != 0;
   const int chunk = wk->w.chunk;
   int active = 0;
   for (;;) {
@@ -262,10 +283,10 @@ ifl_status run_worker(Worker* wk) {
       src[j] = col.t->dev_field;
       if (wk->cx) {
         src[j + 1] = wk->zero_rows;
-        cx_shift(h, col.t->k[col.scale], &cs.c[j], &cs.c[j + 1]);
+        cx_shift(wk->opt.gamma, col.t->k[col.scale], &cs.c[j], &cs.c[j + 1]);
         mask |= 3ull << j;
       } else {
-        cs.c[j] = h->opt.gamma / std::pow(col.t->k[col.scale], 2.0 * h->op.order);
+        cs.c[j] = wk->opt.gamma / std::pow(col.t->k[col.scale], 2.0 * h->op.order);
         mask |= 1ull << j;
       }
       wk->slot[j] = col;
@@ -277,6 +298,7 @@ ifl_status run_worker(Worker* wk) {
       if (st == IFL_OK) st = batch_init(wk->bm, wk->w, mask, cs, rtol, wk->stream);
       if (st != IFL_OK) return st;
     }
+    if (active == 0 && wk->poly) return IFL_OK;
     if (active == 0) {
       // nothing to run: wait for a submit, a release of memory elsewhere or
       // a cancel (a queued request that does not fit yet must not spin)
@@ -335,6 +357,7 @@ ifl_status run_worker_shifted(Worker* wk) {
   for (;;) {
     cancel_pending(wk);
     stage_admitted(wk);
+    if (wk->pending.empty() && wk->poly) return IFL_OK;
     if (wk->pending.empty()) {
       std::unique_lock<std::mutex> lk(wk->srv->mu);
       if (wk->srv->stop && wk->queue.empty()) return IFL_OK;
@@ -348,8 +371,13 @@ ifl_status run_worker_shifted(Worker* wk) {
     ifl_solve_stats so{};
     ifl_status st;
     {
+      // with the options of ifl_server_add, on the handle's present stream
       std::lock_guard<std::mutex> lk(h->mu);
+      ifl_options now = wk->opt;
+      now.stream = h->opt.stream;
+      std::swap(h->opt, now);
       st = device_solve_shifted_rows(h, t->dev_field, t->k[col.scale], dst, &so);
+      std::swap(h->opt, now);
     }
     if (st != IFL_OK && st != IFL_ENOTCONV) {
       wk->pending.push_front(col);
@@ -366,11 +394,98 @@ ifl_status run_worker_shifted(Worker* wk) {
   }
 }
 
+// The tile of a worker, or what its one-column shifted solves need, with the
+// staging of fields and outputs.
+void close_tile(Worker* wk) {
+  batch_free(&wk->w);
+  if (wk->col_out) (void)hipFree(wk->col_out);
+  if (wk->stage) (void)hipFree(wk->stage);
+  if (wk->zero_rows) (void)hipFree(wk->zero_rows);
+  wk->col_out = wk->stage = wk->zero_rows = nullptr;
+}
+
+ifl_status open_tile(Worker* wk) {
+  const int n_out = wk->shifted ? 1 : wk->R;  // output staging columns
+  ifl_status st = IFL_OK;
+  if (!wk->shifted) {
+    st = batch_alloc(&wk->w, wk->bm, wk->R, wk->opt.precision == IFL_MIXED, wk->cx);
+  } else {
+    size_t bytes = 0;
+    std::lock_guard<std::mutex> lk(wk->h->mu);
+    st = device_shift_work(wk->h, &bytes);
+    if (st == IFL_OK && device_malloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess)  // only the field check's flag
+      st = fail(IFL_ENOMEM, "hipMalloc of the field check flag failed");
+  }
+  if (st == IFL_OK && wk->cx) {
+    wk->w.cx_g = handle_cx_gnorm(wk->h);
+    if (device_malloc((void**)&wk->zero_rows, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
+        hipMemset(wk->zero_rows, 0, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
+        hipDeviceSynchronize() != hipSuccess)
+      st = fail(IFL_ENOMEM, "allocation of the zero imaginary parts failed");
+  }
+  if (st == IFL_OK && device_malloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
+    st = fail(IFL_ENOMEM, "hipMalloc of the field staging failed");
+  if (st == IFL_OK && device_malloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
+    st = fail(IFL_ENOMEM, "hipMalloc of the output staging failed");
+  if (st != IFL_OK) close_tile(wk);
+  return st;
+}
+
+PolyCall poly_call(const Worker* wk, const ifl_ticket* t) {
+  PolyCall c;
+  c.order = wk->h->op.order;
+  c.shifted = wk->opt.solver == IFL_SOLVER_SHIFTED;
+  c.gamma = wk->opt.gamma;
+  c.rtol = wk->opt.rtol;
+  c.max_iter = wk->opt.max_iter;
+  c.n_fields = 1;
+  c.n_scales = t->n_scales;
+  c.fields = t->field;
+  c.fields_host = true;
+  c.k = t->k.data();
+  c.out = t->out;
+  c.out_host = t->out != nullptr;
+  c.stats = const_cast<ifl_solve_stats*>(t->stats.data());
+  c.stream = wk->stream;
+  return c;
+}
+
+// (after a request that did not fit the work space, t->tiled)
+bool poly_serves(const Worker* wk, const ifl_ticket* t) { return !t->tiled && poly_takes(wk->poly, poly_call(wk, t)); }
+
+// Runs the columns in wk->pending, whose requests the engine declined or left
+// unfinished, in the tile, which has the work space's memory meanwhile.
+ifl_status run_in_tile(Worker* wk) {
+  poly_work_destroy(wk->poly_work);
+  wk->poly_work = nullptr;
+  ifl_status st = open_tile(wk);
+  if (st == IFL_ENOMEM) {  // somebody else has taken the memory
+    std::vector<ifl_ticket*> held;
+    for (const Column& c : wk->pending)
+      if (held.empty() || held.back() != c.t) held.push_back(c.t);
+    wk->pending.clear();
+    for (ifl_ticket* t : held) {
+      release_ticket(wk, t);
+      finish_ticket(t, st, "device allocation for the request failed");
+    }
+    return IFL_OK;
+  }
+  if (st != IFL_OK) return st;
+  std::deque<Column> staged;
+  for (size_t i = 0, e; i < wk->pending.size(); i = e) {
+    ifl_ticket* t = wk->pending[i].t;
+    for (e = i; e < wk->pending.size() && wk->pending[e].t == t;) ++e;
+    if (stage_ticket(wk, t)) staged.insert(staged.end(), wk->pending.begin() + i, wk->pending.begin() + e);
+  }
+  wk->pending.swap(staged);
+  st = wk->shifted ? run_worker_shifted(wk) : run_worker(wk);
+  if (st == IFL_OK) close_tile(wk);
+  return st;
+}
+
 // The worker of a handle the polynomial engine serves: a request's columns
-// are one call of it. The field is read, checked and permuted there, and the
-// columns that miss the tolerance go to the handle's own CG.
+// are one call of it. The field is read, checked and permuted there.
 ifl_status run_worker_poly(Worker* wk) {
-  Handle* h = wk->h;
   for (;;) {
     cancel_pending(wk);
     std::vector<ifl_ticket*> adm;
@@ -390,43 +505,42 @@ ifl_status run_worker_poly(Worker* wk) {
     // a request's columns wait together: all of them run, or none has been
     // cancelled yet
     ifl_ticket* t = wk->pending.front().t;
-    PolyCall c;
-    c.order = h->op.order;
-    c.shifted = wk->opt.solver == IFL_SOLVER_SHIFTED;
-    c.gamma = wk->opt.gamma;
-    c.rtol = wk->opt.rtol;
-    c.max_iter = wk->opt.max_iter;
-    c.n_fields = 1;
-    c.n_scales = t->n_scales;
-    c.fields = t->field;
-    c.fields_host = true;
-    c.k = t->k.data();
-    c.out = t->out;
-    c.out_host = t->out != nullptr;
-    c.stats = t->stats.data();
-    c.stream = wk->stream;
     std::vector<int64_t> failed;
     ifl_status st = IFL_EUNSUPPORTED;
-    if (poly_takes(wk->poly, c)) st = poly_filter(wk->poly, wk->poly_work, c, &failed);
-    if (st == IFL_ENOMEM || st == IFL_EUNSUPPORTED) {
-      failed.clear();
-      for (int j = 0; j < t->n_scales; ++j) failed.push_back(j);
-      st = IFL_OK;
+    if (poly_serves(wk, t)) {
+      st = wk->poly_work ? IFL_OK : poly_work_create(wk->poly_limit, &wk->poly_work);
+      if (st == IFL_OK) st = poly_filter(wk->poly, wk->poly_work, poly_call(wk, t), &failed);
     }
-    for (size_t i = 0; st == IFL_OK && i < failed.size(); ++i) {
-      const int64_t j = failed[i];
-      const ifl_status e = device_cg_column(h, t->field, t->k[j], t->out ? t->out + j * wk->L : nullptr, &t->stats[j]);
-      if (e != IFL_OK && e != IFL_ENOTCONV) st = e;
+    const auto next = wk->pending.begin() + t->n_scales;
+    if (st == IFL_OK && failed.empty()) {
+      wk->pending.erase(wk->pending.begin(), next);
+      t->remaining = 0;
+      complete_ticket(wk, t);
+      continue;
     }
-    if (st != IFL_OK && st != IFL_EINVAL) return st;  // with the request still pending
-    wk->pending.erase(wk->pending.begin(), wk->pending.begin() + t->n_scales);
-    t->remaining = 0;
     if (st == IFL_EINVAL) {
+      wk->pending.erase(wk->pending.begin(), next);
+      t->remaining = 0;
       release_ticket(wk, t);
       finish_ticket(t, st, ifl_last_error());
-    } else {
-      complete_ticket(wk, t);
+      continue;
     }
+    if (st != IFL_OK && st != IFL_ENOMEM && st != IFL_EUNSUPPORTED) return st;  // with the request still pending
+    // into the tile: the columns that failed, or all, and the other waiting
+    // requests that the engine declines
+    std::deque<Column> tile;
+    if (st == IFL_OK) {
+      for (int64_t j : failed) tile.push_back({t, (int)j});
+      t->remaining = (int)failed.size();
+    } else {
+      t->tiled = true;
+      tile.insert(tile.end(), wk->pending.begin(), next);
+    }
+    for (auto c = next; c != wk->pending.end(); ++c) (poly_serves(wk, c->t) ? wk->parked : tile).push_back(*c);
+    wk->pending.swap(tile);
+    if ((st = run_in_tile(wk)) != IFL_OK) return st;
+    wk->pending.insert(wk->pending.end(), wk->parked.begin(), wk->parked.end());
+    wk->parked.clear();
   }
 }
 
@@ -441,6 +555,8 @@ void worker_main(Worker* wk) {
     std::vector<ifl_ticket*> held;
     for (int j = 0; j < wk->R; ++j)
       if (wk->slot[j].t) held.push_back(wk->slot[j].t);
+    wk->pending.insert(wk->pending.end(), wk->parked.begin(), wk->parked.end());
+    wk->parked.clear();
     for (const Column& c : wk->pending) held.push_back(c.t);
     std::sort(held.begin(), held.end());
     held.erase(std::unique(held.begin(), held.end()), held.end());
@@ -492,25 +608,29 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
   wk->L = h->op.field_len;
   s->device = h->opt.device;
   if (hipSetDevice(h->opt.device) != hipSuccess) return fail(IFL_EDEVICE, "hipSetDevice failed");
-  wk->cx = handle_cx_tiles(h);
-  wk->shifted = h->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2 && !wk->cx;
-  if (wk->cx) {
-    if (s->slots > 32) return fail(IFL_EINVAL, "complex tiles of order-2 shifted handles hold at most 32 slots");
-    wk->R = 2 * s->slots;
-    wk->bm = handle_batch_matrix_k1(h, wk->R, h->opt.precision == IFL_MIXED);
-  } else {
-    wk->bm = handle_batch_matrix(h, wk->R, h->opt.precision == IFL_MIXED);
-  }
-  const int n_out = wk->shifted ? 1 : wk->R;  // output staging columns
   size_t work = 0;
-  if (wk->shifted) {
+  {
     std::lock_guard<std::mutex> lk(h->mu);
-    if (ifl_status st = device_shift_work(h, &work)) return st;
-  } else {
-    work = batch_bytes(wk->bm.n_pad, wk->R, h->opt.precision == IFL_MIXED, wk->bm.chunk);
-    if (wk->cx) work += sizeof(double) * (size_t)wk->bm.n_pad;  // zero imaginary parts
+    wk->opt = h->opt;
+    const bool mixed = wk->opt.precision == IFL_MIXED;
+    wk->cx = handle_cx_tiles(h);
+    wk->shifted = wk->opt.solver == IFL_SOLVER_SHIFTED && h->op.order >= 2 && !wk->cx;
+    if (wk->cx) {
+      if (s->slots > 32) return fail(IFL_EINVAL, "complex tiles of order-2 shifted handles hold at most 32 slots");
+      wk->R = 2 * s->slots;
+      wk->bm = handle_batch_matrix_k1(h, wk->R, mixed);
+    } else {
+      wk->bm = handle_batch_matrix(h, wk->R, mixed);
+    }
+    if (wk->shifted) {
+      if (ifl_status st = device_shift_work(h, &work)) return st;
+    } else {
+      work = batch_bytes(wk->bm.n_pad, wk->R, mixed, wk->bm.chunk);
+      if (wk->cx) work += sizeof(double) * (size_t)wk->bm.n_pad;  // zero imaginary parts
+    }
   }
-  const size_t tile = work + sizeof(double) * (size_t)(n_out + 1) * wk->L;  // + output and field staging
+  // + output and field staging
+  const size_t tile = work + sizeof(double) * (size_t)((wk->shifted ? 1 : wk->R) + 1) * wk->L;
   {
     std::lock_guard<std::mutex> lk(s->mu);
     if (s->tiles + s->used + tile > s->budget)
@@ -521,7 +641,6 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
   ifl_status st;
   {
     std::lock_guard<std::mutex> lk(h->mu);
-    wk->opt = h->opt;
     st = device_poly(h, &poly);
   }
   // the polynomial engine where the handle leaves the solver to the library
@@ -530,32 +649,16 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
     // reported below
   } else if (poly_work_takes(poly, tile, h->op.order)) {
     wk->poly = poly;
+    wk->poly_limit = tile;
     st = poly_work_create(tile, &wk->poly_work);
-  } else if (!wk->shifted) {
-    st = batch_alloc(&wk->w, wk->bm, wk->R, h->opt.precision == IFL_MIXED, wk->cx);
-  } else if (device_malloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess) {  // only the field check's flag
-    st = fail(IFL_ENOMEM, "hipMalloc of the field check flag failed");
+  } else {
+    st = open_tile(wk.get());
   }
-  if (st == IFL_OK && wk->cx && !wk->poly) {
-    wk->w.cx_g = handle_cx_gnorm(h);
-    if (device_malloc((void**)&wk->zero_rows, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
-        hipMemset(wk->zero_rows, 0, sizeof(double) * (size_t)wk->bm.n_pad) != hipSuccess ||
-        hipDeviceSynchronize() != hipSuccess)
-      st = fail(IFL_ENOMEM, "allocation of the zero imaginary parts failed");
-  }
-  if (st == IFL_OK && !wk->poly && device_malloc((void**)&wk->stage, sizeof(double) * (size_t)wk->L) != hipSuccess)
-    st = fail(IFL_ENOMEM, "hipMalloc of the field staging failed");
-  if (st == IFL_OK && !wk->poly &&
-      device_malloc((void**)&wk->col_out, sizeof(double) * (size_t)n_out * wk->L) != hipSuccess)
-    st = fail(IFL_ENOMEM, "hipMalloc of the output staging failed");
   if (st == IFL_OK && hipStreamCreateWithFlags(&wk->stream, hipStreamNonBlocking) != hipSuccess)
     st = fail(IFL_EDEVICE, "hipStreamCreate failed");
   if (st != IFL_OK) {
-    batch_free(&wk->w);
+    close_tile(wk.get());
     poly_work_destroy(wk->poly_work);
-    if (wk->col_out) (void)hipFree(wk->col_out);
-    if (wk->stage) (void)hipFree(wk->stage);
-    if (wk->zero_rows) (void)hipFree(wk->zero_rows);
     std::lock_guard<std::mutex> lk(s->mu);
     s->tiles -= tile;
     return st;
@@ -685,11 +788,8 @@ void ifl_server_destroy(ifl_server* s) {
     if (wk->th.joinable()) wk->th.join();
     (void)hipSetDevice(s->device);
     if (wk->stream) (void)hipStreamSynchronize(wk->stream);
-    batch_free(&wk->w);
+    close_tile(wk.get());
     poly_work_destroy(wk->poly_work);
-    if (wk->col_out) (void)hipFree(wk->col_out);
-    if (wk->stage) (void)hipFree(wk->stage);
-    if (wk->zero_rows) (void)hipFree(wk->zero_rows);
     for (double* f : wk->field_pool) (void)hipFree(f);
     if (wk->stream) (void)hipStreamDestroy(wk->stream);
   }

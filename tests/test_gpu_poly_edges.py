@@ -226,3 +226,99 @@ def test_handles_on_several_threads(ifl):
     assert not wrong
     for h, *_ in jobs:
         h.close()
+
+
+def _serve(ifl, h, requests, slots=16, change=None):
+    srv = ifl.Server(1 << 30, slots=slots)
+    mid = srv.add(h)
+    if change:
+        h.set_options(**change)
+    tickets = [srv.submit(mid, f, k) for f, k in requests]
+    got = []
+    for (t, _), (f, k) in zip(tickets, requests):
+        code, st, out, _ = srv.wait(t, len(k))
+        got.append((code, st, out))
+    srv.close()
+    return got
+
+
+def _same(a, b):
+    """Requests served alike: codes, iterations, replacements and bits."""
+    for (ca, sa, oa), (cb, sb, ob) in zip(a, b):
+        assert ca == cb
+        assert [(x.iterations, x.refinements, x.status) for x in sa] == [(x.iterations, x.refinements, x.status) for x in sb]
+        assert np.array_equal(oa, ob)
+
+
+def test_served_requests_that_the_engine_declines_run_in_the_tile(ifl):
+    """Among requests that it takes: bitwise those of a server of tiles, and the
+    others those of the engine."""
+    m = W.split_square(64, jitter=0.2)
+    far = 2.0 * np.pi / np.array([1500.0, 1800.0, 2200.0])
+    near = W.log_scales(1.0, 5, lam_max_cells=16.0)
+    fields = [_waves(m, 0.01 * (1 + i)) for i in range(6)]
+    mix = [(fields[0], near), (fields[1], far), (fields[2], far), (fields[3], near), (fields[4], far), (fields[5], near)]
+    auto = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1)
+    tile = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1, batch=16)
+    got = _serve(ifl, auto, mix)
+    _same([got[i] for i in (1, 2, 4)], _serve(ifl, tile, [mix[i] for i in (1, 2, 4)]))
+    for i in (0, 3, 5):
+        assert np.array_equal(got[i][2], auto.filter(fields[i], near)[0][0])
+    # columns that miss the tolerance in the engine, beside columns that do not
+    auto2 = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2)
+    tile2 = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2, batch=16)
+    ks = np.concatenate([2.0 * np.pi / np.array([4.0]), FAILING[:2], 2.0 * np.pi / np.array([6.0])])
+    got = _serve(ifl, auto2, [(fields[0], ks), (fields[1], ks[[0, 3]])])
+    ref = _serve(ifl, tile2, [(fields[0], ks)])
+    assert [x.refinements > 0 for x in got[0][1]] == [False, True, True, False]
+    assert np.array_equal(got[0][2][1:3], ref[0][2][1:3])
+    assert [x.iterations for x in got[0][1][1:3]] == [x.iterations for x in ref[0][1][1:3]]
+    assert np.array_equal(got[1][2], auto2.filter(fields[1], ks[[0, 3]])[0][0])
+    # a mesh whose spectrum a few cells set is a tile's from the start
+    m = W.split_square(64, jitter=0.35)
+    wide = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1)
+    wide_tile = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1, batch=16)
+    reqs = [(_waves(m), near[:1]), (_waves(m), near[1:3])]
+    _same(_serve(ifl, wide, reqs), _serve(ifl, wide_tile, reqs))
+    for h in (auto, tile, auto2, tile2, wide, wide_tile):
+        h.close()
+
+
+def test_served_with_the_options_of_the_time_it_was_added(ifl):
+    """Also requests that leave the engine for the tile, and one column at a
+    time: the tolerance, precision and gamma of ifl_server_add."""
+    m = W.split_square(64, jitter=0.2)
+    far = 2.0 * np.pi / np.array([1500.0, 1800.0])
+    change = dict(gamma=0.7, rtol=1e-6, max_iter=7, precision=ifl.IFL_MIXED)
+    for order, kw in ((1, {}), (1, dict(batch=8)), (3, dict(solver=ifl.IFL_SOLVER_SHIFTED, max_iter=4000))):
+        ks = far if order == 1 else 2.0 * np.pi / np.array([4.0, 6.0])
+        h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, order, **kw)
+        ref = _serve(ifl, h, [(_waves(m), ks)])
+        assert ref[0][0] == 0
+        _same(_serve(ifl, h, [(_waves(m), ks)], change=change), ref)
+        h.close()
+
+
+def test_cancel_among_declined_requests(ifl):
+    """Every request ends, done or cancelled, whichever way it was served."""
+    m = W.split_square(64, jitter=0.2)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1)
+    far = 2.0 * np.pi / np.array([1500.0, 1800.0, 2200.0])
+    near = W.log_scales(1.0, 5, lam_max_cells=16.0)
+    ref = {3: h.filter(_waves(m), far)[0][0], 5: h.filter(_waves(m), near)[0][0]}
+    srv = ifl.Server(1 << 30, slots=4)
+    mid = srv.add(h)
+    for _ in range(3):
+        ks = [far if i % 3 else near for i in range(24)]
+        tickets = [srv.submit(mid, _waves(m), k)[0] for k in ks]
+        srv.wait(tickets[0], len(ks[0]))
+        srv.cancel()
+        for t, k in zip(tickets[1:], ks[1:]):
+            code, st, out, _ = srv.wait(t, len(k))
+            assert code in (0, ifl.IFL_ECANCELED)
+            if code == 0:
+                assert relative_l2(out, ref[len(k)]) <= 1e-8
+    code, _, out, _ = srv.wait(srv.submit(mid, _waves(m), near)[0], 5)
+    assert code == 0 and np.array_equal(out, ref[5])
+    srv.close()
+    h.close()
