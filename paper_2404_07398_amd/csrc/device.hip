@@ -2571,15 +2571,18 @@ ifl_status device_stream_probe(int device, int64_t bytes, int reps, double* best
 }
 
 
-ifl_status device_shift_work(Handle* h, size_t* bytes) {
-  DeviceState* d = h->dev;
-  IFL_HIP(hipSetDevice(d->device));
+size_t device_shift_bytes(Handle* h) {
+  const DeviceState* d = h->dev;
   const size_t np = (size_t)d->m.n_pad;
   // nine FP64 and seven FP32 complex vectors (two parts each), the weighted
   // sum, the partials and the scalars (ensure_shift_work)
-  *bytes = 2 * np * (9 * sizeof(double) + 7 * sizeof(float)) + np * sizeof(double) +
-           sizeof(double) * CP_COUNT * (size_t)d->G + 2 * sizeof(CScalars);
-  return ensure_shift_work(d);
+  return 2 * np * (9 * sizeof(double) + 7 * sizeof(float)) + np * sizeof(double) +
+         sizeof(double) * CP_COUNT * (size_t)d->G + 2 * sizeof(CScalars);
+}
+
+ifl_status device_shift_work(Handle* h) {
+  IFL_HIP(hipSetDevice(h->dev->device));
+  return ensure_shift_work(h->dev);
 }
 
 ifl_status device_solve_shifted_rows(Handle* h, const double* phi_rows, double k, double* out_dev,

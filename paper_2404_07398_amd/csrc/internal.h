@@ -135,9 +135,10 @@ ifl_status device_solve_shifted_rows(Handle* h, const double* phi_rows, double k
 // their own; the caller holds h->mu.
 struct PolyState;
 ifl_status device_poly(Handle* h, PolyState** out);
-// Allocates (once per handle) the work space of the shifted solves and
-// returns its size in bytes; the caller holds h->mu.
-ifl_status device_shift_work(Handle* h, size_t* bytes);
+// Size of the work space of the shifted solves in bytes, and its allocation
+// (once per handle); the caller holds h->mu.
+size_t device_shift_bytes(Handle* h);
+ifl_status device_shift_work(Handle* h);
 ifl_status device_autotune(Handle* h, ifl_tune* out);
 
 }  // namespace ifl

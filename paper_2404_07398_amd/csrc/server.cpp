@@ -410,9 +410,8 @@ ifl_status open_tile(Worker* wk) {
   if (!wk->shifted) {
     st = batch_alloc(&wk->w, wk->bm, wk->R, wk->opt.precision == IFL_MIXED, wk->cx);
   } else {
-    size_t bytes = 0;
     std::lock_guard<std::mutex> lk(wk->h->mu);
-    st = device_shift_work(wk->h, &bytes);
+    st = device_shift_work(wk->h);
     if (st == IFL_OK && device_malloc((void**)&wk->w.flag, sizeof(int)) != hipSuccess)  // only the field check's flag
       st = fail(IFL_ENOMEM, "hipMalloc of the field check flag failed");
   }
@@ -623,7 +622,7 @@ ifl_status ifl_server_add(ifl_server* s, ifl_handle* hh, int32_t* mesh_id) {
       wk->bm = handle_batch_matrix(h, wk->R, mixed);
     }
     if (wk->shifted) {
-      if (ifl_status st = device_shift_work(h, &work)) return st;
+      work = device_shift_bytes(h);
     } else {
       work = batch_bytes(wk->bm.n_pad, wk->R, mixed, wk->bm.chunk);
       if (wk->cx) work += sizeof(double) * (size_t)wk->bm.n_pad;  // zero imaginary parts

@@ -93,6 +93,20 @@ def test_fixed_width_handles_hold_no_patches(ifl):
     h0.close()
 
 
+def _union_jack(n, jitter=0.1):
+    """Periodic square of n x n cells (n even), the diagonals alternating: half
+    of the vertices have 8 neighbours, half 4."""
+    m = W.split_square(n, jitter=jitter)
+    i, j = np.meshgrid(np.arange(n), np.arange(n), indexing="xy")
+    a, b = (i + n * j).ravel(), ((i + 1) % n + n * j).ravel()
+    d, c = (i + n * ((j + 1) % n)).ravel(), ((i + 1) % n + n * ((j + 1) % n)).ravel()
+    even = ((i + j) % 2 == 0).ravel()
+    t1 = np.where(even[:, None], np.stack([a, b, c], 1), np.stack([a, b, d], 1))
+    t2 = np.where(even[:, None], np.stack([a, c, d], 1), np.stack([b, c, d], 1))
+    return W.Mesh(coords=m.coords, tris=np.concatenate([t1, t2]).astype(np.int32), geometry=m.geometry, h=m.h,
+                  period=m.period)
+
+
 # On _waves of the 64 x 64 square, order 2 at 128 cells and more: the
 # sequence's rounding (5e-11 of ||M phi||) stays above what FP64 can attain on
 # a filtered field that small (5e-12), so the check sends the columns to CG.
@@ -320,5 +334,27 @@ def test_cancel_among_declined_requests(ifl):
                 assert relative_l2(out, ref[len(k)]) <= 1e-8
     code, _, out, _ = srv.wait(srv.submit(mid, _waves(m), near)[0], 5)
     assert code == 0 and np.array_equal(out, ref[5])
+    srv.close()
+    h.close()
+
+
+def test_served_shifted_handle_holds_what_it_is_charged(ifl):
+    """Order 2 with shifted solves on rows of 8 neighbours (no complex tile): the
+    engine's work space alone, not the shifted solves' beside it."""
+    import torch
+
+    m = _union_jack(600)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 2, solver=ifl.IFL_SOLVER_SHIFTED)
+    phi, ks = np.random.default_rng(1).normal(size=600 * 600), W.log_scales(1.0, 3, lam_max_cells=8.0)
+    out, st = h.filter(phi, ks)
+    assert all(x.refinements == 0 for x in st)
+    srv = ifl.Server(1 << 30, slots=8)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    mid = srv.add(h)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] <= srv.query()["tiles"] + (8 << 20)
+    code, _, got, _ = srv.wait(srv.submit(mid, phi, ks)[0], 3)
+    assert code == 0 and np.array_equal(got, out[0])
     srv.close()
     h.close()
