@@ -364,6 +364,8 @@ struct Residual {
     a[1] = -i0 / det;
     return std::abs(a[0]) + std::abs(a[1]);
   }
+  // its value at x = 0, z = -1, where T_k is 1 or -1
+  real at_zero(int m) const { return m % 2 ? a[0] - a[1] : a[1] - a[0]; }
 };
 
 }  // namespace
@@ -386,9 +388,12 @@ void poly_coefficients(int order, double c, double lam, int m, double* out, int 
   const int n = order;
   // s = (1 - R) / (z - z_0), from the highest term down (the growing
   // direction of the recurrence); p = s / (c (lam / 2)) for n = 1, and for
-  // n = 2, 1 / |z - z_0|^2 = Im (1 / (z - z_0)) / Im z_0 gives p from Im s
-  const real lead = n == 1 ? 1.0L / ((real)c * 0.5L * (real)lam)
-                           : 1.0L / ((real)c * 0.25L * (real)lam * (real)lam * r.zi);
+  // n = 2, 1 / |z - z_0|^2 = Im (1 / (z - z_0)) / Im z_0 gives p from Im s.
+  // Scaled to p = 1 at x = 0: the largest scales, which hold most of a field's
+  // energy, and constants come out exact, for a residual of twice the size
+  // elsewhere
+  const real lead = (n == 1 ? 1.0L / ((real)c * 0.5L * (real)lam)
+                            : 1.0L / ((real)c * 0.25L * (real)lam * (real)lam * r.zi)) / (1.0L - r.at_zero(m));
   real sr = 0.0L, si = 0.0L, ur = 0.0L, ui = 0.0L;  // s_k, s_{k+1}
   for (int k = m + n; k >= 1; --k) {
     const real q = k > m ? -r.a[k - m - 1] : 0.0L;

@@ -78,8 +78,9 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out);
 // The polynomial p of one filter scale, p(z) = sum_k c_k T_k(z) on the
 // spectrum [0, lam] of M^-1 K, z = 2 x / lam - 1, order 1 or 2: the residual
 // 1 - (1 + c x^n) p is the combination of T_{m+1} .. T_{m+n} that is 1 at the n
-// zeros of 1 + c x^n. poly_degree: the least m at which it stays within tol on
-// [-1, 1], -1 if that is above max_degree or for another order.
+// zeros of 1 + c x^n, but for a factor that makes it 0 at x = 0. poly_degree:
+// the least m at which the combination stays within tol on [-1, 1] (and the
+// residual within 2 tol), -1 if that is above max_degree or for another order.
 int poly_degree(int order, double c, double lam, double tol, int max_degree);
 // c_0 .. c_m of degree m to out[k * stride].
 void poly_coefficients(int order, double c, double lam, int m, double* out, int stride);

@@ -1291,15 +1291,19 @@ void poly_destroy(PolyState* ps) {
 
 namespace {
 
-// What the residual polynomial is kept within: a twentieth of the tolerance,
-// about where CG, which overshoots it between its tests, leaves the error
-// (with a half, the results were 1.5 to 10 times further from an exact
-// solution than CG's; ln 10 costs 13 of 180 products at 32 cells), and less
-// where the masses differ so much that the residual's norm can outgrow the
+// What the residual polynomial is kept within: a fiftieth of the tolerance, of
+// order 2 a hundredth. CG, which overshoots it between its tests, leaves columns
+// 1e-13 from an exact solution, but energies, which feel the large scales most,
+// and columns of the shifted solves only 1e-14 to 4e-14. A twentieth (with a
+// residual that was not 0 at the largest scales) left 2e-14 to 8e-14 of these,
+// and of a spectrum's densities at level 8 7e-12 (n = 2 1e-10) for CG's 5e-12
+// (1.3e-11); now 1e-14 to 3e-14, 2.5e-12 and 3e-12. It costs 3% of the products,
+// and 9% where n = 2 reaches 32 cells: there the least degrees lie 30 apart.
+// Less where the masses differ so much that the residual's norm can outgrow the
 // polynomial's bound (their ratio's root, beyond the 4 that meshes with a
 // coastline have without it).
 double poly_tol(const PolyState* ps, const PolyCall& c) {
-  return std::max(1e-15, 0.05 * c.rtol / std::max(1.0, 0.25 * std::sqrt(ps->mass_ratio)));
+  return std::max(1e-15, (c.order == 1 ? 0.02 : 0.01) * c.rtol / std::max(1.0, 0.25 * std::sqrt(ps->mass_ratio)));
 }
 
 double scale_factor(const PolyCall& c, int32_t j) { return c.gamma / std::pow(c.k[j], 2.0 * c.order); }

@@ -170,3 +170,28 @@ def test_upper_end_of_the_spectrum(steps, least, above):
         assert 1.01 * ritz < values[-1]
     # an exhausted space: the Ritz value is an eigenvalue
     assert bound(alpha.ctypes.data_as(p), beta.ctypes.data_as(p), steps, steps - 1, least) == pytest.approx(1.01 * ritz)
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("b", [0.01, 1.0, 30.0, 1e3, 1e5])
+def test_polynomials(order, b):
+    """p(x) against 1 / (1 + c x^n): 1 at x = 0, the residual within twice the
+    tolerance of the degree on the spectrum, above it for a lower degree."""
+    degree = _function("_ZN3ifl11poly_degreeEidddi", ctypes.c_int, ctypes.c_int, *[ctypes.c_double] * 3, ctypes.c_int)
+    coefficients = _function("_ZN3ifl17poly_coefficientsEiddiPdi", None, ctypes.c_int, ctypes.c_double, ctypes.c_double,
+                             ctypes.c_int, ctypes.POINTER(ctypes.c_double), ctypes.c_int)
+    lam, tol = 3.7, 1e-9
+    c = (b / lam) ** order
+    m = degree(order, c, lam, tol, 100_000)
+    out = np.zeros((m + 1, 2))
+    coefficients(order, c, lam, m, out.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), 2)
+    assert not out[:, 1].any()
+    z = np.cos(np.linspace(0.0, np.pi, 4 * m + 201))
+    x = 0.5 * lam * (z + 1.0)
+    p = np.polynomial.chebyshev.chebval(z, out[:, 0])
+    res = 1.0 - (1.0 + c * x ** order) * p
+    # (the sum of m + 1 coefficients below 2 rounds to (m + 1) u, weighted)
+    u = (m + 1) * 2.0 ** -52
+    assert np.all(np.abs(res) <= 2.0 * tol + u * (1.0 + c * x ** order))
+    assert abs(res[-1]) <= u
+    assert m == 0 or degree(order, c, lam, tol, m - 1) == -1
