@@ -161,10 +161,11 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
         if (!ok) turns.store(false);
       }
     });
-    if (turns.load()) pp.block = 2;
+    if (!turns.load()) return false;
+    pp.block = 2;
   }
-  pp.single = g.n <= poly_single_units(nc, pp.width, pp.block);
-  pp.cap = pp.single ? (int)g.n : poly_patch_units(nc, pp.width, pp.block);
+  pp.single = g.n <= poly_single_units(pp.block);
+  pp.cap = pp.single ? (int)g.n : poly_patch_units(nc, pp.width);
   pp.depth = pp.single ? 0 : poly_patch_depth(nc, pp.width);
 
   // the order: the parts of the rows' own locality order, each bisected
@@ -275,7 +276,6 @@ bool build_patches(const HostOperator& op, bool local_order, PatchPack* out) {
       info.halo = (int64_t)pp.halo.size();
       info.idx = (int64_t)pp.idx.size();
       for (int d = 0; d <= kPolyDepth; ++d) info.end[d] = L.ends[std::min(d, pp.depth)];
-      info.rows = pp.depth ? L.ends[pp.depth - 1] : L.ends[0];
       pp.patches.push_back(info);
       pp.halo.insert(pp.halo.end(), L.units.begin() + L.ends[0], L.units.end());
       pp.idx.insert(pp.idx.end(), L.idx.begin(), L.idx.end());

@@ -18,17 +18,12 @@ constexpr int kPolyDepth = 12;
 // Threads of a patch's workgroup and units per thread; what a patch holds.
 constexpr int kPolyThreads = 512;
 constexpr int kPolySingleThreads = 1024;
-// (block: stored couplings of a neighbour block: 1, or of two components 4, or
-// 2 where every block is [[a, b], [-b, a]], as the vertex vectors' are)
-constexpr int poly_slots(int nc, int width, int block) {
-  return nc == 1 ? (width <= 6 ? 4 : 2) : (width <= 3 || block == 2 ? 2 : 1);
-}
-constexpr int poly_patch_units(int nc, int width, int block) {
-  return nc == 1 ? kPolyThreads * poly_slots(nc, width, block) : 1024;
-}
-constexpr int poly_single_units(int nc, int width, int block) {
-  return kPolySingleThreads * (poly_slots(nc, width, block) >= 2 && block != 2 ? 2 : 1);
-}
+// (block: stored couplings of a neighbour block: 1, of two components 4 where a
+// unit has at most 3 neighbours, as the cell vectors have, and 2 where every
+// block is [[a, b], [-b, a]], as the vertex vectors' are)
+constexpr int poly_slots(int nc, int width) { return nc == 1 && width <= 6 ? 4 : 2; }
+constexpr int poly_patch_units(int nc, int width) { return nc == 1 ? kPolyThreads * poly_slots(nc, width) : 1024; }
+constexpr int poly_single_units(int block) { return kPolySingleThreads * (block == 2 ? 1 : 2); }
 // Rings of large meshes' patches (small ones take what their patches leave).
 constexpr int poly_patch_depth(int nc, int width) { return nc == 1 && width <= 6 ? 8 : 4; }
 
@@ -44,10 +39,9 @@ constexpr int poly_col_record(int width) { return (width + 3) / 4 * 4; }
 
 struct PatchInfo {
   int32_t start;                // first interior position; the interior is contiguous
-  int32_t rows;                 // units with local neighbour numbers (all but the last ring)
   int32_t end[kPolyDepth + 1];  // local units up to and with ring d
   int64_t halo;                 // first halo entry (the positions of local units end[0] ..)
-  int64_t idx;                  // first entry of its rows' offset records
+  int64_t idx;                  // first entry of its rows' offset records (all units' but the last ring's)
 };
 
 // M^-1 K in the patches' own order of the units ("positions"). A unit is a
@@ -71,8 +65,9 @@ struct PatchPack {
 };
 
 // local_order: the rows are in the library's locality order. false (out
-// unspecified): the engine does not take this operator (rows too wide, or a
-// mass that is not positive).
+// unspecified): the engine does not take this operator (rows too wide, a mass
+// that is not positive, or vectors of more than 3 neighbours whose blocks do
+// not turn).
 bool build_patches(const HostOperator& op, bool local_order, PatchPack* out);
 
 // The polynomial p of one filter scale, p(z) = sum_k c_k T_k(z) on the

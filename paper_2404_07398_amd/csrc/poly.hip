@@ -912,14 +912,10 @@ void launch_steps(const PolyState* ps, const Steps& a, hipStream_t s) {
     else steps_of<2, 6, 2, 2, 512>(ps, a, s);
   } else if (ps->block == 2) {
     steps_of<2, 8, 2, 1, 1024>(ps, a, s);
-  } else if (ps->width == 3) {
-    if (L <= 1024) steps_of<2, 3, 4, 2, 512>(ps, a, s);
-    else steps_of<2, 3, 4, 2, 1024>(ps, a, s);
-  } else if (ps->width == 6) {
-    if (L <= 512) steps_of<2, 6, 4, 1, 512>(ps, a, s);
-    else steps_of<2, 6, 4, 1, 1024>(ps, a, s);
+  } else if (L <= 1024) {
+    steps_of<2, 3, 4, 2, 512>(ps, a, s);
   } else {
-    steps_of<2, 8, 4, 1, 1024>(ps, a, s);
+    steps_of<2, 3, 4, 2, 1024>(ps, a, s);
   }
 }
 
@@ -1011,9 +1007,7 @@ void check_scales(const PolyState* ps, int sc, int order, const double* phi, con
       if (ps->width == 6) f<2, 6, 2> __VA_ARGS__;               \
       else f<2, 8, 2> __VA_ARGS__;                              \
     } else {                                                    \
-      if (ps->width == 3) f<2, 3, 4> __VA_ARGS__;               \
-      else if (ps->width == 6) f<2, 6, 4> __VA_ARGS__;          \
-      else f<2, 8, 4> __VA_ARGS__;                              \
+      f<2, 3, 4> __VA_ARGS__;                                   \
     }                                                           \
   } while (0)
 
