@@ -378,3 +378,116 @@ def test_constants_and_energies(ifl, order):
     e = h.spectrum(phi, ks)[0]
     assert np.abs(e / ref - 1.0).max() <= 4e-14
     h.close()
+
+
+def _twelve(n):
+    """Periodic triangular lattice of n x n vertices (n even), every triangle
+    cut into six at its centre and its edges' midpoints: vertices of 12, 6 and
+    4 neighbours, 6 n^2 of them in cells of one size."""
+    x, ext = {}, np.array([float(n), n * np.sqrt(3.0) / 2.0])
+
+    def vertex(p):
+        q = np.mod(p, ext)
+        q[np.isclose(q, ext, atol=1e-9)] = 0.0
+        return x.setdefault((round(q[0], 6), round(q[1], 6)), len(x))
+
+    tris = []
+    for j in range(n):
+        for i in range(n):
+            o = np.array([i + 0.5 * (j % 2), j * np.sqrt(3.0) / 2.0])
+            e, u = np.array([1.0, 0.0]), np.array([0.5, np.sqrt(3.0) / 2.0])
+            for c in ([o, o + e, o + u], [o + e, o + e + u, o + u]):
+                mid = vertex((c[0] + c[1] + c[2]) / 3.0)
+                for a, b in ((0, 1), (1, 2), (2, 0)):
+                    m = vertex(0.5 * (c[a] + c[b]))
+                    tris += [[vertex(c[a]), m, mid], [m, vertex(c[b]), mid]]
+    coords = np.array(sorted(x, key=x.get))
+    return W.Mesh(coords=coords, tris=np.array(tris, np.int32), geometry=W.GEOM_PERIODIC, h=0.4, period=tuple(ext))
+
+
+@pytest.mark.parametrize("kind,n,order", [
+    ("8", 16, 1), ("8", 44, 2), ("8", 46, 1), ("8", 130, 2),      # one patch up to 2,048 units, rings
+    ("12", 8, 1), ("12", 18, 2), ("12", 20, 1), ("12", 64, 1),
+])
+def test_rows_of_8_and_12_neighbours(ifl, kind, n, order):
+    m = _union_jack(n) if kind == "8" else _twelve(n)
+    L = len(m.coords)
+    assert L == (n * n if kind == "8" else 6 * n * n)
+    phi = np.random.default_rng(n).normal(size=(2, L))
+    ks = W.log_scales(m.h, 5, lam_max_cells=12.0)
+    op = O.scalar_operator(m, order)
+    assert np.diff(sp.csr_matrix(op.K).indptr).max() == (9 if kind == "8" else 13)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, order)
+    out, st = h.filter(phi, ks)
+    assert all(x.refinements == 0 for x in st)
+    for f in range(2):
+        ref = O.filter_scalar(op, phi[f], ks)
+        assert max(relative_l2(out[f, j], ref[j]) for j in range(5)) <= TOL
+    h.close()
+
+
+@pytest.mark.parametrize("n", [16, 32, 34, 90])
+def test_vertex_vectors_of_8_neighbours(ifl, n):
+    """Turning blocks of 8 neighbours: one patch up to 1,024 units, rings."""
+    m = _union_jack(n)
+    u = np.random.default_rng(n).normal(size=(len(m.tris), 2))
+    ks = W.log_scales(m.h, 3, lam_max_cells=10.0)
+    ref = O.filter_vertex_vector(O.vertex_vector_operator(m, 1), u, ks)
+    h = ifl.prepare_mesh(m, ifl.IFL_VERTEX_VECTOR, 1)
+    out, st = h.filter(h.project_cells(u), ks)
+    assert all(x.refinements == 0 for x in st)
+    for j in range(3):
+        assert relative_l2(out[0, j], np.asarray(ref[j]).reshape(-1)) <= TOL
+    h.close()
+
+
+@pytest.mark.parametrize("placement", ["voronoi", "circumcentre"])
+@pytest.mark.parametrize("nx,order", [(24, 1), (24, 2), (70, 1), (70, 2)])
+def test_other_placements_by_default(ifl, placement, nx, order):
+    """Voronoi control volumes and cell scalars of acute triangles through the
+    engine, in one patch and in rings."""
+    m = W.split_square(nx, jitter=0.0)
+    skew = m.coords - 0.5 * np.stack([m.coords[:, 1], np.zeros(nx * nx)], axis=1)
+    m = W.Mesh(coords=skew * [1.0, np.sqrt(3.0) / 2.0], tris=m.tris, geometry=W.GEOM_PLANAR, h=1.0)
+    tri = m.coords[m.tris]  # without the triangles across the seam
+    inside = (np.ptp(tri[:, :, 0], axis=1) < 2.0) & (np.ptp(tri[:, :, 1], axis=1) < 2.0)
+    m = W.Mesh(coords=m.coords, tris=m.tris[inside], geometry=W.GEOM_PLANAR, h=1.0)
+    if placement == "voronoi":
+        op, place, L = O.voronoi_operator(m, order), ifl.IFL_VORONOI_SCALAR, len(m.coords)
+    else:
+        op, place, L = O.circumcenter_operator(m, order), ifl.IFL_CIRCUMCENTER_SCALAR, len(m.tris)
+    phi = np.random.default_rng(nx).normal(size=L)
+    ks = W.log_scales(1.0, 4, lam_max_cells=8.0)
+    ref = O.filter_scalar(op, phi, ks)
+    h = ifl.prepare_mesh(m, place, order)
+    out, st = h.filter(phi, ks)
+    assert all(x.refinements == 0 for x in st)
+    for j in range(4):
+        assert relative_l2(out[0, j], ref[j]) <= TOL
+    h.close()
+
+
+def test_the_largest_mesh_by_default(ifl):
+    """A level-9 call (2.6 million rows, 8 fields, more scales than a group) on
+    the library's choice: each column's residual by ifl_apply, and a field's
+    result not depending on its company."""
+    import torch
+
+    s = W.icosphere(9)
+    h = ifl.prepare_mesh(s, ifl.IFL_VERTEX_SCALAR, 1)
+    g = torch.Generator().manual_seed(5)
+    fields = torch.randn((8, s.n_vertices), dtype=torch.float64, generator=g).cuda()
+    ks = W.log_scales(s.h, 18, lam_max_cells=24.0)
+    out = torch.zeros((8, 18, s.n_vertices), dtype=torch.float64, device="cuda")
+    _, st = h.filter(fields, ks, out=out)
+    assert all(x.refinements == 0 and x.rel_residual <= 1e-12 for x in st)
+    zero = torch.zeros(s.n_vertices, dtype=torch.float64, device="cuda")
+    y, b = zero.clone(), zero.clone()
+    h.apply(1e30, fields[3], y=b)  # c vanishes: M phi
+    for j in (0, 9, 17):
+        h.apply(float(ks[j]), out[3, j], y=y)
+        assert float((y - b).norm() / b.norm()) <= 1e-12
+    one = torch.zeros((1, 18, s.n_vertices), dtype=torch.float64, device="cuda")
+    h.filter(fields[3].contiguous(), ks, out=one)
+    assert bool((one[0] == out[3]).all())
+    h.close()
