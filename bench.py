@@ -301,10 +301,11 @@ def vector_leg(ifl):
         torch.cuda.synchronize()
         el = time.perf_counter() - t
         res[name] = {"solves_per_s": round(nf * ks.size / el, 2), "unknowns": h.num_dofs,
-                     "mean_cg_iterations": round(sum(x.iterations for x in st) / len(st), 1),
+                     "mean_polynomial_degree": round(sum(x.iterations for x in st) / len(st), 1),
                      "prepare_s": round(prep, 1)}
-        # the same call again with HIP events around the tile's SpMV launches
-        # (not timed above): algorithmic bytes per launch / mean launch time
+        # the same call in CG's tiles with HIP events around their SpMV launches
+        # (another path than the timed call's): algorithmic bytes per launch /
+        # mean launch time
         h.set_options(profile=1)
         h.profile_read(reset=True)
         h.filter(fields, ks, out=dst)
@@ -313,7 +314,8 @@ def vector_leg(ifl):
         if nl:
             us = ms / nl * 1e3
             gbs = b / (us * 1e3)
-            res[name]["roofline"] = {"bound": "hbm", "kernel": h.profile_kernel(), "launches": nl,
+            res[name]["roofline"] = {"of": "the SpMV of the conjugate gradient tiles, a call of its own, not the timed one",
+                                     "bound": "hbm", "kernel": h.profile_kernel(), "launches": nl,
                                      "mean_launch_us": round(us, 2), "bytes_per_launch": round(b),
                                      "achieved_GBs": round(gbs, 1), "peak_GBs": HBM_PEAK_GBS,
                                      "frac": round(gbs / HBM_PEAK_GBS, 4)}
@@ -355,7 +357,7 @@ def c1_leg(ifl):
         el = time.perf_counter() - t
         res[name] = {"solves_per_s": round(reps * ks.size / el, 1),
                      "ms_per_solve": round(el / (reps * ks.size) * 1e3, 3),
-                     "mean_cg_iterations": round(iters / (reps * ks.size), 1),
+                     "mean_cg_iterations" if batch else "mean_polynomial_degree": round(iters / (reps * ks.size), 1),
                      "us_per_iteration": round(el / max(1, iters) * 1e6, 2)}
         h.close()
     return res
@@ -394,9 +396,10 @@ def c2_leg(ifl):
         _, st = h.filter(phi, ks, out=out)
         torch.cuda.synchronize()
         el = time.perf_counter() - t
+        what = "cg_iterations" if batch else "polynomial_degree"
         res[name] = {"solves_per_s": round(ks.size / el, 2),
-                     "mean_cg_iterations": round(sum(x.iterations for x in st) / len(st), 1),
-                     "max_cg_iterations": int(max(x.iterations for x in st)),
+                     "mean_" + what: round(sum(x.iterations for x in st) / len(st), 1),
+                     "max_" + what: int(max(x.iterations for x in st)),
                      "fp64_replacements": int(sum(x.refinements for x in st))}
     res["speedup_default_vs_plain_fp64"] = round(res["default"]["solves_per_s"] /
                                                  res["fp64_single_column"]["solves_per_s"], 3)
@@ -560,7 +563,7 @@ def serve_leg(args, ifl):
             "measured_span_s": round(span, 3),
             "max_submit_lag_s": round(lag, 4),
             "solves": int(solves),
-            "mean_cg_iterations": round(sum(x[4] for x in meas) / max(1, solves), 1),
+            "mean_polynomial_degree": round(sum(x[4] for x in meas) / max(1, solves), 1),
             "p50_latency_ms_by_mesh": {f"L{L}-n{n}": round(float(np.percentile(v, 50)) * 1e3, 1)
                                        for (L, n), v in sorted(per.items())},
             "outputs": "spectrum only (energies)" if spectrum_only else "filtered fields to host",

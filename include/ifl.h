@@ -106,8 +106,12 @@ typedef struct ifl_options {
                         export and save work, solves return IFL_EDEVICE */
   int32_t batch;     /* how ifl_filter solves its columns: 0 = the library's choice (default; orders 1
                         and 2: all scales of a field from one Chebyshev sequence of M^-1 K, FP64 in
-                        either precision; else CG tiles of the autotuner's width, or 32, at most a
-                        quarter of the call's columns), 1 = CG, one solve at a time, 2..64 = CG in a
+                        either precision, in up to 12 GB of work space and two vectors a field; up to
+                        16 GB of such space stay allocated on a device between calls, shared by its
+                        handles and given back to any allocation of the library that needs them.
+                        Where the sequence does not pay, and for columns that miss the tolerance in
+                        it, CG tiles of the autotuner's width, or 32, at most a quarter of the call's
+                        columns), 1 = CG, one solve at a time, 2..64 = CG in a
                         fixed tile (columns per tile, rounded down to a power of two) */
   void* stream;      /* hipStream_t to run on; NULL = the handle's own stream */
   int32_t reorder;   /* 1 = locality ordering of the rows (default): reverse Cuthill-McKee, on meshes of
@@ -420,10 +424,11 @@ ifl_status ifl_server_create(size_t hbm_budget_bytes, int32_t slots, ifl_server*
  * same mesh prepared for n = 1 and n = 2 are separate entries. The handle's
  * options at this call fix how its requests run: with batch = 0 and n <= 2 a
  * request's scales together, as ifl_filter does, in a work space of a tile's
- * size; else in a tile of 'slots' columns (IFL_SOLVER_KN; also where a tile
- * of so few slots is too small for that), or, for n >= 2 with
- * IFL_SOLVER_SHIFTED, one column at a time through the shifted first-order
- * solves. IFL_ENOMEM when
+ * size, whose place the tile takes for requests that ifl_filter would leave to
+ * CG; else in a tile of 'slots' columns (IFL_SOLVER_KN; also where a tile of so
+ * few slots is too small for that, or a few small cells stretch the operator's
+ * spectrum), or, for n >= 2 with IFL_SOLVER_SHIFTED, one column at a time
+ * through the shifted first-order solves. IFL_ENOMEM when
  * the work space (tile, or shifted-solve vectors, plus staging) does not fit
  * the budget. */
 ifl_status ifl_server_add(ifl_server* s, ifl_handle* h, int32_t* mesh_id);

@@ -2378,10 +2378,10 @@ ifl_status filter_cg(Handle* h, int64_t ncols, int32_t n_fields, const double* f
 // by CG in one call, of the width that the whole call would have had: every
 // field with such a column at every scale that has one, since a tile costs
 // about the same however full it is (2 of 8 scales one by one 31 ms, all 8 in
-// one tile 23; fewer fields at a time where memory is short). The fields come from the engine's rows, since out, which may
-// overlap fields, has been written.
-ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t>& failed, int32_t n_fields, int32_t n_scales,
-                         const double* k, double* out, ifl_solve_stats* stats, double* energy) {
+// one tile 23; fewer fields at a time where memory is short). The fields come
+// from the engine's rows, since out, which may overlap fields, has been written.
+ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t>& failed, int32_t n_fields,
+                         int32_t n_scales, const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   hipStream_t s = stream_of(h);
   const int64_t L = h->op.field_len;
@@ -2416,8 +2416,8 @@ ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t
     const int32_t n = std::min(step, nf - f0);
     for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, w, fs[f0 + f], 1, fields + f * L, s);
     if (st == IFL_OK)
-      st = filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(), !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res,
-                     so.data(), eo.data());
+      st = filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(),
+                     !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res, so.data(), eo.data());
     if (st == IFL_ENOTCONV) st = IFL_OK;
     for (; st == IFL_OK && at < failed.size() && failed[at] / n_scales <= fs[f0 + n - 1]; ++at) {
       const int64_t col = failed[at];
@@ -2426,7 +2426,8 @@ ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t
       if (so[from].status != IFL_OK) agg = IFL_ENOTCONV;
       if (stats) stats[col] = so[from];
       if (energy) energy[col] = eo[from];
-      if (out && !direct && hipMemcpyAsync(out + col * L, res + from * L, sizeof(double) * L, hipMemcpyDefault, s) != hipSuccess)
+      if (out && !direct &&
+          hipMemcpyAsync(out + col * L, res + from * L, sizeof(double) * L, hipMemcpyDefault, s) != hipSuccess)
         st = fail(IFL_EDEVICE, "copy of a column solved by CG failed");
     }
     if (hipStreamSynchronize(s) != hipSuccess && st == IFL_OK) st = fail(IFL_EDEVICE, "hipStreamSynchronize failed");

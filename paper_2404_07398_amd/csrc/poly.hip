@@ -44,9 +44,9 @@ constexpr int kRedBlocks = 512; // blocks of the row kernels that write partial 
 constexpr int kLanczos = 64, kLanczosSmall = 32;
 constexpr int kMaxGroup = 16;   // scales summed together
 
-// Without a limit: about 12 GB of the 288, which at level 9 hold 8 fields
-// with 64 vectors and 32 scales each (a patch's records are read once for
-// them; 4 fields took 7% longer).
+// Without a limit: about 12 GB of the 288, which at level 9 hold 8 fields with
+// 96 vectors of a sequence of 180 and 32 scales each (a patch's records are read
+// once for them; 4 fields took 7% longer).
 constexpr size_t kPolyBudget = (size_t)12 << 30;
 
 struct PolyDev {
@@ -531,7 +531,7 @@ struct GroupScales {
 // (|phi| + |x| + c |A| |z|) (the residual's rounding error is a small multiple
 // of u times their norm; order 2, TWICE: |A| |x| for |z|, from sizes), and of
 // M x^2 per scale. Bound by the gathers, which come from L2: a row and its
-// neighbours, 128 bytes each of 16 scales (8 level-9 fields 1.05 ms, 11 TB/s
+// neighbours, 128 bytes each of 16 scales (8 level-9 fields 1.08 ms, 11 TB/s
 // of gathers, 1.7 TB/s of HBM).
 template <int NC, int W, int BV, int SC, bool TWICE>
 __global__ __launch_bounds__(kRed) void k_poly_check(PolyDev m, const double* __restrict__ phi,
@@ -1197,7 +1197,8 @@ std::mutex g_idle_mu;
 std::vector<PolyWork*> g_idle;  // least recently used first
 
 size_t work_bytes(const PolyWork* w) {
-  return sizeof(double) * (w->phi_n + w->t_n + w->x_n + w->z_n + w->in_n + w->stage_n + w->part_n + w->norm_n + w->coef_n);
+  return sizeof(double) * (w->phi_n + w->t_n + w->x_n + w->z_n + w->in_n + w->stage_n + w->part_n + w->norm_n +
+                           w->coef_n);
 }
 
 // Frees the idle work spaces that 'which' is true of; whether there were any.
@@ -1271,7 +1272,8 @@ hipError_t device_malloc(void** p, size_t bytes) {
   if (e == hipSuccess) return e;
   (void)hipGetLastError();
   int device = 0;
-  if (hipGetDevice(&device) != hipSuccess || !drop_idle([&](const PolyWork* w) { return w->device == device; })) return e;
+  if (hipGetDevice(&device) != hipSuccess || !drop_idle([&](const PolyWork* w) { return w->device == device; }))
+    return e;
   if ((e = hipMalloc(p, bytes)) != hipSuccess) (void)hipGetLastError();
   return e;
 }
@@ -1336,8 +1338,9 @@ bool poly_takes(const PolyState* ps, const PolyCall& c) {
     rounds = rounds || left > c.rtol;
   }
   // a step of the sequence costs less than half a CG iteration of one
-  // column (2.6 M rows: 19 us for 90; 4,096 rows: 1 us for 12); lam exceeds lam_typical where a few cells are much smaller than
-  // the rest, which CG mostly does not feel and the sequence does
+  // column (2.6 M rows: 19 us for 90; 4,096 rows: 1 us for 12); lam exceeds
+  // lam_typical where a few cells are much smaller than the rest, which CG
+  // mostly does not feel and the sequence does
   if (!(most < 0.8 * c.max_iter && most <= 2.0 * cg + 8.0)) return false;
   // 64 x 64, one scale: 250 cells 1.3 ms for CG's 3.4, 1,000 cells 5.1 for 4.1
   if (most > 5.0 * few) return false;

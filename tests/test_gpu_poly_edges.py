@@ -113,6 +113,10 @@ def _union_jack(n, jitter=0.1):
 FAILING = 2.0 * np.pi / np.array([128.0, 145.0, 165.0, 190.0])
 
 
+def _counts(stats):
+    return [(x.iterations, x.refinements, x.status) for x in stats]
+
+
 def test_columns_that_fail_the_check_run_in_tiles(ifl):
     """All of a call's columns: bitwise the call of a handle that stays with CG
     (its launch events asked for), tile width and all."""
@@ -123,7 +127,7 @@ def test_columns_that_fail_the_check_run_in_tiles(ifl):
     out, st = h.filter(fields, FAILING, raise_on_notconv=False)
     ref, rt = cg.filter(fields, FAILING, raise_on_notconv=False)
     assert all(x.refinements > 0 for x in rt)
-    assert [(x.iterations, x.refinements, x.status) for x in st] == [(x.iterations, x.refinements, x.status) for x in rt]
+    assert _counts(st) == _counts(rt)
     assert np.array_equal(out, ref)
     # some of them: the rest keep the engine's results, and those of all
     # fields, apart as their scales are, run in the tile of the whole call
@@ -260,7 +264,7 @@ def _same(a, b):
     """Requests served alike: codes, iterations, replacements and bits."""
     for (ca, sa, oa), (cb, sb, ob) in zip(a, b):
         assert ca == cb
-        assert [(x.iterations, x.refinements, x.status) for x in sa] == [(x.iterations, x.refinements, x.status) for x in sb]
+        assert _counts(sa) == _counts(sb)
         assert np.array_equal(oa, ob)
 
 
@@ -271,7 +275,7 @@ def test_served_requests_that_the_engine_declines_run_in_the_tile(ifl):
     far = 2.0 * np.pi / np.array([1500.0, 1800.0, 2200.0])
     near = W.log_scales(1.0, 5, lam_max_cells=16.0)
     fields = [_waves(m, 0.01 * (1 + i)) for i in range(6)]
-    mix = [(fields[0], near), (fields[1], far), (fields[2], far), (fields[3], near), (fields[4], far), (fields[5], near)]
+    mix = [(f, far if i in (1, 2, 4) else near) for i, f in enumerate(fields)]
     auto = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1)
     tile = ifl.prepare_mesh(m, ifl.IFL_VERTEX_SCALAR, 1, batch=16)
     got = _serve(ifl, auto, mix)
