@@ -2378,9 +2378,10 @@ ifl_status filter_cg(Handle* h, int64_t ncols, int32_t n_fields, const double* f
 // by CG in one call, of the width that the whole call would have had: every
 // field with such a column at every scale that has one, since a tile costs
 // about the same however full it is (2 of 8 scales one by one 31 ms, all 8 in
-// one tile 23; fewer fields at a time where memory is short). The fields come
-// from the engine's rows, since out, which may overlap fields, has been written.
-ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t>& failed, int32_t n_fields,
+// one tile 23). The fields come from the engine's rows, since out, which may
+// overlap fields, has been written. Where memory is short the engine's other
+// vectors make room, and fewer fields go at a time.
+ifl_status filter_failed(Handle* h, PolyWork* w, const std::vector<int64_t>& failed, int32_t n_fields,
                          int32_t n_scales, const double* k, double* out, ifl_solve_stats* stats, double* energy) {
   DeviceState* d = h->dev;
   hipStream_t s = stream_of(h);
@@ -2403,9 +2404,10 @@ ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t
   ifl_status st = IFL_ENOMEM;
   int32_t step = nf;
   for (;; step = (step + 1) / 2) {
-    st = dalloc(&fields, (size_t)step * L * (direct || !out ? 1 : 1 + ns));
-    if (st == IFL_OK || step == 1) break;
-    (void)hipGetLastError();
+    const size_t need = (size_t)step * L * (direct || !out ? 1 : 1 + ns);
+    if ((st = dalloc(&fields, need)) == IFL_OK) break;
+    poly_work_trim(w);
+    if ((st = dalloc(&fields, need)) == IFL_OK || step == 1) break;
   }
   double* res = fields ? fields + (int64_t)step * L : nullptr;
   std::vector<ifl_solve_stats> so((size_t)step * ns);
@@ -2415,9 +2417,14 @@ ifl_status filter_failed(Handle* h, const PolyWork* w, const std::vector<int64_t
   for (int32_t f0 = 0; st == IFL_OK && f0 < nf; f0 += step) {
     const int32_t n = std::min(step, nf - f0);
     for (int32_t f = 0; st == IFL_OK && f < n; ++f) st = poly_fields(d->poly, w, fs[f0 + f], 1, fields + f * L, s);
-    if (st == IFL_OK)
-      st = filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(),
-                     !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res, so.data(), eo.data());
+    const auto cg = [&] {
+      return filter_cg(h, (int64_t)n_fields * n_scales, n, fields, ns, ks.data(),
+                       !out ? nullptr : direct ? out + (int64_t)f0 * n_scales * L : res, so.data(), eo.data());
+    };
+    if (st == IFL_OK && (st = cg()) == IFL_ENOMEM) {
+      poly_work_trim(w);
+      st = cg();
+    }
     if (st == IFL_ENOTCONV) st = IFL_OK;
     for (; st == IFL_OK && at < failed.size() && failed[at] / n_scales <= fs[f0 + n - 1]; ++at) {
       const int64_t col = failed[at];

@@ -152,5 +152,7 @@ ifl_status poly_filter(PolyState* ps, PolyWork* w, const PolyCall& call, std::ve
 // Fields f0 .. f0 + n - 1 of w's last call, in the caller's numbering (0 where
 // there is no row), to device memory.
 ifl_status poly_fields(PolyState* ps, const PolyWork* w, int f0, int n, double* out, hipStream_t stream);
+// Gives back what a work space without a limit holds, but for those fields.
+void poly_work_trim(PolyWork* w);
 
 }  // namespace ifl

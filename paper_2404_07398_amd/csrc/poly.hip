@@ -1146,9 +1146,9 @@ ifl_status poly_create(const HostOperator& op, bool local_order, hipStream_t s, 
   }
 }
 
-static void free_large(PolyWork* w) {
-  for (auto [p, n] : {std::pair<double**, size_t*>{&w->phi, &w->phi_n}, {&w->t, &w->t_n}, {&w->x, &w->x_n},
-                      {&w->z, &w->z_n}, {&w->in, &w->in_n}, {&w->stage, &w->stage_n}}) {
+void poly_work_trim(PolyWork* w) {
+  for (auto [p, n] : {std::pair<double**, size_t*>{&w->t, &w->t_n}, {&w->x, &w->x_n}, {&w->z, &w->z_n},
+                      {&w->in, &w->in_n}, {&w->stage, &w->stage_n}}) {
     if (*p) (void)hipFree(*p);
     *p = nullptr;
     *n = 0;
@@ -1177,7 +1177,10 @@ ifl_status poly_work_create(size_t limit, PolyWork** out) {
 
 void poly_work_destroy(PolyWork* w) {
   if (!w) return;
-  if (!w->limit) free_large(w);
+  if (!w->limit) {
+    poly_work_trim(w);
+    if (w->phi) (void)hipFree(w->phi);
+  }
   void* ptrs[] = {w->arena, w->part, w->norm, w->coef, w->bad};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
